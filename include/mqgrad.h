@@ -298,7 +298,8 @@ mqg_status mqg_aggregate_requantize_minmax(const uint32_t* const* packed, const 
  *   order, the sum is encoded over its own whole-tensor [mn, mx], and range_out receives (mn / W, mx / W),
  *   so that what a worker de-quantizes (mqg_aggregate_update_minmax_tensor with W = 1) is the mean.  The
  *   range of the sum is known only after every element has been decoded, so the W streams are read twice
- *   ((2 W + 1) * bits / 8 bytes per element; no fp32 copy of the sum is written).  Five launches on the stream.
+ *   ((2 W + 1) * bits / 8 bytes per element; no fp32 copy of the sum is written).  Up to three launches on
+ *   the stream (five when packed_out lies over one of the streams it reads).
  *   ranges      HOST array of W device pointers, each to 2 floats (8-byte aligned).
  *   packed_out  device, mqg_packed_words(n, bits) words;  range_out: device, 2 floats, 8-byte aligned.
  */
@@ -321,8 +322,8 @@ mqg_status mqg_aggregate_requantize_minmax_tensor(const uint32_t* const* packed,
  *   bucket > 0   mqg_quantize_minmax for every layer in ONE launch; items[i].scales_out receives the
  *                layer's 2 * mqg_num_buckets(n, bucket) floats.
  *   bucket == 0  one range per layer, as the paper encodes: mqg_quantize_minmax_tensor for every layer --
- *                a batched range reduction, then a batched encode (four launches for any number of
- *                layers); items[i].scales_out receives the layer's 2 floats.
+ *                a batched range reduction, then a batched encode (up to three launches for any number
+ *                of layers); items[i].scales_out receives the layer's 2 floats.
  *   items[i].scales_out must be 8-byte aligned; items[i].scales_in must be NULL (MQG_EINVAL otherwise);
  *   items[i].elem_base is not read (no random numbers are drawn).
  * mqg_aggregate_update_minmax_tensors: mqg_aggregate_update_minmax (bucket > 0) or

@@ -410,6 +410,7 @@ mqg_status mqg_quantize_minmax_tensors(const mqg_quantize_item* items, uint32_t 
         rb.grad[i] = nullptr;
         rb.n[i] = 0;
         rb.range[i] = nullptr;
+        rb.parts[i] = nullptr;
         if (i >= count) continue;
         const mqg_quantize_item& it = items[i];
         if (it.scales_in != nullptr) return MQG_EINVAL;   // this encoder derives every range from the data
@@ -422,6 +423,7 @@ mqg_status mqg_quantize_minmax_tensors(const mqg_quantize_item* items, uint32_t 
             rb.grad[i] = it.grad;
             rb.n[i] = it.n;
             rb.range[i] = it.scales_out;
+            rb.parts[i] = it.packed_out;
         } else {
             a.t[i] = mqg::BatchQuantizeArgs::Tensor{it.grad, it.n, 0, it.packed_out, it.scales_out, nullptr};
         }
@@ -431,7 +433,7 @@ mqg_status mqg_quantize_minmax_tensors(const mqg_quantize_item* items, uint32_t 
     a.tile_start[mqg::kMaxBatchTensors] = (uint32_t)tiles;
     if (tiles == 0) return MQG_OK;
     hipError_t err = hipSuccess;
-    if (per_tensor) err = mqg::launch_tensor_range_batch(rb, count, static_cast<hipStream_t>(stream));
+    if (per_tensor) err = mqg::launch_tensor_ranges(rb, count, static_cast<hipStream_t>(stream));
     if (err == hipSuccess) err = mqg::launch_quantize_minmax_tensors(a, (uint32_t)tiles, static_cast<hipStream_t>(stream));
     return err == hipSuccess ? MQG_OK : MQG_ELAUNCH;
 }
@@ -519,18 +521,13 @@ mqg_status mqg_quantize_minmax_tensor(const float* grad, uint64_t n, uint32_t bi
     if (grad == nullptr || packed_out == nullptr || range_out == nullptr) return MQG_EINVAL;
     if (n > (UINT64_MAX >> 4)) return MQG_EINVAL;
     if (misaligned4(grad) || misaligned4(packed_out) || misaligned8(range_out)) return MQG_EALIGN;
-    hipError_t err = mqg::launch_tensor_range(grad, n, range_out, static_cast<hipStream_t>(stream));
-    if (err != hipSuccess) return MQG_ELAUNCH;
     mqg::QuantizeArgs a = {};
     a.grad = grad;
     a.n = n;
     a.bits = bits;
-    a.bucket = 1024u;            // tiling only: every chunk takes the one range in scales_in
-    a.bucket_shift = 10;
-    a.scales_in = range_out;
     a.packed = packed_out;
-    a.scales = nullptr;          // not written when the range is given
-    err = mqg::launch_quantize_minmax(a, static_cast<hipStream_t>(stream));
+    a.scales = range_out;
+    const hipError_t err = mqg::launch_quantize_minmax_tensor(a, static_cast<hipStream_t>(stream));
     return err == hipSuccess ? MQG_OK : MQG_ELAUNCH;
 }
 

@@ -112,13 +112,16 @@ hipError_t launch_aggregate_minmax(const AggregateArgs& a, hipStream_t stream);
 hipError_t launch_requantize_minmax(const RequantArgs& a, hipStream_t stream);
 hipError_t launch_requantize_minmax_tensor(const RequantArgs& a, hipStream_t stream);   // one range per worker and for the mean
 hipError_t launch_tensor_range(const float* grad, uint64_t n, float* range_out, hipStream_t stream);
-// the same for several layer tensors per launch
+// the same for several tensors that are encoded next, with their code words as the workgroups' scratch memory
 struct TensorRangeBatch {
     const float* grad[kMaxBatchTensors];
-    uint64_t n[kMaxBatchTensors];
-    float* range[kMaxBatchTensors];   // 2 floats each; nullptr: no such tensor (or an empty one)
+    uint64_t n[kMaxBatchTensors];        // 0: no such tensor (or an empty one)
+    float* range[kMaxBatchTensors];      // 2 floats each
+    uint32_t* parts[kMaxBatchTensors];   // the tensor's code words
+    uint32_t block_start[kMaxBatchTensors + 1];   // filled by the launch: prefix sums of the tensors' workgroups
 };
-hipError_t launch_tensor_range_batch(const TensorRangeBatch& b, uint32_t count, hipStream_t stream);
+hipError_t launch_tensor_ranges(TensorRangeBatch& b, uint32_t count, hipStream_t stream);
+hipError_t launch_quantize_minmax_tensor(const QuantizeArgs& a, hipStream_t stream);    // a.scales: the one range; a.bucket unused
 uint32_t quantize_minmax_wave_block_elems(uint32_t bucket);                                       // quantize_wave.hip
 hipError_t launch_quantize_minmax_tensors_wave(const BatchQuantizeArgs& a, uint32_t blocks, hipStream_t stream);
 uint32_t quantize_minmax_batch_tile(uint32_t bucket, int bucket_shift);   // elements per workgroup
