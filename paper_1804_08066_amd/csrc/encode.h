@@ -88,6 +88,39 @@ __device__ __forceinline__ uint32_t wave_min_from_cells_u32(uint32_t m, uint32_t
     return min(m, bpermute_xor32_u32(m, lane));
 }
 
+// Largest magnitude, minimum and maximum of a quad: two instructions each.  fmaxf / fminf on loaded values cost
+// one canonicalising instruction per value on top (a signalling NaN must be quieted before it can be
+// dropped); the instructions themselves drop a quiet NaN in the same way, and what a signalling one does to
+// its own bucket is unspecified for a gradient anyway (L2 scale, 10 M elements: 11.7 -> 11.5 us).
+__device__ __forceinline__ float quad_absmax(const float4& v) {
+    float m, r;
+    asm("v_max_f32_e64 %0, |%1|, |%2|" : "=v"(m) : "v"(v.x), "v"(v.y));
+    asm("v_max3_f32 %0, |%1|, |%2|, %3" : "=v"(r) : "v"(v.z), "v"(v.w), "v"(m));
+    return r;
+}
+__device__ __forceinline__ float quad_min(float a, float b, float c, float d) {
+    float m, r;
+    asm("v_min_f32_e32 %0, %1, %2" : "=v"(m) : "v"(a), "v"(b));
+    asm("v_min3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(c), "v"(d), "v"(m));
+    return r;
+}
+__device__ __forceinline__ float quad_max(float a, float b, float c, float d) {
+    float m, r;
+    asm("v_max_f32_e32 %0, %1, %2" : "=v"(m) : "v"(a), "v"(b));
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(c), "v"(d), "v"(m));
+    return r;
+}
+__device__ __forceinline__ float max_f32(float a, float b) {
+    float m;
+    asm("v_max_f32_e32 %0, %1, %2" : "=v"(m) : "v"(a), "v"(b));
+    return m;
+}
+__device__ __forceinline__ float min_f32(float a, float b) {
+    float m;
+    asm("v_min_f32_e32 %0, %1, %2" : "=v"(m) : "v"(a), "v"(b));
+    return m;
+}
+
 // fp32 -> uint32 whose unsigned order is the order of the floats, and back
 __device__ __forceinline__ uint32_t order_key(float f) {
     const uint32_t u = __builtin_bit_cast(uint32_t, f);
@@ -185,6 +218,16 @@ __device__ __forceinline__ uint32_t pack_quad_hi(uint32_t t0, uint32_t t1, uint3
     asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1" : "=v"(v3) : "s"(s3), "v"(t3));
     asm("v_or_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1 src1_sel:DWORD" : "=v"(v0) : "v"(t0), "v"(v1));
     return v0 | v2 | v3;
+}
+
+// Nearest level of the [min, max] grid: clamp(rint((x - mn) * ai), 0, L).  The clamp comes first (0 and L
+// are integers, and the median drops a NaN position to 0), and the rounding to the nearest even integer is
+// that of a product with 2^-149: the result's bits are the code.  One full-rate operation per element beside
+// three that co-issue, where rint, max, min and the conversion took four (with quad_min / quad_max: 46.4 -> 44.8 us
+// for the exchange of 7.2 M elements at 6 bits, one range per 2304).
+__device__ __forceinline__ uint32_t nearest_code(float x, float mn, float ai, float Lf) {
+    const float v = __builtin_amdgcn_fmed3f((x - mn) * ai, 0.0f, Lf);
+    return __builtin_bit_cast(uint32_t, v * 0x1p-149f);
 }
 
 }  // namespace encode

@@ -21,6 +21,7 @@ struct QuantizeArgs {
                              // (min, max) pair that holds for the whole tensor)
     uint32_t* packed;        // ceil(n*bits/32) words
     float* scales;           // ceil(n/bucket) floats
+    uint32_t drop_nan = 0;       // [min, max] ranges: 1: a NaN takes no part, also where a lane holds nothing else (whole-tensor ranges)
     uint32_t stream_codes = 0;   // 1: the code words are stored with the streaming hint instead of agent scope
 };
 

@@ -112,20 +112,27 @@ __device__ __forceinline__ void encode_minmax_tile(const QuantizeArgs& a, const 
     for (int j = 0; j < R; ++j) {
         const uint32_t el = 4u * (j * NT + tid);
         if (FULL) {
-            lo[j] = fminf(fminf(x[j].x, x[j].y), fminf(x[j].z, x[j].w));
-            hi[j] = fmaxf(fmaxf(x[j].x, x[j].y), fmaxf(x[j].z, x[j].w));
+            lo[j] = quad_min(x[j].x, x[j].y, x[j].z, x[j].w);
+            hi[j] = quad_max(x[j].x, x[j].y, x[j].z, x[j].w);
         } else {   // elements past the end take no part
             const bool v0 = el + 0u < tile_count, v1 = el + 1u < tile_count;
             const bool v2 = el + 2u < tile_count, v3 = el + 3u < tile_count;
-            lo[j] = fminf(fminf(v0 ? x[j].x : inf, v1 ? x[j].y : inf), fminf(v2 ? x[j].z : inf, v3 ? x[j].w : inf));
-            hi[j] = fmaxf(fmaxf(v0 ? x[j].x : -inf, v1 ? x[j].y : -inf), fmaxf(v2 ? x[j].z : -inf, v3 ? x[j].w : -inf));
+            lo[j] = quad_min(v0 ? x[j].x : inf, v1 ? x[j].y : inf, v2 ? x[j].z : inf, v3 ? x[j].w : inf);
+            hi[j] = quad_max(v0 ? x[j].x : -inf, v1 ? x[j].y : -inf, v2 ? x[j].z : -inf, v3 ? x[j].w : -inf);
         }
     }
     if (kOne) {   // the tile is one bucket: fold the lane's rows first
 #pragma unroll
         for (int j = 1; j < R; ++j) {
-            lo[0] = fminf(lo[0], lo[j]);
-            hi[0] = fmaxf(hi[0], hi[j]);
+            lo[0] = min_f32(lo[0], lo[j]);
+            hi[0] = max_f32(hi[0], hi[j]);
+        }
+    }
+    if (a.drop_nan != 0u) {
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            lo[j] = min_f32(lo[j], inf);
+            hi[j] = max_f32(hi[j], -inf);
         }
     }
     // across lanes on order-preserving integer keys, stage by stage over the rows
@@ -192,11 +199,10 @@ __device__ __forceinline__ void encode_minmax_tile(const QuantizeArgs& a, const 
         const uint32_t ql = j * NT + tid;
         const uint32_t el = 4u * ql;
         const float mn = sm.mn[bl[j]], ai = sm.a[bl[j]];
-        // fmaxf drops a NaN position to 0; positions are integers after rint
-        uint32_t k0 = (uint32_t)fminf(fmaxf(__builtin_rintf((x[j].x - mn) * ai), 0.0f), Lf);
-        uint32_t k1 = (uint32_t)fminf(fmaxf(__builtin_rintf((x[j].y - mn) * ai), 0.0f), Lf);
-        uint32_t k2 = (uint32_t)fminf(fmaxf(__builtin_rintf((x[j].z - mn) * ai), 0.0f), Lf);
-        uint32_t k3 = (uint32_t)fminf(fmaxf(__builtin_rintf((x[j].w - mn) * ai), 0.0f), Lf);
+        uint32_t k0 = nearest_code(x[j].x, mn, ai, Lf);
+        uint32_t k1 = nearest_code(x[j].y, mn, ai, Lf);
+        uint32_t k2 = nearest_code(x[j].z, mn, ai, Lf);
+        uint32_t k3 = nearest_code(x[j].w, mn, ai, Lf);
         if (!FULL) {   // elements past the end contribute zero bits
             if (el + 0u >= tile_count) k0 = 0u;
             if (el + 1u >= tile_count) k1 = 0u;
@@ -642,8 +648,8 @@ __device__ __forceinline__ void block_range(const float* __restrict__ g, const u
     const uint64_t nq = n >> 2;
     const uint64_t rows = nq / kSumThreads;
     const auto fold = [&](const v4f t) {
-        lo = fminf(lo, fminf(fminf(t.x, t.y), fminf(t.z, t.w)));
-        hi = fmaxf(hi, fmaxf(fmaxf(t.x, t.y), fmaxf(t.z, t.w)));
+        lo = min_f32(lo, quad_min(t.x, t.y, t.z, t.w));
+        hi = max_f32(hi, quad_max(t.x, t.y, t.z, t.w));
     };
     for (uint64_t r = block; r < rows; r += 4u * (uint64_t)nblocks) {
         v4f t[4];
@@ -924,6 +930,7 @@ hipError_t launch_quantize_minmax_tensor(const QuantizeArgs& a_in, hipStream_t s
     a.bucket = 1024u;            // the range is given: the bucket only shapes the launch
     a.bucket_shift = 10;
     if (a.n <= kOneBucketElems) {
+        a.drop_nan = 1u;
         while (a.bucket < a.n) {
             a.bucket <<= 1;
             a.bucket_shift += 1;
@@ -977,6 +984,7 @@ hipError_t launch_requantize_minmax_tensor(const RequantArgs& ra_in, hipStream_t
         RequantArgs one = ra_in;
         one.q.bucket = 4096u;
         one.q.bucket_shift = 12;
+        one.q.drop_nan = 1u;
         while (one.q.bucket < one.q.n) {
             one.q.bucket <<= 1;
             one.q.bucket_shift += 1;

@@ -186,7 +186,7 @@ __device__ __forceinline__ void quantize_tile(const QuantizeArgs& a, const uint6
             uint32_t m[R];   // bit patterns of non-negative floats: integer order = value order
 #pragma unroll
             for (int j = 0; j < R; ++j) {
-                m[j] = __builtin_bit_cast(uint32_t, fmaxf(fmaxf(fabsf(x[j].x), fabsf(x[j].y)), fmaxf(fabsf(x[j].z), fabsf(x[j].w))));
+                m[j] = __builtin_bit_cast(uint32_t, quad_absmax(x[j]));
             }
             if (kOne) {
 #pragma unroll
@@ -205,7 +205,7 @@ __device__ __forceinline__ void quantize_tile(const QuantizeArgs& a, const uint6
 #pragma unroll
             for (int j = 0; j < R; ++j) {
                 const uint32_t el = 4u * (j * kThreads + tid);
-                const float mf = fmaxf(fmaxf(fabsf(x[j].x), fabsf(x[j].y)), fmaxf(fabsf(x[j].z), fabsf(x[j].w)));
+                const float mf = quad_absmax(x[j]);
                 const uint32_t m = cell_max_u32(__builtin_bit_cast(uint32_t, mf));
                 if ((tid & 7u) == 0u && (FULL || el < tile_count)) atomicMax(&sm.bmax[bl[j]], m);
             }

@@ -192,14 +192,14 @@ __device__ __forceinline__ void reduce_ranges(const float4 (&x)[R], uint32_t lan
     float m[R];
 #pragma unroll
     for (int j = 0; j < R; ++j) {
-        m[j] = fmaxf(fmaxf(fabsf(x[j].x), fabsf(x[j].y)), fmaxf(fabsf(x[j].z), fabsf(x[j].w)));
+        m[j] = quad_absmax(x[j]);
     }
     // fold the rows of one bucket into its first row
 #pragma unroll
     for (int step = 1; step < R; step <<= 1) {
         if (rpb > (uint32_t)step) {
 #pragma unroll
-            for (int j = 0; j + step < R; j += 2 * step) m[j] = fmaxf(m[j], m[j + step]);
+            for (int j = 0; j + step < R; j += 2 * step) m[j] = max_f32(m[j], m[j + step]);
         }
     }
     // reduce across the lanes of the bucket; the first lane of each bucket publishes the result
@@ -536,7 +536,7 @@ __device__ __forceinline__ void quantize_cells_block(const QuantizeArgs& a, cons
         uint32_t m[R];   // bit patterns of non-negative floats: integer order = value order
 #pragma unroll
         for (int j = 0; j < R; ++j) {
-            m[j] = __builtin_bit_cast(uint32_t, fmaxf(fmaxf(fabsf(x[j].x), fabsf(x[j].y)), fmaxf(fabsf(x[j].z), fabsf(x[j].w))));
+            m[j] = __builtin_bit_cast(uint32_t, quad_absmax(x[j]));
         }
 #pragma unroll
         for (int j = 0; j < R; ++j) m[j] = max(m[j], dpp_u32<kDppQuadSwap1>(m[j]));
@@ -828,19 +828,19 @@ struct WaveLows {
 template <int R, int WPB, int NW, bool FULL>
 __device__ __forceinline__ void reduce_minmax(const float4 (&x)[R], uint32_t count, uint32_t lane, uint32_t wave,
                                               const uint32_t (&slot)[R], uint32_t seg_lanes, uint32_t rpb,
-                                              WaveShared<R, NW>& sm, WaveLows<R, NW>& lw) {
+                                              WaveShared<R, NW>& sm, WaveLows<R, NW>& lw, const bool drop_nan) {
     const float inf = __builtin_inff();
     float lo[R], hi[R];
 #pragma unroll
     for (int j = 0; j < R; ++j) {
         if (FULL) {
-            lo[j] = fminf(fminf(x[j].x, x[j].y), fminf(x[j].z, x[j].w));
-            hi[j] = fmaxf(fmaxf(x[j].x, x[j].y), fmaxf(x[j].z, x[j].w));
+            lo[j] = quad_min(x[j].x, x[j].y, x[j].z, x[j].w);
+            hi[j] = quad_max(x[j].x, x[j].y, x[j].z, x[j].w);
         } else {   // elements past the end take no part
             const uint32_t el = 4u * (j * 64u + lane);
             const bool v0 = el + 0u < count, v1 = el + 1u < count, v2 = el + 2u < count, v3 = el + 3u < count;
-            lo[j] = fminf(fminf(v0 ? x[j].x : inf, v1 ? x[j].y : inf), fminf(v2 ? x[j].z : inf, v3 ? x[j].w : inf));
-            hi[j] = fmaxf(fmaxf(v0 ? x[j].x : -inf, v1 ? x[j].y : -inf), fmaxf(v2 ? x[j].z : -inf, v3 ? x[j].w : -inf));
+            lo[j] = quad_min(v0 ? x[j].x : inf, v1 ? x[j].y : inf, v2 ? x[j].z : inf, v3 ? x[j].w : inf);
+            hi[j] = quad_max(v0 ? x[j].x : -inf, v1 ? x[j].y : -inf, v2 ? x[j].z : -inf, v3 ? x[j].w : -inf);
         }
     }
     // fold the rows of one bucket into its first row
@@ -849,9 +849,16 @@ __device__ __forceinline__ void reduce_minmax(const float4 (&x)[R], uint32_t cou
         if (rpb > (uint32_t)step) {
 #pragma unroll
             for (int j = 0; j + step < R; j += 2 * step) {
-                lo[j] = fminf(lo[j], lo[j + step]);
-                hi[j] = fmaxf(hi[j], hi[j + step]);
+                lo[j] = min_f32(lo[j], lo[j + step]);
+                hi[j] = max_f32(hi[j], hi[j + step]);
             }
+        }
+    }
+    if (drop_nan) {
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            lo[j] = min_f32(lo[j], inf);
+            hi[j] = max_f32(hi[j], -inf);
         }
     }
     uint32_t kh[R], nl[R];
@@ -931,11 +938,10 @@ __device__ __forceinline__ void encode_minmax_and_pack(const QuantizeArgs& a, ui
         const uint32_t ql = j * 64u + lane;
         const uint32_t el = 4u * ql;
         const float mn = lw.lo[wave][slot[j]], ai = sm.ainv[wave][slot[j]];
-        // fmaxf drops a NaN position to 0; positions are integers after rint
-        uint32_t k0 = (uint32_t)fminf(fmaxf(__builtin_rintf((x[j].x - mn) * ai), 0.0f), Lf);
-        uint32_t k1 = (uint32_t)fminf(fmaxf(__builtin_rintf((x[j].y - mn) * ai), 0.0f), Lf);
-        uint32_t k2 = (uint32_t)fminf(fmaxf(__builtin_rintf((x[j].z - mn) * ai), 0.0f), Lf);
-        uint32_t k3 = (uint32_t)fminf(fmaxf(__builtin_rintf((x[j].w - mn) * ai), 0.0f), Lf);
+        uint32_t k0 = nearest_code(x[j].x, mn, ai, Lf);
+        uint32_t k1 = nearest_code(x[j].y, mn, ai, Lf);
+        uint32_t k2 = nearest_code(x[j].z, mn, ai, Lf);
+        uint32_t k3 = nearest_code(x[j].w, mn, ai, Lf);
         if (!FULL) {   // elements past the end contribute zero bits
             if (el + 0u >= count) k0 = 0u;
             if (el + 1u >= count) k1 = 0u;
@@ -972,9 +978,9 @@ __device__ __forceinline__ void quantize_minmax_wave_block(const QuantizeArgs& a
     clear_words<R, NW>(lane, wave, sm);   // while the loads are in flight
     if (a.scales_in == nullptr) {
         if (c.full) {
-            reduce_minmax<R, WPB, NW, true>(x, c.count, lane, wave, slot, c.seg_lanes, c.rpb, sm, lw);
+            reduce_minmax<R, WPB, NW, true>(x, c.count, lane, wave, slot, c.seg_lanes, c.rpb, sm, lw, a.drop_nan != 0u);
         } else {
-            reduce_minmax<R, WPB, NW, false>(x, c.count, lane, wave, slot, c.seg_lanes, c.rpb, sm, lw);
+            reduce_minmax<R, WPB, NW, false>(x, c.count, lane, wave, slot, c.seg_lanes, c.rpb, sm, lw, a.drop_nan != 0u);
         }
     }
     if (WPB > 1) __syncthreads();   // every wave of the group arrives here exactly once

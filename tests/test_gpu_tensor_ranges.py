@@ -53,3 +53,13 @@ def test_batched_tensor_ranges_mix_one_and_several_workgroups(sizes):
             pk_o, rg_o = ref.quantize_minmax(g.cpu().numpy(), bits, g.numel())
             assert rg.cpu().numpy().tobytes() == rg_o.tobytes()
             assert np.array_equal(to_u32(pk), pk_o)
+
+
+@pytest.mark.parametrize("n", [5000, 16384, 70001])
+def test_values_that_are_not_numbers_take_no_part_in_a_tensors_range(n):
+    g = workloads.normal(n, 1e-2, 9, DEV)
+    g[8:12] = float("nan")           # all that one lane holds
+    rest = torch.cat([g[:8], g[12:]])
+    _, rg = mqgrad.mqg_quantize_minmax_tensor(g, 4)
+    torch.cuda.synchronize()
+    assert rg.tolist() == [rest.min().item(), rest.max().item()]
