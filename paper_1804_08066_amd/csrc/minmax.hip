@@ -13,6 +13,7 @@
 // LDS and whole words are stored coalesced.
 
 #include <mutex>
+#include <type_traits>
 
 #include "decode.h"
 #include "encode.h"
@@ -34,11 +35,19 @@ constexpr uint32_t kSumBlocks = 512;
 // Largest tensor that one workgroup encodes in registers, whatever the encoder: the largest bucket.
 constexpr uint64_t kOneBucketElems = 16384;
 
-// NT lanes own a tile of at most 4*NT*R elements
-template <int R, int NT>
+// A workgroup's tile: whole buckets.
+struct TileGeometry {
+    uint32_t elems;     // buckets * bucket
+    uint32_t buckets;
+    uint32_t magic;     // ceil(65536 / (bucket / 32)): (cell * magic) >> 16 = cell / (bucket / 32) for a tile's cells (at most 224)
+};
+// which parts of a tile can lie past its last element: none, whole quads only, or single elements
+constexpr int kTailNone = 0, kTailQuads = 1, kTailElements = 2;
+
+// NT lanes own a tile of at most 4*NT*R elements.  ONE: the tile is one bucket (of more than 4096 elements).
+template <int R, int NT, bool ONE>
 struct Shared {
     static constexpr uint32_t kCap = 4u * NT * R;
-    static constexpr bool kOneBucket = kCap > 4096u;   // tiles above 4096 elements are chosen for one large bucket
     uint32_t words[kCap * 8u / 32u + 4];
     uint32_t kmin[128];
     uint32_t kmax[128];
@@ -47,15 +56,17 @@ struct Shared {
 };
 
 // one HBM pass: the tile of the gradient into registers
-template <int R, int NT, bool FULL>
+template <int R, int NT, int TAIL>
 __device__ __forceinline__ void load_grad_tile(const float* __restrict__ g, const uint32_t tile_count, float4 (&x)[R]) {
     const uint32_t tid = threadIdx.x;
 #pragma unroll
     for (int j = 0; j < R; ++j) {
         const uint32_t el = 4u * (j * NT + tid);
-        if (FULL || el + 4u <= tile_count) {
+        if (TAIL == kTailNone || el + 4u <= tile_count) {
             const v4f t = __builtin_nontemporal_load(reinterpret_cast<const v4f_a4*>(g + el));
             x[j] = make_float4(t.x, t.y, t.z, t.w);
+        } else if (TAIL == kTailQuads) {
+            x[j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         } else {
             x[j].x = (el + 0u < tile_count) ? g[el + 0] : 0.0f;
             x[j].y = (el + 1u < tile_count) ? g[el + 1] : 0.0f;
@@ -65,8 +76,8 @@ __device__ __forceinline__ void load_grad_tile(const float* __restrict__ g, cons
     }
 }
 
-template <int R, int NT>
-__device__ __forceinline__ void clear_shared(Shared<R, NT>& sm, uint32_t tile_count, uint32_t b) {
+template <int R, int NT, bool ONE>
+__device__ __forceinline__ void clear_shared(Shared<R, NT, ONE>& sm, uint32_t tile_count, uint32_t b) {
     const uint32_t tid = threadIdx.x;
     const uint32_t nwords = (tile_count * b + 31u) >> 5;
     for (uint32_t i = tid; i < nwords; i += NT) sm.words[i] = 0u;
@@ -76,44 +87,53 @@ __device__ __forceinline__ void clear_shared(Shared<R, NT>& sm, uint32_t tile_co
     }
 }
 
+// buckets that begin inside the tile
+template <bool ONE>
+__device__ __forceinline__ uint32_t buckets_in_tile(const uint32_t bucket, const TileGeometry& g, const uint32_t tile_count) {
+    if (ONE) return 1u;
+    return tile_count == g.elems ? g.buckets : (tile_count + bucket - 1u) / bucket;
+}
+
 // The tile, once its values are in registers; enters right after the barrier that follows
 // clear_shared.  range_div: the stored range is [mn, mx] / range_div (1 for a plain encode, W for the
 // server's mean).
 // GIVEN: one (min, max) pair for every element, `given` (the whole-tensor range found by an earlier
 // pass); no range is reduced and none is stored.
-template <int R, int NT, bool FULL, bool GIVEN = false>
-__device__ __forceinline__ void encode_minmax_tile(const QuantizeArgs& a, const uint64_t tile_base,
-                                                   const uint32_t tile_count, const float4 (&x)[R],
-                                                   const float range_div, Shared<R, NT>& sm,
+template <int R, int NT, int TAIL, bool ONE, bool GIVEN = false>
+__device__ __forceinline__ void encode_minmax_tile(const QuantizeArgs& a, const TileGeometry& g, const uint32_t tile,
+                                                   const uint64_t tile_base, const uint32_t tile_count,
+                                                   const float4 (&x)[R], const float range_div, Shared<R, NT, ONE>& sm,
                                                    const float2 given = make_float2(0.0f, 0.0f)) {
     const uint32_t tid = threadIdx.x;
     const float inf = __builtin_inff();
     const uint32_t b = a.bits;
     const uint32_t nwords = (tile_count * b + 31u) >> 5;
 
-    const uint32_t nbt = (GIVEN || Shared<R, NT>::kOneBucket) ? 1u : (tile_count + a.bucket - 1u) / a.bucket;   // buckets in the tile
-    const uint64_t kb0 = GIVEN ? 0u : tile_base / a.bucket;
+    const uint32_t nbt = GIVEN ? 1u : buckets_in_tile<ONE>(a.bucket, g, tile_count);
+    const uint64_t kb0 = GIVEN ? 0u : (uint64_t)tile * g.buckets;
     uint32_t bl[R];
 #pragma unroll
     for (int j = 0; j < R; ++j) {
         const uint32_t el = 4u * (j * NT + tid);
-        bl[j] = (GIVEN || Shared<R, NT>::kOneBucket) ? 0u : (a.bucket_shift >= 0 ? (el >> a.bucket_shift) : (el / a.bucket));
+        bl[j] = (GIVEN || ONE) ? 0u : ((el >> 5) * g.magic) >> 16;
     }
 
     // ---- bucket range: 8-lane cells by DPP; whole waves when a wave's row lies in one bucket -------
     // (every lane of a cell, or of a wave, then holds the same value, and one lane folds it into the
     // bucket's LDS slot: few atomics per slot, since same-address LDS atomics serialize)
-    constexpr bool kOne = Shared<R, NT>::kOneBucket;
     const uint32_t lane = tid & 63u;
-    const bool row_in_bucket = kOne || (a.bucket & 255u) == 0u;   // uniform over the launch
+    const bool row_in_bucket = ONE || (a.bucket & 255u) == 0u;   // uniform over the launch
     if (!GIVEN) {
     float lo[R], hi[R];
 #pragma unroll
     for (int j = 0; j < R; ++j) {
         const uint32_t el = 4u * (j * NT + tid);
-        if (FULL) {
+        if (TAIL != kTailElements) {
+            const bool in = TAIL == kTailNone || el < tile_count;
             lo[j] = quad_min(x[j].x, x[j].y, x[j].z, x[j].w);
             hi[j] = quad_max(x[j].x, x[j].y, x[j].z, x[j].w);
+            lo[j] = in ? lo[j] : inf;
+            hi[j] = in ? hi[j] : -inf;
         } else {   // elements past the end take no part
             const bool v0 = el + 0u < tile_count, v1 = el + 1u < tile_count;
             const bool v2 = el + 2u < tile_count, v3 = el + 3u < tile_count;
@@ -121,7 +141,7 @@ __device__ __forceinline__ void encode_minmax_tile(const QuantizeArgs& a, const 
             hi[j] = quad_max(v0 ? x[j].x : -inf, v1 ? x[j].y : -inf, v2 ? x[j].z : -inf, v3 ? x[j].w : -inf);
         }
     }
-    if (kOne) {   // the tile is one bucket: fold the lane's rows first
+    if (ONE) {   // the tile is one bucket: fold the lane's rows first
 #pragma unroll
         for (int j = 1; j < R; ++j) {
             lo[0] = min_f32(lo[0], lo[j]);
@@ -138,20 +158,20 @@ __device__ __forceinline__ void encode_minmax_tile(const QuantizeArgs& a, const 
     // across lanes on order-preserving integer keys, stage by stage over the rows
     uint32_t kl[R], kh[R];
 #pragma unroll
-    for (int j = 0; j < (kOne ? 1 : R); ++j) {
+    for (int j = 0; j < (ONE ? 1 : R); ++j) {
         kl[j] = cell_min_u32(order_key(lo[j]));
         kh[j] = cell_max_u32(order_key(hi[j]));
     }
     if (row_in_bucket) {
 #pragma unroll
-        for (int j = 0; j < (kOne ? 1 : R); ++j) {
+        for (int j = 0; j < (ONE ? 1 : R); ++j) {
             kl[j] = wave_min_from_cells_u32(kl[j], lane);
             kh[j] = wave_max_from_cells_u32(kh[j], lane);
         }
 #pragma unroll
-        for (int j = 0; j < (kOne ? 1 : R); ++j) {
+        for (int j = 0; j < (ONE ? 1 : R); ++j) {
             const uint32_t row_first = 4u * (j * NT + (tid & ~63u));   // first element of the wave's row
-            if (lane == 0u && (FULL || kOne || row_first < tile_count)) {
+            if (lane == 0u && (TAIL == kTailNone || ONE || row_first < tile_count)) {
                 atomicMin(&sm.kmin[bl[j]], kl[j]);
                 atomicMax(&sm.kmax[bl[j]], kh[j]);
             }
@@ -160,7 +180,7 @@ __device__ __forceinline__ void encode_minmax_tile(const QuantizeArgs& a, const 
 #pragma unroll
         for (int j = 0; j < R; ++j) {
             const uint32_t el = 4u * (j * NT + tid);
-            if ((tid & 7u) == 0u && (FULL || el < tile_count)) {
+            if ((tid & 7u) == 0u && (TAIL == kTailNone || el < tile_count)) {
                 atomicMin(&sm.kmin[bl[j]], kl[j]);
                 atomicMax(&sm.kmax[bl[j]], kh[j]);
             }
@@ -203,14 +223,14 @@ __device__ __forceinline__ void encode_minmax_tile(const QuantizeArgs& a, const 
         uint32_t k1 = nearest_code(x[j].y, mn, ai, Lf);
         uint32_t k2 = nearest_code(x[j].z, mn, ai, Lf);
         uint32_t k3 = nearest_code(x[j].w, mn, ai, Lf);
-        if (!FULL) {   // elements past the end contribute zero bits
+        if (TAIL == kTailElements) {   // elements past the end contribute zero bits
             if (el + 0u >= tile_count) k0 = 0u;
             if (el + 1u >= tile_count) k1 = 0u;
             if (el + 2u >= tile_count) k2 = 0u;
             if (el + 3u >= tile_count) k3 = 0u;
         }
         const uint32_t v = (((((k3 << b) | k2) << b) | k1) << b) | k0;
-        if (FULL || el < tile_count) {
+        if (TAIL == kTailNone || el < tile_count) {
             const uint32_t w0 = (ql >> 3) * b + word_in_cell;
             atomicOr(&sm.words[w0], v << sh);
             if (straddle) atomicOr(&sm.words[w0 + 1u], v >> (32u - sh));
@@ -223,37 +243,39 @@ __device__ __forceinline__ void encode_minmax_tile(const QuantizeArgs& a, const 
 }
 
 // Bucket sizes that are not powers of two (the others take the wave-local kernel in quantize_wave.hip).
-template <int R, int NT>
-__device__ __forceinline__ void quantize_minmax_tile(const QuantizeArgs& a, const uint32_t tile, const uint32_t tile_elems,
-                                                     Shared<R, NT>& sm) {
-    const uint64_t tile_base = (uint64_t)tile * tile_elems;
-    const uint64_t left = a.n - tile_base;
-    const uint32_t tile_count = left < tile_elems ? (uint32_t)left : tile_elems;
+template <int R, int NT, int TAIL, bool ONE>
+__device__ __forceinline__ void quantize_minmax_loaded(const QuantizeArgs& a, const TileGeometry& g, const uint32_t tile,
+                                                       const uint64_t tile_base, const uint32_t tile_count, Shared<R, NT, ONE>& sm) {
     float4 x[R];
-    if (tile_count == Shared<R, NT>::kCap) {
-        load_grad_tile<R, NT, true>(a.grad + tile_base, tile_count, x);
-        clear_shared<R, NT>(sm, tile_count, a.bits);   // while the loads are in flight
-        __syncthreads();
-        encode_minmax_tile<R, NT, true>(a, tile_base, tile_count, x, 1.0f, sm);
+    load_grad_tile<R, NT, TAIL>(a.grad + tile_base, tile_count, x);
+    clear_shared(sm, tile_count, a.bits);   // while the loads are in flight
+    __syncthreads();
+    encode_minmax_tile<R, NT, TAIL>(a, g, tile, tile_base, tile_count, x, 1.0f, sm);
+}
+template <int R, int NT, bool ONE>
+__device__ __forceinline__ void quantize_minmax_tile(const QuantizeArgs& a, const TileGeometry& g, const uint32_t tile,
+                                                     Shared<R, NT, ONE>& sm) {
+    const uint64_t tile_base = (uint64_t)tile * g.elems;
+    const uint64_t left = a.n - tile_base;
+    const uint32_t tile_count = left < g.elems ? (uint32_t)left : g.elems;
+    if ((tile_count & 3u) == 0u) {   // every tile but the one that holds the tensor's ragged end
+        quantize_minmax_loaded<R, NT, kTailQuads>(a, g, tile, tile_base, tile_count, sm);
     } else {
-        load_grad_tile<R, NT, false>(a.grad + tile_base, tile_count, x);
-        clear_shared<R, NT>(sm, tile_count, a.bits);
-        __syncthreads();
-        encode_minmax_tile<R, NT, false>(a, tile_base, tile_count, x, 1.0f, sm);
+        quantize_minmax_loaded<R, NT, kTailElements>(a, g, tile, tile_base, tile_count, sm);
     }
 }
 
-template <int R, int NT>
-__global__ __launch_bounds__(NT) void quantize_minmax_kernel(const QuantizeArgs a, const uint32_t tile_elems) {
-    __shared__ Shared<R, NT> sm;
-    quantize_minmax_tile<R, NT>(a, blockIdx.x, tile_elems, sm);
+template <int R, int NT, bool ONE>
+__global__ __launch_bounds__(NT) void quantize_minmax_kernel(const QuantizeArgs a, const TileGeometry g) {
+    __shared__ Shared<R, NT, ONE> sm;
+    quantize_minmax_tile(a, g, blockIdx.x, sm);
 }
 
 // Several layer tensors in one launch: workgroup -> (tensor, tile of the tensor) through the prefix
 // table of tile counts.
-template <int R, int NT>
-__global__ __launch_bounds__(NT) void quantize_minmax_tensors_kernel(const BatchQuantizeArgs ba) {
-    __shared__ Shared<R, NT> sm;
+template <int R, int NT, bool ONE>
+__global__ __launch_bounds__(NT) void quantize_minmax_tensors_kernel(const BatchQuantizeArgs ba, const TileGeometry g) {
+    __shared__ Shared<R, NT, ONE> sm;
     uint32_t lo = 0, hi = ba.count;          // tile_start[lo] <= blockIdx.x < tile_start[hi]
     while (hi - lo > 1u) {
         const uint32_t mid = (lo + hi) >> 1;
@@ -264,38 +286,40 @@ __global__ __launch_bounds__(NT) void quantize_minmax_tensors_kernel(const Batch
     a.n = ba.t[lo].n;
     a.packed = ba.t[lo].packed;
     a.scales = ba.t[lo].scales;
-    quantize_minmax_tile<R, NT>(a, blockIdx.x - ba.tile_start[lo], ba.tile_elems, sm);
+    quantize_minmax_tile(a, g, blockIdx.x - ba.tile_start[lo], sm);
 }
 
 // The server's re-encoding step of the full exchange (ReceiveQGThenSendQG): the tile's values are the
 // sum over the W workers' de-quantized gradients, decoded from their streams in worker order; the
 // stored range is divided by W.  (step, min) of every worker's buckets of the tile sit in an LDS table.
-template <int NT, bool STRADDLE, bool ONCE>
-__global__ __launch_bounds__(NT) void requantize_minmax_kernel(const RequantArgs ra, const uint32_t tile_elems) {
+// Bound by latency: left alone the compiler took 107 registers (four waves per SIMD) for eight workers' words and
+// their table entries; with four workers' words in flight and seven waves the step of 7.2 M elements, 4
+// workers, 6 bits, bucket 2304 takes 14.9 us instead of 22.2 (17.5 with the new tile alone).
+template <int NT, bool ONE, bool STRADDLE, bool ONCE>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 768 ? 6 : 7, 8))) void requantize_minmax_kernel(const RequantArgs ra, const TileGeometry g) {
     constexpr int R = 4;
-    constexpr int CH = 8;   // workers whose code loads are in flight together
-    __shared__ Shared<R, NT> sm;
+    constexpr int CH = 4;   // workers whose code loads are in flight together
+    __shared__ Shared<R, NT, ONE> sm;
     extern __shared__ float2 s_tab[];   // [W][buckets of the tile]
     const QuantizeArgs& a = ra.q;
     const uint32_t tid = threadIdx.x;
-    const uint64_t tile_base = (uint64_t)blockIdx.x * tile_elems;
+    const uint64_t tile_base = (uint64_t)blockIdx.x * g.elems;
     const uint64_t left = a.n - tile_base;
-    const uint32_t tile_count = left < tile_elems ? (uint32_t)left : tile_elems;
-    const bool full = tile_count == Shared<R, NT>::kCap;
+    const uint32_t tile_count = left < g.elems ? (uint32_t)left : g.elems;
     const uint32_t b = a.bits;
     const float Lf = (float)((1u << b) - 1u);
 
     const decode::CodeWindows<R> cw = decode::code_windows<R, NT>(a.n, tile_base, b, tid);
     decode::CodeRegs<R, CH> c;
     decode::fetch_codes<R, CH, ONCE>(ra.packed, ra.W, 0u, cw, c);   // in flight while the table is filled
-    const uint32_t nbt = Shared<R, NT>::kOneBucket ? 1u : (tile_count + a.bucket - 1u) / a.bucket;
-    const uint64_t kb0 = tile_base / a.bucket;
+    const uint32_t nbt = buckets_in_tile<ONE>(a.bucket, g, tile_count);
+    const uint64_t kb0 = (uint64_t)blockIdx.x * g.buckets;
     for (uint32_t i = tid; i < ra.W * nbt; i += NT) {
         const uint32_t w = i / nbt, kb = i - w * nbt;
         const float2 rg = reinterpret_cast<const float2*>(ra.scales[w])[kb0 + kb];   // (min, max)
         s_tab[i] = make_float2((rg.y - rg.x) / Lf, rg.x);                            // IEEE-correct fp32 division
     }
-    clear_shared<R, NT>(sm, tile_count, b);
+    clear_shared(sm, tile_count, b);
     __syncthreads();
 
     uint32_t bl[R];
@@ -303,7 +327,7 @@ __global__ __launch_bounds__(NT) void requantize_minmax_kernel(const RequantArgs
 #pragma unroll
     for (int j = 0; j < R; ++j) {
         const uint32_t el = 4u * (j * NT + tid);
-        bl[j] = Shared<R, NT>::kOneBucket ? 0u : (a.bucket_shift >= 0 ? (el >> a.bucket_shift) : (el / a.bucket));
+        bl[j] = ONE ? 0u : ((el >> 5) * g.magic) >> 16;
         if (bl[j] >= nbt) bl[j] = nbt - 1u;   // quads past the end: any valid slot
         x[j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     }
@@ -322,10 +346,12 @@ __global__ __launch_bounds__(NT) void requantize_minmax_kernel(const RequantArgs
         }
     }
     const float Wf = (float)ra.W;
-    if (full) {
-        encode_minmax_tile<R, NT, true>(a, tile_base, tile_count, x, Wf, sm);
+    if (tile_count == Shared<R, NT, ONE>::kCap) {
+        encode_minmax_tile<R, NT, kTailNone>(a, g, blockIdx.x, tile_base, tile_count, x, Wf, sm);
+    } else if ((tile_count & 3u) == 0u) {   // elements past the end are decoded but take no part
+        encode_minmax_tile<R, NT, kTailQuads>(a, g, blockIdx.x, tile_base, tile_count, x, Wf, sm);
     } else {
-        encode_minmax_tile<R, NT, false>(a, tile_base, tile_count, x, Wf, sm);   // ignores elements past the end
+        encode_minmax_tile<R, NT, kTailElements>(a, g, blockIdx.x, tile_base, tile_count, x, Wf, sm);
     }
 }
 
@@ -498,9 +524,10 @@ __global__ __launch_bounds__(kFoldThreads) void fold_sum_range_kernel(uint32_t* 
 template <int NT, bool STRADDLE, bool ONCE>
 __global__ __launch_bounds__(NT) void requantize_minmax_tensor_kernel(const RequantArgs ra, const float* sum_range) {
     constexpr int R = 4;
-    constexpr uint32_t kCap = Shared<R, NT>::kCap;
-    __shared__ Shared<R, NT> sm;
+    constexpr uint32_t kCap = Shared<R, NT, false>::kCap;
+    __shared__ Shared<R, NT, false> sm;
     __shared__ float2 s_tab[MQG_MAX_WORKERS];
+    const TileGeometry none = {};   // the range is given: no buckets
     const uint64_t end = blockIdx.x + 1u == gridDim.x ? ra.q.n : (uint64_t)(blockIdx.x + 1u) * kCap;
     // every lane holds the sum's range before the first barrier below; the words are overwritten after it
     const float* slot = sum_range != nullptr ? sum_range
@@ -509,13 +536,13 @@ __global__ __launch_bounds__(NT) void requantize_minmax_tensor_kernel(const Requ
     for (uint64_t tile_base = (uint64_t)blockIdx.x * kCap; tile_base < end; tile_base += kCap) {
         const uint64_t left = end - tile_base;
         const uint32_t tile_count = left < kCap ? (uint32_t)left : kCap;
-        clear_shared<R, NT>(sm, tile_count, ra.q.bits);
+        clear_shared(sm, tile_count, ra.q.bits);
         float4 x[R];
         decode_sum_tile_tensor<NT, STRADDLE, ONCE>(ra, tile_base, s_tab, x);   // its barrier also covers clear_shared
         if (tile_count == kCap) {
-            encode_minmax_tile<R, NT, true, true>(ra.q, tile_base, tile_count, x, 1.0f, sm, range);
+            encode_minmax_tile<R, NT, kTailNone, false, true>(ra.q, none, 0u, tile_base, tile_count, x, 1.0f, sm, range);
         } else {
-            encode_minmax_tile<R, NT, false, true>(ra.q, tile_base, tile_count, x, 1.0f, sm, range);
+            encode_minmax_tile<R, NT, kTailElements, false, true>(ra.q, none, 0u, tile_base, tile_count, x, 1.0f, sm, range);
         }
         __syncthreads();   // the staged words are stored before the next tile clears them
     }
@@ -810,16 +837,53 @@ __global__ __launch_bounds__(64) void sum_squares_finish_kernel(const double* __
     if (threadIdx.x == 0u) out[blockIdx.x] = acc;
 }
 
-template <int R, int NT>
-hipError_t launch_quantize_r(const QuantizeArgs& a, hipStream_t stream) {
-    const uint32_t cap = Shared<R, NT>::kCap;
-    const uint32_t tile_elems = (cap / a.bucket) * a.bucket;   // whole buckets, >= 1 by choice of R
-    const uint64_t tiles = (a.n + tile_elems - 1) / tile_elems;
-    if (tiles > 0x7FFFFFFFull) return hipErrorInvalidValue;
-    const dim3 grid((uint32_t)tiles), block(NT);
-    if (a.scales_in != nullptr) return hipErrorInvalidValue;   // a given range is tiled with a power-of-two bucket
-    hipLaunchKernelGGL((quantize_minmax_kernel<R, NT>), grid, block, 0, stream, a, tile_elems);
-    return hipGetLastError();
+// Calls f(straddle, once): whether a quad of this width can spill over its word, and whether the code words take
+// streaming loads.
+template <class F>
+void with_codes(uint32_t bits, F f) {
+    const bool straddle = (32u % bits) != 0u, once = decode::codes_read_once(bits);
+    if (straddle && once) f(std::true_type{}, std::true_type{});
+    else if (straddle) f(std::true_type{}, std::false_type{});
+    else if (once) f(std::false_type{}, std::true_type{});
+    else f(std::false_type{}, std::false_type{});
+}
+
+// Workgroup size of a bucket: 4 NT R elements with R = 4, so NT / 64 waves of 1024 elements.  Buckets of more than
+// 4096 elements: one per workgroup, the fewest waves that hold it.  Smaller ones: four waves unless five, six or
+// seven are filled at least a tenth better by whole buckets (powers of two fill four).  The exchange of 7 M
+// elements, 4 workers, 4 bits: bucket 2304 (56 % of four waves, 90 % of five) 44.7 -> 35.4 us at 6 bits, 2752 40.0 ->
+// 33.5, 4128 (half of a workgroup of 8192) 40.3 -> 34.1; 4064, which keeps its four waves, 35.9 -> 32.8.
+uint32_t tile_waves(uint32_t bucket) {
+    if (bucket > 4096u) return (bucket + 1023u) / 1024u;
+    uint32_t nw = 4u;
+    for (uint32_t w = 5u; w <= 7u; ++w) {   // used fractions, compared by cross-multiplication
+        if (((w * 1024u) / bucket) * nw * 10u > ((nw * 1024u) / bucket) * w * 11u) nw = w;
+    }
+    return nw;
+}
+TileGeometry tile_geometry(uint32_t bucket) {
+    const uint32_t buckets = (tile_waves(bucket) * 1024u) / bucket, cells = bucket / 32u;
+    return {buckets * bucket, buckets, (65536u + cells - 1u) / cells};
+}
+// Calls f(NT, ONE) with the workgroup size as a compile-time constant.
+template <class F>
+void with_tile_waves(uint32_t bucket, F f) {
+    using std::integral_constant;
+    using several = std::false_type;
+    using one = std::true_type;
+    const uint32_t nw = tile_waves(bucket);
+    if (bucket <= 4096u) {
+        switch (nw) {
+            case 5: return f(integral_constant<int, 320>{}, several{});
+            case 6: return f(integral_constant<int, 384>{}, several{});
+            case 7: return f(integral_constant<int, 448>{}, several{});
+            default: return f(integral_constant<int, 256>{}, several{});
+        }
+    }
+    if (nw <= 6u) return f(integral_constant<int, 384>{}, one{});
+    if (nw <= 8u) return f(integral_constant<int, 512>{}, one{});
+    if (nw <= 12u) return f(integral_constant<int, 768>{}, one{});
+    return f(integral_constant<int, 1024>{}, one{});
 }
 
 template <bool STRADDLE>
@@ -836,55 +900,49 @@ hipError_t launch_aggregate_s(const AggregateArgs& a, hipStream_t stream) {
     return hipGetLastError();
 }
 
-template <int NT>
-hipError_t launch_requant_nt(const RequantArgs& ra, hipStream_t stream) {
-    const uint32_t cap = Shared<4, NT>::kCap;
-    // whole buckets per tile, and at most 4096 table entries (32 KB of LDS)
-    uint32_t nb_tile = cap / ra.q.bucket;
-    const uint32_t max_nb = 4096u / ra.W;   // >= 64
-    if (nb_tile > max_nb) nb_tile = max_nb;
-    const uint32_t tile_elems = nb_tile * ra.q.bucket;
-    const uint64_t tiles = (ra.q.n + tile_elems - 1) / tile_elems;
-    if (tiles > 0x7FFFFFFFull) return hipErrorInvalidValue;
-    const dim3 grid((uint32_t)tiles), block(NT);
-    const size_t lds = sizeof(float2) * ra.W * nb_tile;
-    const bool straddle = (32u % ra.q.bits) != 0u;
-    const bool once = decode::codes_read_once(ra.q.bits);
-    if (straddle) {
-        if (once) hipLaunchKernelGGL((requantize_minmax_kernel<NT, true, true>), grid, block, lds, stream, ra, tile_elems);
-        else hipLaunchKernelGGL((requantize_minmax_kernel<NT, true, false>), grid, block, lds, stream, ra, tile_elems);
-    } else {
-        if (once) hipLaunchKernelGGL((requantize_minmax_kernel<NT, false, true>), grid, block, lds, stream, ra, tile_elems);
-        else hipLaunchKernelGGL((requantize_minmax_kernel<NT, false, false>), grid, block, lds, stream, ra, tile_elems);
-    }
-    return hipGetLastError();
-}
-
 }  // namespace
 
 // ra.scales[w]: worker w's (min, max) pairs; ra.q.scales: (min, max) pairs of the mean
 hipError_t launch_requantize_minmax(const RequantArgs& ra, hipStream_t stream) {
     if (ra.q.n == 0) return hipSuccess;
-    if (ra.q.bucket <= 4096u) return launch_requant_nt<256>(ra, stream);
-    if (ra.q.bucket <= 8192u) return launch_requant_nt<512>(ra, stream);
-    return launch_requant_nt<1024>(ra, stream);
+    TileGeometry g = tile_geometry(ra.q.bucket);
+    const uint32_t max_nb = 4096u / ra.W;   // at most 4096 table entries (32 KB of LDS); >= 64
+    if (g.buckets > max_nb) {
+        g.buckets = max_nb;
+        g.elems = max_nb * ra.q.bucket;
+    }
+    const uint64_t tiles = (ra.q.n + g.elems - 1) / g.elems;
+    if (tiles > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    const size_t lds = sizeof(float2) * ra.W * g.buckets;
+    with_tile_waves(ra.q.bucket, [&](auto nt, auto one) {
+        with_codes(ra.q.bits, [&](auto straddle, auto once) {
+            constexpr int NT = decltype(nt)::value;
+            hipLaunchKernelGGL((requantize_minmax_kernel<NT, decltype(one)::value, decltype(straddle)::value, decltype(once)::value>),
+                               dim3((uint32_t)tiles), dim3(NT), lds, stream, ra, g);
+        });
+    });
+    return hipGetLastError();
 }
 
 // a.scales: 2 floats (min, max) per bucket; a.scale_mode, key, iteration, worker, elem_base unused
 hipError_t launch_quantize_minmax(const QuantizeArgs& a, hipStream_t stream) {
     if (a.n == 0) return hipSuccess;
     if (quantize_minmax_wave_supported(a)) return launch_quantize_minmax_wave(a, stream);   // power-of-two buckets
-    // four float4 per lane at every bucket size; larger buckets take larger workgroups
-    if (a.bucket <= 4096u) return launch_quantize_r<4, 256>(a, stream);
-    if (a.bucket <= 8192u) return launch_quantize_r<4, 512>(a, stream);
-    return launch_quantize_r<4, 1024>(a, stream);
+    if (a.scales_in != nullptr) return hipErrorInvalidValue;   // a given range is tiled with a power-of-two bucket
+    const TileGeometry g = tile_geometry(a.bucket);
+    const uint64_t tiles = (a.n + g.elems - 1) / g.elems;
+    if (tiles > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    with_tile_waves(a.bucket, [&](auto nt, auto one) {
+        constexpr int NT = decltype(nt)::value;
+        hipLaunchKernelGGL((quantize_minmax_kernel<4, NT, decltype(one)::value>), dim3((uint32_t)tiles), dim3(NT), 0, stream, a, g);
+    });
+    return hipGetLastError();
 }
 
-// The general tile of the batched encoder: R = 4 with the workgroup size that the bucket needs.
+// The tile of the batched encoder.
 uint32_t quantize_minmax_batch_tile(uint32_t bucket, int bucket_shift) {
     if (bucket_shift >= 5) return quantize_minmax_wave_block_elems(bucket);
-    const uint32_t cap = bucket <= 4096u ? Shared<4, 256>::kCap : (bucket <= 8192u ? Shared<4, 512>::kCap : Shared<4, 1024>::kCap);
-    return (cap / bucket) * bucket;
+    return tile_geometry(bucket).elems;
 }
 
 // a.t[i].scales: (min, max) pairs of tensor i's buckets; a.t[i].scales_in: nullptr, or the ONE (min, max)
@@ -893,10 +951,11 @@ uint32_t quantize_minmax_batch_tile(uint32_t bucket, int bucket_shift) {
 hipError_t launch_quantize_minmax_tensors(const BatchQuantizeArgs& a, uint32_t tiles, hipStream_t stream) {
     if (tiles == 0) return hipSuccess;
     if (a.common.bucket_shift >= 5) return launch_quantize_minmax_tensors_wave(a, tiles, stream);
-    const dim3 grid(tiles);
-    if (a.common.bucket <= 4096u) hipLaunchKernelGGL((quantize_minmax_tensors_kernel<4, 256>), grid, dim3(256), 0, stream, a);
-    else if (a.common.bucket <= 8192u) hipLaunchKernelGGL((quantize_minmax_tensors_kernel<4, 512>), grid, dim3(512), 0, stream, a);
-    else hipLaunchKernelGGL((quantize_minmax_tensors_kernel<4, 1024>), grid, dim3(1024), 0, stream, a);
+    const TileGeometry g = tile_geometry(a.common.bucket);
+    with_tile_waves(a.common.bucket, [&](auto nt, auto one) {
+        constexpr int NT = decltype(nt)::value;
+        hipLaunchKernelGGL((quantize_minmax_tensors_kernel<4, NT, decltype(one)::value>), dim3(tiles), dim3(NT), 0, stream, a, g);
+    });
     return hipGetLastError();
 }
 
