@@ -1,4 +1,5 @@
-"""Build libmqgrad.so (gfx950 kernels + C ABI + host MDP) in-tree with hipcc, and libmqgrad_bench.so
+"""Build libmqgrad.so (gfx950 kernels + C ABI + host MDP) in-tree with hipcc, _marshal.so (the Python
+binding's argument tables) and libmqgrad_bench.so
 (the streaming kernels that bench.py uses as its measured ceilings; not part of the library)."""
 import os
 import shutil
@@ -13,6 +14,8 @@ LIB = os.path.join(HERE, "libmqgrad.so")
 BENCH_LIB = os.path.join(HERE, "libmqgrad_bench.so")
 SOURCES = ["api.hip", "quantize_pack.hip", "quantize_wave.hip", "aggregate_update.hip", "minmax.hip", "mdp.cpp"]
 BENCH_SOURCES = ["bench_stream.hip"]
+MARSHAL = os.path.join(HERE, "_marshal.so")   # the binding's argument tables: host code against torch and Python
+MARSHAL_SOURCE = "marshal.cpp"
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
@@ -36,7 +39,7 @@ def needs_build():
     """True when a library is missing or older than any of its sources or headers."""
     deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith((".h", ".hip", ".cpp"))] + \
         [os.path.join(ROOT, "include", "mqgrad.h")]
-    for lib in (LIB, BENCH_LIB):
+    for lib in (LIB, BENCH_LIB, MARSHAL):
         if not os.path.exists(lib):
             return True
         t = os.path.getmtime(lib)
@@ -61,11 +64,42 @@ def _link(names, out, tmpdir, verbose, extra_flags):
     os.replace(tmp, out)
 
 
+def _build_marshal(verbose):
+    import sysconfig
+    import torch
+    at = os.path.dirname(torch.__file__)
+    inc = [os.path.join(at, "include"), os.path.join(at, "include", "torch", "csrc", "api", "include"), sysconfig.get_paths()["include"]]
+    tmp = MARSHAL + ".tmp.%d" % os.getpid()
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch.compiled_with_cxx11_abi()), "-I", os.path.join(ROOT, "include"),
+           *[x for d in inc for x in ("-isystem", d)], os.path.join(CSRC, MARSHAL_SOURCE),
+           "-L", os.path.join(at, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-o", tmp]
+    if verbose:
+        print(" ".join(cmd))
+    subprocess.check_call(cmd)
+    os.replace(tmp, MARSHAL)
+
+
+def load_marshal():
+    """The _marshal module (built first only if it does not exist)."""
+    import importlib.machinery
+    import importlib.util
+    if not os.path.exists(MARSHAL):
+        _build_marshal(False)
+    loader = importlib.machinery.ExtensionFileLoader("_marshal", MARSHAL)
+    module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_marshal", loader))
+    loader.exec_module(module)
+    return module
+
+
 def build(verbose=False, extra_flags=()):
-    """Compile every source (one hipcc process per file, in parallel) and link both libraries."""
+    """Compile every source (one hipcc process per file, in parallel) and link the libraries."""
     tmpdir = tempfile.mkdtemp(prefix="mqgrad_build_")
     try:
-        _link(SOURCES, LIB, tmpdir, verbose, extra_flags)
+        with ThreadPoolExecutor(max_workers=1) as pool:
+            marshal = pool.submit(_build_marshal, verbose)
+            _link(SOURCES, LIB, tmpdir, verbose, extra_flags)
+            marshal.result()
         _link(BENCH_SOURCES, BENCH_LIB, tmpdir, verbose, extra_flags)
     finally:
         shutil.rmtree(tmpdir, ignore_errors=True)

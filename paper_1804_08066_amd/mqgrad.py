@@ -69,6 +69,7 @@ MQG_MAX_TENSORS = 32
 MQG_MAX_TENSOR_POINTERS = 256
 
 _lib = None
+_marshal = None   # argument tables in native code (csrc/marshal.cpp), loaded with the library
 
 
 def lib():
@@ -85,7 +86,7 @@ def lib():
             import warnings
             warnings.warn("libmqgrad.so is older than its sources: run paper_1804_08066_amd/build.py (loading the stale library)")
     L = C.CDLL(path)
-    vp, u32, u64, f32 = C.c_void_p, C.c_uint32, C.c_uint64, C.c_float
+    vp, u32, u64, f32 = C.c_void_p, C.c_uint32, C.c_uint64, C.c_float   # vp also takes HOST tables: ctypes arrays, bytes
     L.mqg_status_string.argtypes = [C.c_int]
     L.mqg_status_string.restype = C.c_char_p
     L.mqg_num_buckets.argtypes = [u64, u32]
@@ -100,41 +101,41 @@ def lib():
     L.mqg_quantize_mode.restype = C.c_int
     L.mqg_quantize_with_scales.argtypes = [vp, u64, u32, u32, u64, u32, u32, u64, vp, vp, vp, vp]
     L.mqg_quantize_with_scales.restype = C.c_int
-    L.mqg_aggregate_update.argtypes = [C.POINTER(vp), C.POINTER(vp), u32, u64, u32, u32, f32, vp, vp]
+    L.mqg_aggregate_update.argtypes = [vp, vp, u32, u64, u32, u32, f32, vp, vp]
     L.mqg_aggregate_update.restype = C.c_int
-    L.mqg_aggregate_update_from.argtypes = [C.POINTER(vp), C.POINTER(vp), u32, u64, u32, u32, f32, vp, C.c_int, vp]
+    L.mqg_aggregate_update_from.argtypes = [vp, vp, u32, u64, u32, u32, f32, vp, C.c_int, vp]
     L.mqg_aggregate_update_from.restype = C.c_int
-    L.mqg_aggregate_requantize.argtypes = [C.POINTER(vp), C.POINTER(vp), u32, u64, u32, u32, u64, u32, u32, u64, vp, vp, vp]
+    L.mqg_aggregate_requantize.argtypes = [vp, vp, u32, u64, u32, u32, u64, u32, u32, u64, vp, vp, vp]
     L.mqg_aggregate_requantize.restype = C.c_int
-    L.mqg_aggregate_requantize_mode.argtypes = [C.POINTER(vp), C.POINTER(vp), u32, u64, u32, u32, C.c_int, u64, u32, u32, u64, vp, vp, vp]
+    L.mqg_aggregate_requantize_mode.argtypes = [vp, vp, u32, u64, u32, u32, C.c_int, u64, u32, u32, u64, vp, vp, vp]
     L.mqg_aggregate_requantize_mode.restype = C.c_int
     L.mqg_dequantize_update.argtypes = [vp, vp, u64, u32, u32, f32, vp, vp]
     L.mqg_dequantize_update.restype = C.c_int
-    L.mqg_quantize_tensors.argtypes = [C.POINTER(QuantizeItem), u32, u32, u32, u64, u32, u32, vp]
+    L.mqg_quantize_tensors.argtypes = [vp, u32, u32, u32, u64, u32, u32, vp]
     L.mqg_quantize_tensors.restype = C.c_int
-    L.mqg_quantize_tensors_mode.argtypes = [C.POINTER(QuantizeItem), u32, u32, u32, C.c_int, u64, u32, u32, vp]
+    L.mqg_quantize_tensors_mode.argtypes = [vp, u32, u32, u32, C.c_int, u64, u32, u32, vp]
     L.mqg_quantize_tensors_mode.restype = C.c_int
-    L.mqg_aggregate_update_tensors.argtypes = [C.POINTER(UpdateItem), u32, u32, u32, u32, f32, vp]
+    L.mqg_aggregate_update_tensors.argtypes = [vp, u32, u32, u32, u32, f32, vp]
     L.mqg_aggregate_update_tensors.restype = C.c_int
-    L.mqg_aggregate_update_minmax_tensors.argtypes = [C.POINTER(UpdateItem), u32, u32, u32, u32, f32, vp]
+    L.mqg_aggregate_update_minmax_tensors.argtypes = [vp, u32, u32, u32, u32, f32, vp]
     L.mqg_aggregate_update_minmax_tensors.restype = C.c_int
-    L.mqg_quantize_minmax_tensors.argtypes = [C.POINTER(QuantizeItem), u32, u32, u32, vp]
+    L.mqg_quantize_minmax_tensors.argtypes = [vp, u32, u32, u32, vp]
     L.mqg_quantize_minmax_tensors.restype = C.c_int
     L.mqg_quantize_minmax.argtypes = [vp, u64, u32, u32, vp, vp, vp]
     L.mqg_quantize_minmax.restype = C.c_int
-    L.mqg_aggregate_update_minmax.argtypes = [C.POINTER(vp), C.POINTER(vp), u32, u64, u32, u32, f32, vp, vp]
+    L.mqg_aggregate_update_minmax.argtypes = [vp, vp, u32, u64, u32, u32, f32, vp, vp]
     L.mqg_aggregate_update_minmax.restype = C.c_int
-    L.mqg_aggregate_requantize_minmax.argtypes = [C.POINTER(vp), C.POINTER(vp), u32, u64, u32, u32, vp, vp, vp]
+    L.mqg_aggregate_requantize_minmax.argtypes = [vp, vp, u32, u64, u32, u32, vp, vp, vp]
     L.mqg_aggregate_requantize_minmax.restype = C.c_int
     L.mqg_tensor_range.argtypes = [vp, u64, vp, vp]
     L.mqg_tensor_range.restype = C.c_int
     L.mqg_quantize_minmax_tensor.argtypes = [vp, u64, u32, vp, vp, vp]
     L.mqg_quantize_minmax_tensor.restype = C.c_int
-    L.mqg_aggregate_update_minmax_tensor.argtypes = [C.POINTER(vp), C.POINTER(vp), u32, u64, u32, f32, vp, vp]
+    L.mqg_aggregate_update_minmax_tensor.argtypes = [vp, vp, u32, u64, u32, f32, vp, vp]
     L.mqg_aggregate_update_minmax_tensor.restype = C.c_int
-    L.mqg_aggregate_requantize_minmax_tensor.argtypes = [C.POINTER(vp), C.POINTER(vp), u32, u64, u32, vp, vp, vp]
+    L.mqg_aggregate_requantize_minmax_tensor.argtypes = [vp, vp, u32, u64, u32, vp, vp, vp]
     L.mqg_aggregate_requantize_minmax_tensor.restype = C.c_int
-    L.mqg_aggregate_mean.argtypes = [C.POINTER(vp), C.POINTER(vp), u32, u64, u32, u32, vp, vp]
+    L.mqg_aggregate_mean.argtypes = [vp, vp, u32, u64, u32, u32, vp, vp]
     L.mqg_aggregate_mean.restype = C.c_int
     L.mqg_sum_squares.argtypes = [vp, u64, vp, vp]
     L.mqg_sum_squares.restype = C.c_int
@@ -174,6 +175,8 @@ def lib():
     L.mqg_mdp_set_weights.restype = None
     L.mqg_mdp_q_values.argtypes = [vp, C.POINTER(C.c_double), C.POINTER(C.c_double)]
     L.mqg_mdp_q_values.restype = None
+    global _marshal
+    _marshal = _build.load_marshal()
     _lib = L
     return L
 
@@ -191,14 +194,56 @@ def mqg_packed_words(n, bits):
 
 
 def _stream_handle(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream)
+    if stream is None:   # torch.cuda.current_stream() without the Stream object around it
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def _check(t, dtype, what):
     if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == dtype and t.is_contiguous()):
         raise TypeError("%s must be a contiguous CUDA tensor of %s" % (what, dtype))
+
+
+_SCALES, _PAIRS, _ONE_PAIR = 0, 1, 2   # floats beside the code words: one scale per bucket, a (min, max) pair per bucket, one pair
+
+
+def _num_floats(n, bucket, kind):
+    return mqg_num_buckets(n, bucket) if kind == _SCALES else (2 * mqg_num_buckets(n, bucket) if kind == _PAIRS else 2)
+
+
+def _encoder_args(grad, packed_out, floats_out, bits, bucket, kind):
+    """(n, grad, packed, floats): sizes and addresses of an encoder call whose buffers exist, checked."""
+    L = lib()
+    args = _marshal.stream(grad, packed_out, floats_out, bits, bucket, kind)
+    if args is not None:
+        return L, args
+    _check(grad, torch.float32, "grad")
+    n = grad.numel()
+    _check(packed_out, torch.int32, "packed_out")
+    _check(floats_out, torch.float32, "scales_out" if kind == _SCALES else ("ranges_out" if kind == _PAIRS else "range_out"))
+    if packed_out.numel() < mqg_packed_words(n, bits) or floats_out.numel() < _num_floats(n, bucket, kind):
+        raise ValueError("output buffers too small")
+    return L, (n, grad.data_ptr(), packed_out.data_ptr(), floats_out.data_ptr())
+
+
+def _worker_arrays(packed, scales, n, bits, bucket, kind=_SCALES):
+    """(W, code-word pointers, range pointers): HOST tables of the W workers' streams, checked."""
+    lib()
+    arrays = _marshal.pointers(packed, scales, n, bits, bucket, kind)
+    if arrays is not None:
+        return arrays
+    W = len(packed)
+    name = "scales" if kind == _SCALES else "ranges"
+    if W != len(scales):
+        raise ValueError("packed and %s must have one entry per worker" % name)
+    for p, s in zip(packed, scales):
+        _check(p, torch.int32, "packed[w]")
+        _check(s, torch.float32, name + "[w]")
+        if p.numel() < mqg_packed_words(n, bits) or s.numel() < _num_floats(n, bucket, kind):
+            raise ValueError("a worker's buffers are too small for n")
+    pa = (C.c_void_p * max(W, 1))(*[p.data_ptr() for p in packed])
+    sa = (C.c_void_p * max(W, 1))(*[s.data_ptr() for s in scales])
+    return W, pa, sa
 
 
 def alloc_outputs(n, bits, bucket, device):
@@ -213,34 +258,24 @@ def mqg_quantize(grad, bits, bucket, seed, iteration=0, worker=0, elem_base=0,
 
     mode selects mqg_quantize_mode; scales_in selects mqg_quantize_with_scales; dest (MQG_CODES_KEEP_CACHED /
     MQG_CODES_TO_MEMORY) selects mqg_quantize_to."""
-    _check(grad, torch.float32, "grad")
-    n = grad.numel()
     if packed_out is None or scales_out is None:
-        p, s = alloc_outputs(n, bits, bucket, grad.device)
+        _check(grad, torch.float32, "grad")
+        p, s = alloc_outputs(grad.numel(), bits, bucket, grad.device)
         packed_out = p if packed_out is None else packed_out
         scales_out = s if scales_out is None else scales_out
-    _check(packed_out, torch.int32, "packed_out")
-    _check(scales_out, torch.float32, "scales_out")
-    if packed_out.numel() < mqg_packed_words(n, bits) or scales_out.numel() < mqg_num_buckets(n, bucket):
-        raise ValueError("output buffers too small")
-    L = lib()
+    L, (n, gp, pp, sp) = _encoder_args(grad, packed_out, scales_out, bits, bucket, _SCALES)
     sh = _stream_handle(stream)
     if scales_in is not None:
         _check(scales_in, torch.float32, "scales_in")
         if scales_in.numel() < mqg_num_buckets(n, bucket):
             raise ValueError("scales_in too small")
-        st = L.mqg_quantize_with_scales(grad.data_ptr(), n, bits, bucket, seed, iteration, worker,
-                                        elem_base, scales_in.data_ptr(), packed_out.data_ptr(),
-                                        scales_out.data_ptr(), sh)
+        st = L.mqg_quantize_with_scales(gp, n, bits, bucket, seed, iteration, worker, elem_base, scales_in.data_ptr(), pp, sp, sh)
     elif mode is not None:
-        st = L.mqg_quantize_mode(grad.data_ptr(), n, bits, bucket, int(mode), seed, iteration, worker,
-                                 elem_base, packed_out.data_ptr(), scales_out.data_ptr(), sh)
+        st = L.mqg_quantize_mode(gp, n, bits, bucket, int(mode), seed, iteration, worker, elem_base, pp, sp, sh)
     elif dest is not None:
-        st = L.mqg_quantize_to(grad.data_ptr(), n, bits, bucket, seed, iteration, worker, elem_base,
-                               packed_out.data_ptr(), scales_out.data_ptr(), int(dest), sh)
+        st = L.mqg_quantize_to(gp, n, bits, bucket, seed, iteration, worker, elem_base, pp, sp, int(dest), sh)
     else:
-        st = L.mqg_quantize(grad.data_ptr(), n, bits, bucket, seed, iteration, worker, elem_base,
-                            packed_out.data_ptr(), scales_out.data_ptr(), sh)
+        st = L.mqg_quantize(gp, n, bits, bucket, seed, iteration, worker, elem_base, pp, sp, sh)
     if st != MQG_OK:
         raise MqgError(st, "mqg_quantize")
     return packed_out, scales_out
@@ -250,37 +285,14 @@ def mqg_aggregate_update(packed, scales, n, bits, bucket, lr, params, stream=Non
     """Server side.  packed / scales: lists of W CUDA tensors; params: fp32 CUDA tensor, updated in place.
     origin: MQG_CODES_FROM_MEMORY when the streams were not written by this GPU just before (same results,
     streaming loads of the code words at every width)."""
-    W = len(packed)
-    if W != len(scales):
-        raise ValueError("packed and scales must have one entry per worker")
+    W, pa, sa = _worker_arrays(packed, scales, n, bits, bucket)
     _check(params, torch.float32, "params")
     if params.numel() != n:
         raise ValueError("params must have n elements")
-    for p, s in zip(packed, scales):
-        _check(p, torch.int32, "packed[w]")
-        _check(s, torch.float32, "scales[w]")
-        if p.numel() < mqg_packed_words(n, bits) or s.numel() < mqg_num_buckets(n, bucket):
-            raise ValueError("a worker's buffers are too small for n")
-    pa = (C.c_void_p * max(W, 1))(*[p.data_ptr() for p in packed])
-    sa = (C.c_void_p * max(W, 1))(*[s.data_ptr() for s in scales])
     st = lib().mqg_aggregate_update_from(pa, sa, W, n, bits, bucket, lr, params.data_ptr(), int(origin), _stream_handle(stream))
     if st != MQG_OK:
         raise MqgError(st, "mqg_aggregate_update")
     return params
-
-
-def _worker_arrays(packed, scales, n, bits, bucket):
-    W = len(packed)
-    if W != len(scales):
-        raise ValueError("packed and scales must have one entry per worker")
-    for p, s in zip(packed, scales):
-        _check(p, torch.int32, "packed[w]")
-        _check(s, torch.float32, "scales[w]")
-        if p.numel() < mqg_packed_words(n, bits) or s.numel() < mqg_num_buckets(n, bucket):
-            raise ValueError("a worker's buffers are too small for n")
-    pa = (C.c_void_p * max(W, 1))(*[p.data_ptr() for p in packed])
-    sa = (C.c_void_p * max(W, 1))(*[s.data_ptr() for s in scales])
-    return W, pa, sa
 
 
 def mqg_aggregate_mean(packed, scales, n, bits, bucket, mean_out=None, stream=None):
@@ -338,12 +350,25 @@ def mqg_quantize_tensors(grads, bits, bucket, seed, iteration=0, worker=0, elem_
     scale_mode: the bucket range of the layers whose scales are computed; scales_in: optional list with, per
     layer, None or a float32 tensor of scales to use instead.  Returns a list of (packed, scales) per layer."""
     count = len(grads)
+    if outputs is None:
+        outputs = [alloc_outputs(g.numel(), bits, bucket, g.device) for g in grads]
+    lib()
+    items = _marshal.quantize_items(grads, outputs, elem_bases, bits, bucket, _SCALES) if scales_in is None else None
+    if items is None:
+        items = _quantize_items(grads, bits, bucket, elem_bases, outputs, scales_in)
+    st = lib().mqg_quantize_tensors_mode(items, count, bits, bucket, int(scale_mode), seed, iteration, worker,
+                                         _stream_handle(stream))
+    if st != MQG_OK:
+        raise MqgError(st, "mqg_quantize_tensors")
+    return outputs
+
+
+def _quantize_items(grads, bits, bucket, elem_bases, outputs, scales_in):
+    count = len(grads)
     if scales_in is None:
         scales_in = [None] * count
     if elem_bases is None:
         elem_bases = [0] * count
-    if outputs is None:
-        outputs = [alloc_outputs(g.numel(), bits, bucket, g.device) for g in grads]
     items = (QuantizeItem * max(count, 1))()
     for i, g in enumerate(grads):
         _check(g, torch.float32, "grads[%d]" % i)
@@ -359,11 +384,7 @@ def mqg_quantize_tensors(grads, bits, bucket, seed, iteration=0, worker=0, elem_
                 raise ValueError("scales_in too small")
         items[i] = QuantizeItem(g.data_ptr(), g.numel(), elem_bases[i], p.data_ptr(), s.data_ptr(),
                                 si.data_ptr() if si is not None else None)
-    st = lib().mqg_quantize_tensors_mode(items, count, bits, bucket, int(scale_mode), seed, iteration, worker,
-                                         _stream_handle(stream))
-    if st != MQG_OK:
-        raise MqgError(st, "mqg_quantize_tensors")
-    return outputs
+    return items
 
 
 def mqg_aggregate_update_tensors(layers, W, bits, bucket, lr, stream=None):
@@ -381,6 +402,10 @@ def mqg_aggregate_update_tensors(layers, W, bits, bucket, lr, stream=None):
 def _update_items(layers, W, bits, bucket, ranges):
     """The HOST table of a batched server step.  ranges: 0 = one scale per bucket, 1 = a (min, max) pair per
     bucket, 2 = one (min, max) pair per layer.  Returns (items, objects to keep alive during the call)."""
+    lib()
+    table = _marshal.update_items(layers, W, bits, bucket, ranges)
+    if table is not None:
+        return table, None
     count = len(layers)
     items = (UpdateItem * max(count, 1))()
     keep = []
@@ -424,15 +449,18 @@ def mqg_quantize_minmax_tensors(grads, bits, bucket, outputs=None, stream=None):
     if outputs is None:
         outputs = [(torch.empty(mqg_packed_words(g.numel(), bits), dtype=torch.int32, device=g.device),
                     torch.empty(nr(g.numel()), dtype=torch.float32, device=g.device)) for g in grads]
-    items = (QuantizeItem * max(count, 1))()
-    for i, g in enumerate(grads):
-        _check(g, torch.float32, "grads[%d]" % i)
-        p, r = outputs[i]
-        _check(p, torch.int32, "packed_out")
-        _check(r, torch.float32, "ranges_out")
-        if p.numel() < mqg_packed_words(g.numel(), bits) or r.numel() < nr(g.numel()):
-            raise ValueError("output buffers too small")
-        items[i] = QuantizeItem(g.data_ptr(), g.numel(), 0, p.data_ptr(), r.data_ptr(), None)
+    lib()
+    items = _marshal.quantize_items(grads, outputs, None, bits, bucket, _PAIRS if bucket else _ONE_PAIR)
+    if items is None:
+        items = (QuantizeItem * max(count, 1))()
+        for i, g in enumerate(grads):
+            _check(g, torch.float32, "grads[%d]" % i)
+            p, r = outputs[i]
+            _check(p, torch.int32, "packed_out")
+            _check(r, torch.float32, "ranges_out")
+            if p.numel() < mqg_packed_words(g.numel(), bits) or r.numel() < nr(g.numel()):
+                raise ValueError("output buffers too small")
+            items[i] = QuantizeItem(g.data_ptr(), g.numel(), 0, p.data_ptr(), r.data_ptr(), None)
     st = lib().mqg_quantize_minmax_tensors(items, count, bits, bucket, _stream_handle(stream))
     if st != MQG_OK:
         raise MqgError(st, "mqg_quantize_minmax_tensors")
@@ -451,18 +479,14 @@ def mqg_aggregate_update_minmax_tensors(layers, W, bits, bucket, lr, stream=None
 
 def mqg_quantize_minmax(grad, bits, bucket, packed_out=None, ranges_out=None, stream=None):
     """Deterministic [min, max] range-linear encode. Returns (packed int32 words, ranges fp32 (min, max) pairs)."""
-    _check(grad, torch.float32, "grad")
-    n = grad.numel()
+    if packed_out is None or ranges_out is None:
+        _check(grad, torch.float32, "grad")
     if packed_out is None:
-        packed_out = torch.empty(mqg_packed_words(n, bits), dtype=torch.int32, device=grad.device)
+        packed_out = torch.empty(mqg_packed_words(grad.numel(), bits), dtype=torch.int32, device=grad.device)
     if ranges_out is None:
-        ranges_out = torch.empty(2 * mqg_num_buckets(n, bucket), dtype=torch.float32, device=grad.device)
-    _check(packed_out, torch.int32, "packed_out")
-    _check(ranges_out, torch.float32, "ranges_out")
-    if packed_out.numel() < mqg_packed_words(n, bits) or ranges_out.numel() < 2 * mqg_num_buckets(n, bucket):
-        raise ValueError("output buffers too small")
-    st = lib().mqg_quantize_minmax(grad.data_ptr(), n, bits, bucket, packed_out.data_ptr(), ranges_out.data_ptr(),
-                                   _stream_handle(stream))
+        ranges_out = torch.empty(2 * mqg_num_buckets(grad.numel(), bucket), dtype=torch.float32, device=grad.device)
+    L, (n, gp, pp, rp) = _encoder_args(grad, packed_out, ranges_out, bits, bucket, _PAIRS)
+    st = L.mqg_quantize_minmax(gp, n, bits, bucket, pp, rp, _stream_handle(stream))
     if st != MQG_OK:
         raise MqgError(st, "mqg_quantize_minmax")
     return packed_out, ranges_out
@@ -472,16 +496,7 @@ def mqg_aggregate_update_minmax(packed, ranges, n, bits, bucket, lr, params, str
     _check(params, torch.float32, "params")
     if params.numel() != n:
         raise ValueError("params must have n elements")
-    W = len(packed)
-    if W != len(ranges):
-        raise ValueError("packed and ranges must have one entry per worker")
-    for p, r in zip(packed, ranges):
-        _check(p, torch.int32, "packed[w]")
-        _check(r, torch.float32, "ranges[w]")
-        if p.numel() < mqg_packed_words(n, bits) or r.numel() < 2 * mqg_num_buckets(n, bucket):
-            raise ValueError("a worker's buffers are too small for n")
-    pa = (C.c_void_p * max(W, 1))(*[p.data_ptr() for p in packed])
-    ra = (C.c_void_p * max(W, 1))(*[r.data_ptr() for r in ranges])
+    W, pa, ra = _worker_arrays(packed, ranges, n, bits, bucket, _PAIRS)
     st = lib().mqg_aggregate_update_minmax(pa, ra, W, n, bits, bucket, lr, params.data_ptr(), _stream_handle(stream))
     if st != MQG_OK:
         raise MqgError(st, "mqg_aggregate_update_minmax")
@@ -489,14 +504,7 @@ def mqg_aggregate_update_minmax(packed, ranges, n, bits, bucket, lr, params, str
 
 def mqg_aggregate_requantize_minmax(packed, ranges, n, bits, bucket, packed_out=None, ranges_out=None, stream=None):
     """Server side of the full exchange with the [min, max] encoding. Returns (packed, ranges) of the mean."""
-    W = len(packed)
-    if W != len(ranges):
-        raise ValueError("packed and ranges must have one entry per worker")
-    for p, r in zip(packed, ranges):
-        _check(p, torch.int32, "packed[w]")
-        _check(r, torch.float32, "ranges[w]")
-        if p.numel() < mqg_packed_words(n, bits) or r.numel() < 2 * mqg_num_buckets(n, bucket):
-            raise ValueError("a worker's buffers are too small for n")
+    W, pa, ra = _worker_arrays(packed, ranges, n, bits, bucket, _PAIRS)
     dev = packed[0].device
     if packed_out is None:
         packed_out = torch.empty(mqg_packed_words(n, bits), dtype=torch.int32, device=dev)
@@ -506,8 +514,6 @@ def mqg_aggregate_requantize_minmax(packed, ranges, n, bits, bucket, packed_out=
     _check(ranges_out, torch.float32, "ranges_out")
     if packed_out.numel() < mqg_packed_words(n, bits) or ranges_out.numel() < 2 * mqg_num_buckets(n, bucket):
         raise ValueError("output buffers too small")
-    pa = (C.c_void_p * max(W, 1))(*[p.data_ptr() for p in packed])
-    ra = (C.c_void_p * max(W, 1))(*[r.data_ptr() for r in ranges])
     st = lib().mqg_aggregate_requantize_minmax(pa, ra, W, n, bits, bucket, packed_out.data_ptr(),
                                                ranges_out.data_ptr(), _stream_handle(stream))
     if st != MQG_OK:
@@ -529,18 +535,14 @@ def mqg_tensor_range(grad, range_out=None, stream=None):
 
 def mqg_quantize_minmax_tensor(grad, bits, packed_out=None, range_out=None, stream=None):
     """The paper's encoder: one [min, max] for the whole tensor. Returns (packed, range)."""
-    _check(grad, torch.float32, "grad")
-    n = grad.numel()
+    if packed_out is None or range_out is None:
+        _check(grad, torch.float32, "grad")
     if packed_out is None:
-        packed_out = torch.empty(mqg_packed_words(n, bits), dtype=torch.int32, device=grad.device)
+        packed_out = torch.empty(mqg_packed_words(grad.numel(), bits), dtype=torch.int32, device=grad.device)
     if range_out is None:
         range_out = torch.zeros(2, dtype=torch.float32, device=grad.device)
-    _check(packed_out, torch.int32, "packed_out")
-    _check(range_out, torch.float32, "range_out")
-    if packed_out.numel() < mqg_packed_words(n, bits) or range_out.numel() < 2:
-        raise ValueError("output buffers too small")
-    st = lib().mqg_quantize_minmax_tensor(grad.data_ptr(), n, bits, packed_out.data_ptr(), range_out.data_ptr(),
-                                          _stream_handle(stream))
+    L, (n, gp, pp, rp) = _encoder_args(grad, packed_out, range_out, bits, 0, _ONE_PAIR)
+    st = L.mqg_quantize_minmax_tensor(gp, n, bits, pp, rp, _stream_handle(stream))
     if st != MQG_OK:
         raise MqgError(st, "mqg_quantize_minmax_tensor")
     return packed_out, range_out
@@ -550,16 +552,7 @@ def mqg_aggregate_update_minmax_tensor(packed, ranges, n, bits, lr, params, stre
     _check(params, torch.float32, "params")
     if params.numel() != n:
         raise ValueError("params must have n elements")
-    W = len(packed)
-    if W != len(ranges):
-        raise ValueError("packed and ranges must have one entry per worker")
-    for p, r in zip(packed, ranges):
-        _check(p, torch.int32, "packed[w]")
-        _check(r, torch.float32, "ranges[w]")
-        if p.numel() < mqg_packed_words(n, bits) or r.numel() < 2:
-            raise ValueError("a worker's buffers are too small for n")
-    pa = (C.c_void_p * max(W, 1))(*[p.data_ptr() for p in packed])
-    ra = (C.c_void_p * max(W, 1))(*[r.data_ptr() for r in ranges])
+    W, pa, ra = _worker_arrays(packed, ranges, n, bits, 0, _ONE_PAIR)
     st = lib().mqg_aggregate_update_minmax_tensor(pa, ra, W, n, bits, lr, params.data_ptr(), _stream_handle(stream))
     if st != MQG_OK:
         raise MqgError(st, "mqg_aggregate_update_minmax_tensor")
@@ -567,14 +560,7 @@ def mqg_aggregate_update_minmax_tensor(packed, ranges, n, bits, lr, params, stre
 
 def mqg_aggregate_requantize_minmax_tensor(packed, ranges, n, bits, packed_out=None, range_out=None, stream=None):
     """Server side of the full exchange with ONE [min, max] range per tensor. Returns (packed, range) of the mean."""
-    W = len(packed)
-    if W != len(ranges):
-        raise ValueError("packed and ranges must have one entry per worker")
-    for p, r in zip(packed, ranges):
-        _check(p, torch.int32, "packed[w]")
-        _check(r, torch.float32, "ranges[w]")
-        if p.numel() < mqg_packed_words(n, bits) or r.numel() < 2:
-            raise ValueError("a worker's buffers are too small for n")
+    W, pa, ra = _worker_arrays(packed, ranges, n, bits, 0, _ONE_PAIR)
     dev = packed[0].device
     if packed_out is None:
         packed_out = torch.empty(mqg_packed_words(n, bits), dtype=torch.int32, device=dev)
@@ -584,8 +570,6 @@ def mqg_aggregate_requantize_minmax_tensor(packed, ranges, n, bits, packed_out=N
     _check(range_out, torch.float32, "range_out")
     if packed_out.numel() < mqg_packed_words(n, bits) or range_out.numel() < 2:
         raise ValueError("output buffers too small")
-    pa = (C.c_void_p * max(W, 1))(*[p.data_ptr() for p in packed])
-    ra = (C.c_void_p * max(W, 1))(*[r.data_ptr() for r in ranges])
     st = lib().mqg_aggregate_requantize_minmax_tensor(pa, ra, W, n, bits, packed_out.data_ptr(), range_out.data_ptr(),
                                                       _stream_handle(stream))
     if st != MQG_OK:
