@@ -325,7 +325,8 @@ mqg_status mqg_quantize_tensors_mode(const mqg_quantize_item* items, uint32_t co
     if (items == nullptr) return MQG_EINVAL;
     mqg::BatchQuantizeArgs a;
     a.common.grad = nullptr;
-    a.common.n = 0;
+    a.common.n = 0;   // of all layers together: the launch picks its shape by it
+    for (uint32_t i = 0; i < count; ++i) a.common.n = items[i].n > UINT64_MAX - a.common.n ? UINT64_MAX : a.common.n + items[i].n;
     a.common.bits = bits;
     a.common.bucket = bucket;
     a.common.bucket_shift = log2_if_pow2(bucket);

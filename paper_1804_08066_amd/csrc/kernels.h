@@ -77,7 +77,7 @@ struct BatchQuantizeArgs {
         float* scales;
         const float* scales_in;   // nullable: the layer's scales are read, not computed
     };
-    QuantizeArgs common;      // bits, bucket, stream selection; per-tensor fields are taken from t[]
+    QuantizeArgs common;      // bits, bucket, stream selection, n = elements of all tensors; the other per-tensor fields are taken from t[]
     uint32_t count;
     uint32_t tile_elems;
     uint32_t tile_start[kMaxBatchTensors + 1];
@@ -87,7 +87,7 @@ struct BatchQuantizeArgs {
 uint32_t aggregate_batch_tile();
 hipError_t launch_aggregate_tensors(const BatchAggregateArgs& a, uint32_t tiles, hipStream_t stream);
 uint32_t quantize_batch_tile(const BatchQuantizeArgs& a);   // elements per workgroup of the kernel the batch will run (reads a.common only)
-uint32_t quantize_wave_block_elems(uint32_t bucket, uint32_t bits);                             // quantize_wave.hip
+uint32_t quantize_wave_block_elems(uint32_t bucket, uint32_t bits, uint64_t n);                             // quantize_wave.hip
 hipError_t launch_quantize_tensors_wave(const BatchQuantizeArgs& a, uint32_t blocks, hipStream_t stream);
 hipError_t launch_quantize_tensors(const BatchQuantizeArgs& a, uint32_t tiles, hipStream_t stream);
 

@@ -448,7 +448,7 @@ static bool batch_takes_wave_kernel(int bucket_shift) { return bucket_shift >= 5
 
 uint32_t quantize_batch_tile(const BatchQuantizeArgs& a) {
     const uint32_t bucket = a.common.bucket;
-    if (batch_takes_wave_kernel(a.common.bucket_shift)) return quantize_wave_block_elems(bucket, a.common.bits);
+    if (batch_takes_wave_kernel(a.common.bucket_shift)) return quantize_wave_block_elems(bucket, a.common.bits, a.common.n);
     if (quantize_tensors_cells_supported(a)) return quantize_cells_tile_elems(bucket);
     const uint32_t cap = bucket <= 4096u ? Tile<4>::kCap : (bucket <= 8192u ? Tile<8>::kCap : Tile<16>::kCap);
     return (cap / bucket) * bucket;

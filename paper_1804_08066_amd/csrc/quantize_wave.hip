@@ -1048,8 +1048,21 @@ auto with_wave_shape_w(uint32_t bucket, uint32_t bits, F f) {
             return f(integral_constant<int, 8>{}, integral_constant<int, 1>{}, integral_constant<int, 4>{}, integral_constant<int, 5>{}, late{});
     }
 }
+// n: elements of the launch.  Where a launch does not fill the chip several times over, what counts is the length of
+// a wave's own chain of loads, random numbers and stores, and how many compute units have a wave at all: a wave
+// then holds 1024 elements, or 512.  65,536 elements, bucket 512, 4 bits: 4.8 us with 2048, 4.0 with 1024, 3.5 with
+// 512; ten layers of 1.07 M in all at 2 bits: 5.7, 4.6, 4.3; 10 M with the L2 norm: 11.0, 10.8, 12.2; from
+// 25.6 M on 2048 are as fast (20 us) or faster.
+constexpr uint64_t kShortLaunch = 1ull << 24, kTinyLaunch = 1ull << 21;
 template <class F>
-auto with_wave_shape(uint32_t bucket, uint32_t bits, F f) {
+auto with_wave_shape(uint32_t bucket, uint32_t bits, uint64_t n, F f) {
+    using std::integral_constant;
+    if (bucket <= 512u && n <= kTinyLaunch) {
+        return f(integral_constant<int, 2>{}, integral_constant<int, 1>{}, integral_constant<int, 4>{}, integral_constant<int, 8>{}, std::false_type{});
+    }
+    if (bucket <= 1024u && n <= kShortLaunch) {
+        return f(integral_constant<int, 4>{}, integral_constant<int, 1>{}, integral_constant<int, 4>{}, integral_constant<int, 8>{}, std::false_type{});
+    }
     return bits == 8u ? with_wave_shape_w<true>(bucket, bits, f) : with_wave_shape_w<false>(bucket, bits, f);
 }
 
@@ -1069,12 +1082,12 @@ hipError_t launch_wave(const QuantizeArgs& a, hipStream_t stream) {
 bool quantize_wave_supported(const QuantizeArgs& a) { return a.bucket_shift >= 5; }
 
 // elements per workgroup of the wave-local kernel at this bucket size
-uint32_t quantize_wave_block_elems(uint32_t bucket, uint32_t bits) {
-    return with_wave_shape(bucket, bits, [](auto r, auto, auto nw, auto, auto) { return (uint32_t)(decltype(nw)::value * 256 * decltype(r)::value); });
+uint32_t quantize_wave_block_elems(uint32_t bucket, uint32_t bits, uint64_t n) {
+    return with_wave_shape(bucket, bits, n, [](auto r, auto, auto nw, auto, auto) { return (uint32_t)(decltype(nw)::value * 256 * decltype(r)::value); });
 }
 
 hipError_t launch_quantize_tensors_wave(const BatchQuantizeArgs& a, uint32_t blocks, hipStream_t stream) {
-    return with_wave_shape(a.common.bucket, a.common.bits, [&](auto r, auto wpb, auto nw, auto occ, auto hoist) {
+    return with_wave_shape(a.common.bucket, a.common.bits, a.common.n, [&](auto r, auto wpb, auto nw, auto occ, auto hoist) {
         constexpr int R = decltype(r)::value, WPB = decltype(wpb)::value, NW = decltype(nw)::value, OCC = decltype(occ)::value;
         constexpr bool HOIST = decltype(hoist)::value;
         hipLaunchKernelGGL((quantize_tensors_wave_kernel<R, WPB, NW, OCC, HOIST>), dim3(blocks), dim3(64 * NW), 0, stream, a);
@@ -1083,7 +1096,7 @@ hipError_t launch_quantize_tensors_wave(const BatchQuantizeArgs& a, uint32_t blo
 }
 
 hipError_t launch_quantize_wave(const QuantizeArgs& a, hipStream_t stream) {
-    return with_wave_shape(a.bucket, a.bits, [&](auto r, auto wpb, auto nw, auto occ, auto hoist) {
+    return with_wave_shape(a.bucket, a.bits, a.n, [&](auto r, auto wpb, auto nw, auto occ, auto hoist) {
         return launch_wave<decltype(r)::value, decltype(wpb)::value, decltype(nw)::value, decltype(occ)::value,
                            decltype(hoist)::value>(a, stream);
     });
