@@ -267,6 +267,7 @@ __device__ __forceinline__ void quantize_minmax_tile(const QuantizeArgs& a, cons
 
 template <int R, int NT, bool ONE>
 __global__ __launch_bounds__(NT) void quantize_minmax_kernel(const QuantizeArgs a, const TileGeometry g) {
+    drop_every_nan();
     __shared__ Shared<R, NT, ONE> sm;
     quantize_minmax_tile(a, g, blockIdx.x, sm);
 }
@@ -275,6 +276,7 @@ __global__ __launch_bounds__(NT) void quantize_minmax_kernel(const QuantizeArgs 
 // table of tile counts.
 template <int R, int NT, bool ONE>
 __global__ __launch_bounds__(NT) void quantize_minmax_tensors_kernel(const BatchQuantizeArgs ba, const TileGeometry g) {
+    drop_every_nan();
     __shared__ Shared<R, NT, ONE> sm;
     uint32_t lo = 0, hi = ba.count;          // tile_start[lo] <= blockIdx.x < tile_start[hi]
     while (hi - lo > 1u) {
@@ -694,8 +696,8 @@ __device__ __forceinline__ void block_range(const float* __restrict__ g, const u
         if (q < nq) fold(__builtin_nontemporal_load(g4 + q));
         if (tid < (n & 3u)) {
             const float v = g[(nq << 2) + tid];
-            lo = fminf(lo, v);
-            hi = fmaxf(hi, v);
+            lo = min_f32(lo, v);
+            hi = max_f32(hi, v);
         }
     }
     kl = order_key(lo);
@@ -706,6 +708,7 @@ __device__ __forceinline__ void block_range(const float* __restrict__ g, const u
 // Range alone (two floats are all the memory there is): the workgroups meet in atomics on the two words.
 __global__ __launch_bounds__(kSumThreads) void tensor_range_kernel(const float* __restrict__ g, const uint64_t n,
                                                                    uint32_t* keys) {
+    drop_every_nan();
     __shared__ uint32_t s_lo[kSumThreads / 64], s_hi[kSumThreads / 64];
     uint32_t kl, kh;
     block_range(g, n, blockIdx.x, gridDim.x, kl, kh, s_lo, s_hi);
@@ -718,6 +721,7 @@ __global__ __launch_bounds__(kSumThreads) void tensor_range_kernel(const float* 
 // 15 us with atomics; the ten layers' two largest, 0.9 M elements: 4 us, 14 us with atomics).
 // A tensor of one workgroup gets its range at once.
 __global__ __launch_bounds__(kSumThreads) void tensor_range_parts_kernel(const TensorRangeBatch b, const uint32_t count) {
+    drop_every_nan();
     __shared__ uint32_t s_lo[kSumThreads / 64], s_hi[kSumThreads / 64];
     uint32_t k = 0, end = count;          // block_start[k] <= blockIdx.x < block_start[end]
     while (end - k > 1u) {

@@ -322,6 +322,7 @@ __device__ __forceinline__ void clear_shared(Shared<R>& sm, uint32_t tile_count,
 
 template <int R>
 __global__ __launch_bounds__(kThreads) void quantize_pack_kernel(const QuantizeArgs a, const uint32_t tile_elems) {
+    drop_every_nan();
     __shared__ Shared<R> sm;
     const uint64_t tile_base = (uint64_t)blockIdx.x * tile_elems;
     const uint64_t left = a.n - tile_base;
@@ -369,6 +370,7 @@ __global__ __launch_bounds__(kThreads) void requantize_pack_kernel(const Requant
 // Several layer tensors of one worker in one launch: block -> (tensor, tile) through the prefix table.
 template <int R>
 __global__ __launch_bounds__(kThreads) void quantize_tensors_kernel(const BatchQuantizeArgs ba) {
+    drop_every_nan();
     __shared__ Shared<R> sm;
     uint32_t lo = 0, hi = ba.count;          // tile_start[lo] <= blockIdx.x < tile_start[hi]
     while (hi - lo > 1u) {

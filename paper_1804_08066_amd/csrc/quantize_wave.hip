@@ -467,6 +467,7 @@ __device__ __forceinline__ void quantize_wave_block(const QuantizeArgs& a, const
 // elements, buckets 128 and 1024: -2..-4 us and +1..+3 us), so the launch picks the cap by the width.
 template <int R, int WPB, int NW, int OCC, bool HOIST>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1, OCC))) void quantize_wave_kernel(const QuantizeArgs a) {
+    drop_every_nan();
     __shared__ WaveShared<R, NW> sm;
     quantize_wave_block<R, WPB, NW, HOIST>(a, blockIdx.x, sm);
 }
@@ -475,6 +476,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1, OCC)
 // the prefix table of block counts.
 template <int R, int WPB, int NW, int OCC, bool HOIST>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1, OCC))) void quantize_tensors_wave_kernel(const BatchQuantizeArgs ba) {
+    drop_every_nan();
     __shared__ WaveShared<R, NW> sm;
     uint32_t lo = 0, hi = ba.count;          // tile_start[lo] <= blockIdx.x < tile_start[hi]
     while (hi - lo > 1u) {
@@ -647,6 +649,7 @@ __device__ __forceinline__ void quantize_cells_block(const QuantizeArgs& a, cons
 
 template <int NW, int OCC, bool HOIST>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1, OCC))) void quantize_cells_kernel(const QuantizeArgs a, const CellGeometry g) {
+    drop_every_nan();
     __shared__ WaveShared<8, NW> sm;
     __shared__ CellShared<NW> cs;
     quantize_cells_block<NW, HOIST>(a, g, blockIdx.x, sm, cs);
@@ -655,6 +658,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1, OCC)
 // Several layer tensors of one worker in one launch, as quantize_tensors_wave_kernel maps them.
 template <int NW, int OCC, bool HOIST>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1, OCC))) void quantize_tensors_cells_kernel(const BatchQuantizeArgs ba, const CellGeometry g) {
+    drop_every_nan();
     __shared__ WaveShared<8, NW> sm;
     __shared__ CellShared<NW> cs;
     uint32_t lo = 0, hi = ba.count;          // tile_start[lo] <= blockIdx.x < tile_start[hi]
@@ -1018,6 +1022,7 @@ __device__ __forceinline__ void quantize_minmax_wave_block(const QuantizeArgs& a
 
 template <int R, int WPB, int NW>
 __global__ __launch_bounds__(64 * NW) void quantize_minmax_wave_kernel(const QuantizeArgs a) {
+    drop_every_nan();
     __shared__ WaveShared<R, NW> sm;
     __shared__ WaveLows<R, NW> lw;
     quantize_minmax_wave_block<R, WPB, NW>(a, blockIdx.x, sm, lw);
@@ -1026,6 +1031,7 @@ __global__ __launch_bounds__(64 * NW) void quantize_minmax_wave_kernel(const Qua
 // Several layer tensors in one launch, as quantize_tensors_wave_kernel maps them.
 template <int R, int WPB, int NW>
 __global__ __launch_bounds__(64 * NW) void quantize_minmax_tensors_wave_kernel(const BatchQuantizeArgs ba) {
+    drop_every_nan();
     __shared__ WaveShared<R, NW> sm;
     __shared__ WaveLows<R, NW> lw;
     uint32_t lo = 0, hi = ba.count;          // tile_start[lo] <= blockIdx.x < tile_start[hi]
