@@ -69,6 +69,7 @@ MQG_MAX_TENSORS = 32
 MQG_MAX_TENSOR_POINTERS = 256
 
 _lib = None
+_tables = None    # the same library with HOST tables as plain addresses, for the binding's own calls
 _marshal = None   # argument tables in native code (csrc/marshal.cpp), loaded with the library
 
 
@@ -86,7 +87,7 @@ def lib():
             import warnings
             warnings.warn("libmqgrad.so is older than its sources: run paper_1804_08066_amd/build.py (loading the stale library)")
     L = C.CDLL(path)
-    vp, u32, u64, f32 = C.c_void_p, C.c_uint32, C.c_uint64, C.c_float   # vp also takes HOST tables: ctypes arrays, bytes
+    vp, u32, u64, f32 = C.c_void_p, C.c_uint32, C.c_uint64, C.c_float
     L.mqg_status_string.argtypes = [C.c_int]
     L.mqg_status_string.restype = C.c_char_p
     L.mqg_num_buckets.argtypes = [u64, u32]
@@ -101,41 +102,41 @@ def lib():
     L.mqg_quantize_mode.restype = C.c_int
     L.mqg_quantize_with_scales.argtypes = [vp, u64, u32, u32, u64, u32, u32, u64, vp, vp, vp, vp]
     L.mqg_quantize_with_scales.restype = C.c_int
-    L.mqg_aggregate_update.argtypes = [vp, vp, u32, u64, u32, u32, f32, vp, vp]
+    L.mqg_aggregate_update.argtypes = [C.POINTER(vp), C.POINTER(vp), u32, u64, u32, u32, f32, vp, vp]
     L.mqg_aggregate_update.restype = C.c_int
-    L.mqg_aggregate_update_from.argtypes = [vp, vp, u32, u64, u32, u32, f32, vp, C.c_int, vp]
+    L.mqg_aggregate_update_from.argtypes = [C.POINTER(vp), C.POINTER(vp), u32, u64, u32, u32, f32, vp, C.c_int, vp]
     L.mqg_aggregate_update_from.restype = C.c_int
-    L.mqg_aggregate_requantize.argtypes = [vp, vp, u32, u64, u32, u32, u64, u32, u32, u64, vp, vp, vp]
+    L.mqg_aggregate_requantize.argtypes = [C.POINTER(vp), C.POINTER(vp), u32, u64, u32, u32, u64, u32, u32, u64, vp, vp, vp]
     L.mqg_aggregate_requantize.restype = C.c_int
-    L.mqg_aggregate_requantize_mode.argtypes = [vp, vp, u32, u64, u32, u32, C.c_int, u64, u32, u32, u64, vp, vp, vp]
+    L.mqg_aggregate_requantize_mode.argtypes = [C.POINTER(vp), C.POINTER(vp), u32, u64, u32, u32, C.c_int, u64, u32, u32, u64, vp, vp, vp]
     L.mqg_aggregate_requantize_mode.restype = C.c_int
     L.mqg_dequantize_update.argtypes = [vp, vp, u64, u32, u32, f32, vp, vp]
     L.mqg_dequantize_update.restype = C.c_int
-    L.mqg_quantize_tensors.argtypes = [vp, u32, u32, u32, u64, u32, u32, vp]
+    L.mqg_quantize_tensors.argtypes = [C.POINTER(QuantizeItem), u32, u32, u32, u64, u32, u32, vp]
     L.mqg_quantize_tensors.restype = C.c_int
-    L.mqg_quantize_tensors_mode.argtypes = [vp, u32, u32, u32, C.c_int, u64, u32, u32, vp]
+    L.mqg_quantize_tensors_mode.argtypes = [C.POINTER(QuantizeItem), u32, u32, u32, C.c_int, u64, u32, u32, vp]
     L.mqg_quantize_tensors_mode.restype = C.c_int
-    L.mqg_aggregate_update_tensors.argtypes = [vp, u32, u32, u32, u32, f32, vp]
+    L.mqg_aggregate_update_tensors.argtypes = [C.POINTER(UpdateItem), u32, u32, u32, u32, f32, vp]
     L.mqg_aggregate_update_tensors.restype = C.c_int
-    L.mqg_aggregate_update_minmax_tensors.argtypes = [vp, u32, u32, u32, u32, f32, vp]
+    L.mqg_aggregate_update_minmax_tensors.argtypes = [C.POINTER(UpdateItem), u32, u32, u32, u32, f32, vp]
     L.mqg_aggregate_update_minmax_tensors.restype = C.c_int
-    L.mqg_quantize_minmax_tensors.argtypes = [vp, u32, u32, u32, vp]
+    L.mqg_quantize_minmax_tensors.argtypes = [C.POINTER(QuantizeItem), u32, u32, u32, vp]
     L.mqg_quantize_minmax_tensors.restype = C.c_int
     L.mqg_quantize_minmax.argtypes = [vp, u64, u32, u32, vp, vp, vp]
     L.mqg_quantize_minmax.restype = C.c_int
-    L.mqg_aggregate_update_minmax.argtypes = [vp, vp, u32, u64, u32, u32, f32, vp, vp]
+    L.mqg_aggregate_update_minmax.argtypes = [C.POINTER(vp), C.POINTER(vp), u32, u64, u32, u32, f32, vp, vp]
     L.mqg_aggregate_update_minmax.restype = C.c_int
-    L.mqg_aggregate_requantize_minmax.argtypes = [vp, vp, u32, u64, u32, u32, vp, vp, vp]
+    L.mqg_aggregate_requantize_minmax.argtypes = [C.POINTER(vp), C.POINTER(vp), u32, u64, u32, u32, vp, vp, vp]
     L.mqg_aggregate_requantize_minmax.restype = C.c_int
     L.mqg_tensor_range.argtypes = [vp, u64, vp, vp]
     L.mqg_tensor_range.restype = C.c_int
     L.mqg_quantize_minmax_tensor.argtypes = [vp, u64, u32, vp, vp, vp]
     L.mqg_quantize_minmax_tensor.restype = C.c_int
-    L.mqg_aggregate_update_minmax_tensor.argtypes = [vp, vp, u32, u64, u32, f32, vp, vp]
+    L.mqg_aggregate_update_minmax_tensor.argtypes = [C.POINTER(vp), C.POINTER(vp), u32, u64, u32, f32, vp, vp]
     L.mqg_aggregate_update_minmax_tensor.restype = C.c_int
-    L.mqg_aggregate_requantize_minmax_tensor.argtypes = [vp, vp, u32, u64, u32, vp, vp, vp]
+    L.mqg_aggregate_requantize_minmax_tensor.argtypes = [C.POINTER(vp), C.POINTER(vp), u32, u64, u32, vp, vp, vp]
     L.mqg_aggregate_requantize_minmax_tensor.restype = C.c_int
-    L.mqg_aggregate_mean.argtypes = [vp, vp, u32, u64, u32, u32, vp, vp]
+    L.mqg_aggregate_mean.argtypes = [C.POINTER(vp), C.POINTER(vp), u32, u64, u32, u32, vp, vp]
     L.mqg_aggregate_mean.restype = C.c_int
     L.mqg_sum_squares.argtypes = [vp, u64, vp, vp]
     L.mqg_sum_squares.restype = C.c_int
@@ -175,10 +176,23 @@ def lib():
     L.mqg_mdp_set_weights.restype = None
     L.mqg_mdp_q_values.argtypes = [vp, C.POINTER(C.c_double), C.POINTER(C.c_double)]
     L.mqg_mdp_q_values.restype = None
-    global _marshal
+    global _marshal, _tables
     _marshal = _build.load_marshal()
+    T = C.CDLL(path)   # the library loaded once more: function objects of its own, whose tables may be bytes
+    tables = (C.POINTER(vp), C.POINTER(QuantizeItem), C.POINTER(UpdateItem))
+    for name in _TAKES_TABLES:
+        strict, loose = getattr(L, name), getattr(T, name)
+        loose.argtypes = [vp if t in tables else t for t in strict.argtypes]
+        loose.restype = strict.restype
+    _tables = T
     _lib = L
     return L
+
+
+_TAKES_TABLES = ("mqg_aggregate_update_from", "mqg_aggregate_requantize_mode", "mqg_aggregate_mean", "mqg_quantize_tensors_mode",
+                 "mqg_aggregate_update_tensors", "mqg_aggregate_update_minmax_tensors", "mqg_quantize_minmax_tensors",
+                 "mqg_aggregate_update_minmax", "mqg_aggregate_requantize_minmax", "mqg_aggregate_update_minmax_tensor",
+                 "mqg_aggregate_requantize_minmax_tensor")
 
 
 def status_string(status):
@@ -289,7 +303,7 @@ def mqg_aggregate_update(packed, scales, n, bits, bucket, lr, params, stream=Non
     _check(params, torch.float32, "params")
     if params.numel() != n:
         raise ValueError("params must have n elements")
-    st = lib().mqg_aggregate_update_from(pa, sa, W, n, bits, bucket, lr, params.data_ptr(), int(origin), _stream_handle(stream))
+    st = _tables.mqg_aggregate_update_from(pa, sa, W, n, bits, bucket, lr, params.data_ptr(), int(origin), _stream_handle(stream))
     if st != MQG_OK:
         raise MqgError(st, "mqg_aggregate_update")
     return params
@@ -303,7 +317,7 @@ def mqg_aggregate_mean(packed, scales, n, bits, bucket, mean_out=None, stream=No
     _check(mean_out, torch.float32, "mean_out")
     if mean_out.numel() != n:
         raise ValueError("mean_out must have n elements")
-    st = lib().mqg_aggregate_mean(pa, sa, W, n, bits, bucket, mean_out.data_ptr(), _stream_handle(stream))
+    st = _tables.mqg_aggregate_mean(pa, sa, W, n, bits, bucket, mean_out.data_ptr(), _stream_handle(stream))
     if st != MQG_OK:
         raise MqgError(st, "mqg_aggregate_mean")
     return mean_out
@@ -323,7 +337,7 @@ def mqg_aggregate_requantize(packed, scales, n, bits, bucket, seed, iteration=0,
     _check(scales_out, torch.float32, "scales_out")
     if packed_out.numel() < mqg_packed_words(n, bits) or scales_out.numel() < mqg_num_buckets(n, bucket):
         raise ValueError("output buffers too small")
-    st = lib().mqg_aggregate_requantize_mode(pa, sa, W, n, bits, bucket, int(mode), seed, iteration, worker, elem_base,
+    st = _tables.mqg_aggregate_requantize_mode(pa, sa, W, n, bits, bucket, int(mode), seed, iteration, worker, elem_base,
                                              packed_out.data_ptr(), scales_out.data_ptr(), _stream_handle(stream))
     if st != MQG_OK:
         raise MqgError(st, "mqg_aggregate_requantize")
@@ -356,7 +370,7 @@ def mqg_quantize_tensors(grads, bits, bucket, seed, iteration=0, worker=0, elem_
     items = _marshal.quantize_items(grads, outputs, elem_bases, bits, bucket, _SCALES) if scales_in is None else None
     if items is None:
         items = _quantize_items(grads, bits, bucket, elem_bases, outputs, scales_in)
-    st = lib().mqg_quantize_tensors_mode(items, count, bits, bucket, int(scale_mode), seed, iteration, worker,
+    st = _tables.mqg_quantize_tensors_mode(items, count, bits, bucket, int(scale_mode), seed, iteration, worker,
                                          _stream_handle(stream))
     if st != MQG_OK:
         raise MqgError(st, "mqg_quantize_tensors")
@@ -393,7 +407,7 @@ def mqg_aggregate_update_tensors(layers, W, bits, bucket, lr, stream=None):
     Each layer is a dict with "params" and either ("packed": [W tensors], "scales": [W tensors]) for a
     quantized layer or "raw": [W fp32 gradient tensors] for a layer sent uncompressed."""
     items, keep = _update_items(layers, W, bits, bucket, 0)
-    st = lib().mqg_aggregate_update_tensors(items, len(layers), W, bits, bucket, lr, _stream_handle(stream))
+    st = _tables.mqg_aggregate_update_tensors(items, len(layers), W, bits, bucket, lr, _stream_handle(stream))
     del keep
     if st != MQG_OK:
         raise MqgError(st, "mqg_aggregate_update_tensors")
@@ -461,7 +475,7 @@ def mqg_quantize_minmax_tensors(grads, bits, bucket, outputs=None, stream=None):
             if p.numel() < mqg_packed_words(g.numel(), bits) or r.numel() < nr(g.numel()):
                 raise ValueError("output buffers too small")
             items[i] = QuantizeItem(g.data_ptr(), g.numel(), 0, p.data_ptr(), r.data_ptr(), None)
-    st = lib().mqg_quantize_minmax_tensors(items, count, bits, bucket, _stream_handle(stream))
+    st = _tables.mqg_quantize_minmax_tensors(items, count, bits, bucket, _stream_handle(stream))
     if st != MQG_OK:
         raise MqgError(st, "mqg_quantize_minmax_tensors")
     return outputs
@@ -471,7 +485,7 @@ def mqg_aggregate_update_minmax_tensors(layers, W, bits, bucket, lr, stream=None
     """mqg_aggregate_update_minmax for a list of layers in one launch (bucket = 0: one (min, max) pair per worker
     and layer).  Layers as in mqg_aggregate_update_tensors, "scales" holding the range arrays."""
     items, keep = _update_items(layers, W, bits, bucket, 1 if bucket else 2)
-    st = lib().mqg_aggregate_update_minmax_tensors(items, len(layers), W, bits, bucket, lr, _stream_handle(stream))
+    st = _tables.mqg_aggregate_update_minmax_tensors(items, len(layers), W, bits, bucket, lr, _stream_handle(stream))
     del keep
     if st != MQG_OK:
         raise MqgError(st, "mqg_aggregate_update_minmax_tensors")
@@ -497,7 +511,7 @@ def mqg_aggregate_update_minmax(packed, ranges, n, bits, bucket, lr, params, str
     if params.numel() != n:
         raise ValueError("params must have n elements")
     W, pa, ra = _worker_arrays(packed, ranges, n, bits, bucket, _PAIRS)
-    st = lib().mqg_aggregate_update_minmax(pa, ra, W, n, bits, bucket, lr, params.data_ptr(), _stream_handle(stream))
+    st = _tables.mqg_aggregate_update_minmax(pa, ra, W, n, bits, bucket, lr, params.data_ptr(), _stream_handle(stream))
     if st != MQG_OK:
         raise MqgError(st, "mqg_aggregate_update_minmax")
 
@@ -514,7 +528,7 @@ def mqg_aggregate_requantize_minmax(packed, ranges, n, bits, bucket, packed_out=
     _check(ranges_out, torch.float32, "ranges_out")
     if packed_out.numel() < mqg_packed_words(n, bits) or ranges_out.numel() < 2 * mqg_num_buckets(n, bucket):
         raise ValueError("output buffers too small")
-    st = lib().mqg_aggregate_requantize_minmax(pa, ra, W, n, bits, bucket, packed_out.data_ptr(),
+    st = _tables.mqg_aggregate_requantize_minmax(pa, ra, W, n, bits, bucket, packed_out.data_ptr(),
                                                ranges_out.data_ptr(), _stream_handle(stream))
     if st != MQG_OK:
         raise MqgError(st, "mqg_aggregate_requantize_minmax")
@@ -553,7 +567,7 @@ def mqg_aggregate_update_minmax_tensor(packed, ranges, n, bits, lr, params, stre
     if params.numel() != n:
         raise ValueError("params must have n elements")
     W, pa, ra = _worker_arrays(packed, ranges, n, bits, 0, _ONE_PAIR)
-    st = lib().mqg_aggregate_update_minmax_tensor(pa, ra, W, n, bits, lr, params.data_ptr(), _stream_handle(stream))
+    st = _tables.mqg_aggregate_update_minmax_tensor(pa, ra, W, n, bits, lr, params.data_ptr(), _stream_handle(stream))
     if st != MQG_OK:
         raise MqgError(st, "mqg_aggregate_update_minmax_tensor")
 
@@ -570,7 +584,7 @@ def mqg_aggregate_requantize_minmax_tensor(packed, ranges, n, bits, packed_out=N
     _check(range_out, torch.float32, "range_out")
     if packed_out.numel() < mqg_packed_words(n, bits) or range_out.numel() < 2:
         raise ValueError("output buffers too small")
-    st = lib().mqg_aggregate_requantize_minmax_tensor(pa, ra, W, n, bits, packed_out.data_ptr(), range_out.data_ptr(),
+    st = _tables.mqg_aggregate_requantize_minmax_tensor(pa, ra, W, n, bits, packed_out.data_ptr(), range_out.data_ptr(),
                                                       _stream_handle(stream))
     if st != MQG_OK:
         raise MqgError(st, "mqg_aggregate_requantize_minmax_tensor")

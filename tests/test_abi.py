@@ -211,3 +211,23 @@ def test_header_compiles_as_plain_c(tmp_path):
     r = subprocess.run([gcc, "-std=c99", "-Wall", "-Wextra", "-Werror", "-pedantic", "-I", os.path.join(root, "include"),
                         "-c", str(src), "-o", str(tmp_path / "use_header.o")], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
+
+
+def test_tables_of_the_wrong_kind_are_refused():
+    """The prototypes of lib() tell a table of addresses, of layers to quantize and of layers to update apart."""
+    L = mqgrad.lib()
+    pointers, quantize, update = (C.c_void_p * 1)(), (mqgrad.QuantizeItem * 1)(), (mqgrad.UpdateItem * 1)()
+    calls = [(lambda t: L.mqg_quantize_tensors(t, 0, 4, 512, 0, 0, 0, None), quantize),
+             (lambda t: L.mqg_quantize_tensors_mode(t, 0, 4, 512, 0, 0, 0, 0, None), quantize),
+             (lambda t: L.mqg_quantize_minmax_tensors(t, 0, 4, 512, None), quantize),
+             (lambda t: L.mqg_aggregate_update_tensors(t, 0, 1, 4, 512, 0.1, None), update),
+             (lambda t: L.mqg_aggregate_update_minmax_tensors(t, 0, 1, 4, 512, 0.1, None), update),
+             (lambda t: L.mqg_aggregate_update(t, t, 1, 0, 4, 512, 0.1, None, None), pointers),
+             (lambda t: L.mqg_aggregate_mean(t, t, 1, 0, 4, 512, None, None), pointers),
+             (lambda t: L.mqg_aggregate_update_minmax_tensor(t, t, 1, 0, 4, 0.1, None, None), pointers)]
+    for call, right in calls:
+        assert call(right) in (mqgrad.MQG_OK, mqgrad.MQG_EINVAL)
+        for wrong in (pointers, quantize, update, b"12345678", 0x1000):
+            if wrong is not right:
+                with pytest.raises(C.ArgumentError):
+                    call(wrong)
