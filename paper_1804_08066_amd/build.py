@@ -1,5 +1,5 @@
-"""Build libmqgrad.so (gfx950 kernels + C ABI + host MDP) in-tree with hipcc, _marshal.so (the Python
-binding's argument tables) and libmqgrad_bench.so
+"""Build libmqgrad.so (gfx950 kernels + C ABI + host MDP) in-tree with hipcc, _marshal.<key>.so (the
+Python binding's argument tables) and libmqgrad_bench.so
 (the streaming kernels that bench.py uses as its measured ceilings; not part of the library)."""
 import os
 import shutil
@@ -14,8 +14,7 @@ LIB = os.path.join(HERE, "libmqgrad.so")
 BENCH_LIB = os.path.join(HERE, "libmqgrad_bench.so")
 SOURCES = ["api.hip", "quantize_pack.hip", "quantize_wave.hip", "aggregate_update.hip", "minmax.hip", "mdp.cpp"]
 BENCH_SOURCES = ["bench_stream.hip"]
-MARSHAL = os.path.join(HERE, "_marshal.so")   # the binding's argument tables: host code against torch and Python
-MARSHAL_SOURCE = "marshal.cpp"
+MARSHAL_SOURCE = "marshal.cpp"   # the binding's argument tables: host code against torch and Python
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
@@ -36,10 +35,13 @@ def sources():
 
 
 def needs_build():
-    """True when a library is missing or older than any of its sources or headers."""
+    """True when a library is missing or older than any of its sources or headers, or there is no binding module of
+    the present sources, Python and torch."""
     deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith((".h", ".hip", ".cpp"))] + \
         [os.path.join(ROOT, "include", "mqgrad.h")]
-    for lib in (LIB, BENCH_LIB, MARSHAL):
+    if not os.path.exists(marshal_path()):
+        return True
+    for lib in (LIB, BENCH_LIB):
         if not os.path.exists(lib):
             return True
         t = os.path.getmtime(lib)
@@ -64,12 +66,28 @@ def _link(names, out, tmpdir, verbose, extra_flags):
     os.replace(tmp, out)
 
 
+def marshal_path():
+    """The binding's module, named by what it was compiled from and against: its sources (the layout of the item structs
+    among them), the Python it is loaded into and the torch whose classes it has inlined."""
+    import hashlib
+    import sysconfig
+    import torch
+    key = hashlib.sha256()
+    for path in (os.path.join(CSRC, MARSHAL_SOURCE), os.path.join(ROOT, "include", "mqgrad.h")):
+        with open(path, "rb") as f:
+            key.update(f.read())
+    key.update(repr((sysconfig.get_config_var("EXT_SUFFIX"), torch.__version__, torch.version.git_version,
+                     torch.compiled_with_cxx11_abi())).encode())
+    return os.path.join(HERE, "_marshal.%s.so" % key.hexdigest()[:16])
+
+
 def _build_marshal(verbose):
     import sysconfig
     import torch
     at = os.path.dirname(torch.__file__)
     inc = [os.path.join(at, "include"), os.path.join(at, "include", "torch", "csrc", "api", "include"), sysconfig.get_paths()["include"]]
-    tmp = MARSHAL + ".tmp.%d" % os.getpid()
+    out = marshal_path()
+    tmp = out + ".tmp.%d" % os.getpid()
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall",
            "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch.compiled_with_cxx11_abi()), "-I", os.path.join(ROOT, "include"),
            *[x for d in inc for x in ("-isystem", d)], os.path.join(CSRC, MARSHAL_SOURCE),
@@ -77,32 +95,44 @@ def _build_marshal(verbose):
     if verbose:
         print(" ".join(cmd))
     subprocess.check_call(cmd)
-    os.replace(tmp, MARSHAL)
+    os.replace(tmp, out)
 
 
 def load_marshal():
-    """The _marshal module (built first only if it does not exist)."""
+    """The binding's module (built first only if there is none of the present sources, Python and torch), or None, with a
+    warning, where it can be neither built nor loaded: the binding then makes its tables itself."""
     import importlib.machinery
     import importlib.util
-    if not os.path.exists(MARSHAL):
-        _build_marshal(False)
-    loader = importlib.machinery.ExtensionFileLoader("_marshal", MARSHAL)
-    module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_marshal", loader))
-    loader.exec_module(module)
-    return module
+    try:
+        if not os.path.exists(marshal_path()):
+            _build_marshal(False)
+        loader = importlib.machinery.ExtensionFileLoader("_marshal", marshal_path())
+        module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_marshal", loader))
+        loader.exec_module(module)
+        return module
+    except (OSError, ImportError, subprocess.CalledProcessError) as e:
+        import warnings
+        warnings.warn("the binding's native argument tables are not available (%s): each call takes longer" % e)
+        return None
 
 
-def build(verbose=False, extra_flags=()):
-    """Compile every source (one hipcc process per file, in parallel) and link the libraries."""
+def build_libraries(verbose=False, extra_flags=()):
+    """Compile the libraries' sources (one hipcc process per file, in parallel) and link them."""
     tmpdir = tempfile.mkdtemp(prefix="mqgrad_build_")
     try:
-        with ThreadPoolExecutor(max_workers=1) as pool:
-            marshal = pool.submit(_build_marshal, verbose)
-            _link(SOURCES, LIB, tmpdir, verbose, extra_flags)
-            marshal.result()
+        _link(SOURCES, LIB, tmpdir, verbose, extra_flags)
         _link(BENCH_SOURCES, BENCH_LIB, tmpdir, verbose, extra_flags)
     finally:
         shutil.rmtree(tmpdir, ignore_errors=True)
+    return LIB
+
+
+def build(verbose=False, extra_flags=()):
+    """Build everything: the libraries and the binding's module."""
+    with ThreadPoolExecutor(max_workers=1) as pool:
+        marshal = pool.submit(_build_marshal, verbose)
+        build_libraries(verbose, extra_flags)
+        marshal.result()
     return LIB
 
 

@@ -82,7 +82,7 @@ def lib():
     if path is None:
         path = _build.LIB
         if not os.path.exists(path):
-            _build.build()
+            _build.build_libraries()
         elif _build.needs_build():
             import warnings
             warnings.warn("libmqgrad.so is older than its sources: run paper_1804_08066_amd/build.py (loading the stale library)")
@@ -177,7 +177,7 @@ def lib():
     L.mqg_mdp_q_values.argtypes = [vp, C.POINTER(C.c_double), C.POINTER(C.c_double)]
     L.mqg_mdp_q_values.restype = None
     global _marshal, _tables
-    _marshal = _build.load_marshal()
+    _marshal = _build.load_marshal() or _NoTables
     T = C.CDLL(path)   # the library loaded once more: function objects of its own, whose tables may be bytes
     tables = (C.POINTER(vp), C.POINTER(QuantizeItem), C.POINTER(UpdateItem))
     for name in _TAKES_TABLES:
@@ -187,6 +187,12 @@ def lib():
     _tables = T
     _lib = L
     return L
+
+
+class _NoTables:
+    """Stands in for the native argument tables where they are not available: nothing is accepted, and the binding's own
+    checks make every table."""
+    pointers = stream = quantize_items = update_items = staticmethod(lambda *args: None)
 
 
 _TAKES_TABLES = ("mqg_aggregate_update_from", "mqg_aggregate_requantize_mode", "mqg_aggregate_mean", "mqg_quantize_tensors_mode",
@@ -207,9 +213,12 @@ def mqg_packed_words(n, bits):
     return int(lib().mqg_packed_words(n, bits))
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)   # not public: a torch may come without it
+
+
 def _stream_handle(stream):
-    if stream is None:   # torch.cuda.current_stream() without the Stream object around it
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if stream is None:   # torch.cuda.current_stream(), without the Stream object around it where that can be had
+        return torch.cuda.current_stream().cuda_stream if _raw_stream is None else _raw_stream(torch.cuda.current_device())
     return stream.cuda_stream
 
 
