@@ -364,10 +364,16 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 768 ? 
 // which pass 2 overwrites anyway; one workgroup in between folds them, stores the mean's range and puts
 // the sum's range into the first two words of every pass-2 workgroup's own output, where no other
 // workgroup writes; pass 2 picks it up there, decodes again and encodes over it.  Three launches.  With
-// the keys folded by atomics on one address (and launches to prime, convert and divide them) pass 1 took
-// 26-31 us instead of 19-20 us at 8.8 M elements, 12 workers, 4 bits, and the step 60 us instead of 44.
-// That form (range_out as the place of both the keys and the sum's range) serves the calls whose
-// packed_out lies over one of the streams they read, where nothing may be written before pass 2.
+// the keys folded by atomics on one address (and launches to prime, convert and divide them) the step takes 50 us
+// instead of 39 at 10 M elements, 12 workers, 4 bits.  That form (range_out as the place of both the keys and the
+// sum's range) serves the calls whose packed_out lies over one of the streams they read, where nothing may be
+// written before pass 2, and the largest: one workgroup's time grows with the tiles, and so few of very many
+// workgroups move a key that the atomics cost little.  us with the fold / with atomics, 4 bits:
+//   elements     1 worker     4          12           24 workers
+//   20 M         26 /  41     37 /  40    65 /  71    114 / 122
+//   50 M         58 /  69     78 /  84   153 / 151    289 / 279
+//   100 M       110 / 103    147 / 140   290 / 287    569 / 548
+//   400 M                    558 / 511  1137 / 1086
 // Every worker has one (min, max) pair; s_tab[w] = (step, min) of worker w.
 template <int NT, bool STRADDLE, bool ONCE>
 __device__ __forceinline__ void decode_sum_tile_tensor(const RequantArgs& ra, const uint64_t tile_base, float2* s_tab,
@@ -451,11 +457,11 @@ __global__ void range_divide_kernel(float* range, float Wf) {
     range[1] = range[1] / Wf;
 }
 
-// Both passes: workgroup g owns tile g of kSumTile elements; the last one also takes a tail that has
-// fewer than two words of its own.
+// Both passes: one workgroup per tile of kSumTile elements.  (A loop for a tail without two words of its own in place of
+// the borrowed elements below took 96 registers instead of 70, five waves per SIMD instead of seven.)
 constexpr int kSumTileThreads = 256;
 constexpr uint32_t kSumTile = 4u * kSumTileThreads * 4u;
-constexpr uint32_t kSumTileWords = kSumTile / 32u;   // per bit of width
+constexpr uint64_t kMostFoldedTiles = 16384;   // 67 M elements
 
 template <int NT, bool STRADDLE, bool ONCE>
 __global__ __launch_bounds__(NT) void sum_range_minmax_tensor_kernel(const RequantArgs ra, uint32_t* keys) {
@@ -464,23 +470,20 @@ __global__ __launch_bounds__(NT) void sum_range_minmax_tensor_kernel(const Requa
     __shared__ float2 s_tab[MQG_MAX_WORKERS];
     __shared__ uint32_t s_lo[NT / 64], s_hi[NT / 64];
     const uint32_t tid = threadIdx.x;
-    const uint64_t end = blockIdx.x + 1u == gridDim.x ? ra.q.n : (uint64_t)(blockIdx.x + 1u) * kCap;
+    const uint64_t tile_base = (uint64_t)blockIdx.x * kCap;
+    const uint64_t left = ra.q.n - tile_base;
+    const uint32_t tile_count = left < kCap ? (uint32_t)left : kCap;
+    float4 x[R];
+    decode_sum_tile_tensor<NT, STRADDLE, ONCE>(ra, tile_base, s_tab, x);
     const float inf = __builtin_inff();
     float lo = inf, hi = -inf;
-    for (uint64_t tile_base = (uint64_t)blockIdx.x * kCap; tile_base < end; tile_base += kCap) {
-        const uint64_t left = end - tile_base;
-        const uint32_t tile_count = left < kCap ? (uint32_t)left : kCap;
-        float4 x[R];
-        decode_sum_tile_tensor<NT, STRADDLE, ONCE>(ra, tile_base, s_tab, x);
 #pragma unroll
-        for (int j = 0; j < R; ++j) {   // elements past the end take no part
-            const uint32_t el = 4u * (j * NT + tid);
-            if (el + 0u < tile_count) { lo = fminf(lo, x[j].x); hi = fmaxf(hi, x[j].x); }
-            if (el + 1u < tile_count) { lo = fminf(lo, x[j].y); hi = fmaxf(hi, x[j].y); }
-            if (el + 2u < tile_count) { lo = fminf(lo, x[j].z); hi = fmaxf(hi, x[j].z); }
-            if (el + 3u < tile_count) { lo = fminf(lo, x[j].w); hi = fmaxf(hi, x[j].w); }
-        }
-        __syncthreads();   // s_tab is written again when a tail follows
+    for (int j = 0; j < R; ++j) {   // elements past the end take no part
+        const uint32_t el = 4u * (j * NT + tid);
+        if (el + 0u < tile_count) { lo = fminf(lo, x[j].x); hi = fmaxf(hi, x[j].x); }
+        if (el + 1u < tile_count) { lo = fminf(lo, x[j].y); hi = fmaxf(hi, x[j].y); }
+        if (el + 2u < tile_count) { lo = fminf(lo, x[j].z); hi = fmaxf(hi, x[j].z); }
+        if (el + 3u < tile_count) { lo = fminf(lo, x[j].w); hi = fmaxf(hi, x[j].w); }
     }
     uint32_t kl = order_key(lo), kh = order_key(hi);
     fold_keys<NT>(kl, kh, s_lo, s_hi);
@@ -494,16 +497,22 @@ __global__ __launch_bounds__(NT) void sum_range_minmax_tensor_kernel(const Requa
     }
 }
 
+// First element of pass 2's tile `tile` of `tiles`.  borrowed: elements that the last tile takes from the one before
+// it, so that it has two words of its own to find the range of the sum in.
+__device__ __forceinline__ uint64_t second_pass_base(uint32_t tile, uint32_t tiles, uint32_t borrowed) {
+    return (uint64_t)tile * kSumTile - (tile + 1u == tiles ? borrowed : 0u);
+}
+
 // One workgroup: all keys are read before the barrier of fold_keys, the words that receive the sum's range
 // (they overlap the keys) are written after it.
 constexpr int kFoldThreads = 1024;
-__global__ __launch_bounds__(kFoldThreads) void fold_sum_range_kernel(uint32_t* packed, const uint32_t groups,
-                                                                      const uint32_t slot_words, float* range, const float Wf) {
+__global__ __launch_bounds__(kFoldThreads) void fold_sum_range_kernel(uint32_t* packed, const uint32_t tiles, const uint32_t borrowed,
+                                                                      const uint32_t bits, float* range, const float Wf) {
     __shared__ uint32_t s_lo[kFoldThreads / 64], s_hi[kFoldThreads / 64];
     __shared__ float2 s_range;
     const uint32_t tid = threadIdx.x;
     uint32_t kl = 0xFFFFFFFFu, kh = 0u;
-    for (uint32_t i = tid; i < groups; i += kFoldThreads) {
+    for (uint32_t i = tid; i < tiles; i += kFoldThreads) {
         kl = min(kl, packed[2u * i]);
         kh = max(kh, packed[2u * i + 1u]);
     }
@@ -516,37 +525,35 @@ __global__ __launch_bounds__(kFoldThreads) void fold_sum_range_kernel(uint32_t* 
     }
     __syncthreads();
     const float2 r = s_range;
-    for (uint32_t i = tid; i < groups; i += kFoldThreads) {
-        uint32_t* slot = packed + (uint64_t)i * slot_words;
+    for (uint32_t i = tid; i < tiles; i += kFoldThreads) {
+        uint32_t* slot = packed + (second_pass_base(i, tiles, borrowed) >> 5) * bits;
         slot[0] = __builtin_bit_cast(uint32_t, r.x);
         slot[1] = __builtin_bit_cast(uint32_t, r.y);
     }
 }
 
 template <int NT, bool STRADDLE, bool ONCE>
-__global__ __launch_bounds__(NT) void requantize_minmax_tensor_kernel(const RequantArgs ra, const float* sum_range) {
+__global__ __launch_bounds__(NT) void requantize_minmax_tensor_kernel(const RequantArgs ra, const float* sum_range,
+                                                                      const uint32_t borrowed) {
     constexpr int R = 4;
     constexpr uint32_t kCap = Shared<R, NT, false>::kCap;
+    static_assert(kCap == kSumTile, "one workgroup per tile");
     __shared__ Shared<R, NT, false> sm;
     __shared__ float2 s_tab[MQG_MAX_WORKERS];
     const TileGeometry none = {};   // the range is given: no buckets
-    const uint64_t end = blockIdx.x + 1u == gridDim.x ? ra.q.n : (uint64_t)(blockIdx.x + 1u) * kCap;
-    // every lane holds the sum's range before the first barrier below; the words are overwritten after it
-    const float* slot = sum_range != nullptr ? sum_range
-                                             : reinterpret_cast<const float*>(ra.q.packed + (uint64_t)blockIdx.x * (kCap / 32u) * ra.q.bits);
+    const uint64_t tile_base = second_pass_base(blockIdx.x, gridDim.x, borrowed);
+    const uint64_t end = blockIdx.x + 1u == gridDim.x ? ra.q.n : second_pass_base(blockIdx.x + 1u, gridDim.x, borrowed);
+    const uint32_t tile_count = (uint32_t)(end - tile_base);
+    // every lane holds the sum's range before the barrier below; the words are overwritten after it
+    const float* slot = sum_range != nullptr ? sum_range : reinterpret_cast<const float*>(ra.q.packed + (tile_base >> 5) * ra.q.bits);
     const float2 range = make_float2(slot[0], slot[1]);
-    for (uint64_t tile_base = (uint64_t)blockIdx.x * kCap; tile_base < end; tile_base += kCap) {
-        const uint64_t left = end - tile_base;
-        const uint32_t tile_count = left < kCap ? (uint32_t)left : kCap;
-        clear_shared(sm, tile_count, ra.q.bits);
-        float4 x[R];
-        decode_sum_tile_tensor<NT, STRADDLE, ONCE>(ra, tile_base, s_tab, x);   // its barrier also covers clear_shared
-        if (tile_count == kCap) {
-            encode_minmax_tile<R, NT, kTailNone, false, true>(ra.q, none, 0u, tile_base, tile_count, x, 1.0f, sm, range);
-        } else {
-            encode_minmax_tile<R, NT, kTailElements, false, true>(ra.q, none, 0u, tile_base, tile_count, x, 1.0f, sm, range);
-        }
-        __syncthreads();   // the staged words are stored before the next tile clears them
+    clear_shared(sm, tile_count, ra.q.bits);
+    float4 x[R];
+    decode_sum_tile_tensor<NT, STRADDLE, ONCE>(ra, tile_base, s_tab, x);   // its barrier also covers clear_shared
+    if (tile_count == kCap) {
+        encode_minmax_tile<R, NT, kTailNone, false, true>(ra.q, none, 0u, tile_base, tile_count, x, 1.0f, sm, range);
+    } else {
+        encode_minmax_tile<R, NT, kTailElements, false, true>(ra.q, none, 0u, tile_base, tile_count, x, 1.0f, sm, range);
     }
 }
 
@@ -1054,22 +1061,22 @@ hipError_t launch_requantize_minmax_tensor(const RequantArgs& ra_in, hipStream_t
         }
         return launch_requantize_minmax(one, stream);
     }
-    uint64_t groups = (ra_in.q.n + kSumTile - 1) / kSumTile;
-    if (groups > 0x7FFFFFFFull) return hipErrorInvalidValue;
-    const uint64_t tail = ra_in.q.n % kSumTile;
-    if (tail != 0 && tail * ra_in.q.bits <= 32u) groups -= 1u;   // no second word for the range of the sum
+    const uint64_t tiles = (ra_in.q.n + kSumTile - 1) / kSumTile;
+    if (tiles > 0x7FFFFFFFull) return hipErrorInvalidValue;
     const uint64_t words = (ra_in.q.n >> 5) * ra_in.q.bits + (((ra_in.q.n & 31u) * ra_in.q.bits + 31u) >> 5);
-    bool in_place = false;
+    bool atomics = tiles > kMostFoldedTiles;
     for (uint32_t w = 0; w < ra_in.W; ++w) {
         const uint64_t in = reinterpret_cast<uintptr_t>(ra_in.packed[w]), out = reinterpret_cast<uintptr_t>(ra_in.q.packed);
-        in_place = in_place || (in < out + 4u * words && out < in + 4u * words);
+        atomics = atomics || (in < out + 4u * words && out < in + 4u * words);
     }
-    uint32_t* keys = in_place ? reinterpret_cast<uint32_t*>(ra_in.q.scales) : nullptr;
-    const float* sum_range = in_place ? ra_in.q.scales : nullptr;
-    const dim3 grid((uint32_t)groups), block(NT);
+    const uint64_t tail = ra_in.q.n % kSumTile;
+    const uint32_t borrowed = !atomics && tail != 0 && tail * ra_in.q.bits <= 32u ? 64u : 0u;   // 64 elements are two words at one bit
+    uint32_t* keys = atomics ? reinterpret_cast<uint32_t*>(ra_in.q.scales) : nullptr;
+    const float* sum_range = atomics ? ra_in.q.scales : nullptr;
+    const dim3 grid((uint32_t)tiles), block(NT);
     const bool straddle = (32u % ra_in.q.bits) != 0u;
     const bool once = decode::codes_read_once(ra_in.q.bits);
-    if (in_place) hipLaunchKernelGGL(range_init_kernel, dim3(1), dim3(1), 0, stream, keys);
+    if (atomics) hipLaunchKernelGGL(range_init_kernel, dim3(1), dim3(1), 0, stream, keys);
     if (straddle) {
         if (once) hipLaunchKernelGGL((sum_range_minmax_tensor_kernel<NT, true, true>), grid, block, 0, stream, ra_in, keys);
         else hipLaunchKernelGGL((sum_range_minmax_tensor_kernel<NT, true, false>), grid, block, 0, stream, ra_in, keys);
@@ -1077,22 +1084,22 @@ hipError_t launch_requantize_minmax_tensor(const RequantArgs& ra_in, hipStream_t
         if (once) hipLaunchKernelGGL((sum_range_minmax_tensor_kernel<NT, false, true>), grid, block, 0, stream, ra_in, keys);
         else hipLaunchKernelGGL((sum_range_minmax_tensor_kernel<NT, false, false>), grid, block, 0, stream, ra_in, keys);
     }
-    if (in_place) {
+    if (atomics) {
         hipLaunchKernelGGL(range_finish_kernel, dim3(1), dim3(1), 0, stream, keys);
     } else {
-        hipLaunchKernelGGL(fold_sum_range_kernel, dim3(1), dim3(kFoldThreads), 0, stream, ra_in.q.packed, (uint32_t)groups,
-                           kSumTileWords * ra_in.q.bits, ra_in.q.scales, (float)ra_in.W);
+        hipLaunchKernelGGL(fold_sum_range_kernel, dim3(1), dim3(kFoldThreads), 0, stream, ra_in.q.packed, (uint32_t)tiles,
+                           borrowed, ra_in.q.bits, ra_in.q.scales, (float)ra_in.W);
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (straddle) {
-        if (once) hipLaunchKernelGGL((requantize_minmax_tensor_kernel<NT, true, true>), grid, block, 0, stream, ra_in, sum_range);
-        else hipLaunchKernelGGL((requantize_minmax_tensor_kernel<NT, true, false>), grid, block, 0, stream, ra_in, sum_range);
+        if (once) hipLaunchKernelGGL((requantize_minmax_tensor_kernel<NT, true, true>), grid, block, 0, stream, ra_in, sum_range, borrowed);
+        else hipLaunchKernelGGL((requantize_minmax_tensor_kernel<NT, true, false>), grid, block, 0, stream, ra_in, sum_range, borrowed);
     } else {
-        if (once) hipLaunchKernelGGL((requantize_minmax_tensor_kernel<NT, false, true>), grid, block, 0, stream, ra_in, sum_range);
-        else hipLaunchKernelGGL((requantize_minmax_tensor_kernel<NT, false, false>), grid, block, 0, stream, ra_in, sum_range);
+        if (once) hipLaunchKernelGGL((requantize_minmax_tensor_kernel<NT, false, true>), grid, block, 0, stream, ra_in, sum_range, borrowed);
+        else hipLaunchKernelGGL((requantize_minmax_tensor_kernel<NT, false, false>), grid, block, 0, stream, ra_in, sum_range, borrowed);
     }
-    if (in_place) hipLaunchKernelGGL(range_divide_kernel, dim3(1), dim3(1), 0, stream, ra_in.q.scales, (float)ra_in.W);
+    if (atomics) hipLaunchKernelGGL(range_divide_kernel, dim3(1), dim3(1), 0, stream, ra_in.q.scales, (float)ra_in.W);
     return hipGetLastError();
 }
 

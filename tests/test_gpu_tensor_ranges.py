@@ -43,6 +43,33 @@ def test_tensor_range_exchange_at_the_edges(n, bits):
     assert np.array_equal(to_u32(q[1][0]), want_pk)
 
 
+@pytest.mark.parametrize("extra", [0, 1])
+def test_the_largest_folded_step_and_the_first_with_atomics(extra):
+    n, bits, W = 16384 * TILE + extra, 2, 2
+    grads = [workloads.normal(n, 1e-2, 3 + w, DEV) for w in range(W)]
+    grads[1][n - 1] = 0.5
+    q = [mqgrad.mqg_quantize_minmax_tensor(g, bits) for g in grads]
+    pk, rg = mqgrad.mqg_aggregate_requantize_minmax_tensor([x[0] for x in q], [x[1] for x in q], n, bits)
+    torch.cuda.synchronize()
+    want_pk, want_rg = ref.aggregate_requantize_minmax([to_u32(x[0]) for x in q], [x[1].cpu().numpy() for x in q], n, bits, n)
+    assert rg.cpu().numpy().tobytes() == want_rg.tobytes()
+    assert np.array_equal(to_u32(pk), want_pk)
+
+
+@pytest.mark.parametrize("W,bits", [(1, 1), (64, 1), (24, 4)])
+@pytest.mark.parametrize("tail", [1, 4, 8, 9, 32, 33])
+def test_tails_without_two_words_of_their_own(tail, W, bits):
+    for tiles in (4, 5, 41):
+        n = tiles * TILE + tail
+        grads = [workloads.laplace(n, 1e-3, 5 * w + bits, DEV) + 1e-4 * w for w in range(W)]
+        q = [mqgrad.mqg_quantize_minmax_tensor(g, bits) for g in grads]
+        pk, rg = mqgrad.mqg_aggregate_requantize_minmax_tensor([x[0] for x in q], [x[1] for x in q], n, bits)
+        torch.cuda.synchronize()
+        want_pk, want_rg = ref.aggregate_requantize_minmax([to_u32(x[0]) for x in q], [x[1].cpu().numpy() for x in q], n, bits, n)
+        assert rg.cpu().numpy().tobytes() == want_rg.tobytes()
+        assert np.array_equal(to_u32(pk), want_pk)
+
+
 @pytest.mark.parametrize("sizes", [[1, 5, 8191], [16384, 3, 70001], [8 * 8192, 1, 33, 2 * 8192 - 1, 2 * 8192]])
 def test_batched_tensor_ranges_mix_one_and_several_workgroups(sizes):
     grads = [workloads.normal(n, 1e-2, 3 + n, DEV) for n in sizes]
