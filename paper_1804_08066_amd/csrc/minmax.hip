@@ -34,6 +34,7 @@ constexpr int kSumThreads = 512;
 constexpr uint32_t kSumBlocks = 512;
 // Largest tensor that one workgroup encodes in registers, whatever the encoder: the largest bucket.
 constexpr uint64_t kOneBucketElems = 16384;
+constexpr uint32_t kComputeUnits = 256;
 
 // A workgroup's tile: whole buckets.
 struct TileGeometry {
@@ -294,13 +295,25 @@ __global__ __launch_bounds__(NT) void quantize_minmax_tensors_kernel(const Batch
 // The server's re-encoding step of the full exchange (ReceiveQGThenSendQG): the tile's values are the
 // sum over the W workers' de-quantized gradients, decoded from their streams in worker order; the
 // stored range is divided by W.  (step, min) of every worker's buckets of the tile sit in an LDS table.
-// Bound by latency: left alone the compiler took 107 registers (four waves per SIMD) for eight workers' words and
-// their table entries; with four workers' words in flight and seven waves the step of 7.2 M elements, 4
-// workers, 6 bits, bucket 2304 takes 14.9 us instead of 22.2 (17.5 with the new tile alone).
-template <int NT, bool ONE, bool STRADDLE, bool ONCE>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 768 ? 6 : 7, 8))) void requantize_minmax_kernel(const RequantArgs ra, const TileGeometry g) {
+//
+// Bound by latency: that of the code words, hidden by other waves in long launches and by more words in flight in short
+// ones.  CH: workers whose words are in flight together; left alone the compiler takes 112-117 registers for eight
+// and their table entries (four waves per SIMD), with four seven waves fit (MANY and 256 lanes: six, since seven spill).
+// us at 4 bits, eight in flight / four:                 (256 lanes, seven waves with 8-16 bytes of scratch memory)
+//   bucket 1024, 24 workers, 1 M elements     9.0 /  9.4   (11.1)
+//   bucket 4096, 16 workers, 1 M              7.2 /  7.4   ( 8.4)
+//   bucket 1024,  8 workers, 30 M            42.0 / 39.5   (39.9)
+//   bucket 2304,  4 workers, 30 M            63.5 / 35.6
+//   bucket 12320, 8 workers, 30 M            74.1 / 49.2
+// MANY: more than CH workers.  Without the loop over them 58 registers do (eight waves).
+constexpr int requant_waves(int NT, bool one, int CH, bool many) {
+    if (NT == 768) return 6;                     // two workgroups per compute unit
+    if (!one && CH == 8) return 4;
+    return !one && NT == 256 && many ? 6 : 7;
+}
+template <int NT, bool ONE, bool STRADDLE, bool ONCE, int CH, bool MANY>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(requant_waves(NT, ONE, CH, MANY), 8))) void requantize_minmax_kernel(const RequantArgs ra, const TileGeometry g) {
     constexpr int R = 4;
-    constexpr int CH = 4;   // workers whose code loads are in flight together
     __shared__ Shared<R, NT, ONE> sm;
     extern __shared__ float2 s_tab[];   // [W][buckets of the tile]
     const QuantizeArgs& a = ra.q;
@@ -333,7 +346,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 768 ? 
         if (bl[j] >= nbt) bl[j] = nbt - 1u;   // quads past the end: any valid slot
         x[j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     }
-    for (uint32_t w0 = 0; w0 < ra.W; w0 += CH) {
+    for (uint32_t w0 = 0; w0 < (MANY ? ra.W : 1u); w0 += CH) {
         if (w0 > 0) decode::fetch_codes<R, CH, ONCE>(ra.packed, ra.W, w0, cw, c);
 #pragma unroll
         for (int t = 0; t < CH; ++t) {
@@ -872,17 +885,17 @@ uint32_t tile_waves(uint32_t bucket) {
     }
     return nw;
 }
-TileGeometry tile_geometry(uint32_t bucket) {
-    const uint32_t buckets = (tile_waves(bucket) * 1024u) / bucket, cells = bucket / 32u;
+TileGeometry tile_geometry(uint32_t bucket, uint32_t waves) {
+    const uint32_t buckets = (waves * 1024u) / bucket, cells = bucket / 32u;
     return {buckets * bucket, buckets, (65536u + cells - 1u) / cells};
 }
+TileGeometry tile_geometry(uint32_t bucket) { return tile_geometry(bucket, tile_waves(bucket)); }
 // Calls f(NT, ONE) with the workgroup size as a compile-time constant.
 template <class F>
-void with_tile_waves(uint32_t bucket, F f) {
+void with_tile_waves(uint32_t bucket, uint32_t nw, F f) {
     using std::integral_constant;
     using several = std::false_type;
     using one = std::true_type;
-    const uint32_t nw = tile_waves(bucket);
     if (bucket <= 4096u) {
         switch (nw) {
             case 5: return f(integral_constant<int, 320>{}, several{});
@@ -916,7 +929,11 @@ hipError_t launch_aggregate_s(const AggregateArgs& a, hipStream_t stream) {
 // ra.scales[w]: worker w's (min, max) pairs; ra.q.scales: (min, max) pairs of the mean
 hipError_t launch_requantize_minmax(const RequantArgs& ra, hipStream_t stream) {
     if (ra.q.n == 0) return hipSuccess;
-    TileGeometry g = tile_geometry(ra.q.bucket);
+    // Where every compute unit gets at most one workgroup, four waves of fewer buckets end sooner: bucket 2304, 24 workers,
+    // 65,536 elements 9.6 us, with five waves 10.3; at 1 M elements 11.9 and 10.9.
+    uint32_t waves = tile_waves(ra.q.bucket);
+    if (ra.q.bucket <= 4096u && ra.W > 4u && (ra.q.n - 1u) / tile_geometry(ra.q.bucket, 4u).elems < kComputeUnits) waves = 4u;
+    TileGeometry g = tile_geometry(ra.q.bucket, waves);
     const uint32_t max_nb = 4096u / ra.W;   // at most 4096 table entries (32 KB of LDS); >= 64
     if (g.buckets > max_nb) {
         g.buckets = max_nb;
@@ -925,11 +942,25 @@ hipError_t launch_requantize_minmax(const RequantArgs& ra, hipStream_t stream) {
     const uint64_t tiles = (ra.q.n + g.elems - 1) / g.elems;
     if (tiles > 0x7FFFFFFFull) return hipErrorInvalidValue;
     const size_t lds = sizeof(float2) * ra.W * g.buckets;
-    with_tile_waves(ra.q.bucket, [&](auto nt, auto one) {
+    with_tile_waves(ra.q.bucket, waves, [&](auto nt, auto one) {
+        constexpr int NT = decltype(nt)::value;
+        constexpr bool ONE = decltype(one)::value;
+        // Short: at most one workgroup per compute unit, or two of four waves.  Eight in flight / four at 4 bits, 8 workers
+        // (seven waves): bucket 1024 at 1, 2, 3, 5 M elements 0.90, 0.89, 0.95, 1.02 of the time; 2304 at 1, 2, 3 M 0.93,
+        // 0.98, 1.24; 8192 0.95, 0.94, 1.03; 12320 (1024 lanes) 1.00, 1.02, 1.02.
+        const bool short_launch = NT <= 512 && tiles <= (NT == 256 ? 2u : 1u) * kComputeUnits;
         with_codes(ra.q.bits, [&](auto straddle, auto once) {
-            constexpr int NT = decltype(nt)::value;
-            hipLaunchKernelGGL((requantize_minmax_kernel<NT, decltype(one)::value, decltype(straddle)::value, decltype(once)::value>),
-                               dim3((uint32_t)tiles), dim3(NT), lds, stream, ra, g);
+            const auto launch = [&](auto ch, auto many) {
+                hipLaunchKernelGGL((requantize_minmax_kernel<NT, ONE, decltype(straddle)::value, decltype(once)::value, decltype(ch)::value, decltype(many)::value>),
+                                   dim3((uint32_t)tiles), dim3(NT), lds, stream, ra, g);
+            };
+            using four = std::integral_constant<int, 4>;
+            using eight = std::integral_constant<int, 8>;
+            if constexpr (NT <= 512) {
+                if (ra.W > 4u && short_launch) return launch(eight{}, std::true_type{});
+            }
+            if (ra.W <= 4u) launch(four{}, std::bool_constant<ONE>{});
+            else launch(four{}, std::true_type{});
         });
     });
     return hipGetLastError();
@@ -943,7 +974,7 @@ hipError_t launch_quantize_minmax(const QuantizeArgs& a, hipStream_t stream) {
     const TileGeometry g = tile_geometry(a.bucket);
     const uint64_t tiles = (a.n + g.elems - 1) / g.elems;
     if (tiles > 0x7FFFFFFFull) return hipErrorInvalidValue;
-    with_tile_waves(a.bucket, [&](auto nt, auto one) {
+    with_tile_waves(a.bucket, tile_waves(a.bucket), [&](auto nt, auto one) {
         constexpr int NT = decltype(nt)::value;
         hipLaunchKernelGGL((quantize_minmax_kernel<4, NT, decltype(one)::value>), dim3((uint32_t)tiles), dim3(NT), 0, stream, a, g);
     });
@@ -963,7 +994,7 @@ hipError_t launch_quantize_minmax_tensors(const BatchQuantizeArgs& a, uint32_t t
     if (tiles == 0) return hipSuccess;
     if (a.common.bucket_shift >= 5) return launch_quantize_minmax_tensors_wave(a, tiles, stream);
     const TileGeometry g = tile_geometry(a.common.bucket);
-    with_tile_waves(a.common.bucket, [&](auto nt, auto one) {
+    with_tile_waves(a.common.bucket, tile_waves(a.common.bucket), [&](auto nt, auto one) {
         constexpr int NT = decltype(nt)::value;
         hipLaunchKernelGGL((quantize_minmax_tensors_kernel<4, NT, decltype(one)::value>), dim3(tiles), dim3(NT), 0, stream, a, g);
     });

@@ -1,5 +1,5 @@
-"""What the compiler gave the kernels of the built library: the registers that the measured numbers of waves per SIMD
-need."""
+"""What the compiler gave the kernels of the built library: no scratch memory, and the registers that the measured numbers
+of waves per SIMD need."""
 import struct
 
 import msgpack
@@ -42,7 +42,12 @@ def built():
     return found
 
 
-@pytest.mark.parametrize("kernel,waves", [("sum_range_minmax_tensor_kernel", 7), ("requantize_minmax_tensor_kernel", 7)])
+def test_no_kernel_uses_scratch_memory(built):
+    assert {n: k[".private_segment_fixed_size"] for n, k in built.items() if k[".private_segment_fixed_size"]} == {}
+
+
+@pytest.mark.parametrize("kernel,waves", [("sum_range_minmax_tensor_kernel", 7), ("requantize_minmax_tensor_kernel", 7),
+                                          ("requantize_minmax_kernel", 4)])
 def test_waves_per_simd(built, kernel, waves):
     mine = {n: k for n, k in built.items() if kernel in n}
     assert mine
