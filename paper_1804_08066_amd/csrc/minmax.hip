@@ -687,38 +687,35 @@ __global__ __launch_bounds__(kThreads) void aggregate_update_minmax_tensors_kern
 // The paper encodes a tensor over ONE range.  A workgroup folds its share of the tensor into a pair of
 // order-preserving integer keys (exact and order independent); what becomes of the workgroups' keys
 // depends on the memory at hand.
-// min / max keys of the share of g[0..n) that belongs to workgroup `block` of `nblocks`, in thread 0: rows
-// of 2048 elements (one float4 per lane), nblocks apart, four in flight per lane.
+// min / max keys of the share of g[0..n) that belongs to workgroup `block` of `nblocks`, in thread 0: contiguous pieces
+// of four rows of 2048 elements (one float4 per lane, four in flight), and what is left spread over all.  (Single rows,
+// nblocks apart: mqg_tensor_range at 10 M elements 19 us instead of 14, at 100 M 66 instead of 62.)
 __device__ __forceinline__ void block_range(const float* __restrict__ g, const uint64_t n, const uint32_t block,
                                             const uint32_t nblocks, uint32_t& kl, uint32_t& kh, uint32_t* s_lo, uint32_t* s_hi) {
     const uint32_t tid = threadIdx.x;
     float lo = __builtin_inff(), hi = -__builtin_inff();
     const v4f_a4* __restrict__ g4 = reinterpret_cast<const v4f_a4*>(g);   // 128-bit loads need dword alignment only
+    const uint64_t gtid = (uint64_t)block * kSumThreads + tid;
+    const uint64_t stride = (uint64_t)nblocks * kSumThreads;
     const uint64_t nq = n >> 2;
-    const uint64_t rows = nq / kSumThreads;
     const auto fold = [&](const v4f t) {
         lo = min_f32(lo, quad_min(t.x, t.y, t.z, t.w));
         hi = max_f32(hi, quad_max(t.x, t.y, t.z, t.w));
     };
-    for (uint64_t r = block; r < rows; r += 4u * (uint64_t)nblocks) {
+    const uint64_t pieces = nq / (4u * kSumThreads);
+    for (uint64_t pc = block; pc < pieces; pc += nblocks) {
+        const v4f_a4* __restrict__ src = g4 + pc * (4u * kSumThreads) + tid;
         v4f t[4];
-        t[0] = __builtin_nontemporal_load(g4 + r * kSumThreads + tid);
 #pragma unroll
-        for (int u = 1; u < 4; ++u) {   // a row past the end: this one again
-            const uint64_t ru = r + u * (uint64_t)nblocks;
-            t[u] = __builtin_nontemporal_load(g4 + (ru < rows ? ru : r) * kSumThreads + tid);
-        }
+        for (int u = 0; u < 4; ++u) t[u] = __builtin_nontemporal_load(src + u * kSumThreads);
 #pragma unroll
         for (int u = 0; u < 4; ++u) fold(t[u]);
     }
-    if (block + 1u == nblocks) {   // less than one row is left: at most one float4 per lane, then three elements
-        const uint64_t q = rows * kSumThreads + tid;
-        if (q < nq) fold(__builtin_nontemporal_load(g4 + q));
-        if (tid < (n & 3u)) {
-            const float v = g[(nq << 2) + tid];
-            lo = min_f32(lo, v);
-            hi = max_f32(hi, v);
-        }
+    for (uint64_t q = pieces * (4u * kSumThreads) + gtid; q < nq; q += stride) fold(__builtin_nontemporal_load(g4 + q));
+    if (gtid < (n & 3u)) {
+        const float v = g[(nq << 2) + gtid];
+        lo = min_f32(lo, v);
+        hi = max_f32(hi, v);
     }
     kl = order_key(lo);
     kh = order_key(hi);
@@ -737,8 +734,8 @@ __global__ __launch_bounds__(kSumThreads) void tensor_range_kernel(const float* 
 
 // Ranges of tensors that are about to be encoded: every workgroup leaves its keys at the front of the
 // tensor's code words, which the encoder overwrites afterwards, and one workgroup per tensor folds them:
-// no priming launch, no atomics, and as many workgroups as fill the chip (8.8 M elements: 8 us,
-// 15 us with atomics; the ten layers' two largest, 0.9 M elements: 4 us, 14 us with atomics).
+// no priming launch and no atomics (the encode of 8.8 M elements at 4 bits 15.5 us, 23.1 with atomics; the small CNN's two
+// largest layers, 0.9 M elements in all, 4 us for the ranges, 14 with atomics).
 // A tensor of one workgroup gets its range at once.
 __global__ __launch_bounds__(kSumThreads) void tensor_range_parts_kernel(const TensorRangeBatch b, const uint32_t count) {
     drop_every_nan();
@@ -1001,18 +998,17 @@ hipError_t launch_quantize_minmax_tensors(const BatchQuantizeArgs& a, uint32_t t
     return hipGetLastError();
 }
 
-// range[k][0..1] <- min, max of tensor k, whose encoder will overwrite parts[k].  At least 8192 elements per
-// workgroup, so that a tensor's code words hold two words for each; at most kRangeBlocks of them, which
-// is all that the chip holds at once.
+// range[k][0..1] <- min, max of tensor k, whose encoder will overwrite parts[k].  One piece of block_range per
+// workgroup, up to kSumBlocks of them: with 1024 the encode took up to 3 % more from 8.8 M elements on, 5 % at 1 G.
 hipError_t launch_tensor_ranges(TensorRangeBatch& b, uint32_t count, hipStream_t stream) {
-    constexpr uint64_t kRangeBlocks = 1024;
+    constexpr uint64_t kPiece = 16u * kSumThreads;   // elements; 512 words at one bit: two for each workgroup's keys
     uint32_t blocks = 0;
     bool parts = false;
     for (uint32_t k = 0; k < kMaxBatchTensors; ++k) {
         b.block_start[k] = blocks;
         if (k >= count || b.n[k] == 0) continue;
-        const uint64_t most = b.n[k] / 8192u;
-        const uint32_t mine = most < 1u ? 1u : (uint32_t)(most > kRangeBlocks ? kRangeBlocks : most);
+        const uint64_t most = b.n[k] / kPiece;
+        const uint32_t mine = most < 1u ? 1u : (uint32_t)(most > kSumBlocks ? kSumBlocks : most);
         parts = parts || mine > 1u;
         blocks += mine;
     }

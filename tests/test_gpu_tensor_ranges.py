@@ -82,6 +82,19 @@ def test_batched_tensor_ranges_mix_one_and_several_workgroups(sizes):
             assert np.array_equal(to_u32(pk), pk_o)
 
 
+@pytest.mark.parametrize("n", [3, 2047, 8191, 8192, 8195, 4 * 8192 + 2052, 512 * 8192 - 1, 512 * 8192 + 1, 513 * 8192 + 2051])
+def test_ranges_at_the_edges_of_pieces_and_grids(n):
+    g = workloads.normal(n + 1, 1e-2, 5, DEV)[1:]      # off a 16-byte boundary
+    for at in (0, n // 2, n - 1):                      # the extremes where the share of a workgroup begins or ends
+        g[at] = 0.5 + at
+        g[n - 1 - at] = -0.5 - at
+        rg = mqgrad.mqg_tensor_range(g)
+        pk, rt = mqgrad.mqg_quantize_minmax_tensor(g, 3)
+        torch.cuda.synchronize()
+        assert rg.tolist() == rt.tolist() == [g.min().item(), g.max().item()]
+    assert np.array_equal(to_u32(pk), ref.quantize_minmax(g.cpu().numpy(), 3, n)[0])
+
+
 @pytest.mark.parametrize("n", [5000, 16384, 70001])
 def test_values_that_are_not_numbers_take_no_part_in_a_tensors_range(n):
     g = workloads.normal(n, 1e-2, 9, DEV)
