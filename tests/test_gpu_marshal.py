@@ -1,5 +1,8 @@
-"""The binding's native argument tables against its own checks: the same streams from what takes the native path and
-from what does not (a tensor subclass, another container), and the same refusals."""
+"""The binding's native argument tables against its own checks: the same tables and streams from what takes the native
+path and from what does not (a tensor subclass, another container, no native module), and the same refusals."""
+import collections
+import ctypes as C
+
 import pytest
 import torch
 
@@ -19,10 +22,95 @@ def _case():
     return grads, [mqgrad.mqg_quantize(g, BITS, BUCKET, 7, 1, w) for w, g in enumerate(grads)]
 
 
-@pytest.mark.parametrize("wrap", [lambda t: t, lambda t: t.as_subclass(Sub), lambda t: torch.nn.Parameter(t) if t.is_floating_point() else t])
+def native(*args):
+    """What the module makes of (name, arguments): a table, or None for what it leaves to the binding."""
+    return getattr(mqgrad._marshal, args[0])(*args[1:])
+
+
+def parameter(t):
+    return torch.nn.Parameter(t) if t.is_floating_point() else t
+
+
+@pytest.mark.parametrize("kind", [mqgrad._SCALES, mqgrad._PAIRS, mqgrad._ONE_PAIR])
+@pytest.mark.parametrize("order", [list, tuple])
+@pytest.mark.parametrize("wrap", [lambda t: t, parameter])
+def test_plain_arguments_take_the_native_path_and_its_tables_are_the_bindings(wrap, order, kind):
+    mqgrad.lib()
+    bucket = 0 if kind == mqgrad._ONE_PAIR else BUCKET
+    grads, q = _case()
+    wide = [torch.zeros(2 * x[1].numel(), device=DEV) for x in q]     # pairs need twice the scales' room
+    packed, scales = order(wrap(x[0]) for x in q), order(wrap(x) for x in wide)
+    W_, pa, sa = native("pointers", packed, scales, N, BITS, bucket, kind)
+    assert W_ == W and list((C.c_uint64 * W).from_buffer_copy(pa)) == [x.data_ptr() for x in packed]
+    assert list((C.c_uint64 * W).from_buffer_copy(sa)) == [x.data_ptr() for x in scales]
+    assert native("stream", wrap(grads[0]), packed[0], scales[0], BITS, bucket, kind) == \
+        (N, grads[0].data_ptr(), packed[0].data_ptr(), scales[0].data_ptr())
+
+    outputs, bases = order(order((p, s)) for p, s in zip(packed, scales)), order([0, 8, 1 << 40])
+    table = (mqgrad.QuantizeItem * W).from_buffer_copy(native("quantize_items", order(grads), outputs, bases, BITS, bucket, kind))
+    for i, t in enumerate(table):
+        assert (t.grad, t.n, t.elem_base, t.packed_out, t.scales_out, t.scales_in) == \
+            (grads[i].data_ptr(), N, bases[i], packed[i].data_ptr(), scales[i].data_ptr(), None)
+
+    params = [wrap(torch.ones(N, device=DEV)) for _ in range(2)]
+    layers = order([{"params": params[0], "raw": order(grads)}, {"params": params[1], "packed": packed, "scales": scales}])
+    made = native("update_items", layers, W, BITS, bucket, kind)
+    raw, encoded = (mqgrad.UpdateItem * 2).from_buffer_copy(made)
+    assert [t.n for t in (raw, encoded)] == [N, N] and [t.params for t in (raw, encoded)] == [p.data_ptr() for p in params]
+    assert not raw.packed and not raw.scales and not encoded.raw
+    assert raw.raw[:W] == [g.data_ptr() for g in grads]
+    assert encoded.packed[:W] == [x.data_ptr() for x in packed] and encoded.scales[:W] == [x.data_ptr() for x in scales]
+
+
+def test_what_the_native_path_leaves_to_the_binding():
+    mqgrad.lib()
+    grads, q = _case()
+    pk, sc = [x[0] for x in q], [x[1] for x in q]
+    p = torch.ones(N, device=DEV)
+    plain = [("pointers", pk, sc, N, BITS, BUCKET, 0), ("stream", grads[0], pk[0], sc[0], BITS, BUCKET, 0),
+             ("quantize_items", grads, q, None, BITS, BUCKET, 0),
+             ("update_items", [{"params": p, "packed": pk, "scales": sc}], W, BITS, BUCKET, 0)]
+    for args in plain:
+        assert native(*args) is not None
+    sub = [x.as_subclass(Sub) for x in pk]
+    short, other, double = [x[:-1] for x in pk], collections.UserList(pk), [s.double() for s in sc]
+    for refused in [("pointers", sub, sc, N, BITS, BUCKET, 0), ("pointers", other, sc, N, BITS, BUCKET, 0),
+                    ("pointers", short, sc, N, BITS, BUCKET, 0), ("pointers", pk, double, N, BITS, BUCKET, 0),
+                    ("pointers", pk, sc[:2], N, BITS, BUCKET, 0), ("pointers", pk, sc, N, 9, BUCKET, 0),
+                    ("pointers", pk, sc, -1, BITS, BUCKET, 0), ("pointers", pk, sc, N, BITS, 48, 0),
+                    ("stream", grads[0].cpu(), pk[0], sc[0], BITS, BUCKET, 0), ("stream", grads[0], pk[0], sc[0], BITS, BUCKET, 1),
+                    ("stream", grads[0][::2], pk[0], sc[0], BITS, BUCKET, 0), ("stream", grads[0].to("meta"), pk[0], sc[0], BITS, BUCKET, 0),
+                    ("quantize_items", grads, q[:2], None, BITS, BUCKET, 0), ("quantize_items", grads, q, [0, 0], BITS, BUCKET, 0),
+                    ("update_items", [{"params": p, "packed": pk, "scales": sc[:2]}], W, BITS, BUCKET, 0),
+                    ("update_items", [{"params": p, "raw": [g[:-1] for g in grads]}], W, BITS, BUCKET, 0),
+                    ("update_items", [{"params": p}], W, BITS, BUCKET, 0), ("update_items", plain[3][1], 0, BITS, BUCKET, 0)]:
+        assert native(*refused) is None, refused[0]
+
+
+def test_without_the_module_the_results_are_the_same(monkeypatch):
+    mqgrad.lib()
+    assert mqgrad._marshal is not mqgrad._NoTables
+    for native_tables in (True, False):
+        if not native_tables:
+            monkeypatch.setattr(mqgrad, "_marshal", mqgrad._NoTables)
+        grads, q = _case()
+        params, raw = torch.ones(N, device=DEV), torch.ones(N, device=DEV)
+        mqgrad.mqg_aggregate_update([x[0] for x in q], [x[1] for x in q], N, BITS, BUCKET, 0.1, params)
+        mqgrad.mqg_aggregate_update_tensors([{"params": raw, "raw": grads}, {"params": params, "packed": [x[0] for x in q], "scales": [x[1] for x in q]}],
+                                            W, BITS, BUCKET, 0.1)
+        many = mqgrad.mqg_quantize_tensors(grads, BITS, BUCKET, 7, 1, 1, elem_bases=[0, 8, 16])
+        one = mqgrad.mqg_quantize_minmax_tensors(grads, BITS, 0)
+        results = [x for t in q + many + one for x in t] + [params, raw]
+        if native_tables:
+            want = results
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(results, want))
+
+
+@pytest.mark.parametrize("wrap", [lambda t: t, lambda t: t.as_subclass(Sub), parameter])
 def test_every_form_of_argument_gives_the_same_results(wrap):
     grads, q = _case()
-    for order in (list, tuple):
+    for order in (list, tuple, collections.UserList):
         again = mqgrad.mqg_quantize(wrap(grads[1]), BITS, BUCKET, 7, 1, 1, packed_out=wrap(torch.zeros_like(q[1][0])), scales_out=wrap(torch.zeros_like(q[1][1])))
         assert torch.equal(again[0], q[1][0]) and torch.equal(again[1], q[1][1])
         many = mqgrad.mqg_quantize_tensors(order(wrap(g) for g in grads), BITS, BUCKET, 7, 1, 1, elem_bases=order([0, 0, 0]))
