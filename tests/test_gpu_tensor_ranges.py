@@ -95,11 +95,67 @@ def test_ranges_at_the_edges_of_pieces_and_grids(n):
     assert np.array_equal(to_u32(pk), ref.quantize_minmax(g.cpu().numpy(), 3, n)[0])
 
 
+def codes(pk, n, bits):
+    return ref.unpack(to_u32(pk), n, bits)
+
+
 @pytest.mark.parametrize("n", [5000, 16384, 70001])
 def test_values_that_are_not_numbers_take_no_part_in_a_tensors_range(n):
+    bits = 4
     g = workloads.normal(n, 1e-2, 9, DEV)
     g[8:12] = float("nan")           # all that one lane holds
-    rest = torch.cat([g[:8], g[12:]])
-    _, rg = mqgrad.mqg_quantize_minmax_tensor(g, 4)
+    g[n - 7] = float("nan")
+    numbers = ~torch.isnan(g)
+    mn, mx = g[numbers].min().item(), g[numbers].max().item()
+    filled = torch.where(numbers, g, torch.full_like(g, mn))       # the oracle's codes over the same range
+    want = codes(torch.from_numpy(ref.quantize_minmax(filled.cpu().numpy(), bits, n)[0].view(np.int32)), n, bits)
+    batch = mqgrad.mqg_quantize_minmax_tensors([filled, g, g[:33]], bits, 0)[1]
+    for pk, rg in (mqgrad.mqg_quantize_minmax_tensor(g, bits), batch):
+        torch.cuda.synchronize()
+        assert rg.tolist() == [mn, mx]
+        assert np.array_equal(codes(pk, n, bits), want)            # a NaN's own code is 0, which is the smallest value's
+    assert mqgrad.mqg_tensor_range(g).tolist() == [mn, mx]
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), float("-inf")])
+@pytest.mark.parametrize("n", [5000, 16384, 16385, 70001])
+def test_one_workers_range_that_is_not_finite(n, bad):
+    """The sum has no number in it, or infinities of one sign: small tensors (one workgroup) and larger ones agree on
+    the rule, and on the codes."""
+    bits, W = 4, 3
+    grads = [workloads.normal(n, 1e-2, 9 + w, DEV) for w in range(W)]
+    q = [mqgrad.mqg_quantize_minmax_tensor(g, bits) for g in grads]
+    q[1][1][:] = bad
+    pk, rg = mqgrad.mqg_aggregate_requantize_minmax_tensor([x[0] for x in q], [x[1] for x in q], n, bits)
     torch.cuda.synchronize()
-    assert rg.tolist() == [rest.min().item(), rest.max().item()]
+    # a step of inf - inf or NaN makes every value of that worker NaN: the empty range, and code 0 throughout
+    assert rg.tolist() == [float("inf"), float("-inf")]
+    assert not codes(pk, n, bits).any()
+
+
+@pytest.mark.parametrize("bucket", [32, 1024, 96, 2304, 4128, 8192])
+def test_infinities_and_zeros_of_both_signs_in_a_bucket(bucket):
+    """A bucket with infinities has them as its range and code 0 throughout; a bucket of values from 0 up with zeros of both
+    signs has the range from +0 and code 0 for either zero.  Its neighbours are as ever."""
+    bits, n = 3, 6 * bucket
+    g = workloads.normal(n, 1e-2, 4, DEV)
+    g[bucket + 5] = float("inf")
+    g[2 * bucket + 7] = float("-inf")
+    g[3 * bucket + 1], g[3 * bucket + 2] = float("inf"), float("-inf")
+    g[4 * bucket:5 * bucket] = g[4 * bucket:5 * bucket].abs()
+    g[4 * bucket:5 * bucket:3] = 0.0
+    g[4 * bucket + 1:5 * bucket:3] = -0.0
+    host = g.cpu().numpy()
+    batch = mqgrad.mqg_quantize_minmax_tensors([g], bits, bucket)[0]
+    for pk, rg in (mqgrad.mqg_quantize_minmax(g, bits, bucket), batch):
+        torch.cuda.synchronize()
+        rg, code = rg.cpu().numpy().reshape(-1, 2), codes(pk, n, bits)
+        for k in range(6):
+            part = host[k * bucket:(k + 1) * bucket]
+            assert rg[k].tolist() == [part.min(), part.max()]
+            if k in (1, 2, 3):
+                assert not code[k * bucket:(k + 1) * bucket].any()
+            else:
+                assert np.array_equal(code[k * bucket:(k + 1) * bucket], codes(torch.from_numpy(ref.quantize_minmax(part, bits, bucket)[0].view(np.int32)), bucket, bits))
+        assert not np.signbit(rg[4, 0])
+        assert not code[4 * bucket:5 * bucket:3].any() and not code[4 * bucket + 1:5 * bucket:3].any()
