@@ -624,10 +624,11 @@ def time_minmax(wl, bits, bucket, lr, steps, warmup):
             "quantize_minmax": row("quantize_minmax_wave_kernel", q_bytes, q_ms),
             "aggregate_update_minmax": row("aggregate_update_minmax_kernel", a_bytes, a_ms),
             "sum_squares": row("sum_squares_kernel", s_bytes, s_ms),
-            "quantize_minmax_tensor": row("tensor_range_kernel + quantize_minmax_wave_kernel", t_bytes, t_ms),
+            "quantize_minmax_tensor": row("tensor_range_parts + fold_parts + quantize_minmax_wave kernels", t_bytes, t_ms),
             "requantize_minmax": alu_row("requantize_minmax_kernel", r_ms, r_ops),
-            "requantize_minmax_tensor": alu_row("range_init + sum_range_minmax_tensor + range_finish + "
-                                                "requantize_minmax_tensor + range_divide kernels", rt_ms,
+            "requantize_minmax_tensor": alu_row(
+                ("range_init + sum_range_minmax_tensor + range_finish + requantize_minmax_tensor + range_divide kernels" if n > 1 << 26
+                 else "sum_range_minmax_tensor + fold_sum_range + requantize_minmax_tensor kernels"), rt_ms,
                                                 n * (8.0 * W + 14.0),   # two decodes of W workers, min/max, encode
                                                 {"algorithmic_bytes_per_launch": rt_bytes, "hbm_gbs": rt_bytes / (rt_ms * 1e-3) / 1e9})}
 

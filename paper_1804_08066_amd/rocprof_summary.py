@@ -25,12 +25,12 @@ import sys
 KERNELS = ("requantize_wave_kernel", "requantize_pack_kernel", "requantize_minmax_tensor_kernel", "requantize_minmax_kernel",
            "sum_range_minmax_tensor_kernel", "aggregate_update_rows_kernel", "aggregate_update_lds_kernel",
            "aggregate_update_minmax_tensors_kernel", "aggregate_update_minmax_kernel", "aggregate_update_tensors_kernel",
-           "aggregate_mean_kernel", "tensor_range_batch_kernel", "tensor_range_kernel", "sum_squares_partial_kernel",
+           "aggregate_mean_kernel", "tensor_range_parts_kernel", "tensor_range_kernel", "sum_squares_partial_kernel",
            "sum_squares_finish_kernel", "sum_squares_kernel", "quantize_minmax_tensors_wave_kernel",
            "quantize_minmax_tensors_kernel", "quantize_minmax_wave_kernel", "quantize_minmax_kernel",
            "quantize_tensors_wave_kernel", "quantize_tensors_cells_kernel", "quantize_tensors_kernel", "quantize_wave_kernel",
            "quantize_cells_kernel", "quantize_pack_kernel", "stream_quantize_kernel", "stream_update_kernel", "range_",
-           "clear_", "finish_")
+           "clear_", "finish_", "fold_")
 
 
 def short(name):

@@ -111,3 +111,28 @@ def test_traffic_summary_ends_with_the_line_the_benchmark_reads(tmp_path):
     assert d["commit"] == "abc1234" and d["workload"]["n"] == n
     assert d["quantize_wave_kernel"] == pytest.approx((2 * 1000.0 + 100.0) * 1024, rel=1e-6)
     assert d["aggregate_update_rows_kernel"] == pytest.approx((2 * 3000.0 + 4000.0) * 1024, rel=1e-6)
+
+
+def library_kernels():
+    """Names of the __global__ functions of the library's sources."""
+    import re
+    from paper_1804_08066_amd import build
+    text = "".join(open(p).read() for p in build.sources())
+    return set(re.findall(r"__global__[^;{]*?\b([a-z0-9_]+_kernel)\(", text))
+
+
+def test_every_kernel_of_the_library_has_a_row_in_the_summaries():
+    names = library_kernels()
+    assert len(names) > 25
+    for name in names:
+        assert rs.short("void mqg::(anonymous namespace)::%s<4>(unsigned int)" % name) == name
+
+
+def test_the_kernels_that_the_minmax_rows_name_exist():
+    import inspect
+    import re
+    text = inspect.getsource(bench.time_minmax)
+    named = set(re.findall(r"\b([a-z0-9_]+_kernel)\b", text))
+    for several in re.findall(r'"([a-z0-9_ +]+) kernels"', text):
+        named |= {k.strip() + "_kernel" for k in several.split("+")}
+    assert {"fold_sum_range_kernel", "tensor_range_parts_kernel", "requantize_minmax_kernel"} <= named <= library_kernels()
