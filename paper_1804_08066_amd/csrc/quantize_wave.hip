@@ -80,8 +80,8 @@ __device__ __forceinline__ double dpp_f64(double v) {
 // The same butterfly as a sum in fp64 (L2 scale).  After the stages of lane ^ 1 and lane ^ 2 a quad's lanes hold the
 // same sum, so mirrored lanes stand for lane ^ 4 and lane ^ 8: the additions, and every bit, are the butterfly's,
 // but four of its six trips through the LDS pipe are operand permutations.  Up to four rows per lane: with
-// eight the kernel would take 88 registers instead of 78 and lose a wave per SIMD in both scale modes.
-// 10 M elements, bucket 512: 11.7 -> 11.0 us.
+// eight the kernel takes 88 registers instead of 78, which costs a wave per SIMD in both scale modes up to 3 bits
+// (from 4 bits on it runs five waves anyway; not measured there).  10 M elements, bucket 512: 11.7 -> 11.0 us.
 template <int R, int STRIDE>
 __device__ __forceinline__ void segment_sum_rows(double (&q)[R], uint32_t seg_lanes) {
     uint32_t first = 1;
@@ -1080,9 +1080,21 @@ auto with_wave_shape_w(uint32_t bucket, uint32_t bits, F f) {
 }
 // n: elements of the launch.  Where a launch does not fill the chip several times over, what counts is the length of
 // a wave's own chain of loads, random numbers and stores, and how many compute units have a wave at all: a wave
-// then holds 1024 elements, or 512.  65,536 elements, bucket 512, 4 bits: 4.8 us with 2048, 4.0 with 1024, 3.5 with
-// 512; ten layers of 1.07 M in all at 2 bits: 5.7, 4.6, 4.3; 10 M with the L2 norm: 11.0, 10.8, 12.2; from
-// 25.6 M on 2048 are as fast (20 us) or faster.
+// then holds 1024 elements, or 512.  us with 2048 / 1024 / 512 elements per wave (the L2 butterfly below four rows per
+// lane as it is in segment_sum_rows):
+//                 bucket 512, 4 bits     512, 8 bits (no 2048)   64, 4 bits           512, 4 bits, L2
+//   65,536         3.8 /  3.0 /  2.6       3.0 /  2.6             3.6 /  2.9 /  2.6    4.9 /  3.6 /  3.2
+//   1 M            4.5 /  3.2 /  2.9       3.2 /  2.8             4.3 /  3.1 /  2.8    5.5 /  3.7 /  3.3
+//   2 M            4.5 /  3.6 /  3.5       3.5 /  3.5             4.5 /  3.4 /  3.3    5.6 /  4.2 /  4.0
+//   3 M            5.1 /  4.4 /  4.3       4.0 /  4.0             5.0 /  4.3 /  4.3    6.3 /  5.0 /  5.0
+//   4 M            5.0 /  4.9 /  4.8       4.3 /  4.7             4.9 /  4.4 /  4.6    6.3 /  5.7 /  5.6
+//   8 M            7.5 /  7.0 /  7.8       6.8 /  7.9             7.3 /  6.9 /  7.6    9.1 /  8.4 /  9.3
+//   16 M          13.1 / 12.8 / 13.7      13.3 / 14.1            13.2 / 12.7 / 13.5   15.6 / 14.6 / 16.1
+//   24 M          18.6 / 18.2 / 19.9      20.1 / 20.7            19.0 / 18.4 / 19.8   21.7 / 20.9 / 23.8
+//   32 M          23.9 / 23.8 / 26.1      25.1 / 27.5            24.5 / 24.0 / 26.9   28.1 / 27.3 / 31.0
+// Buckets of 2048 and more have 1024 elements per wave at any size (16384: 2048), the [min, max] encoder at any bucket
+// size too, and the cell-granular kernel and the re-quantizing step have one shape each: none of them was measured with
+// shorter chunks.
 constexpr uint64_t kShortLaunch = 1ull << 24, kTinyLaunch = 1ull << 21;
 template <class F>
 auto with_wave_shape(uint32_t bucket, uint32_t bits, uint64_t n, F f) {
