@@ -36,16 +36,16 @@ def test_single_tensors_at_the_larger_edge(n):
     check(got, g, 4, 512, 5, 0)
 
 
-@pytest.mark.parametrize("total", [TINY, TINY + 1])
-def test_layers_together_choose_the_shape(total):
+@pytest.mark.parametrize("total,bits", [(TINY, 6), (TINY + 1, 6), (SHORT, 6), (SHORT + 1, 6), (SHORT + 1, 3)])
+def test_layers_together_choose_the_shape(total, bits):
     sizes = [5, 0, 1000003, 4096, total - 1000003 - 4096 - 5 - 700, 700]
     grads = [workloads.laplace(max(n, 1), 1e-3, i, DEV)[:n] for i, n in enumerate(sizes)]
     bases = [8 * 1024 * i for i in range(len(sizes))]
-    got = mqgrad.mqg_quantize_tensors(grads, 6, 64, 11, 2, 5, bases)
+    got = mqgrad.mqg_quantize_tensors(grads, bits, 64, 11, 2, 5, bases)
     torch.cuda.synchronize()
     for g, q, base in zip(grads, got, bases):
         if g.numel():
-            check(q, g, 6, 64, 5, base)
+            check(q, g, bits, 64, 5, base)
 
 
 @pytest.mark.parametrize("bucket", [32, 64, 128, 256, 512, 1024])
