@@ -70,6 +70,46 @@ def test_captured_step_replays_like_eager_launches():
         torch.cuda.synchronize()
 
 
+@pytest.mark.parametrize("in_place", [False, True])
+@pytest.mark.parametrize("n", [9000, 5 * 4096 + 4, 300017])
+def test_captured_whole_tensor_exchange_replays_on_new_gradients(n, in_place):
+    """One [min, max] range per tensor: the workgroups' keys pass through the code words between the launches, or through
+    atomics where the mean's codes lie over a worker's."""
+    W, bits = 3, 4
+    grads = [torch.empty(n, device=DEV) for _ in range(W)]
+    words = lambda: torch.empty(mqgrad.mqg_packed_words(n, bits), dtype=torch.int32, device=DEV)
+    pk, rg = [words() for _ in range(W)], [torch.empty(2, device=DEV) for _ in range(W)]
+    mean, mean_range = pk[1] if in_place else words(), torch.empty(2, device=DEV)
+
+    def step():
+        for w in range(W):
+            mqgrad.mqg_quantize_minmax_tensor(grads[w], bits, pk[w], rg[w])
+        mqgrad.mqg_aggregate_requantize_minmax_tensor(pk, rg, n, bits, mean, mean_range)
+
+    for g in grads:
+        g.normal_()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        step()
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step()
+    for replay in range(4):
+        for w, g in enumerate(grads):
+            g.copy_(workloads.laplace(n, 1e-3 * (replay + 1), 7 * replay + w, DEV))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        want = [ref.quantize_minmax(g.cpu().numpy(), bits, n) for g in grads]
+        want_pk, want_rg = ref.aggregate_requantize_minmax([x[0] for x in want], [x[1] for x in want], n, bits, n)
+        assert mean_range.cpu().numpy().tobytes() == want_rg.tobytes(), "replay %d" % replay
+        assert np.array_equal(to_u32(mean), want_pk), "replay %d" % replay
+        mean.zero_()
+
+
 def test_workers_on_concurrent_streams_give_the_sequential_result():
     # the library keeps no state between or across calls: W quantize calls in flight on W streams at
     # once (default priority) write exactly what they write one after the other
