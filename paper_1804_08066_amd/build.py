@@ -12,7 +12,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmqgrad.so")
 BENCH_LIB = os.path.join(HERE, "libmqgrad_bench.so")
-SOURCES = ["api.hip", "quantize_pack.hip", "quantize_wave.hip", "aggregate_update.hip", "minmax.hip", "mdp.cpp"]
+SOURCES = ["api.hip", "quantize_pack.hip", "quantize_wave.hip", "aggregate_update.hip", "minmax.hip", "requantize_cells.hip", "mdp.cpp"]
 BENCH_SOURCES = ["bench_stream.hip"]
 MARSHAL_SOURCE = "marshal.cpp"   # the binding's argument tables: host code against torch and Python
 

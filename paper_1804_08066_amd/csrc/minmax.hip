@@ -381,12 +381,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(requant_wave
 // instead of 39 at 10 M elements, 12 workers, 4 bits.  That form (range_out as the place of both the keys and the
 // sum's range) serves the calls whose packed_out lies over one of the streams they read, where nothing may be
 // written before pass 2, and the largest: one workgroup's time grows with the tiles, and so few of very many
-// workgroups move a key that the atomics cost little.  us with the fold / with atomics, 4 bits:
-//   elements     1 worker     4          12           24 workers
-//   20 M         26 /  41     37 /  40    65 /  71    114 / 122
-//   50 M         58 /  69     78 /  84   153 / 151    289 / 279
-//   100 M       110 / 103    147 / 140   290 / 287    569 / 548
-//   400 M                    558 / 511  1137 / 1086
+// workgroups move a key that the atomics cost little.  us with the fold / with atomics, 4 bits, passes of requantize_cells.hip:
+//   elements     1 worker     4          12 workers
+//   30 M         21 /  42     37 /  58     76 /  83
+//   100 M        55 /  85     98 / 113    236 / 251
+//   200 M       100 / 123    201 / 208    486 / 488
+//   400 M       191 / 196    398 / 392    950 / 930
+// The passes below are those of small tensors (see tensor_cells_supported); larger ones hold a cell per lane.
 // Every worker has one (min, max) pair; s_tab[w] = (step, min) of worker w.
 template <int NT, bool STRADDLE, bool ONCE>
 __device__ __forceinline__ void decode_sum_tile_tensor(const RequantArgs& ra, const uint64_t tile_base, float2* s_tab,
@@ -474,7 +475,7 @@ __global__ void range_divide_kernel(float* range, float Wf) {
 // the borrowed elements below took 96 registers instead of 70, five waves per SIMD instead of seven.)
 constexpr int kSumTileThreads = 256;
 constexpr uint32_t kSumTile = 4u * kSumTileThreads * 4u;
-constexpr uint64_t kMostFoldedTiles = 16384;   // 67 M elements
+constexpr uint64_t kMostFoldedTiles = 32768;   // 268 M elements at 8192 per tile
 
 template <int NT, bool STRADDLE, bool ONCE>
 __global__ __launch_bounds__(NT) void sum_range_minmax_tensor_kernel(const RequantArgs ra, uint32_t* keys) {
@@ -510,16 +511,16 @@ __global__ __launch_bounds__(NT) void sum_range_minmax_tensor_kernel(const Requa
     }
 }
 
-// First element of pass 2's tile `tile` of `tiles`.  borrowed: elements that the last tile takes from the one before
+// First element of pass 2's tile `tile` of `tiles`, tile_elems each.  borrowed: elements that the last tile takes from the one before
 // it, so that it has two words of its own to find the range of the sum in.
-__device__ __forceinline__ uint64_t second_pass_base(uint32_t tile, uint32_t tiles, uint32_t borrowed) {
-    return (uint64_t)tile * kSumTile - (tile + 1u == tiles ? borrowed : 0u);
+__device__ __forceinline__ uint64_t second_pass_base(uint32_t tile, uint32_t tiles, uint32_t borrowed, uint32_t tile_elems) {
+    return (uint64_t)tile * tile_elems - (tile + 1u == tiles ? borrowed : 0u);
 }
 
 // One workgroup: all keys are read before the barrier of fold_keys, the words that receive the sum's range
 // (they overlap the keys) are written after it.
 constexpr int kFoldThreads = 1024;
-__global__ __launch_bounds__(kFoldThreads) void fold_sum_range_kernel(uint32_t* packed, const uint32_t tiles, const uint32_t borrowed,
+__global__ __launch_bounds__(kFoldThreads) void fold_sum_range_kernel(uint32_t* packed, const uint32_t tiles, const uint32_t tile_elems, const uint32_t borrowed,
                                                                       const uint32_t bits, float* range, const float Wf) {
     __shared__ uint32_t s_lo[kFoldThreads / 64], s_hi[kFoldThreads / 64];
     __shared__ float2 s_range;
@@ -539,7 +540,7 @@ __global__ __launch_bounds__(kFoldThreads) void fold_sum_range_kernel(uint32_t* 
     __syncthreads();
     const float2 r = s_range;
     for (uint32_t i = tid; i < tiles; i += kFoldThreads) {
-        uint32_t* slot = packed + (second_pass_base(i, tiles, borrowed) >> 5) * bits;
+        uint32_t* slot = packed + (second_pass_base(i, tiles, borrowed, tile_elems) >> 5) * bits;
         slot[0] = __builtin_bit_cast(uint32_t, r.x);
         slot[1] = __builtin_bit_cast(uint32_t, r.y);
     }
@@ -554,8 +555,8 @@ __global__ __launch_bounds__(NT) void requantize_minmax_tensor_kernel(const Requ
     __shared__ Shared<R, NT, false> sm;
     __shared__ float2 s_tab[MQG_MAX_WORKERS];
     const TileGeometry none = {};   // the range is given: no buckets
-    const uint64_t tile_base = second_pass_base(blockIdx.x, gridDim.x, borrowed);
-    const uint64_t end = blockIdx.x + 1u == gridDim.x ? ra.q.n : second_pass_base(blockIdx.x + 1u, gridDim.x, borrowed);
+    const uint64_t tile_base = second_pass_base(blockIdx.x, gridDim.x, borrowed, kSumTile);
+    const uint64_t end = blockIdx.x + 1u == gridDim.x ? ra.q.n : second_pass_base(blockIdx.x + 1u, gridDim.x, borrowed, kSumTile);
     const uint32_t tile_count = (uint32_t)(end - tile_base);
     // every lane holds the sum's range before the barrier below; the words are overwritten after it
     const float* slot = sum_range != nullptr ? sum_range : reinterpret_cast<const float*>(ra.q.packed + (tile_base >> 5) * ra.q.bits);
@@ -1088,7 +1089,9 @@ hipError_t launch_requantize_minmax_tensor(const RequantArgs& ra_in, hipStream_t
         }
         return launch_requantize_minmax(one, stream);
     }
-    const uint64_t tiles = (ra_in.q.n + kSumTile - 1) / kSumTile;
+    const bool cells = tensor_cells_supported(ra_in);
+    const uint32_t tile = cells ? tensor_cells_tile(ra_in) : kSumTile;
+    const uint64_t tiles = (ra_in.q.n + tile - 1) / tile;
     if (tiles > 0x7FFFFFFFull) return hipErrorInvalidValue;
     const uint64_t words = (ra_in.q.n >> 5) * ra_in.q.bits + (((ra_in.q.n & 31u) * ra_in.q.bits + 31u) >> 5);
     bool atomics = tiles > kMostFoldedTiles;
@@ -1096,35 +1099,34 @@ hipError_t launch_requantize_minmax_tensor(const RequantArgs& ra_in, hipStream_t
         const uint64_t in = reinterpret_cast<uintptr_t>(ra_in.packed[w]), out = reinterpret_cast<uintptr_t>(ra_in.q.packed);
         atomics = atomics || (in < out + 4u * words && out < in + 4u * words);
     }
-    const uint64_t tail = ra_in.q.n % kSumTile;
+    const uint64_t tail = ra_in.q.n % tile;
     const uint32_t borrowed = !atomics && tail != 0 && tail * ra_in.q.bits <= 32u ? 64u : 0u;   // 64 elements are two words at one bit
     uint32_t* keys = atomics ? reinterpret_cast<uint32_t*>(ra_in.q.scales) : nullptr;
     const float* sum_range = atomics ? ra_in.q.scales : nullptr;
     const dim3 grid((uint32_t)tiles), block(NT);
-    const bool straddle = (32u % ra_in.q.bits) != 0u;
-    const bool once = decode::codes_read_once(ra_in.q.bits);
     if (atomics) hipLaunchKernelGGL(range_init_kernel, dim3(1), dim3(1), 0, stream, keys);
-    if (straddle) {
-        if (once) hipLaunchKernelGGL((sum_range_minmax_tensor_kernel<NT, true, true>), grid, block, 0, stream, ra_in, keys);
-        else hipLaunchKernelGGL((sum_range_minmax_tensor_kernel<NT, true, false>), grid, block, 0, stream, ra_in, keys);
+    if (cells) {
+        launch_sum_range_cells(ra_in, (uint32_t)tiles, tile, keys, stream);
     } else {
-        if (once) hipLaunchKernelGGL((sum_range_minmax_tensor_kernel<NT, false, true>), grid, block, 0, stream, ra_in, keys);
-        else hipLaunchKernelGGL((sum_range_minmax_tensor_kernel<NT, false, false>), grid, block, 0, stream, ra_in, keys);
+        with_codes(ra_in.q.bits, [&](auto straddle, auto once) {
+            hipLaunchKernelGGL((sum_range_minmax_tensor_kernel<NT, decltype(straddle)::value, decltype(once)::value>), grid, block, 0, stream, ra_in, keys);
+        });
     }
     if (atomics) {
         hipLaunchKernelGGL(range_finish_kernel, dim3(1), dim3(1), 0, stream, keys);
     } else {
-        hipLaunchKernelGGL(fold_sum_range_kernel, dim3(1), dim3(kFoldThreads), 0, stream, ra_in.q.packed, (uint32_t)tiles,
+        hipLaunchKernelGGL(fold_sum_range_kernel, dim3(1), dim3(kFoldThreads), 0, stream, ra_in.q.packed, (uint32_t)tiles, tile,
                            borrowed, ra_in.q.bits, ra_in.q.scales, (float)ra_in.W);
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (straddle) {
-        if (once) hipLaunchKernelGGL((requantize_minmax_tensor_kernel<NT, true, true>), grid, block, 0, stream, ra_in, sum_range, borrowed);
-        else hipLaunchKernelGGL((requantize_minmax_tensor_kernel<NT, true, false>), grid, block, 0, stream, ra_in, sum_range, borrowed);
+    if (cells) {
+        launch_requantize_tensor_cells(ra_in, (uint32_t)tiles, tile, sum_range, borrowed, stream);
     } else {
-        if (once) hipLaunchKernelGGL((requantize_minmax_tensor_kernel<NT, false, true>), grid, block, 0, stream, ra_in, sum_range, borrowed);
-        else hipLaunchKernelGGL((requantize_minmax_tensor_kernel<NT, false, false>), grid, block, 0, stream, ra_in, sum_range, borrowed);
+        with_codes(ra_in.q.bits, [&](auto straddle, auto once) {
+            hipLaunchKernelGGL((requantize_minmax_tensor_kernel<NT, decltype(straddle)::value, decltype(once)::value>), grid, block, 0, stream, ra_in,
+                               sum_range, borrowed);
+        });
     }
     if (atomics) hipLaunchKernelGGL(range_divide_kernel, dim3(1), dim3(1), 0, stream, ra_in.q.scales, (float)ra_in.W);
     return hipGetLastError();

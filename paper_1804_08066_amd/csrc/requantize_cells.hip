@@ -1,0 +1,481 @@
+// The server's re-encoding steps of the full exchange (ReceiveQGThenSendQG of Algorithm 1), one cell per lane: the W
+// workers' code streams are decoded, added in worker order and encoded again.  Code words are all that these steps
+// read or write -- the sum exists in registers only -- so a lane can own a CELL's worth of codes, 32 elements, which
+// is `bits` whole words at every width:
+//   - a wave's loads of one worker's codes are 64 * bits consecutive words, up to 128 bits per lane and load, and
+//     nothing is fetched twice;
+//   - the width is a compile-time number, so every code's place in its word is one too;
+//   - a lane packs its own words: no staging of the output, no LDS atomics;
+//   - buckets are whole cells, so a lane has one step per worker and one range, and a Philox call's eight elements lie
+//     in one lane.
+// The kernels of quantize_wave.hip and minmax.hip that decode into the layout of fp32 rows (four elements per lane) load
+// each code word in up to eight lanes, pack through LDS and, below 5 bits, were bound by LDS gathers.
+
+#include "encode.h"
+#include "kernels.h"
+
+#include <type_traits>
+
+namespace mqg {
+namespace {
+
+using namespace encode;
+
+constexpr uint32_t kCell = 32;          // elements
+
+// How much there is to do.  kShort: the launch does not fill the chip several times over, and what counts is a wave's own
+// chain and how many compute units have a wave: small tiles, many words in flight.  kStream: the streams together exceed
+// the last-level cache, and streaming loads are faster where a wave's loads leave no gaps (4, 6 and 8 bits).  us, ordinary /
+// streaming loads: 8 bits, 16 workers, 30 M elements, [min, max] 95.6 / 87.8; 6 bits, 16 workers, 60 M 144 / 136; 5 bits 121 / 129;
+// 7 bits 165 / 179; with the streams in the cache (8 workers, 25.6 M, 4 bits) 25.5 / 27.5.
+enum class Size { kShort, kLong, kStream };
+
+typedef float v2f __attribute__((ext_vector_type(2)));
+typedef uint32_t v2u __attribute__((ext_vector_type(2)));
+typedef v2u v2u_a4 __attribute__((aligned(4)));
+
+// ---- a lane's words -----------------------------------------------------------------------------------
+// At 6 and 8 bits a lane holds two half cells, 64 half cells apart: with whole ones its loads would lie 24 or 32 bytes
+// apart, and the second half of each cache line be fetched again.
+template <int B>
+struct Parts {
+    static constexpr int kCount = B == 6 || B == 8 ? 2 : 1;
+    static constexpr int kWords = B / kCount;
+    static constexpr int kElems = 32 / kCount;
+};
+
+template <int N, bool NT>
+__device__ __forceinline__ void load_words(const uint32_t* p, uint32_t* w) {
+    if constexpr (N >= 4) {
+        const v4u_a4* q = reinterpret_cast<const v4u_a4*>(p);
+        const v4u t = NT ? __builtin_nontemporal_load(q) : *q;
+        w[0] = t.x; w[1] = t.y; w[2] = t.z; w[3] = t.w;
+        if constexpr (N > 4) load_words<N - 4, NT>(p + 4, w + 4);
+    } else if constexpr (N >= 2) {
+        const v2u_a4* q = reinterpret_cast<const v2u_a4*>(p);
+        const v2u t = NT ? __builtin_nontemporal_load(q) : *q;
+        w[0] = t.x; w[1] = t.y;
+        if constexpr (N > 2) load_words<N - 2, NT>(p + 2, w + 2);
+    } else {
+        w[0] = NT ? __builtin_nontemporal_load(p) : *p;
+    }
+}
+template <int N>
+__device__ __forceinline__ void store_words(uint32_t* p, const uint32_t* w) {
+    if constexpr (N >= 4) {
+        const v4u t = {w[0], w[1], w[2], w[3]};
+        __builtin_nontemporal_store(t, reinterpret_cast<v4u_a4*>(p));
+        if constexpr (N > 4) store_words<N - 4>(p + 4, w + 4);
+    } else if constexpr (N >= 2) {
+        const v2u t = {w[0], w[1]};
+        __builtin_nontemporal_store(t, reinterpret_cast<v2u_a4*>(p));
+        if constexpr (N > 2) store_words<N - 2>(p + 2, w + 2);
+    } else {
+        __builtin_nontemporal_store(w[0], p);
+    }
+}
+
+// Where the lane's parts sit in a tile of `cells` cells (lanes past the last cell stand in for it: they read what it
+// reads and write nothing) that starts at element tile_base and ends at tile_end.
+template <int B>
+struct Window {
+    static constexpr int P = Parts<B>::kCount;
+    uint64_t tile_word;    // the tile's first word in every stream
+    uint32_t word[P];      // first word of the part, from there
+    int from[P];           // the part's words are read from here, so that no load leaves the stream (at least kWords long)
+    uint32_t cell[P];      // cell of the tile
+    uint32_t count[P];     // elements of the part that are the lane's to write
+
+    __device__ __forceinline__ Window(const uint64_t n, const uint64_t tile_base, const uint64_t tile_end, const uint32_t cells) {
+        const uint32_t tid = threadIdx.x;
+        tile_word = (tile_base >> 5) * B;
+        const uint64_t words = (n >> 5) * B + (((n & 31u) * B + 31u) >> 5);
+        const uint64_t room = words - tile_word;
+        const int last = (int)(room > 0x3FFFFFFFull ? 0x3FFFFFFFu : (uint32_t)room) - Parts<B>::kWords;   // may lie before the tile
+        const uint32_t elems = (uint32_t)(tile_end - tile_base);
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            const uint32_t mine = P == 1 ? tid : (tid >> 6) * 128u + p * 64u + (tid & 63u);
+            const uint32_t u = mine < cells * P ? mine : cells * P - 1u;
+            word[p] = u * Parts<B>::kWords;
+            from[p] = (int)word[p] < last ? (int)word[p] : last;
+            cell[p] = u / P;
+            const uint32_t el = u * Parts<B>::kElems;
+            const uint32_t left = el < elems ? elems - el : 0u;
+            count[p] = mine != u ? 0u : (left < (uint32_t)Parts<B>::kElems ? left : (uint32_t)Parts<B>::kElems);
+        }
+    }
+};
+template <int B, Size SIZE, bool WHOLE>
+__device__ __forceinline__ void fetch(const uint32_t* stream, const Window<B>& at, uint32_t (&w)[B]) {
+    constexpr int PW = Parts<B>::kWords;
+    const uint32_t* __restrict__ tile = stream + at.tile_word;
+#pragma unroll
+    for (int p = 0; p < Parts<B>::kCount; ++p) {
+        if (WHOLE) load_words<PW, SIZE == Size::kStream>(tile + at.word[p], w + p * PW);
+        else load_words<PW, SIZE == Size::kStream>(tile + at.from[p], w + p * PW);
+    }
+}
+// the words of a part that was read from before its first one, in their places (past the end of the stream: any)
+template <int B>
+__device__ __forceinline__ void settle(const Window<B>& at, const uint32_t (&w)[B], uint32_t (&o)[B]) {
+    constexpr int PW = Parts<B>::kWords;
+#pragma unroll
+    for (int p = 0; p < Parts<B>::kCount; ++p) {
+        const uint32_t by = (uint32_t)((int)at.word[p] - at.from[p]);
+#pragma unroll
+        for (int i = 0; i < PW; ++i) o[p * PW + i] = w[p * PW + i];
+        const auto down = [&](auto by_words) {
+            constexpr int D = decltype(by_words)::value;
+#pragma unroll
+            for (int i = 0; i + D < PW; ++i) {
+                const uint32_t here = o[p * PW + i], there = o[p * PW + i + D];
+                o[p * PW + i] = (by & D) != 0u ? there : here;
+            }
+        };
+        if constexpr (PW > 1) down(std::integral_constant<int, 1>{});
+        if constexpr (PW > 2) down(std::integral_constant<int, 2>{});
+        if constexpr (PW > 4) down(std::integral_constant<int, 4>{});
+    }
+}
+
+// ---- decode -------------------------------------------------------------------------------------------
+// Constants that stay in vector registers: with a scalar operand an fma, add or and issues at half the rate.
+__device__ __forceinline__ float in_vector(float f) {
+    asm volatile("" : "+v"(f));
+    return f;
+}
+__device__ __forceinline__ uint32_t in_vector(uint32_t u) {
+    asm volatile("" : "+v"(u));
+    return u;
+}
+
+// Calls f(k, c) for the lane's codes, c = TIMES * code as fp32 (exact; TIMES is a power of two).
+// 1, 2, 4 bits: a mask and a shift put every (8 / B)-th code of a word into a byte of its own, and the byte read as a
+// FP8 number (E4M3: 0 .. 15 are the multiples of 2^-9 up to 15 * 2^-9) converts two at a time.
+// 8 bits: a byte converts in one instruction.  Others: bit field, convert.
+template <int B, class F>
+__device__ __forceinline__ void for_codes(const uint32_t (&w)[B], const uint32_t byte_mask, const float scale, F f) {
+    if constexpr (B == 1 || B == 2 || B == 4) {
+        constexpr int PER = 8 / B;       // codes per byte
+#pragma unroll
+        for (int i = 0; i < B; ++i) {
+#pragma unroll
+            for (int s = 0; s < PER; ++s) {
+                const uint32_t t = (s == 0 ? w[i] : (w[i] >> (s * B))) & byte_mask;
+                const v2f lo = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(t, scale, false);
+                const v2f hi = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(t, scale, true);
+                const int k = i * (32 / B) + s;
+                f(k, lo.x);
+                f(k + PER, lo.y);
+                f(k + 2 * PER, hi.x);
+                f(k + 3 * PER, hi.y);
+            }
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < 32; ++k) {
+            constexpr uint32_t kMask = (1u << B) - 1u;
+            const int i = k * B / 32, sh = k * B % 32;
+            uint32_t c;
+            if (sh + B > 32) c = __builtin_amdgcn_alignbit(w[i + 1 < B ? i + 1 : i], w[i], sh) & kMask;
+            else if (sh + B == 32) c = w[i] >> sh;
+            else c = __builtin_amdgcn_ubfe(w[i], sh, B);
+            f(k, (float)c);
+        }
+    }
+}
+template <int B>
+__device__ __forceinline__ uint32_t byte_mask() {
+    return in_vector(((1u << B) - 1u) * 0x01010101u);
+}
+
+// What adds one worker's codes to the sum's values.
+struct MinmaxSum {   // acc <- acc + fma(c, step, min)
+    using Step = float2;
+    static __device__ __forceinline__ Step step(const float* ranges, const uint64_t k, const float Lf) {
+        const float2 rg = reinterpret_cast<const float2*>(ranges)[k];   // (min, max)
+        return make_float2((rg.y - rg.x) / Lf, rg.x);                   // IEEE-correct fp32 division
+    }
+    template <int B>
+    struct Consts {
+        uint32_t mask;
+        float scale;
+        __device__ __forceinline__ Consts() : mask(byte_mask<B>()), scale(in_vector(0x1p9f)) {}
+    };
+    template <int B>
+    static __device__ __forceinline__ void add(const uint32_t (&w)[B], const Consts<B>& k, const Step (&s)[Parts<B>::kCount], float (&v)[32]) {
+        for_codes<B>(w, k.mask, k.scale, [&](int i, float c) {
+            const Step& sm = s[i / Parts<B>::kElems];
+            v[i] = v[i] + __builtin_fmaf(c, sm.x, sm.y);
+        });
+    }
+};
+// Workers whose code words are in flight together: as soon as a worker's words are decoded, those of the worker
+// in_flight places on are requested in their stead.
+template <int B, Size SIZE>
+constexpr int in_flight() { return SIZE == Size::kShort ? (B <= 4 ? 8 : 5) : (B == 1 ? 8 : B == 2 ? 4 : 2); }
+
+// v <- the sum over the W workers, in worker order.  table[w * stride + bucket]: worker w's step in the bucket of each
+// of the lane's parts; complete after the barrier in here.
+template <int B, Size SIZE, bool WHOLE, class Sum>
+__device__ __forceinline__ void decode_sum(const RequantArgs& ra, const Window<B>& at, const typename Sum::Step* table, const uint32_t stride,
+                                           const uint32_t (&bucket)[Parts<B>::kCount], float (&v)[32]) {
+    constexpr int CH = in_flight<B, SIZE>();
+    const uint32_t W = ra.W;
+    uint32_t c[CH][B];
+#pragma unroll
+    for (int t = 0; t < CH; ++t) fetch<B, SIZE, WHOLE>(ra.packed[(uint32_t)t < W ? t : W - 1u], at, c[t]);
+    const typename Sum::template Consts<B> k;
+#pragma unroll
+    for (int i = 0; i < 32; ++i) v[i] = 0.0f;
+    __syncthreads();
+    const auto add = [&](const uint32_t w, const uint32_t (&words)[B]) {
+        typename Sum::Step s[Parts<B>::kCount];
+#pragma unroll
+        for (int p = 0; p < Parts<B>::kCount; ++p) s[p] = table[w * stride + bucket[p]];
+        if constexpr (WHOLE) {
+            Sum::template add<B>(words, k, s, v);
+        } else {
+            uint32_t settled[B];
+            settle<B>(at, words, settled);
+            Sum::template add<B>(settled, k, s, v);
+        }
+    };
+    uint32_t w0 = 0;
+    for (; w0 + CH < W; w0 += CH) {
+#pragma unroll
+        for (int t = 0; t < CH; ++t) {
+            add(w0 + t, c[t]);
+            const uint32_t next = w0 + CH + t;
+            fetch<B, SIZE, WHOLE>(ra.packed[next < W ? next : W - 1u], at, c[t]);
+            __builtin_amdgcn_sched_barrier(0);   // left alone the compiler converts several workers' codes ahead and spills
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < CH; ++t) {
+        if (w0 + t < W) add(w0 + t, c[t]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// ---- encode -------------------------------------------------------------------------------------------
+// bits [k * B, k * B + 32) of the lane's words <- v, which has no bit past the last code it holds
+template <int B>
+__device__ __forceinline__ void place(uint32_t (&o)[B], const int k, const uint32_t v, const int codes) {
+    const int i = k * B / 32, sh = k * B % 32;
+    o[i] = sh == 0 ? v : (o[i] | v << sh);
+    if (sh + codes * B > 32) o[i + 1 < B ? i + 1 : i] = v >> (32 - sh);
+}
+template <int B, bool WHOLE>
+__device__ __forceinline__ void store_parts(uint32_t* __restrict__ out, const Window<B>& at, const uint32_t (&o)[B]) {
+    constexpr int PW = Parts<B>::kWords;
+#pragma unroll
+    for (int p = 0; p < Parts<B>::kCount; ++p) {
+        uint32_t* __restrict__ dst = out + at.tile_word + at.word[p];
+        if (WHOLE) {
+            if (at.count[p] != 0u) store_words<PW>(dst, o + p * PW);
+        } else {
+            const uint32_t words = (at.count[p] * B + 31u) >> 5;
+#pragma unroll
+            for (int i = 0; i < PW; ++i) {
+                if ((uint32_t)i < words) store_words<1>(dst + i, o + p * PW + i);
+            }
+        }
+    }
+}
+// is the lane's element k inside the tensor?
+template <int B, bool WHOLE>
+__device__ __forceinline__ bool inside(const Window<B>& at, const int k) {
+    return WHOLE || (uint32_t)(k % Parts<B>::kElems) < at.count[k / Parts<B>::kElems];
+}
+
+template <int B, bool WHOLE>
+__device__ __forceinline__ void encode_minmax(uint32_t* out, const Window<B>& at, const float (&v)[32], const float (&mn)[Parts<B>::kCount],
+                                              const float (&a)[Parts<B>::kCount]) {
+    const float Lf = (float)((1 << B) - 1);
+    uint32_t o[B];
+#pragma unroll
+    for (int k = 0; k < 32; ++k) {
+        const int p = k / Parts<B>::kElems;
+        const uint32_t code = nearest_code(v[k], mn[p], a[p], Lf);
+        place<B>(o, k, inside<B, WHOLE>(at, k) ? code : 0u, 1);   // elements past the end contribute zero bits
+    }
+    store_parts<B, WHOLE>(out, at, o);
+}
+__device__ __forceinline__ float inverse_step(float mn, float mx, float Lf) {
+    const float r = mx - mn;
+    return (r >= 0x1p-96f) ? Lf / r : 0.0f;   // IEEE-correct fp32 division
+}
+
+// Extremes of each part's values; elements past the end take no part (none at all: +inf, -inf), nor does a NaN unless
+// there is nothing else.
+template <int B, bool WHOLE>
+__device__ __forceinline__ void part_ranges(const float (&v)[32], const Window<B>& at, float (&lo)[Parts<B>::kCount], float (&hi)[Parts<B>::kCount]) {
+    constexpr int E = Parts<B>::kElems;
+    const float inf = __builtin_inff();
+#pragma unroll
+    for (int p = 0; p < Parts<B>::kCount; ++p) {
+        const int f = p * E;
+        lo[p] = inside<B, WHOLE>(at, f) ? v[f] : inf;
+        hi[p] = inside<B, WHOLE>(at, f) ? v[f] : -inf;
+#pragma unroll
+        for (int k = f + 1; k < f + E; ++k) {
+            if (WHOLE) {
+                if (k + 1 < f + E && ((k - f) & 1)) {
+                    asm("v_min3_f32 %0, %1, %2, %0" : "+v"(lo[p]) : "v"(v[k]), "v"(v[k + 1 < 32 ? k + 1 : k]));
+                    asm("v_max3_f32 %0, %1, %2, %0" : "+v"(hi[p]) : "v"(v[k]), "v"(v[k + 1 < 32 ? k + 1 : k]));
+                } else if ((k - f) & 1) {
+                    lo[p] = min_f32(lo[p], v[k]);
+                    hi[p] = max_f32(hi[p], v[k]);
+                }
+            } else {
+                lo[p] = min_f32(lo[p], inside<B, WHOLE>(at, k) ? v[k] : inf);
+                hi[p] = max_f32(hi[p], inside<B, WHOLE>(at, k) ? v[k] : -inf);
+            }
+        }
+    }
+}
+
+// ---- one [min, max] range for the whole tensor ------------------------------------------------------------
+// Two passes over the streams, as the range of the sum is known only at the end of the first (see
+// launch_requantize_minmax_tensor for where the keys and the range live in between).
+__device__ __forceinline__ void fill_tensor_table(const RequantArgs& ra, const float Lf, float2* s_tab) {
+    for (uint32_t w = threadIdx.x; w < ra.W; w += blockDim.x) s_tab[w] = MinmaxSum::step(ra.scales[w], 0u, Lf);
+}
+
+template <int B, Size SIZE, bool WHOLE>
+__device__ __forceinline__ void sum_range_tile(const RequantArgs& ra, uint32_t* keys, const uint64_t tile_base, float2* s_tab,
+                                               uint32_t* s_lo, uint32_t* s_hi) {
+    const uint32_t tid = threadIdx.x;
+    const Window<B> at(ra.q.n, tile_base, WHOLE ? tile_base + blockDim.x * kCell : ra.q.n, blockDim.x);
+    fill_tensor_table(ra, (float)((1 << B) - 1), s_tab);
+    float v[32], lo[Parts<B>::kCount], hi[Parts<B>::kCount];
+    const uint32_t bucket[Parts<B>::kCount] = {};
+    decode_sum<B, SIZE, WHOLE, MinmaxSum>(ra, at, s_tab, 1u, bucket, v);
+    part_ranges<B, WHOLE>(v, at, lo, hi);
+    float l = __builtin_inff(), h = -__builtin_inff();   // a NaN has no part in a tensor's range, whatever the lane holds
+#pragma unroll
+    for (int p = 0; p < Parts<B>::kCount; ++p) {
+        l = min_f32(l, lo[p]);
+        h = max_f32(h, hi[p]);
+    }
+    uint32_t kl = wave_min_from_cells_u32(cell_min_u32(order_key(l)), tid & 63u);
+    uint32_t kh = wave_max_from_cells_u32(cell_max_u32(order_key(h)), tid & 63u);
+    if ((tid & 63u) == 0u) {
+        s_lo[tid >> 6] = kl;
+        s_hi[tid >> 6] = kh;
+    }
+    __syncthreads();
+    if (tid == 0u) {
+        for (uint32_t w = 1; w < blockDim.x / 64u; ++w) {
+            kl = min(kl, s_lo[w]);
+            kh = max(kh, s_hi[w]);
+        }
+        if (keys != nullptr) {   // look first: same-address atomics serialize, and the keys only ever move one way
+            if (kl < __atomic_load_n(&keys[0], __ATOMIC_RELAXED)) atomicMin(&keys[0], kl);
+            if (kh > __atomic_load_n(&keys[1], __ATOMIC_RELAXED)) atomicMax(&keys[1], kh);
+        } else {
+            ra.q.packed[2u * blockIdx.x] = kl;
+            ra.q.packed[2u * blockIdx.x + 1u] = kh;
+        }
+    }
+}
+template <int B, Size SIZE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SIZE == Size::kShort ? 4 : 5, 8))) void sum_range_cells_kernel(const RequantArgs ra, uint32_t* keys) {
+    __shared__ float2 s_tab[MQG_MAX_WORKERS];
+    __shared__ uint32_t s_lo[4], s_hi[4];
+    const uint64_t tile_base = (uint64_t)blockIdx.x * (blockDim.x * kCell);
+    if (tile_base + blockDim.x * kCell <= ra.q.n) sum_range_tile<B, SIZE, true>(ra, keys, tile_base, s_tab, s_lo, s_hi);
+    else sum_range_tile<B, SIZE, false>(ra, keys, tile_base, s_tab, s_lo, s_hi);
+}
+
+template <int B, Size SIZE, bool WHOLE>
+__device__ __forceinline__ void requantize_tensor_tile(const RequantArgs& ra, const float* sum_range, const uint64_t tile_base,
+                                                       const uint64_t tile_end, float2* s_tab) {
+    constexpr int P = Parts<B>::kCount;
+    const float Lf = (float)((1 << B) - 1);
+    const Window<B> at(ra.q.n, tile_base, tile_end, blockDim.x);
+    // every lane holds the sum's range before the barrier in decode_sum; the words are overwritten after it
+    const float* slot = sum_range != nullptr ? sum_range : reinterpret_cast<const float*>(ra.q.packed + at.tile_word);
+    const float lowest = in_vector(slot[0]), highest = in_vector(slot[1]);
+    fill_tensor_table(ra, Lf, s_tab);
+    float v[32];
+    const uint32_t bucket[P] = {};
+    decode_sum<B, SIZE, WHOLE, MinmaxSum>(ra, at, s_tab, 1u, bucket, v);
+    float mn[P], a[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        mn[p] = lowest;
+        a[p] = inverse_step(lowest, highest, Lf);
+    }
+    encode_minmax<B, WHOLE>(ra.q.packed, at, v, mn, a);
+}
+template <int B, Size SIZE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SIZE == Size::kShort ? 4 : 5, 8))) void requantize_tensor_cells_kernel(const RequantArgs ra, const float* sum_range, const uint32_t borrowed) {
+    __shared__ float2 s_tab[MQG_MAX_WORKERS];
+    const uint32_t tile = blockDim.x * kCell;
+    const bool last = blockIdx.x + 1u == gridDim.x;
+    const uint64_t tile_base = (uint64_t)blockIdx.x * tile - (last ? borrowed : 0u);
+    const uint64_t tile_end = last ? ra.q.n : (uint64_t)(blockIdx.x + 1u) * tile - (blockIdx.x + 2u == gridDim.x ? borrowed : 0u);
+    if (tile_end - tile_base == tile) requantize_tensor_tile<B, SIZE, true>(ra, sum_range, tile_base, tile_end, s_tab);
+    else requantize_tensor_tile<B, SIZE, false>(ra, sum_range, tile_base, tile_end, s_tab);
+}
+
+// Calls f(B) with the width as a compile-time constant.
+template <class F>
+void with_bits(uint32_t bits, F f) {
+    using std::integral_constant;
+    switch (bits) {
+        case 1: return f(integral_constant<int, 1>{});
+        case 2: return f(integral_constant<int, 2>{});
+        case 3: return f(integral_constant<int, 3>{});
+        case 4: return f(integral_constant<int, 4>{});
+        case 5: return f(integral_constant<int, 5>{});
+        case 6: return f(integral_constant<int, 6>{});
+        case 7: return f(integral_constant<int, 7>{});
+        default: return f(integral_constant<int, 8>{});
+    }
+}
+
+Size size_of(const RequantArgs& ra) {
+    constexpr uint64_t kShortElems = 1ull << 21, kLastLevelCache = 256ull << 20;
+    if (ra.q.n <= kShortElems) return Size::kShort;
+    const bool gapless = ra.q.bits == 4u || ra.q.bits == 6u || ra.q.bits == 8u;
+    return gapless && (ra.q.n >> 3) * ra.q.bits * ra.W > kLastLevelCache ? Size::kStream : Size::kLong;
+}
+// Calls f(B, SIZE) with the width and the size as compile-time constants.
+template <class F>
+void with_shape(const RequantArgs& ra, F f) {
+    const Size size = size_of(ra);
+    with_bits(ra.q.bits, [&](auto b) {
+        constexpr int B = decltype(b)::value;
+        if (size == Size::kShort) return f(b, std::integral_constant<Size, Size::kShort>{});
+        if constexpr (B == 4 || B == 6 || B == 8) {
+            if (size == Size::kStream) return f(b, std::integral_constant<Size, Size::kStream>{});
+        }
+        f(b, std::integral_constant<Size, Size::kLong>{});
+    });
+}
+
+}  // namespace
+
+// ---- one range for the whole tensor: the passes of launch_requantize_minmax_tensor (minmax.hip) -------------------
+// From 1.5 M elements on; below, a wave's chain counts, and that of the rows form is half as long (sixteen elements per
+// lane).  us, rows / cells: 3 bits, 12 workers, 1 M elements 12.8 / 14.6, 4 bits 13.8 / 13.1; 2 M 3 bits 15.5 / 15.1; 10 M, 4
+// workers, 3 bits 22.9 / 16.6, 4 bits 23.1 / 16.8; 12 workers, 4 bits 41 / 33, 6 bits 51 / 38; 100 M 300 / 236.
+bool tensor_cells_supported(const RequantArgs& ra) { return ra.q.n > 3ull << 19; }
+uint32_t tensor_cells_tile(const RequantArgs& ra) { return size_of(ra) == Size::kShort ? 64u * kCell : 256u * kCell; }
+void launch_sum_range_cells(const RequantArgs& ra, uint32_t tiles, uint32_t tile, uint32_t* keys, hipStream_t stream) {
+    with_shape(ra, [&](auto b, auto size) {
+        hipLaunchKernelGGL((sum_range_cells_kernel<decltype(b)::value, decltype(size)::value>), dim3(tiles), dim3(tile / kCell), 0, stream, ra, keys);
+    });
+}
+void launch_requantize_tensor_cells(const RequantArgs& ra, uint32_t tiles, uint32_t tile, const float* sum_range, uint32_t borrowed, hipStream_t stream) {
+    with_shape(ra, [&](auto b, auto size) {
+        hipLaunchKernelGGL((requantize_tensor_cells_kernel<decltype(b)::value, decltype(size)::value>), dim3(tiles), dim3(tile / kCell), 0, stream, ra, sum_range,
+                           borrowed);
+    });
+}
+
+}  // namespace mqg
