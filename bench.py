@@ -612,8 +612,9 @@ def time_minmax(wl, bits, bucket, lr, steps, warmup):
     s_bytes = 4.0 * n
     t_bytes = n * (8.0 + bits / 8.0)   # two passes over the gradient (range, then encode)
     frac = lambda by, ms: by / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS
+    cells = n > 1 << 20 and (bucket >= 128 or W <= 8)
     decode = 2.9 if bits in (1, 2, 4) else (3.0 if bits == 8 else 4.0)   # extract, convert, fma, add per worker
-    r_ops = n * (4.0 * W + 12.0)                  # encode about 12
+    r_ops = n * ((decode if cells else 4.0) * W + 12.0)                  # encode about 12
     log("minmax b=%d B=%d: quantize %.1f us (%.1f%%), aggregate %.1f us (%.1f%%), sum_squares %.1f us (%.1f%%), "
         "requantize %.1f us (%.1f T lane-ops/s), whole-tensor range + encode %.1f us (%.1f%%)" %
         (bits, bucket, q_ms * 1e3, 100 * frac(q_bytes, q_ms), a_ms * 1e3, 100 * frac(a_bytes, a_ms), s_ms * 1e3,
@@ -626,7 +627,7 @@ def time_minmax(wl, bits, bucket, lr, steps, warmup):
             "aggregate_update_minmax": row("aggregate_update_minmax_kernel", a_bytes, a_ms),
             "sum_squares": row("sum_squares_kernel", s_bytes, s_ms),
             "quantize_minmax_tensor": row("tensor_range_parts + fold_parts + quantize_minmax_wave kernels", t_bytes, t_ms),
-            "requantize_minmax": alu_row("requantize_minmax_kernel", r_ms, r_ops),
+            "requantize_minmax": alu_row("requantize_cells_kernel" if cells else "requantize_minmax_kernel", r_ms, r_ops),
             "requantize_minmax_tensor": alu_row(
                 ("range_init + sum_range_cells + range_finish + requantize_tensor_cells + range_divide kernels" if n > 1 << 28
                  else "sum_range_cells + fold_sum_range + requantize_tensor_cells kernels" if n > 3 << 19

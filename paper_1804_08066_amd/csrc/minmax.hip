@@ -927,6 +927,7 @@ hipError_t launch_aggregate_s(const AggregateArgs& a, hipStream_t stream) {
 // ra.scales[w]: worker w's (min, max) pairs; ra.q.scales: (min, max) pairs of the mean
 hipError_t launch_requantize_minmax(const RequantArgs& ra, hipStream_t stream) {
     if (ra.q.n == 0) return hipSuccess;
+    if (requantize_minmax_cells_supported(ra)) return launch_requantize_minmax_cells(ra, stream);
     // Where every compute unit gets at most one workgroup, four waves of fewer buckets end sooner: bucket 2304, 24 workers,
     // 65,536 elements 9.6 us, with five waves 10.3; at 1 M elements 11.9 and 10.9.
     uint32_t waves = tile_waves(ra.q.bucket);

@@ -422,6 +422,199 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SIZE == Siz
     else requantize_tensor_tile<B, SIZE, false>(ra, sum_range, tile_base, tile_end, s_tab);
 }
 
+// ---- one range per bucket ------------------------------------------------------------------------------------
+// A workgroup owns a tile of whole buckets.  LOCAL: a bucket is 1, 2, 4 .. 64 cells and a wave holds whole ones, so its
+// range stays in the wave; otherwise the waves' shares of a bucket meet in one LDS slot behind a barrier.
+struct CellTile {
+    uint32_t cells, buckets;   // of a tile
+    uint32_t bucket_cells;     // bucket / 32
+    uint32_t magic;            // ceil(2^20 / bucket_cells): (cell * magic) >> 16 = cell / bucket_cells below 512 cells
+};
+constexpr uint32_t kMostLanes = 512;                      // the largest bucket is 512 cells
+constexpr uint32_t kMostSharedBuckets = kMostLanes / 3;   // buckets of a tile that is not LOCAL: at least three cells each
+
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_or_zero(uint32_t v) {   // lanes without a source read 0
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
+}
+// Maximum over each group of 2^k neighbouring lanes that a bucket is (LOCAL); every lane of the group gets it.
+template <int N>
+__device__ __forceinline__ void group_max(uint32_t (&m)[N], const uint32_t lanes, const uint32_t lane) {
+    if (lanes >= 2u) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) m[i] = max(m[i], dpp_u32<kDppQuadSwap1>(m[i]));
+    }
+    if (lanes >= 4u) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) m[i] = max(m[i], dpp_u32<kDppQuadSwap2>(m[i]));
+    }
+    if (lanes >= 8u) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) m[i] = max(m[i], dpp_u32<kDppRowHalfMirror>(m[i]));
+    }
+    if (lanes >= 16u) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) m[i] = max(m[i], dpp_u32<kDppRowMirror>(m[i]));
+    }
+    if (lanes >= 32u) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) m[i] = max(m[i], swizzle_xor16_u32(m[i]));
+    }
+    if (lanes >= 64u) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) m[i] = max(m[i], bpermute_xor32_u32(m[i], lane));
+    }
+}
+// Maximum over the lanes of a bucket up to and including each lane: before = lanes of the wave in front of this one that
+// belong to its bucket.  0 is the identity.
+template <int N>
+__device__ __forceinline__ void segment_max(uint32_t (&m)[N], const uint32_t before, const uint32_t lane) {
+    const auto step = [&](auto ctrl, const bool reaches) {
+        constexpr int CTRL = decltype(ctrl)::value;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const uint32_t t = dpp_or_zero<CTRL>(m[i]);
+            m[i] = max(m[i], reaches ? t : 0u);
+        }
+    };
+    using std::integral_constant;
+    const uint32_t in_row = lane & 15u;
+    step(integral_constant<int, 0x111>{}, before >= 1u && in_row >= 1u);   // row_shr:1
+    step(integral_constant<int, 0x112>{}, before >= 2u && in_row >= 2u);   // row_shr:2
+    step(integral_constant<int, 0x114>{}, before >= 4u && in_row >= 4u);   // row_shr:4
+    step(integral_constant<int, 0x118>{}, before >= 8u && in_row >= 8u);   // row_shr:8
+    step(integral_constant<int, 0x142>{}, (lane & 16u) != 0u && before > in_row);          // row_bcast:15: rows 1 and 3
+    step(integral_constant<int, 0x143>{}, (lane & 32u) != 0u && before > (lane & 31u));    // row_bcast:31: rows 2 and 3
+}
+
+// Where a lane holds two half cells (lane l: halves of cells l / 2 and 32 + l / 2 of the wave): maxima of the halves to
+// the lanes that stand for the cells, and values of the cells to the halves.
+template <int P>
+__device__ __forceinline__ uint32_t cell_from_parts(const uint32_t (&m)[P], const uint32_t lane) {
+    if constexpr (P == 1) {
+        return m[0];
+    } else {
+        const uint32_t a = max(m[0], dpp_u32<kDppQuadSwap1>(m[0])), b = max(m[1], dpp_u32<kDppQuadSwap1>(m[1]));
+        const int from = (int)((lane & 31u) << 3);   // lane 2 (l mod 32), in bytes
+        const uint32_t x = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)a), y = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)b);
+        return lane < 32u ? x : y;
+    }
+}
+template <int P>
+__device__ __forceinline__ void parts_from_cell(const float c, const uint32_t lane, float (&o)[P]) {
+    if constexpr (P == 1) {
+        o[0] = c;
+    } else {
+        const int v = __builtin_bit_cast(int, c);
+        o[0] = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute((int)((lane >> 1) << 2), v));
+        o[1] = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute((int)((32u + (lane >> 1)) << 2), v));
+    }
+}
+
+// The range of the lane's cell's bucket from the parts' maxima m[p][0 .. N), each an unsigned key whose identity is 0.
+template <int B, bool LOCAL, int N>
+__device__ __forceinline__ void bucket_max(const uint32_t (&m)[N][Parts<B>::kCount], const CellTile& g, const uint32_t cell, const uint32_t bucket,
+                                           uint32_t (*s_max)[kMostSharedBuckets], uint32_t (&out)[N]) {
+    const uint32_t lane = threadIdx.x & 63u;
+#pragma unroll
+    for (int i = 0; i < N; ++i) out[i] = cell_from_parts<Parts<B>::kCount>(m[i], lane);
+    if constexpr (LOCAL) {
+        group_max(out, g.bucket_cells, lane);
+    } else {
+        const uint32_t in_bucket = cell - bucket * g.bucket_cells;
+        segment_max(out, in_bucket < lane ? in_bucket : lane, lane);
+        if (lane == 63u || in_bucket + 1u == g.bucket_cells) {   // the wave's last lane of the bucket
+#pragma unroll
+            for (int i = 0; i < N; ++i) atomicMax(&s_max[i][bucket], out[i]);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < N; ++i) out[i] = s_max[i][bucket];
+    }
+}
+
+// What the two encodings do with the sum's values.
+struct MinmaxCode {
+    using Sum = MinmaxSum;
+    static constexpr int kKeys = 2;
+    template <int B, bool WHOLE>
+    static __device__ __forceinline__ void keys(const float (&v)[32], const Window<B>& at, uint32_t (&m)[2][Parts<B>::kCount]) {
+        float lo[Parts<B>::kCount], hi[Parts<B>::kCount];
+        part_ranges<B, WHOLE>(v, at, lo, hi);
+#pragma unroll
+        for (int p = 0; p < Parts<B>::kCount; ++p) {
+            m[0][p] = ~order_key(lo[p]);
+            m[1][p] = order_key(hi[p]);
+        }
+    }
+    template <int B, bool WHOLE>
+    static __device__ __forceinline__ void encode(const RequantArgs& ra, const Window<B>& at, const uint64_t, const float (&v)[32], const uint32_t (&key)[2],
+                                                  const bool stores, const uint64_t bucket) {
+        const float Lf = (float)((1 << B) - 1), Wf = (float)ra.W;
+        float lo = key_value(~key[0]), hi = key_value(key[1]);
+        if (lo == 0.0f) lo = 0.0f;   // a zero bound is stored as +0
+        if (hi == 0.0f) hi = 0.0f;
+        if (stores) reinterpret_cast<float2*>(ra.q.scales)[bucket] = make_float2(lo / Wf, hi / Wf);
+        const uint32_t lane = threadIdx.x & 63u;
+        float mn[Parts<B>::kCount], a[Parts<B>::kCount];
+        parts_from_cell<Parts<B>::kCount>(lo, lane, mn);
+        parts_from_cell<Parts<B>::kCount>(inverse_step(lo, hi, Lf), lane, a);
+        encode_minmax<B, WHOLE>(ra.q.packed, at, v, mn, a);
+    }
+};
+template <int B, class Code, bool LOCAL, Size SIZE, bool WHOLE>
+__device__ __forceinline__ void requantize_cells_tile(const RequantArgs& ra, const CellTile& g, const uint64_t tile_base, typename Code::Sum::Step* s_tab,
+                                                      uint32_t (*s_max)[kMostSharedBuckets]) {
+    constexpr int P = Parts<B>::kCount;
+    const uint32_t tid = threadIdx.x;
+    const uint64_t tile_end = WHOLE ? tile_base + g.cells * kCell : ra.q.n;
+    const uint32_t buckets = WHOLE ? g.buckets : ((uint32_t)(tile_end - tile_base) + ra.q.bucket - 1u) / ra.q.bucket;   // that begin in the tile
+    const uint64_t first_bucket = (uint64_t)blockIdx.x * g.buckets;
+    const Window<B> at(ra.q.n, tile_base, tile_end, g.cells);
+    const auto bucket_of = [&](const uint32_t cell) {
+        const uint32_t k = (cell * g.magic) >> 20;
+        return WHOLE || k < buckets ? k : buckets - 1u;   // cells past the end: any
+    };
+    uint32_t bucket[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) bucket[p] = bucket_of(at.cell[p]);
+    for (uint32_t i = tid; i < ra.W * buckets; i += blockDim.x) {
+        const uint32_t w = i / buckets, k = i - w * buckets;
+        s_tab[i] = Code::Sum::step(ra.scales[w], first_bucket + k, (float)((1 << B) - 1));
+    }
+    if constexpr (!LOCAL) {
+        for (uint32_t i = tid; i < g.buckets; i += blockDim.x) {
+#pragma unroll
+            for (int u = 0; u < Code::kKeys; ++u) s_max[u][i] = 0u;
+        }
+    }
+    float v[32];
+    decode_sum<B, SIZE, WHOLE, typename Code::Sum>(ra, at, s_tab, buckets, bucket, v);
+
+    uint32_t m[Code::kKeys][P], key[Code::kKeys];
+    Code::template keys<B, WHOLE>(v, at, m);
+    const uint32_t cell = tid < g.cells ? tid : g.cells - 1u;   // the cell that this lane stands for
+    const uint32_t mine = (cell * g.magic) >> 20;
+    bucket_max<B, LOCAL, Code::kKeys>(m, g, cell, mine, s_max, key);
+    const bool stores = tid < g.cells && cell == mine * g.bucket_cells && mine < buckets;
+    Code::template encode<B, WHOLE>(ra, at, tile_base, v, key, stores, first_bucket + mine);
+}
+// Waves per SIMD: what the registers of that many words in flight leave without scratch memory.
+template <int B, class Code, Size SIZE>
+constexpr int bucketed_waves() {
+    constexpr bool most = B == 8 && Code::kKeys == 2;
+    return SIZE == Size::kShort ? (most ? 3 : 4) : (most ? 5 : 6);
+}
+template <int B, class Code, bool LOCAL, Size SIZE>
+__global__ __launch_bounds__(LOCAL ? 256 : 512) __attribute__((amdgpu_waves_per_eu(bucketed_waves<B, Code, SIZE>(), 8))) void requantize_cells_kernel(const RequantArgs ra, const CellTile g) {
+    extern __shared__ float2 s_dyn[];   // [W][buckets of the tile]: steps
+    __shared__ uint32_t s_max[LOCAL ? 1 : Code::kKeys][kMostSharedBuckets];
+    const uint64_t tile_base = (uint64_t)blockIdx.x * (g.cells * kCell);
+    auto* s_tab = reinterpret_cast<typename Code::Sum::Step*>(s_dyn);
+    if (tile_base + g.cells * kCell <= ra.q.n) requantize_cells_tile<B, Code, LOCAL, SIZE, true>(ra, g, tile_base, s_tab, s_max);
+    else requantize_cells_tile<B, Code, LOCAL, SIZE, false>(ra, g, tile_base, s_tab, s_max);
+}
+
 // Calls f(B) with the width as a compile-time constant.
 template <class F>
 void with_bits(uint32_t bits, F f) {
@@ -458,6 +651,47 @@ void with_shape(const RequantArgs& ra, F f) {
     });
 }
 
+bool local_buckets(const QuantizeArgs& a) { return a.bucket_shift >= 5 && a.bucket <= 64u * kCell; }
+
+// The tile of a bucket size.  Short launches: as few waves as hold a bucket (the tensor passes likewise).  Others: up to 256
+// cells, or 320 where whole buckets fill them a tenth better; one bucket where it has more cells.  At 4 M elements, 8 workers,
+// 2 bits the small tiles take 9.9 us at bucket 2304 (72 cells in two waves) and the large ones 7.8; 16 workers, 8 bits, bucket
+// 1024 15.1 and 12.8; at 2 M they are level or better.  At most 4096 steps in LDS.
+CellTile cell_tile(const RequantArgs& ra, uint32_t* lanes) {
+    const uint32_t bc = ra.q.bucket / kCell;
+    const bool local = local_buckets(ra.q);
+    uint32_t waves = (bc + 63u) / 64u;
+    if (size_of(ra) != Size::kShort && bc <= 256u) {
+        waves = !local && (320u / bc) * 4u * 10u > (256u / bc) * 5u * 11u ? 5u : 4u;   // used fractions, compared by cross-multiplication
+    }
+    uint32_t buckets = (waves * 64u) / bc;
+    const uint32_t most = 4096u / ra.W;   // >= 64
+    if (buckets > most) buckets = local ? 64u / bc : most;
+    const uint32_t cells = buckets * bc;
+    *lanes = (cells + 63u) / 64u * 64u;
+    return {cells, buckets, bc, ((1u << 20) + bc - 1u) / bc};
+}
+
+template <class Code>
+hipError_t launch_requantize_cells(const RequantArgs& ra, hipStream_t stream) {
+    uint32_t lanes;
+    const CellTile g = cell_tile(ra, &lanes);
+    const uint64_t elems = (uint64_t)g.cells * kCell;
+    const uint64_t tiles = (ra.q.n + elems - 1) / elems;
+    if (tiles > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    const size_t lds = sizeof(typename Code::Sum::Step) * ra.W * g.buckets;
+    with_shape(ra, [&](auto b, auto size) {
+        constexpr int B = decltype(b)::value;
+        constexpr Size SIZE = decltype(size)::value;
+        if (local_buckets(ra.q)) {
+            hipLaunchKernelGGL((requantize_cells_kernel<B, Code, true, SIZE>), dim3((uint32_t)tiles), dim3(lanes), lds, stream, ra, g);
+        } else {
+            hipLaunchKernelGGL((requantize_cells_kernel<B, Code, false, SIZE>), dim3((uint32_t)tiles), dim3(lanes), lds, stream, ra, g);
+        }
+    });
+    return hipGetLastError();
+}
+
 }  // namespace
 
 // ---- one range for the whole tensor: the passes of launch_requantize_minmax_tensor (minmax.hip) -------------------
@@ -477,5 +711,20 @@ void launch_requantize_tensor_cells(const RequantArgs& ra, uint32_t tiles, uint3
                            borrowed);
     });
 }
+
+// ---- one range per bucket -------------------------------------------------------------------------------------------
+// us, rows / cells:      64 K           1 M           2 M           10 M          25.6 M elements
+//   1024, 8, 4 bits       5.0 /  4.4    5.6 /  4.6    6.5 /  5.5   17.8 / 12.0   36.8 / 25.5
+//   1024, 8, 8 bits       5.1 /  4.9    5.6 /  5.0    6.9 /  6.3   20.6 / 15.6   44.3 / 35.9
+//   2304, 8, 4 bits       5.2 /  5.4    5.9 /  6.3    7.4 /  6.6   21.3 / 14.0   45.2 / 29.2
+//   2304, 16, 2 bits      7.1 /  7.1    7.9 /  8.8   10.0 /  9.4   32.1 / 20.3
+//   32, 24, 4 bits       11.7 / 13.4   13.8 / 14.4   15.6 / 20.0   55.0 / 57.4   (a division per lane and worker in either)
+//   64, 24, 6 bits       11.3 / 12.4   12.9 / 14.5   15.0 / 17.0
+bool requantize_minmax_cells_supported(const RequantArgs& ra) {
+    if (ra.q.drop_nan != 0u) return false;   // a whole tensor as one bucket
+    if (ra.q.n <= 1ull << 20) return ra.q.n >= 1ull << 16 && ra.q.bucket >= 128u && local_buckets(ra.q);
+    return ra.q.bucket >= 128u || ra.W <= 8u;
+}
+hipError_t launch_requantize_minmax_cells(const RequantArgs& ra, hipStream_t stream) { return launch_requantize_cells<MinmaxCode>(ra, stream); }
 
 }  // namespace mqg

@@ -22,7 +22,8 @@ import subprocess
 import sys
 
 # matched as substrings, first hit wins: a name that contains another comes before it
-KERNELS = ("requantize_tensor_cells_kernel", "sum_range_cells_kernel", "requantize_wave_kernel", "requantize_pack_kernel", "requantize_minmax_tensor_kernel", "requantize_minmax_kernel",
+KERNELS = ("requantize_tensor_cells_kernel", "sum_range_cells_kernel", "requantize_cells_kernel",
+           "requantize_wave_kernel", "requantize_pack_kernel", "requantize_minmax_tensor_kernel", "requantize_minmax_kernel",
            "sum_range_minmax_tensor_kernel", "aggregate_update_rows_kernel", "aggregate_update_lds_kernel",
            "aggregate_update_minmax_tensors_kernel", "aggregate_update_minmax_kernel", "aggregate_update_tensors_kernel",
            "aggregate_mean_kernel", "tensor_range_parts_kernel", "tensor_range_kernel", "sum_squares_partial_kernel",

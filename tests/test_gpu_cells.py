@@ -18,6 +18,27 @@ def gradients(n, W, seed):
     return [workloads.laplace(n, 1e-3, 31 * seed + w, DEV) + 1e-4 * w for w in range(W)]
 
 
+def check_minmax(q, n, bits, bucket):
+    pk, rg = mqgrad.mqg_aggregate_requantize_minmax([x[0] for x in q], [x[1] for x in q], n, bits, bucket)
+    torch.cuda.synchronize()
+    want_pk, want_rg = ref.aggregate_requantize_minmax([to_u32(x[0]) for x in q], [x[1].cpu().numpy() for x in q], n, bits, bucket)
+    assert rg.cpu().numpy().tobytes() == want_rg.tobytes(), first_mismatch(rg.cpu().numpy(), want_rg)
+    assert np.array_equal(to_u32(pk), want_pk), first_mismatch(to_u32(pk), want_pk)
+
+
+# (bucket, workers, elements): a bucket is one lane, two, a wave's half, a whole wave; cells of three; two waves and a bit;
+# one workgroup of 129, 257 and 512 cells
+SHAPES = [(32, 3, M + 1), (64, 9, M + 31), (1024, 5, M + 2048 + 33), (2048, 2, 2 * M + 7), (96, 6, M + 65), (2304, 4, M + 5000),
+          (4128, 1, M + 4129), (8224, 2, 2 * M + 32 * 5 + 17), (16384, 3, M + 16384 - 1)]
+
+
+@pytest.mark.parametrize("bits", range(1, 9))
+@pytest.mark.parametrize("bucket,W,n", SHAPES)
+def test_bucketed_steps_match_the_oracle(bucket, W, n, bits):
+    grads = gradients(n, W, bits)
+    check_minmax([mqgrad.mqg_quantize_minmax(g, bits, bucket) for g in grads], n, bits, bucket)
+
+
 @pytest.mark.parametrize("bits", range(1, 9))
 @pytest.mark.parametrize("n,W", [(3 * M // 2 + 1, 3), (3 * M // 2 + 2048, 1), (2 * M + 4, 9), (2 * M + 8192 + 33, 4), (2 * M + 77 * 32, 2)])
 def test_whole_tensor_steps_match_the_oracle(n, W, bits):
@@ -34,6 +55,29 @@ def test_whole_tensor_steps_match_the_oracle(n, W, bits):
     assert np.array_equal(to_u32(q[0][0]), want_pk)
 
 
+@pytest.mark.parametrize("bits", [4, 6, 8])
+def test_streams_larger_than_the_last_level_cache(bits):
+    """64 workers that send one of two streams: as many bytes as the rule counts, few to make.  The parts of a tensor that are
+    whole buckets come out alike alone, where the streams fit the cache."""
+    n, bucket, W = (256 << 20) // 64 * 8 // bits + 32 * 100 + 13, 1024, 64
+    half = n // 2 // bucket * bucket
+    assert half * bits // 8 * W < 256 << 20 < n // 8 * bits * W
+    a, b = gradients(n, 2, bits)
+    pick = lambda q, which, first, count: [q[w % 2][which][first:first + count] for w in range(W)]
+    for kind in ("minmax",):
+        per = 2
+        q = [mqgrad.mqg_quantize_minmax(g, bits, bucket) for g in (a, b)]
+        call = lambda pk, sc, n, base: mqgrad.mqg_aggregate_requantize_minmax(pk, sc, n, bits, bucket)
+        words, ranges = q[0][0].numel(), q[0][1].numel()
+        whole = call(pick(q, 0, 0, words), pick(q, 1, 0, ranges), n, 0)
+        w0, r0 = half // 32 * bits, per * half // bucket
+        first = call(pick(q, 0, 0, w0), pick(q, 1, 0, r0), half, 0)
+        rest = call(pick(q, 0, w0, words - w0), pick(q, 1, r0, ranges - r0), n - half, half)
+        torch.cuda.synchronize()
+        assert torch.equal(whole[1], torch.cat([first[1], rest[1]])), kind
+        assert torch.equal(whole[0], torch.cat([first[0], rest[0]])), kind
+
+
 def test_whole_tensor_streams_larger_than_the_last_level_cache():
     bits, W = 8, 64
     n = (256 << 20) // W + 32 * 100 + 13
@@ -43,6 +87,30 @@ def test_whole_tensor_streams_larger_than_the_last_level_cache():
     want = ref.aggregate_requantize_minmax([to_u32(q[w % 2][0]) for w in range(W)], [q[w % 2][1].cpu().numpy() for w in range(W)], n, bits, n)
     assert rg.cpu().numpy().tobytes() == want[1].tobytes()
     assert np.array_equal(to_u32(pk), want[0]), first_mismatch(to_u32(pk), want[0])
+
+
+@pytest.mark.parametrize("bits", [1, 4, 6, 7])
+@pytest.mark.parametrize("bucket", [128, 1024, 2304])
+def test_values_that_are_not_finite_as_in_a_smaller_tensor(bucket, bits):
+    """The first buckets of a large tensor, where one worker's gradient holds infinities, values that are not numbers, a
+    range that overflows, zeros or the smallest numbers, come out as those buckets alone do (the kernels of small tensors)."""
+    W, n = 3, M + 33 * bucket
+    grads = gradients(n, W, bits)
+    head = 7 * bucket
+    g = grads[1]
+    g[bucket + 5] = float("inf")
+    g[2 * bucket + 7], g[2 * bucket + 40] = float("inf"), float("-inf")
+    g[3 * bucket:4 * bucket] = float("nan")
+    g[4 * bucket + 1], g[4 * bucket + 2] = 3e38, -3e38
+    for w in range(W):
+        grads[w][5 * bucket:6 * bucket] = 0.0 if w == 1 else 1e-44
+    cut = lambda q, per: ([x[0][:head // 32 * bits].clone() for x in q], [x[1][:7 * per].clone() for x in q])
+    q = [mqgrad.mqg_quantize_minmax(x, bits, bucket) for x in grads]
+    small = mqgrad.mqg_aggregate_requantize_minmax(*cut(q, 2), head, bits, bucket)
+    large = mqgrad.mqg_aggregate_requantize_minmax([x[0] for x in q], [x[1] for x in q], n, bits, bucket)
+    torch.cuda.synchronize()
+    assert large[1][:14].cpu().numpy().tobytes() == small[1].cpu().numpy().tobytes()
+    assert np.array_equal(to_u32(large[0][:head // 32 * bits]), to_u32(small[0]))
 
 
 @pytest.mark.parametrize("bad", [float("nan"), float("inf"), float("-inf")])
