@@ -435,9 +435,8 @@ def alu_row(kernel, ms, ops, extra=None):
 def time_exchange(wl, bits, bucket, lr, steps, warmup):
     """The second leg of Algorithm 1: mqg_aggregate_requantize (server) + mqg_dequantize_update (worker).
 
-    The re-quantize kernel is bound by vector-ALU issue, not by HBM: per element it executes
-    W * 4 (bit-field extract, 2c - L, convert, fma) + about 17 (range, rounding, Philox / 8, packing)
-    vector operations while moving only (W + 1) * bits / 8 bytes."""
+    The re-quantize kernel's vector operations take about as long as its (W + 1) * bits / 8 bytes per element:
+    per element 3 to 4 per worker (extract and convert, 2c - L, fma) + about 12 (range, rounding, Philox / 8, packing)."""
     import torch
     from paper_1804_08066_amd import mqgrad
     n, W = wl.n, wl.W
@@ -468,17 +467,22 @@ def time_exchange(wl, bits, bucket, lr, steps, warmup):
     m_bytes = W * (n * bits / 8.0 + 4.0 * nb) + 4.0 * n
     r_bytes = (W + 1) * (n * bits / 8.0 + 4.0 * nb)
     d_bytes = n * bits / 8.0 + 4.0 * nb + 8.0 * n
-    # vector operations the kernel's algorithm issues per element: per worker's code 1.5 (1 bit: quad table)
-    # or 1.75 (2-4 bits: pair table) for table offsets + the chain's fma, 3 at 8 bits, 3.5 at 5-7 bits
-    # (arithmetic decode); about 14 to encode (range, Philox / 8, fixed-point rounding, packing)
-    per_code = 1.5 if bits == 1 else (1.75 if bits <= 4 else (3.0 if bits == 8 else 3.5))
-    r_ops = n * (per_code * W + 14.0)
+    # a cell per lane, or rows: the smallest tensors, and 1 and 2 bits with more than four workers (a table in LDS there)
+    cells = not (bucket & (bucket - 1) == 0 and bucket >= 128) or (n > 1 << 20 and (bits > 2 or W <= 4))
+    # vector operations the kernel's algorithm issues per element: per worker's code 1.5 (1 bit: quad table) or 1.75
+    # (pair table) for table offsets + the chain's fma in the rows form, 3 at 8 bits, 3.5 at 5-7 bits; with cells 2.9 at 1, 2
+    # and 4 bits, 3 at 8, 4 at the others; about 14 (12) to encode (range, Philox / 8, fixed-point rounding, packing)
+    if cells:
+        per_code = 2.9 if bits in (1, 2, 4) else (3.0 if bits == 8 else 4.0)
+    else:
+        per_code = 1.5 if bits == 1 else (1.75 if bits <= 4 else (3.0 if bits == 8 else 3.5))
+    r_ops = n * (per_code * W + (12.0 if cells else 14.0))
     log("exchange: requantize %.1f us (%.1f T lane-ops/s, %.0f GB/s), dequantize_update %.1f us (%.0f GB/s), "
         "aggregate_mean %.1f us (%.0f GB/s)" %
         (r_ms * 1e3, r_ops / (r_ms * 1e-3) / 1e12, r_bytes / (r_ms * 1e-3) / 1e9, d_ms * 1e3, d_bytes / (d_ms * 1e-3) / 1e9,
          m_ms * 1e3, m_bytes / (m_ms * 1e-3) / 1e9))
     return {
-        "requantize": alu_row("requantize_wave_kernel", r_ms, r_ops,
+        "requantize": alu_row("requantize_cells_kernel" if cells else "requantize_wave_kernel", r_ms, r_ops,
                               {"algorithmic_bytes_per_launch": r_bytes, "hbm_gbs": r_bytes / (r_ms * 1e-3) / 1e9}),
         "dequantize_update": {"kernel": "aggregate_update_rows_kernel (W=1)", "avg_launch_us": d_ms * 1e3, "bound": "hbm",
                               "achieved": d_bytes / (d_ms * 1e-3) / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",

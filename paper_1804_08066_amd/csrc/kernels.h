@@ -120,6 +120,8 @@ void launch_sum_range_cells(const RequantArgs& a, uint32_t tiles, uint32_t tile,
 void launch_requantize_tensor_cells(const RequantArgs& a, uint32_t tiles, uint32_t tile, const float* sum_range, uint32_t borrowed, hipStream_t stream);
 bool requantize_minmax_cells_supported(const RequantArgs& a);
 hipError_t launch_requantize_minmax_cells(const RequantArgs& a, hipStream_t stream);
+bool requantize_centred_cells_supported(const RequantArgs& a);
+hipError_t launch_requantize_centred_cells(const RequantArgs& a, hipStream_t stream);
 hipError_t launch_tensor_range(const float* grad, uint64_t n, float* range_out, hipStream_t stream);
 // the same for several tensors that are encoded next, with their code words as the workgroups' scratch memory
 struct TensorRangeBatch {

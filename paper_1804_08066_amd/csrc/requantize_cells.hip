@@ -60,18 +60,23 @@ __device__ __forceinline__ void load_words(const uint32_t* p, uint32_t* w) {
         w[0] = NT ? __builtin_nontemporal_load(p) : *p;
     }
 }
-template <int N>
+// AGENT: written through to memory at once, the line stays in L2 (as store_v4u_agent, but no lane's address is uniform here);
+// else streaming.
+template <int N, bool AGENT>
 __device__ __forceinline__ void store_words(uint32_t* p, const uint32_t* w) {
     if constexpr (N >= 4) {
         const v4u t = {w[0], w[1], w[2], w[3]};
-        __builtin_nontemporal_store(t, reinterpret_cast<v4u_a4*>(p));
-        if constexpr (N > 4) store_words<N - 4>(p + 4, w + 4);
+        if (AGENT) asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(p), "v"(t) : "memory");
+        else __builtin_nontemporal_store(t, reinterpret_cast<v4u_a4*>(p));
+        if constexpr (N > 4) store_words<N - 4, AGENT>(p + 4, w + 4);
     } else if constexpr (N >= 2) {
         const v2u t = {w[0], w[1]};
-        __builtin_nontemporal_store(t, reinterpret_cast<v2u_a4*>(p));
-        if constexpr (N > 2) store_words<N - 2>(p + 2, w + 2);
+        if (AGENT) asm volatile("global_store_dwordx2 %0, %1, off sc1" ::"v"(p), "v"(t) : "memory");
+        else __builtin_nontemporal_store(t, reinterpret_cast<v2u_a4*>(p));
+        if constexpr (N > 2) store_words<N - 2, AGENT>(p + 2, w + 2);
     } else {
-        __builtin_nontemporal_store(w[0], p);
+        if (AGENT) asm volatile("global_store_dword %0, %1, off sc1" ::"v"(p), "v"(w[0]) : "memory");
+        else __builtin_nontemporal_store(w[0], p);
     }
 }
 
@@ -211,6 +216,25 @@ struct MinmaxSum {   // acc <- acc + fma(c, step, min)
         });
     }
 };
+struct CentredSum {   // acc <- fma(2c - L, step, acc)
+    using Step = float;
+    static __device__ __forceinline__ Step step(const float* scales, const uint64_t k, const float Lf) { return scales[k] / Lf; }
+    template <int B>
+    struct Consts {
+        uint32_t mask;
+        float scale, minus_top;
+        __device__ __forceinline__ Consts()
+            : mask(byte_mask<B>()), scale(in_vector(0x1p10f)), minus_top(in_vector(-(float)((1 << B) - 1))) {}
+    };
+    template <int B>
+    static __device__ __forceinline__ void add(const uint32_t (&w)[B], const Consts<B>& k, const Step (&s)[Parts<B>::kCount], float (&v)[32]) {
+        for_codes<B>(w, k.mask, k.scale, [&](int i, float c) {
+            const float centred = B == 1 || B == 2 || B == 4 ? c + k.minus_top : __builtin_fmaf(c, 2.0f, k.minus_top);   // there c is twice the code
+            v[i] = __builtin_fmaf(centred, s[i / Parts<B>::kElems], v[i]);
+        });
+    }
+};
+
 // Workers whose code words are in flight together: as soon as a worker's words are decoded, those of the worker
 // in_flight places on are requested in their stead.
 template <int B, Size SIZE>
@@ -267,19 +291,19 @@ __device__ __forceinline__ void place(uint32_t (&o)[B], const int k, const uint3
     o[i] = sh == 0 ? v : (o[i] | v << sh);
     if (sh + codes * B > 32) o[i + 1 < B ? i + 1 : i] = v >> (32 - sh);
 }
-template <int B, bool WHOLE>
+template <int B, bool WHOLE, bool AGENT>
 __device__ __forceinline__ void store_parts(uint32_t* __restrict__ out, const Window<B>& at, const uint32_t (&o)[B]) {
     constexpr int PW = Parts<B>::kWords;
 #pragma unroll
     for (int p = 0; p < Parts<B>::kCount; ++p) {
         uint32_t* __restrict__ dst = out + at.tile_word + at.word[p];
         if (WHOLE) {
-            if (at.count[p] != 0u) store_words<PW>(dst, o + p * PW);
+            if (at.count[p] != 0u) store_words<PW, AGENT>(dst, o + p * PW);
         } else {
             const uint32_t words = (at.count[p] * B + 31u) >> 5;
 #pragma unroll
             for (int i = 0; i < PW; ++i) {
-                if ((uint32_t)i < words) store_words<1>(dst + i, o + p * PW + i);
+                if ((uint32_t)i < words) store_words<1, AGENT>(dst + i, o + p * PW + i);
             }
         }
     }
@@ -301,7 +325,7 @@ __device__ __forceinline__ void encode_minmax(uint32_t* out, const Window<B>& at
         const uint32_t code = nearest_code(v[k], mn[p], a[p], Lf);
         place<B>(o, k, inside<B, WHOLE>(at, k) ? code : 0u, 1);   // elements past the end contribute zero bits
     }
-    store_parts<B, WHOLE>(out, at, o);
+    store_parts<B, WHOLE, false>(out, at, o);
 }
 __device__ __forceinline__ float inverse_step(float mn, float mx, float Lf) {
     const float r = mx - mn;
@@ -562,6 +586,60 @@ struct MinmaxCode {
         encode_minmax<B, WHOLE>(ra.q.packed, at, v, mn, a);
     }
 };
+struct CentredCode {
+    using Sum = CentredSum;
+    static constexpr int kKeys = 1;
+    template <int B, bool WHOLE>
+    static __device__ __forceinline__ void keys(const float (&v)[32], const Window<B>& at, uint32_t (&m)[1][Parts<B>::kCount]) {
+        constexpr int E = Parts<B>::kElems;
+#pragma unroll
+        for (int p = 0; p < Parts<B>::kCount; ++p) {
+            float r = 0.0f;
+#pragma unroll
+            for (int k = p * E; k < p * E + E; k += 2) {   // non-negative floats order like their bit patterns
+                const float x = inside<B, WHOLE>(at, k) ? v[k] : 0.0f, y = inside<B, WHOLE>(at, k + 1) ? v[k + 1] : 0.0f;
+                asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(r) : "v"(x), "v"(y));
+            }
+            m[0][p] = __builtin_bit_cast(uint32_t, r);
+        }
+    }
+    template <int B, bool WHOLE>
+    static __device__ __forceinline__ void encode(const RequantArgs& ra, const Window<B>& at, const uint64_t tile_base, const float (&v)[32],
+                                                  const uint32_t (&key)[1], const bool stores, const uint64_t bucket) {
+        constexpr int P = Parts<B>::kCount, E = Parts<B>::kElems;
+        const QuantizeArgs& a = ra.q;
+        const float halfL = 0.5f * (float)((1 << B) - 1);
+        float s = __builtin_bit_cast(float, key[0]);
+        if (!(s >= 0x1p-96f)) s = 0.0f;
+        if (stores) a.scales[bucket] = s / (float)ra.W;
+        float a16[P];
+        parts_from_cell<P>((s > 0.0f) ? (halfL / s) * 65536.0f : 0.0f, threadIdx.x & 63u, a16);   // IEEE-correct fp32 division, times 2^16 (exact)
+        FixedGrid fg = fixed_grid(B);
+        fg.half16 = in_vector(fg.half16);
+        uint32_t o[B];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {   // one Philox call covers eight consecutive elements
+            const int p = 8 * q / E;
+            const uint64_t grp = (a.elem_base + tile_base + (uint64_t)(at.word[p] / (Parts<B>::kWords) * E + (8 * q) % E)) >> 3;
+            uint32_t h[4];
+            philox4x32_10<true>((uint32_t)grp, (uint32_t)(grp >> 32), a.iteration, a.worker, a.key0, a.key1, h);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                uint32_t t[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int k = 8 * q + 4 * u + e;
+                    const uint32_t word = h[2 * u + e / 2];
+                    t[e] = round_code_hi(v[k], a16[p], fg, (e & 1) != 0 ? word >> 16 : word & 0xFFFFu);
+                    if (!inside<B, WHOLE>(at, k)) t[e] = 0u;   // elements past the end contribute zero bits
+                }
+                place<B>(o, 8 * q + 4 * u, pack_quad_hi(t[0], t[1], t[2], t[3], B, 2 * B, 3 * B), 4);
+            }
+        }
+        store_parts<B, WHOLE, true>(a.packed, at, o);   // 1 % of the exchange of 25.6 M elements, 8 workers, 4 bits: the worker's update reads them next
+    }
+};
+
 template <int B, class Code, bool LOCAL, Size SIZE, bool WHOLE>
 __device__ __forceinline__ void requantize_cells_tile(const RequantArgs& ra, const CellTile& g, const uint64_t tile_base, typename Code::Sum::Step* s_tab,
                                                       uint32_t (*s_max)[kMostSharedBuckets]) {
@@ -726,5 +804,20 @@ bool requantize_minmax_cells_supported(const RequantArgs& ra) {
     return ra.q.bucket >= 128u || ra.W <= 8u;
 }
 hipError_t launch_requantize_minmax_cells(const RequantArgs& ra, hipStream_t stream) { return launch_requantize_cells<MinmaxCode>(ra, stream); }
+
+// us, the kernels of quantize_wave.hip (power-of-two buckets from 128) or quantize_pack.hip (others) / cells:
+//                         64 K           1 M           4 M           10 M          25.6 M elements
+//   1024, 8, 1 bit        4.4 /  4.8    4.7 /  5.1    6.6 /  6.7   11.0 / 11.9   23.4 / 26.5
+//   1024, 8, 4 bits       4.6 /  4.7    4.8 /  5.1    8.5 /  8.2   15.7 / 12.5   30.9 / 27.2
+//   1024, 8, 7 bits       4.7 /  5.3    5.2 /  5.7   10.5 /  8.8   19.6 / 15.3   44.0 / 36.0
+//   2304, 8, 4 bits       7.6 /  5.6    7.9 /  6.4   17.6 /  8.9   35.9 / 14.5   85.0 / 33.5
+//   64, 8, 4 bits         6.5 /  5.7    6.8 /  6.0                 23.2 / 15.1
+//   32, 24, 6 bits       14.6 / 15.6   16.3 / 17.2   (2 M: 18.5 / 22.6)
+bool requantize_centred_cells_supported(const RequantArgs& ra) {
+    if (ra.q.scale_mode != MQG_SCALE_MAXABS || ra.q.n < kCell) return false;   // a lane reads its words at once: the stream must hold as many
+    if (requantize_wave_supported(ra)) return ra.q.n > 1ull << 20 && (ra.q.bits > 2u || ra.W <= 4u);
+    return ra.q.bucket > 32u || ra.W <= 8u || ra.q.n > 1ull << 21;
+}
+hipError_t launch_requantize_centred_cells(const RequantArgs& ra, hipStream_t stream) { return launch_requantize_cells<CentredCode>(ra, stream); }
 
 }  // namespace mqg

@@ -26,6 +26,14 @@ def check_minmax(q, n, bits, bucket):
     assert np.array_equal(to_u32(pk), want_pk), first_mismatch(to_u32(pk), want_pk)
 
 
+def check_centred(q, n, bits, bucket, elem_base=0):
+    pk, sc = mqgrad.mqg_aggregate_requantize([x[0] for x in q], [x[1] for x in q], n, bits, bucket, 11, 5, 3, elem_base)
+    torch.cuda.synchronize()
+    want_pk, want_sc = ref.aggregate_requantize([to_u32(x[0]) for x in q], [x[1].cpu().numpy() for x in q], n, bits, bucket, 11, 5, 3, elem_base)
+    assert sc.cpu().numpy().tobytes() == want_sc.tobytes(), first_mismatch(sc.cpu().numpy(), want_sc)
+    assert np.array_equal(to_u32(pk), want_pk), first_mismatch(to_u32(pk), want_pk)
+
+
 # (bucket, workers, elements): a bucket is one lane, two, a wave's half, a whole wave; cells of three; two waves and a bit;
 # one workgroup of 129, 257 and 512 cells
 SHAPES = [(32, 3, M + 1), (64, 9, M + 31), (1024, 5, M + 2048 + 33), (2048, 2, 2 * M + 7), (96, 6, M + 65), (2304, 4, M + 5000),
@@ -37,6 +45,14 @@ SHAPES = [(32, 3, M + 1), (64, 9, M + 31), (1024, 5, M + 2048 + 33), (2048, 2, 2
 def test_bucketed_steps_match_the_oracle(bucket, W, n, bits):
     grads = gradients(n, W, bits)
     check_minmax([mqgrad.mqg_quantize_minmax(g, bits, bucket) for g in grads], n, bits, bucket)
+    check_centred([mqgrad.mqg_quantize(g, bits, bucket, 7, 2, w) for w, g in enumerate(grads)], n, bits, bucket, elem_base=(1 << 33) + 8)
+
+
+@pytest.mark.parametrize("bits", range(1, 9))
+@pytest.mark.parametrize("n,bucket,W", [(32, 32, 2), (33, 64, 3), (95, 96, 17), (2081, 2304, 5), (4100, 4128, 8), (20011, 12320, 9)])
+def test_small_tensors_with_the_max_abs_range(n, bucket, W, bits):
+    grads = gradients(n, W, bits)
+    check_centred([mqgrad.mqg_quantize(g, bits, bucket, 7, 2, w) for w, g in enumerate(grads)], n, bits, bucket)
 
 
 @pytest.mark.parametrize("bits", range(1, 9))
@@ -64,10 +80,14 @@ def test_streams_larger_than_the_last_level_cache(bits):
     assert half * bits // 8 * W < 256 << 20 < n // 8 * bits * W
     a, b = gradients(n, 2, bits)
     pick = lambda q, which, first, count: [q[w % 2][which][first:first + count] for w in range(W)]
-    for kind in ("minmax",):
-        per = 2
-        q = [mqgrad.mqg_quantize_minmax(g, bits, bucket) for g in (a, b)]
-        call = lambda pk, sc, n, base: mqgrad.mqg_aggregate_requantize_minmax(pk, sc, n, bits, bucket)
+    for kind in ("minmax", "centred"):
+        per = 1 if kind == "centred" else 2
+        if kind == "centred":
+            q = [mqgrad.mqg_quantize(g, bits, bucket, 7, 2, w) for w, g in enumerate((a, b))]
+            call = lambda pk, sc, n, base: mqgrad.mqg_aggregate_requantize(pk, sc, n, bits, bucket, 11, 5, 3, base)
+        else:
+            q = [mqgrad.mqg_quantize_minmax(g, bits, bucket) for g in (a, b)]
+            call = lambda pk, sc, n, base: mqgrad.mqg_aggregate_requantize_minmax(pk, sc, n, bits, bucket)
         words, ranges = q[0][0].numel(), q[0][1].numel()
         whole = call(pick(q, 0, 0, words), pick(q, 1, 0, ranges), n, 0)
         w0, r0 = half // 32 * bits, per * half // bucket
@@ -111,6 +131,13 @@ def test_values_that_are_not_finite_as_in_a_smaller_tensor(bucket, bits):
     torch.cuda.synchronize()
     assert large[1][:14].cpu().numpy().tobytes() == small[1].cpu().numpy().tobytes()
     assert np.array_equal(to_u32(large[0][:head // 32 * bits]), to_u32(small[0]))
+    if bucket & (bucket - 1) == 0:      # with the max-abs range the other buckets have one kernel for every size
+        q = [mqgrad.mqg_quantize(x, bits, bucket, 7, 2, w) for w, x in enumerate(grads)]
+        small = mqgrad.mqg_aggregate_requantize(*cut(q, 1), head, bits, bucket, 11, 5, 3)
+        large = mqgrad.mqg_aggregate_requantize([x[0] for x in q], [x[1] for x in q], n, bits, bucket, 11, 5, 3)
+        torch.cuda.synchronize()
+        assert large[1][:7].cpu().numpy().tobytes() == small[1].cpu().numpy().tobytes()
+        assert np.array_equal(to_u32(large[0][:head // 32 * bits]), to_u32(small[0]))
 
 
 @pytest.mark.parametrize("bad", [float("nan"), float("inf"), float("-inf")])
