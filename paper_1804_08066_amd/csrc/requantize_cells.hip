@@ -31,7 +31,6 @@ constexpr uint32_t kCell = 32;          // elements
 enum class Size { kShort, kLong, kStream };
 
 typedef float v2f __attribute__((ext_vector_type(2)));
-typedef uint32_t v2u __attribute__((ext_vector_type(2)));
 typedef v2u v2u_a4 __attribute__((aligned(4)));
 
 // ---- a lane's words -----------------------------------------------------------------------------------
@@ -60,22 +59,21 @@ __device__ __forceinline__ void load_words(const uint32_t* p, uint32_t* w) {
         w[0] = NT ? __builtin_nontemporal_load(p) : *p;
     }
 }
-// AGENT: written through to memory at once, the line stays in L2 (as store_v4u_agent, but no lane's address is uniform here);
-// else streaming.
+// AGENT: written through to memory at once, the line stays in L2 (store_v4u_agent and store_u32_agent); else streaming.
 template <int N, bool AGENT>
 __device__ __forceinline__ void store_words(uint32_t* p, const uint32_t* w) {
     if constexpr (N >= 4) {
         const v4u t = {w[0], w[1], w[2], w[3]};
-        if (AGENT) asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(p), "v"(t) : "memory");
+        if (AGENT) store_v4u_agent(p, t);
         else __builtin_nontemporal_store(t, reinterpret_cast<v4u_a4*>(p));
         if constexpr (N > 4) store_words<N - 4, AGENT>(p + 4, w + 4);
     } else if constexpr (N >= 2) {
         const v2u t = {w[0], w[1]};
-        if (AGENT) asm volatile("global_store_dwordx2 %0, %1, off sc1" ::"v"(p), "v"(t) : "memory");
+        if (AGENT) store_v2u_agent(p, t);
         else __builtin_nontemporal_store(t, reinterpret_cast<v2u_a4*>(p));
         if constexpr (N > 2) store_words<N - 2, AGENT>(p + 2, w + 2);
     } else {
-        if (AGENT) asm volatile("global_store_dword %0, %1, off sc1" ::"v"(p), "v"(w[0]) : "memory");
+        if (AGENT) store_u32_agent(p, w[0]);
         else __builtin_nontemporal_store(w[0], p);
     }
 }
