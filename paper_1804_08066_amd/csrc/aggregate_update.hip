@@ -23,6 +23,7 @@
 // them back with v_readlane -- no LDS, no barrier.  Any other bucket size: a table in LDS, one
 // barrier.
 
+#include "batch.h"
 #include "decode.h"
 #include "kernels.h"
 #include "tile_io.h"
@@ -266,11 +267,7 @@ __global__ __launch_bounds__(kThreads) void aggregate_mean_kernel(const Aggregat
 template <bool STRADDLE, bool ONCE>
 __global__ __launch_bounds__(kThreads) void aggregate_update_tensors_kernel(const BatchAggregateArgs a) {
     extern __shared__ float s_step[];
-    uint32_t lo = 0, hi = a.count;           // tile_start[lo] <= blockIdx.x < tile_start[hi]
-    while (hi - lo > 1u) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (blockIdx.x >= a.tile_start[mid]) lo = mid; else hi = mid;
-    }
+    const uint32_t lo = tensor_of_block(a.tile_start, a.count, blockIdx.x);
     const BatchAggregateArgs::Tensor& t = a.t[lo];
     const uint64_t tile_base = (uint64_t)(blockIdx.x - a.tile_start[lo]) * kLdsTile;
     const void* const* ptrs = a.ptrs + t.first_ptr;

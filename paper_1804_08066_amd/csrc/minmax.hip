@@ -15,6 +15,7 @@
 #include <mutex>
 #include <type_traits>
 
+#include "batch.h"
 #include "decode.h"
 #include "encode.h"
 #include "kernels.h"
@@ -279,11 +280,7 @@ template <int R, int NT, bool ONE>
 __global__ __launch_bounds__(NT) void quantize_minmax_tensors_kernel(const BatchQuantizeArgs ba, const TileGeometry g) {
     drop_every_nan();
     __shared__ Shared<R, NT, ONE> sm;
-    uint32_t lo = 0, hi = ba.count;          // tile_start[lo] <= blockIdx.x < tile_start[hi]
-    while (hi - lo > 1u) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (blockIdx.x >= ba.tile_start[mid]) lo = mid; else hi = mid;
-    }
+    const uint32_t lo = tensor_of_block(ba.tile_start, ba.count, blockIdx.x);
     QuantizeArgs a = ba.common;
     a.grad = ba.t[lo].grad;
     a.n = ba.t[lo].n;
@@ -666,11 +663,7 @@ __global__ __launch_bounds__(kThreads) void aggregate_update_minmax_kernel(const
 template <bool STRADDLE, bool ONCE>
 __global__ __launch_bounds__(kThreads) void aggregate_update_minmax_tensors_kernel(const BatchAggregateArgs a) {
     extern __shared__ float2 s_tab[];
-    uint32_t lo = 0, hi = a.count;           // tile_start[lo] <= blockIdx.x < tile_start[hi]
-    while (hi - lo > 1u) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (blockIdx.x >= a.tile_start[mid]) lo = mid; else hi = mid;
-    }
+    const uint32_t lo = tensor_of_block(a.tile_start, a.count, blockIdx.x);
     const BatchAggregateArgs::Tensor& bt = a.t[lo];
     const void* const* ptrs = a.ptrs + bt.first_ptr;
     const TileCommon c = {a.W, a.bits, a.bucket, a.bucket_shift, a.per_tensor, a.neg_c};
@@ -741,11 +734,7 @@ __global__ __launch_bounds__(kSumThreads) void tensor_range_kernel(const float* 
 __global__ __launch_bounds__(kSumThreads) void tensor_range_parts_kernel(const TensorRangeBatch b, const uint32_t count) {
     drop_every_nan();
     __shared__ uint32_t s_lo[kSumThreads / 64], s_hi[kSumThreads / 64];
-    uint32_t k = 0, end = count;          // block_start[k] <= blockIdx.x < block_start[end]
-    while (end - k > 1u) {
-        const uint32_t mid = (k + end) >> 1;
-        if (blockIdx.x >= b.block_start[mid]) k = mid; else end = mid;
-    }
+    const uint32_t k = tensor_of_block(b.block_start, count, blockIdx.x);
     const uint32_t block = blockIdx.x - b.block_start[k], nblocks = b.block_start[k + 1u] - b.block_start[k];
     uint32_t kl, kh;
     block_range(b.grad[k], b.n[k], block, nblocks, kl, kh, s_lo, s_hi);

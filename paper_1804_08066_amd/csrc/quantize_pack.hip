@@ -27,6 +27,7 @@
 // away, the even lane computes the pair's call for row j and the odd lane the call for row j+1;
 // they swap halves with one DPP quad permute per word.
 
+#include "batch.h"
 #include "decode.h"
 #include "encode.h"
 #include "kernels.h"
@@ -372,11 +373,7 @@ template <int R>
 __global__ __launch_bounds__(kThreads) void quantize_tensors_kernel(const BatchQuantizeArgs ba) {
     drop_every_nan();
     __shared__ Shared<R> sm;
-    uint32_t lo = 0, hi = ba.count;          // tile_start[lo] <= blockIdx.x < tile_start[hi]
-    while (hi - lo > 1u) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (blockIdx.x >= ba.tile_start[mid]) lo = mid; else hi = mid;
-    }
+    const uint32_t lo = tensor_of_block(ba.tile_start, ba.count, blockIdx.x);
     QuantizeArgs a = ba.common;
     a.grad = ba.t[lo].grad;
     a.n = ba.t[lo].n;

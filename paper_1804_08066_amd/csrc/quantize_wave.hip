@@ -22,6 +22,7 @@
 // its HBM-bound duration), so work is moved off the vector ALU where possible: cross-lane exchange through LDS-pipe swizzles, per-bucket
 // values through small per-wave LDS tables, bit placement through LDS atomics.
 
+#include "batch.h"
 #include "decode.h"
 #include "encode.h"
 #include "kernels.h"
@@ -478,11 +479,7 @@ template <int R, int WPB, int NW, int OCC, bool HOIST>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1, OCC))) void quantize_tensors_wave_kernel(const BatchQuantizeArgs ba) {
     drop_every_nan();
     __shared__ WaveShared<R, NW> sm;
-    uint32_t lo = 0, hi = ba.count;          // tile_start[lo] <= blockIdx.x < tile_start[hi]
-    while (hi - lo > 1u) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (blockIdx.x >= ba.tile_start[mid]) lo = mid; else hi = mid;
-    }
+    const uint32_t lo = tensor_of_block(ba.tile_start, ba.count, blockIdx.x);
     QuantizeArgs a = ba.common;
     a.grad = ba.t[lo].grad;
     a.n = ba.t[lo].n;
@@ -661,11 +658,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1, OCC)
     drop_every_nan();
     __shared__ WaveShared<8, NW> sm;
     __shared__ CellShared<NW> cs;
-    uint32_t lo = 0, hi = ba.count;          // tile_start[lo] <= blockIdx.x < tile_start[hi]
-    while (hi - lo > 1u) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (blockIdx.x >= ba.tile_start[mid]) lo = mid; else hi = mid;
-    }
+    const uint32_t lo = tensor_of_block(ba.tile_start, ba.count, blockIdx.x);
     QuantizeArgs a = ba.common;
     a.grad = ba.t[lo].grad;
     a.n = ba.t[lo].n;
@@ -1034,11 +1027,7 @@ __global__ __launch_bounds__(64 * NW) void quantize_minmax_tensors_wave_kernel(c
     drop_every_nan();
     __shared__ WaveShared<R, NW> sm;
     __shared__ WaveLows<R, NW> lw;
-    uint32_t lo = 0, hi = ba.count;          // tile_start[lo] <= blockIdx.x < tile_start[hi]
-    while (hi - lo > 1u) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (blockIdx.x >= ba.tile_start[mid]) lo = mid; else hi = mid;
-    }
+    const uint32_t lo = tensor_of_block(ba.tile_start, ba.count, blockIdx.x);
     QuantizeArgs a = ba.common;
     a.grad = ba.t[lo].grad;
     a.n = ba.t[lo].n;
