@@ -184,6 +184,8 @@ def lib():
         strict, loose = getattr(L, name), getattr(T, name)
         loose.argtypes = [vp if t in tables else t for t in strict.argtypes]
         loose.restype = strict.restype
+    _marshal.bind(_raw_stream, getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device),
+                  *[C.cast(getattr(T, name), vp).value for name in _CALLED])
     _tables = T
     _lib = L
     return L
@@ -193,8 +195,14 @@ class _NoTables:
     """Stands in for the native argument tables where they are not available: nothing is accepted, and the binding's own
     checks make every table."""
     pointers = stream = quantize_items = update_items = staticmethod(lambda *args: None)
+    bind = quantize = quantize_minmax = update = requantize = dequantize_update = quantize_tensors = update_tensors = pointers
 
 
+# the entries that the native module calls itself, in its order
+_CALLED = ("mqg_quantize_mode", "mqg_quantize_minmax", "mqg_quantize_minmax_tensor", "mqg_aggregate_update_from",
+           "mqg_aggregate_update_minmax", "mqg_aggregate_update_minmax_tensor", "mqg_aggregate_requantize_mode",
+           "mqg_aggregate_requantize_minmax", "mqg_aggregate_requantize_minmax_tensor", "mqg_dequantize_update", "mqg_quantize_tensors_mode",
+           "mqg_quantize_minmax_tensors", "mqg_aggregate_update_tensors", "mqg_aggregate_update_minmax_tensors")
 _TAKES_TABLES = ("mqg_aggregate_update_from", "mqg_aggregate_requantize_mode", "mqg_aggregate_mean", "mqg_quantize_tensors_mode",
                  "mqg_aggregate_update_tensors", "mqg_aggregate_update_minmax_tensors", "mqg_quantize_minmax_tensors",
                  "mqg_aggregate_update_minmax", "mqg_aggregate_requantize_minmax", "mqg_aggregate_update_minmax_tensor",
@@ -286,6 +294,14 @@ def mqg_quantize(grad, bits, bucket, seed, iteration=0, worker=0, elem_base=0,
         p, s = alloc_outputs(grad.numel(), bits, bucket, grad.device)
         packed_out = p if packed_out is None else packed_out
         scales_out = s if scales_out is None else scales_out
+    _lib or lib()
+    if scales_in is None and dest is None:
+        st = _marshal.quantize(grad, packed_out, scales_out, bits, bucket, MQG_SCALE_MAXABS if mode is None else mode, seed, iteration,
+                               worker, elem_base, stream)
+        if st == MQG_OK:
+            return packed_out, scales_out
+        if st is not None:
+            raise MqgError(st, "mqg_quantize")
     L, (n, gp, pp, sp) = _encoder_args(grad, packed_out, scales_out, bits, bucket, _SCALES)
     sh = _stream_handle(stream)
     if scales_in is not None:
@@ -308,6 +324,12 @@ def mqg_aggregate_update(packed, scales, n, bits, bucket, lr, params, stream=Non
     """Server side.  packed / scales: lists of W CUDA tensors; params: fp32 CUDA tensor, updated in place.
     origin: MQG_CODES_FROM_MEMORY when the streams were not written by this GPU just before (same results,
     streaming loads of the code words at every width)."""
+    _lib or lib()
+    st = _marshal.update(packed, scales, n, bits, bucket, _SCALES, lr, params, origin, stream)
+    if st == MQG_OK:
+        return params
+    if st is not None:
+        raise MqgError(st, "mqg_aggregate_update")
     W, pa, sa = _worker_arrays(packed, scales, n, bits, bucket)
     _check(params, torch.float32, "params")
     if params.numel() != n:
@@ -336,6 +358,13 @@ def mqg_aggregate_requantize(packed, scales, n, bits, bucket, seed, iteration=0,
                              packed_out=None, scales_out=None, stream=None, mode=MQG_SCALE_MAXABS):
     """Server's half of the full exchange: quantized mean of the W workers' gradients (mode: the bucket
     range of the sum, max-abs or L2 norm).  Returns (packed int32[words], scales fp32[nb])."""
+    _lib or lib()
+    if packed_out is not None and scales_out is not None:
+        st = _marshal.requantize(packed, scales, n, bits, bucket, _SCALES, mode, seed, iteration, worker, elem_base, packed_out, scales_out, stream)
+        if st == MQG_OK:
+            return packed_out, scales_out
+        if st is not None:
+            raise MqgError(st, "mqg_aggregate_requantize")
     W, pa, sa = _worker_arrays(packed, scales, n, bits, bucket)
     dev = packed[0].device if W else "cuda"
     if packed_out is None or scales_out is None:
@@ -355,6 +384,12 @@ def mqg_aggregate_requantize(packed, scales, n, bits, bucket, seed, iteration=0,
 
 def mqg_dequantize_update(packed, scales, n, bits, bucket, lr, params, stream=None):
     """Worker's half of the full exchange: params <- params - lr * De-quantize(packed, scales)."""
+    _lib or lib()
+    st = _marshal.dequantize_update(packed, scales, n, bits, bucket, lr, params, stream)
+    if st == MQG_OK:
+        return params
+    if st is not None:
+        raise MqgError(st, "mqg_dequantize_update")
     _check(packed, torch.int32, "packed")
     _check(scales, torch.float32, "scales")
     _check(params, torch.float32, "params")
@@ -375,7 +410,13 @@ def mqg_quantize_tensors(grads, bits, bucket, seed, iteration=0, worker=0, elem_
     count = len(grads)
     if outputs is None:
         outputs = [alloc_outputs(g.numel(), bits, bucket, g.device) for g in grads]
-    lib()
+    _lib or lib()
+    st = _marshal.quantize_tensors(grads, outputs, elem_bases, bits, bucket, _SCALES, scale_mode, seed, iteration, worker,
+                                   stream) if scales_in is None else None
+    if st == MQG_OK:
+        return outputs
+    if st is not None:
+        raise MqgError(st, "mqg_quantize_tensors")
     items = _marshal.quantize_items(grads, outputs, elem_bases, bits, bucket, _SCALES) if scales_in is None else None
     if items is None:
         items = _quantize_items(grads, bits, bucket, elem_bases, outputs, scales_in)
@@ -415,6 +456,12 @@ def mqg_aggregate_update_tensors(layers, W, bits, bucket, lr, stream=None):
 
     Each layer is a dict with "params" and either ("packed": [W tensors], "scales": [W tensors]) for a
     quantized layer or "raw": [W fp32 gradient tensors] for a layer sent uncompressed."""
+    _lib or lib()
+    st = _marshal.update_tensors(layers, W, bits, bucket, _SCALES, lr, stream)
+    if st == MQG_OK:
+        return
+    if st is not None:
+        raise MqgError(st, "mqg_aggregate_update_tensors")
     items, keep = _update_items(layers, W, bits, bucket, 0)
     st = _tables.mqg_aggregate_update_tensors(items, len(layers), W, bits, bucket, lr, _stream_handle(stream))
     del keep
@@ -472,7 +519,12 @@ def mqg_quantize_minmax_tensors(grads, bits, bucket, outputs=None, stream=None):
     if outputs is None:
         outputs = [(torch.empty(mqg_packed_words(g.numel(), bits), dtype=torch.int32, device=g.device),
                     torch.empty(nr(g.numel()), dtype=torch.float32, device=g.device)) for g in grads]
-    lib()
+    _lib or lib()
+    st = _marshal.quantize_tensors(grads, outputs, None, bits, bucket, _PAIRS if bucket else _ONE_PAIR, 0, 0, 0, 0, stream)
+    if st == MQG_OK:
+        return outputs
+    if st is not None:
+        raise MqgError(st, "mqg_quantize_minmax_tensors")
     items = _marshal.quantize_items(grads, outputs, None, bits, bucket, _PAIRS if bucket else _ONE_PAIR)
     if items is None:
         items = (QuantizeItem * max(count, 1))()
@@ -493,6 +545,12 @@ def mqg_quantize_minmax_tensors(grads, bits, bucket, outputs=None, stream=None):
 def mqg_aggregate_update_minmax_tensors(layers, W, bits, bucket, lr, stream=None):
     """mqg_aggregate_update_minmax for a list of layers in one launch (bucket = 0: one (min, max) pair per worker
     and layer).  Layers as in mqg_aggregate_update_tensors, "scales" holding the range arrays."""
+    _lib or lib()
+    st = _marshal.update_tensors(layers, W, bits, bucket, _PAIRS if bucket else _ONE_PAIR, lr, stream)
+    if st == MQG_OK:
+        return
+    if st is not None:
+        raise MqgError(st, "mqg_aggregate_update_minmax_tensors")
     items, keep = _update_items(layers, W, bits, bucket, 1 if bucket else 2)
     st = _tables.mqg_aggregate_update_minmax_tensors(items, len(layers), W, bits, bucket, lr, _stream_handle(stream))
     del keep
@@ -508,6 +566,12 @@ def mqg_quantize_minmax(grad, bits, bucket, packed_out=None, ranges_out=None, st
         packed_out = torch.empty(mqg_packed_words(grad.numel(), bits), dtype=torch.int32, device=grad.device)
     if ranges_out is None:
         ranges_out = torch.empty(2 * mqg_num_buckets(grad.numel(), bucket), dtype=torch.float32, device=grad.device)
+    _lib or lib()
+    st = _marshal.quantize_minmax(grad, packed_out, ranges_out, bits, bucket, stream) if bucket else None
+    if st == MQG_OK:
+        return packed_out, ranges_out
+    if st is not None:
+        raise MqgError(st, "mqg_quantize_minmax")
     L, (n, gp, pp, rp) = _encoder_args(grad, packed_out, ranges_out, bits, bucket, _PAIRS)
     st = L.mqg_quantize_minmax(gp, n, bits, bucket, pp, rp, _stream_handle(stream))
     if st != MQG_OK:
@@ -516,6 +580,12 @@ def mqg_quantize_minmax(grad, bits, bucket, packed_out=None, ranges_out=None, st
 
 
 def mqg_aggregate_update_minmax(packed, ranges, n, bits, bucket, lr, params, stream=None):
+    _lib or lib()
+    st = _marshal.update(packed, ranges, n, bits, bucket, _PAIRS, lr, params, 0, stream)
+    if st == MQG_OK:
+        return
+    if st is not None:
+        raise MqgError(st, "mqg_aggregate_update_minmax")
     _check(params, torch.float32, "params")
     if params.numel() != n:
         raise ValueError("params must have n elements")
@@ -527,6 +597,13 @@ def mqg_aggregate_update_minmax(packed, ranges, n, bits, bucket, lr, params, str
 
 def mqg_aggregate_requantize_minmax(packed, ranges, n, bits, bucket, packed_out=None, ranges_out=None, stream=None):
     """Server side of the full exchange with the [min, max] encoding. Returns (packed, ranges) of the mean."""
+    _lib or lib()
+    if packed_out is not None and ranges_out is not None:
+        st = _marshal.requantize(packed, ranges, n, bits, bucket, _PAIRS, 0, 0, 0, 0, 0, packed_out, ranges_out, stream)
+        if st == MQG_OK:
+            return packed_out, ranges_out
+        if st is not None:
+            raise MqgError(st, "mqg_aggregate_requantize_minmax")
     W, pa, ra = _worker_arrays(packed, ranges, n, bits, bucket, _PAIRS)
     dev = packed[0].device
     if packed_out is None:
@@ -564,6 +641,12 @@ def mqg_quantize_minmax_tensor(grad, bits, packed_out=None, range_out=None, stre
         packed_out = torch.empty(mqg_packed_words(grad.numel(), bits), dtype=torch.int32, device=grad.device)
     if range_out is None:
         range_out = torch.zeros(2, dtype=torch.float32, device=grad.device)
+    _lib or lib()
+    st = _marshal.quantize_minmax(grad, packed_out, range_out, bits, 0, stream)
+    if st == MQG_OK:
+        return packed_out, range_out
+    if st is not None:
+        raise MqgError(st, "mqg_quantize_minmax_tensor")
     L, (n, gp, pp, rp) = _encoder_args(grad, packed_out, range_out, bits, 0, _ONE_PAIR)
     st = L.mqg_quantize_minmax_tensor(gp, n, bits, pp, rp, _stream_handle(stream))
     if st != MQG_OK:
@@ -572,6 +655,12 @@ def mqg_quantize_minmax_tensor(grad, bits, packed_out=None, range_out=None, stre
 
 
 def mqg_aggregate_update_minmax_tensor(packed, ranges, n, bits, lr, params, stream=None):
+    _lib or lib()
+    st = _marshal.update(packed, ranges, n, bits, 0, _ONE_PAIR, lr, params, 0, stream)
+    if st == MQG_OK:
+        return
+    if st is not None:
+        raise MqgError(st, "mqg_aggregate_update_minmax_tensor")
     _check(params, torch.float32, "params")
     if params.numel() != n:
         raise ValueError("params must have n elements")
@@ -583,6 +672,13 @@ def mqg_aggregate_update_minmax_tensor(packed, ranges, n, bits, lr, params, stre
 
 def mqg_aggregate_requantize_minmax_tensor(packed, ranges, n, bits, packed_out=None, range_out=None, stream=None):
     """Server side of the full exchange with ONE [min, max] range per tensor. Returns (packed, range) of the mean."""
+    _lib or lib()
+    if packed_out is not None and range_out is not None:
+        st = _marshal.requantize(packed, ranges, n, bits, 0, _ONE_PAIR, 0, 0, 0, 0, 0, packed_out, range_out, stream)
+        if st == MQG_OK:
+            return packed_out, range_out
+        if st is not None:
+            raise MqgError(st, "mqg_aggregate_requantize_minmax_tensor")
     W, pa, ra = _worker_arrays(packed, ranges, n, bits, 0, _ONE_PAIR)
     dev = packed[0].device
     if packed_out is None:

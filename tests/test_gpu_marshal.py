@@ -154,3 +154,58 @@ def test_what_the_checks_refuse_is_refused():
     for bits, bucket in ((0, BUCKET), (9, BUCKET), (BITS, 48), (BITS, 0)):
         with pytest.raises((mqgrad.MqgError, ValueError)):
             mqgrad.mqg_quantize_tensors(grads, bits, bucket, 7, outputs=q)
+
+
+def test_calls_from_the_module_are_the_bindings(monkeypatch):
+    """Every entry that the module calls itself, on the default and on another stream, against the binding's own calls."""
+    mqgrad.lib()
+    calls = []
+    for name in ("quantize", "quantize_minmax", "update", "requantize", "dequantize_update", "quantize_tensors", "update_tensors"):
+        def counted(*args, name=name, f=getattr(mqgrad._marshal, name)):
+            st = f(*args)
+            calls.append((name, st))
+            return st
+        monkeypatch.setattr(mqgrad._marshal, name, counted)
+
+    def everything(stream):
+        grads = [workloads.normal(N, 1e-2, w, DEV) for w in range(W)]
+        torch.cuda.synchronize()
+        out = []
+        for bucket in (BUCKET, 0):
+            pairs = lambda: torch.zeros(2 * -(-N // BUCKET) if bucket else 2, device=DEV)
+            words = lambda: torch.zeros(mqgrad.mqg_packed_words(N, BITS), dtype=torch.int32, device=DEV)
+            if bucket:
+                q = [mqgrad.mqg_quantize(g, BITS, BUCKET, -7, 1 << 33, w, 8, words(), torch.zeros(-(-N // BUCKET), device=DEV), stream, mode=w % 2)
+                     for w, g in enumerate(grads)]
+                mean = mqgrad.mqg_aggregate_requantize([x[0] for x in q], [x[1] for x in q], N, BITS, BUCKET, 5, 1, W, 16, words(), torch.zeros_like(q[0][1]), stream)
+                p = [torch.ones(N, device=DEV), torch.ones(N, device=DEV)]
+                mqgrad.mqg_dequantize_update(*mean, N, BITS, BUCKET, 0.1, p[0], stream)
+                mqgrad.mqg_aggregate_update([x[0] for x in q], [x[1] for x in q], N, BITS, BUCKET, 0.1, p[1], stream, mqgrad.MQG_CODES_FROM_MEMORY)
+                out += [t for x in q for t in x] + list(mean) + p
+            encode = (lambda g: mqgrad.mqg_quantize_minmax(g, BITS, bucket, words(), pairs(), stream)) if bucket else \
+                (lambda g: mqgrad.mqg_quantize_minmax_tensor(g, BITS, words(), pairs(), stream))
+            q = [encode(g) for g in grads]
+            pk, rg, p = [x[0] for x in q], [x[1] for x in q], torch.ones(N, device=DEV)
+            if bucket:
+                mean = mqgrad.mqg_aggregate_requantize_minmax(pk, rg, N, BITS, bucket, words(), pairs(), stream)
+                mqgrad.mqg_aggregate_update_minmax(pk, rg, N, BITS, bucket, 0.1, p, stream)
+            else:
+                mean = mqgrad.mqg_aggregate_requantize_minmax_tensor(pk, rg, N, BITS, words(), pairs(), stream)
+                mqgrad.mqg_aggregate_update_minmax_tensor(pk, rg, N, BITS, 0.1, p, stream)
+            many = mqgrad.mqg_quantize_minmax_tensors(grads, BITS, bucket, [(words(), pairs()) for _ in grads], stream)
+            layer = torch.ones(N, device=DEV)
+            mqgrad.mqg_aggregate_update_minmax_tensors([{"params": layer, "packed": pk, "scales": rg}], W, BITS, bucket, 0.1, stream)
+            out += [t for x in q + many for t in x] + list(mean) + [p, layer]
+        torch.cuda.synchronize()
+        return out
+
+    other = torch.cuda.Stream()
+    results = [everything(None), everything(other)]
+    with torch.cuda.stream(other):
+        results.append(everything(None))
+    assert {name for name, _ in calls} == {"quantize", "quantize_minmax", "update", "requantize", "dequantize_update", "quantize_tensors", "update_tensors"}
+    assert all(st == mqgrad.MQG_OK for _, st in calls)
+    monkeypatch.setattr(mqgrad, "_marshal", mqgrad._NoTables)
+    results += [everything(None), everything(other)]
+    for r in results[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(results[0], r))
