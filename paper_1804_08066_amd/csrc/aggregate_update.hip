@@ -264,11 +264,11 @@ __global__ __launch_bounds__(kThreads) void aggregate_mean_kernel(const Aggregat
 
 // Several tensors of a model in one launch: block -> (tensor, tile) through the prefix table of tile
 // counts.  A tensor is either quantized (W packed + W scale pointers) or raw (W fp32 gradients).
-template <bool STRADDLE, bool ONCE>
-__global__ __launch_bounds__(kThreads) void aggregate_update_tensors_kernel(const BatchAggregateArgs a) {
+template <bool STRADDLE, bool ONCE, class Batch>
+__global__ __launch_bounds__(kThreads) void aggregate_update_tensors_kernel(const Batch a) {
     extern __shared__ float s_step[];
     const uint32_t lo = tensor_of_block(a.tile_start, a.count, blockIdx.x);
-    const BatchAggregateArgs::Tensor& t = a.t[lo];
+    const AggregateTensor& t = a.t[lo];
     const uint64_t tile_base = (uint64_t)(blockIdx.x - a.tile_start[lo]) * kLdsTile;
     const void* const* ptrs = a.ptrs + t.first_ptr;
     if (t.raw) {
@@ -342,8 +342,10 @@ hipError_t launch_tensors(const BatchAggregateArgs& a, uint32_t tiles, hipStream
     const dim3 grid(tiles), block(kThreads);
     const size_t lds = sizeof(float) * a.W * kMaxBuckets;
     with_once(decode::codes_read_once(a.bits), [&](auto once) {
-        hipLaunchKernelGGL((aggregate_update_tensors_kernel<STRADDLE, decltype(once)::value>),
-                           grid, block, lds, stream, a);
+        with_few(a, [&](const auto& batch) {
+            hipLaunchKernelGGL((aggregate_update_tensors_kernel<STRADDLE, decltype(once)::value, std::decay_t<decltype(batch)>>),
+                               grid, block, lds, stream, batch);
+        });
     });
     return hipGetLastError();
 }

@@ -107,7 +107,6 @@ mqg_status update_batch_args(const mqg_update_item* items, uint32_t count, uint3
     a.bucket_shift = log2_if_pow2(bucket);
     a.neg_c = -(lr / (float)W);
     a.per_tensor = 0u;
-    for (uint32_t i = 0; i < mqg::kMaxBatchPointers; ++i) a.ptrs[i] = nullptr;
     uint64_t tiles = 0;
     uint32_t used = 0;
     for (uint32_t i = 0; i < mqg::kMaxBatchTensors; ++i) {
@@ -143,6 +142,8 @@ mqg_status update_batch_args(const mqg_update_item* items, uint32_t count, uint3
         if (tiles > 0x7FFFFFFFull) return MQG_EINVAL;
     }
     a.tile_start[mqg::kMaxBatchTensors] = (uint32_t)tiles;
+    for (uint32_t i = used; i < mqg::kMaxBatchPointers; ++i) a.ptrs[i] = nullptr;
+    a.pointers = used;
     *tiles_out = (uint32_t)tiles;
     return MQG_OK;
 }

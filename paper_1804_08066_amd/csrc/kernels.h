@@ -48,41 +48,80 @@ struct RequantArgs {
     uint32_t W;
 };
 
-// Several layer tensors of one model in one launch.
-constexpr uint32_t kMaxBatchTensors = 32;
-constexpr uint32_t kMaxBatchPointers = 256;   // per quantized tensor 2*W pointers, per raw tensor W
+// Several layer tensors of one model in one launch.  A launch's arguments are copied for every launch, at about 0.45 us of
+// the caller's time per KB, so a batch that fits takes the form with room for few (with_few below): the small CNN's two
+// launches carry 1.9 KB instead of 4.8.
+constexpr uint32_t kMaxBatchTensors = 32, kFewTensors = 12;
+constexpr uint32_t kMaxBatchPointers = 256, kFewPointers = 96;   // per quantized tensor 2*W pointers, per raw tensor W
 
-struct BatchAggregateArgs {
-    struct Tensor {
-        uint64_t n;
-        float* params;
-        uint32_t first_ptr;   // index into ptrs: [W packed][W scales], or [W raw gradients]
-        uint32_t raw;         // 1: uncompressed layer
-    };
+struct AggregateTensor {
+    uint64_t n;
+    float* params;
+    uint32_t first_ptr;   // index into ptrs: [W packed][W scales], or [W raw gradients]
+    uint32_t raw;         // 1: uncompressed layer
+};
+struct AggregateBatchHead {
     uint32_t count, W, bits, bucket;
     int bucket_shift;
     float neg_c;
     uint32_t per_tensor;      // [min, max] encoding only: ONE (min, max) pair per worker and tensor
-    uint32_t tile_start[kMaxBatchTensors + 1];   // prefix sums of the tensors' tile counts
-    Tensor t[kMaxBatchTensors];
-    const void* ptrs[kMaxBatchPointers];
+    uint32_t pointers;        // used entries of ptrs
 };
+template <uint32_t TENSORS, uint32_t POINTERS>
+struct AggregateBatch : AggregateBatchHead {
+    using Tensor = AggregateTensor;
+    using Few = AggregateBatch<kFewTensors, kFewPointers>;
+    uint32_t tile_start[TENSORS + 1];   // prefix sums of the tensors' tile counts
+    Tensor t[TENSORS];
+    const void* ptrs[POINTERS];
+    bool few() const { return count <= kFewTensors && pointers <= kFewPointers; }
+    void copy_to(Few& f) const {
+        static_cast<AggregateBatchHead&>(f) = *this;
+        for (uint32_t i = 0; i < kFewTensors; ++i) f.t[i] = t[i];
+        for (uint32_t i = 0; i <= kFewTensors; ++i) f.tile_start[i] = tile_start[i];
+        for (uint32_t i = 0; i < pointers; ++i) f.ptrs[i] = ptrs[i];
+    }
+};
+using BatchAggregateArgs = AggregateBatch<kMaxBatchTensors, kMaxBatchPointers>;
 
-struct BatchQuantizeArgs {
-    struct Tensor {
-        const float* grad;
-        uint64_t n;
-        uint64_t elem_base;
-        uint32_t* packed;
-        float* scales;
-        const float* scales_in;   // nullable: the layer's scales are read, not computed
-    };
+struct QuantizeTensor {
+    const float* grad;
+    uint64_t n;
+    uint64_t elem_base;
+    uint32_t* packed;
+    float* scales;
+    const float* scales_in;   // nullable: the layer's scales are read, not computed
+};
+struct QuantizeBatchHead {
     QuantizeArgs common;      // bits, bucket, stream selection, n = elements of all tensors; the other per-tensor fields are taken from t[]
     uint32_t count;
     uint32_t tile_elems;
-    uint32_t tile_start[kMaxBatchTensors + 1];
-    Tensor t[kMaxBatchTensors];
 };
+template <uint32_t TENSORS>
+struct QuantizeBatch : QuantizeBatchHead {
+    using Tensor = QuantizeTensor;
+    using Few = QuantizeBatch<kFewTensors>;
+    uint32_t tile_start[TENSORS + 1];
+    Tensor t[TENSORS];
+    bool few() const { return count <= kFewTensors; }
+    void copy_to(Few& f) const {
+        static_cast<QuantizeBatchHead&>(f) = *this;
+        for (uint32_t i = 0; i < kFewTensors; ++i) f.t[i] = t[i];
+        for (uint32_t i = 0; i <= kFewTensors; ++i) f.tile_start[i] = tile_start[i];
+    }
+};
+using BatchQuantizeArgs = QuantizeBatch<kMaxBatchTensors>;
+
+// Calls f with the batch, or with its small form where it fits: launch(args) of either type.
+template <class Batch, class F>
+auto with_few(const Batch& a, F f) {
+    if (a.few()) {
+        typename Batch::Few small;
+        a.copy_to(small);
+        return f(small);
+    }
+    return f(a);
+}
 
 uint32_t aggregate_batch_tile();
 hipError_t launch_aggregate_tensors(const BatchAggregateArgs& a, uint32_t tiles, hipStream_t stream);
@@ -124,13 +163,28 @@ bool requantize_centred_cells_supported(const RequantArgs& a);
 hipError_t launch_requantize_centred_cells(const RequantArgs& a, hipStream_t stream);
 hipError_t launch_tensor_range(const float* grad, uint64_t n, float* range_out, hipStream_t stream);
 // the same for several tensors that are encoded next, with their code words as the workgroups' scratch memory
-struct TensorRangeBatch {
-    const float* grad[kMaxBatchTensors];
-    uint64_t n[kMaxBatchTensors];        // 0: no such tensor (or an empty one)
-    float* range[kMaxBatchTensors];      // 2 floats each
-    uint32_t* parts[kMaxBatchTensors];   // the tensor's code words
-    uint32_t block_start[kMaxBatchTensors + 1];   // filled by the launch: prefix sums of the tensors' workgroups
+template <uint32_t TENSORS>
+struct TensorRanges {
+    using Few = TensorRanges<4>;         // one tensor, or the paper's two layers
+    uint32_t count;
+    const float* grad[TENSORS];
+    uint64_t n[TENSORS];                 // 0: no such tensor (or an empty one)
+    float* range[TENSORS];               // 2 floats each
+    uint32_t* parts[TENSORS];            // the tensor's code words
+    uint32_t block_start[TENSORS + 1];   // filled by the launch: prefix sums of the tensors' workgroups
+    bool few() const { return count <= 4u; }
+    void copy_to(Few& f) const {
+        f.count = count;
+        for (uint32_t i = 0; i < 4u; ++i) {
+            f.grad[i] = grad[i];
+            f.n[i] = n[i];
+            f.range[i] = range[i];
+            f.parts[i] = parts[i];
+        }
+        for (uint32_t i = 0; i <= 4u; ++i) f.block_start[i] = block_start[i];
+    }
 };
+using TensorRangeBatch = TensorRanges<kMaxBatchTensors>;
 hipError_t launch_tensor_ranges(TensorRangeBatch& b, uint32_t count, hipStream_t stream);
 hipError_t launch_quantize_minmax_tensor(const QuantizeArgs& a, hipStream_t stream);    // a.scales: the one range; a.bucket unused
 uint32_t quantize_minmax_wave_block_elems(uint32_t bucket);                                       // quantize_wave.hip

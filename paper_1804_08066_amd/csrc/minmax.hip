@@ -276,8 +276,8 @@ __global__ __launch_bounds__(NT) void quantize_minmax_kernel(const QuantizeArgs 
 
 // Several layer tensors in one launch: workgroup -> (tensor, tile of the tensor) through the prefix
 // table of tile counts.
-template <int R, int NT, bool ONE>
-__global__ __launch_bounds__(NT) void quantize_minmax_tensors_kernel(const BatchQuantizeArgs ba, const TileGeometry g) {
+template <int R, int NT, bool ONE, class Batch>
+__global__ __launch_bounds__(NT) void quantize_minmax_tensors_kernel(const Batch ba, const TileGeometry g) {
     drop_every_nan();
     __shared__ Shared<R, NT, ONE> sm;
     const uint32_t lo = tensor_of_block(ba.tile_start, ba.count, blockIdx.x);
@@ -660,11 +660,11 @@ __global__ __launch_bounds__(kThreads) void aggregate_update_minmax_kernel(const
 
 // Several tensors of a model in one launch: block -> (tensor, tile) through the prefix table of tile
 // counts.  A tensor is either encoded (W packed + W range pointers) or raw (W fp32 gradients).
-template <bool STRADDLE, bool ONCE>
-__global__ __launch_bounds__(kThreads) void aggregate_update_minmax_tensors_kernel(const BatchAggregateArgs a) {
+template <bool STRADDLE, bool ONCE, class Batch>
+__global__ __launch_bounds__(kThreads) void aggregate_update_minmax_tensors_kernel(const Batch a) {
     extern __shared__ float2 s_tab[];
     const uint32_t lo = tensor_of_block(a.tile_start, a.count, blockIdx.x);
-    const BatchAggregateArgs::Tensor& bt = a.t[lo];
+    const AggregateTensor& bt = a.t[lo];
     const void* const* ptrs = a.ptrs + bt.first_ptr;
     const TileCommon c = {a.W, a.bits, a.bucket, a.bucket_shift, a.per_tensor, a.neg_c};
     TileTensor t = {nullptr, nullptr, nullptr, bt.n, bt.params};
@@ -731,10 +731,11 @@ __global__ __launch_bounds__(kSumThreads) void tensor_range_kernel(const float* 
 // no priming launch and no atomics (the encode of 8.8 M elements at 4 bits 15.5 us, 23.1 with atomics; the small CNN's two
 // largest layers, 0.9 M elements in all, 4 us for the ranges, 14 with atomics).
 // A tensor of one workgroup gets its range at once.
-__global__ __launch_bounds__(kSumThreads) void tensor_range_parts_kernel(const TensorRangeBatch b, const uint32_t count) {
+template <class Batch>
+__global__ __launch_bounds__(kSumThreads) void tensor_range_parts_kernel(const Batch b) {
     drop_every_nan();
     __shared__ uint32_t s_lo[kSumThreads / 64], s_hi[kSumThreads / 64];
-    const uint32_t k = tensor_of_block(b.block_start, count, blockIdx.x);
+    const uint32_t k = tensor_of_block(b.block_start, b.count, blockIdx.x);
     const uint32_t block = blockIdx.x - b.block_start[k], nblocks = b.block_start[k + 1u] - b.block_start[k];
     uint32_t kl, kh;
     block_range(b.grad[k], b.n[k], block, nblocks, kl, kh, s_lo, s_hi);
@@ -750,7 +751,8 @@ __global__ __launch_bounds__(kSumThreads) void tensor_range_parts_kernel(const T
     }
 }
 constexpr int kFoldPartsThreads = 256;
-__global__ __launch_bounds__(kFoldPartsThreads) void fold_parts_kernel(const TensorRangeBatch b) {
+template <class Batch>
+__global__ __launch_bounds__(kFoldPartsThreads) void fold_parts_kernel(const Batch b) {
     __shared__ uint32_t s_lo[kFoldPartsThreads / 64], s_hi[kFoldPartsThreads / 64];
     const uint32_t k = blockIdx.x;
     const uint32_t parts = b.block_start[k + 1u] - b.block_start[k];
@@ -984,7 +986,9 @@ hipError_t launch_quantize_minmax_tensors(const BatchQuantizeArgs& a, uint32_t t
     const TileGeometry g = tile_geometry(a.common.bucket);
     with_tile_waves(a.common.bucket, tile_waves(a.common.bucket), [&](auto nt, auto one) {
         constexpr int NT = decltype(nt)::value;
-        hipLaunchKernelGGL((quantize_minmax_tensors_kernel<4, NT, decltype(one)::value>), dim3(tiles), dim3(NT), 0, stream, a, g);
+        with_few(a, [&](const auto& batch) {
+            hipLaunchKernelGGL((quantize_minmax_tensors_kernel<4, NT, decltype(one)::value, std::decay_t<decltype(batch)>>), dim3(tiles), dim3(NT), 0, stream, batch, g);
+        });
     });
     return hipGetLastError();
 }
@@ -1005,8 +1009,12 @@ hipError_t launch_tensor_ranges(TensorRangeBatch& b, uint32_t count, hipStream_t
     }
     b.block_start[kMaxBatchTensors] = blocks;
     if (blocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(tensor_range_parts_kernel, dim3(blocks), dim3(kSumThreads), 0, stream, b, count);
-    if (parts) hipLaunchKernelGGL(fold_parts_kernel, dim3(count), dim3(kFoldPartsThreads), 0, stream, b);
+    b.count = count;
+    with_few(b, [&](const auto& batch) {
+        using Batch = std::decay_t<decltype(batch)>;
+        hipLaunchKernelGGL((tensor_range_parts_kernel<Batch>), dim3(blocks), dim3(kSumThreads), 0, stream, batch);
+        if (parts) hipLaunchKernelGGL((fold_parts_kernel<Batch>), dim3(count), dim3(kFoldPartsThreads), 0, stream, batch);
+    });
     return hipGetLastError();
 }
 
@@ -1042,17 +1050,13 @@ uint32_t aggregate_minmax_batch_tile() { return kAggTile; }
 // a.ptrs: per encoded tensor [W packed][W range arrays], per raw tensor [W fp32 gradients]
 hipError_t launch_aggregate_minmax_tensors(const BatchAggregateArgs& a, uint32_t tiles, hipStream_t stream) {
     if (tiles == 0) return hipSuccess;
-    const dim3 grid(tiles), block(kThreads);
     const size_t lds = sizeof(float2) * a.W * kMaxBuckets;
-    const bool straddle = (32u % a.bits) != 0u;
-    const bool once = decode::codes_read_once(a.bits);
-    if (straddle) {
-        if (once) hipLaunchKernelGGL((aggregate_update_minmax_tensors_kernel<true, true>), grid, block, lds, stream, a);
-        else hipLaunchKernelGGL((aggregate_update_minmax_tensors_kernel<true, false>), grid, block, lds, stream, a);
-    } else {
-        if (once) hipLaunchKernelGGL((aggregate_update_minmax_tensors_kernel<false, true>), grid, block, lds, stream, a);
-        else hipLaunchKernelGGL((aggregate_update_minmax_tensors_kernel<false, false>), grid, block, lds, stream, a);
-    }
+    with_codes(a.bits, [&](auto straddle, auto once) {
+        with_few(a, [&](const auto& batch) {
+            hipLaunchKernelGGL((aggregate_update_minmax_tensors_kernel<decltype(straddle)::value, decltype(once)::value, std::decay_t<decltype(batch)>>),
+                               dim3(tiles), dim3(kThreads), lds, stream, batch);
+        });
+    });
     return hipGetLastError();
 }
 

@@ -32,6 +32,8 @@
 #include "encode.h"
 #include "kernels.h"
 
+#include <type_traits>
+
 namespace mqg {
 namespace {
 
@@ -369,8 +371,8 @@ __global__ __launch_bounds__(kThreads) void requantize_pack_kernel(const Requant
 }
 
 // Several layer tensors of one worker in one launch: block -> (tensor, tile) through the prefix table.
-template <int R>
-__global__ __launch_bounds__(kThreads) void quantize_tensors_kernel(const BatchQuantizeArgs ba) {
+template <int R, class Batch>
+__global__ __launch_bounds__(kThreads) void quantize_tensors_kernel(const Batch ba) {
     drop_every_nan();
     __shared__ Shared<R> sm;
     const uint32_t lo = tensor_of_block(ba.tile_start, ba.count, blockIdx.x);
@@ -402,7 +404,9 @@ __global__ __launch_bounds__(kThreads) void quantize_tensors_kernel(const BatchQ
 
 template <int R>
 hipError_t launch_tensors_r(const BatchQuantizeArgs& a, uint32_t tiles, hipStream_t stream) {
-    hipLaunchKernelGGL((quantize_tensors_kernel<R>), dim3(tiles), dim3(kThreads), 0, stream, a);
+    with_few(a, [&](const auto& batch) {
+        hipLaunchKernelGGL((quantize_tensors_kernel<R, std::decay_t<decltype(batch)>>), dim3(tiles), dim3(kThreads), 0, stream, batch);
+    });
     return hipGetLastError();
 }
 

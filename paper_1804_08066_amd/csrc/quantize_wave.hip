@@ -475,8 +475,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1, OCC)
 
 // Several layer tensors of one worker in one launch: workgroup -> (tensor, block of the tensor) through
 // the prefix table of block counts.
-template <int R, int WPB, int NW, int OCC, bool HOIST>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1, OCC))) void quantize_tensors_wave_kernel(const BatchQuantizeArgs ba) {
+template <int R, int WPB, int NW, int OCC, bool HOIST, class Batch>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1, OCC))) void quantize_tensors_wave_kernel(const Batch ba) {
     drop_every_nan();
     __shared__ WaveShared<R, NW> sm;
     const uint32_t lo = tensor_of_block(ba.tile_start, ba.count, blockIdx.x);
@@ -653,8 +653,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1, OCC)
 }
 
 // Several layer tensors of one worker in one launch, as quantize_tensors_wave_kernel maps them.
-template <int NW, int OCC, bool HOIST>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1, OCC))) void quantize_tensors_cells_kernel(const BatchQuantizeArgs ba, const CellGeometry g) {
+template <int NW, int OCC, bool HOIST, class Batch>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1, OCC))) void quantize_tensors_cells_kernel(const Batch ba, const CellGeometry g) {
     drop_every_nan();
     __shared__ WaveShared<8, NW> sm;
     __shared__ CellShared<NW> cs;
@@ -1022,8 +1022,8 @@ __global__ __launch_bounds__(64 * NW) void quantize_minmax_wave_kernel(const Qua
 }
 
 // Several layer tensors in one launch, as quantize_tensors_wave_kernel maps them.
-template <int R, int WPB, int NW>
-__global__ __launch_bounds__(64 * NW) void quantize_minmax_tensors_wave_kernel(const BatchQuantizeArgs ba) {
+template <int R, int WPB, int NW, class Batch>
+__global__ __launch_bounds__(64 * NW) void quantize_minmax_tensors_wave_kernel(const Batch ba) {
     drop_every_nan();
     __shared__ WaveShared<R, NW> sm;
     __shared__ WaveLows<R, NW> lw;
@@ -1121,7 +1121,9 @@ hipError_t launch_quantize_tensors_wave(const BatchQuantizeArgs& a, uint32_t blo
     return with_wave_shape(a.common.bucket, a.common.bits, a.common.n, [&](auto r, auto wpb, auto nw, auto occ, auto hoist) {
         constexpr int R = decltype(r)::value, WPB = decltype(wpb)::value, NW = decltype(nw)::value, OCC = decltype(occ)::value;
         constexpr bool HOIST = decltype(hoist)::value;
-        hipLaunchKernelGGL((quantize_tensors_wave_kernel<R, WPB, NW, OCC, HOIST>), dim3(blocks), dim3(64 * NW), 0, stream, a);
+        with_few(a, [&](const auto& batch) {
+            hipLaunchKernelGGL((quantize_tensors_wave_kernel<R, WPB, NW, OCC, HOIST, std::decay_t<decltype(batch)>>), dim3(blocks), dim3(64 * NW), 0, stream, batch);
+        });
         return hipGetLastError();
     });
 }
@@ -1182,8 +1184,11 @@ static hipError_t launch_cells_nw(const QuantizeArgs& a, const CellGeometry& g, 
 }
 template <int NW>
 static hipError_t launch_tensors_cells_nw(const BatchQuantizeArgs& a, const CellGeometry& g, uint32_t tiles, hipStream_t stream) {
-    if (cells_cap_occupancy(a.common.bits, a.common.bucket)) hipLaunchKernelGGL((quantize_tensors_cells_kernel<NW, 5, false>), dim3(tiles), dim3(64 * NW), 0, stream, a, g);
-    else hipLaunchKernelGGL((quantize_tensors_cells_kernel<NW, 8, false>), dim3(tiles), dim3(64 * NW), 0, stream, a, g);
+    with_few(a, [&](const auto& batch) {
+        using Batch = std::decay_t<decltype(batch)>;
+        if (cells_cap_occupancy(a.common.bits, a.common.bucket)) hipLaunchKernelGGL((quantize_tensors_cells_kernel<NW, 5, false, Batch>), dim3(tiles), dim3(64 * NW), 0, stream, batch, g);
+        else hipLaunchKernelGGL((quantize_tensors_cells_kernel<NW, 8, false, Batch>), dim3(tiles), dim3(64 * NW), 0, stream, batch, g);
+    });
     return hipGetLastError();
 }
 
@@ -1256,7 +1261,9 @@ uint32_t quantize_minmax_wave_block_elems(uint32_t bucket) {
 hipError_t launch_quantize_minmax_tensors_wave(const BatchQuantizeArgs& a, uint32_t blocks, hipStream_t stream) {
     return with_minmax_wave_shape(a.common.bucket, [&](auto r, auto wpb, auto nw) {
         constexpr int R = decltype(r)::value, WPB = decltype(wpb)::value, NW = decltype(nw)::value;
-        hipLaunchKernelGGL((quantize_minmax_tensors_wave_kernel<R, WPB, NW>), dim3(blocks), dim3(64 * NW), 0, stream, a);
+        with_few(a, [&](const auto& batch) {
+            hipLaunchKernelGGL((quantize_minmax_tensors_wave_kernel<R, WPB, NW, std::decay_t<decltype(batch)>>), dim3(blocks), dim3(64 * NW), 0, stream, batch);
+        });
         return hipGetLastError();
     });
 }
