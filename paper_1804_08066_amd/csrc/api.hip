@@ -346,7 +346,7 @@ mqg_status mqg_quantize_tensors_mode(const mqg_quantize_item* items, uint32_t co
     for (uint32_t i = 0; i < mqg::kMaxBatchTensors; ++i) {
         a.tile_start[i] = (uint32_t)tiles;
         mqg::BatchQuantizeArgs::Tensor& t = a.t[i];
-        t = mqg::BatchQuantizeArgs::Tensor{nullptr, 0, 0, nullptr, nullptr, nullptr};
+        t = mqg::BatchQuantizeArgs::Tensor{};
         if (i >= count) continue;
         const mqg_quantize_item& it = items[i];
         if ((it.elem_base & 7u) != 0u) return MQG_EINVAL;
@@ -356,7 +356,7 @@ mqg_status mqg_quantize_tensors_mode(const mqg_quantize_item* items, uint32_t co
         if (misaligned4(it.grad) || misaligned4(it.packed_out) || misaligned4(it.scales_out) || misaligned4(it.scales_in)) {
             return MQG_EALIGN;
         }
-        t = mqg::BatchQuantizeArgs::Tensor{it.grad, it.n, it.elem_base, it.packed_out, it.scales_out, it.scales_in};
+        t = mqg::BatchQuantizeArgs::Tensor{it.grad, it.n, it.elem_base, it.packed_out, it.scales_out, it.scales_in, 0, 0};
         tiles += (it.n + a.tile_elems - 1) / a.tile_elems;
         if (tiles > 0x7FFFFFFFull) return MQG_EINVAL;
     }
@@ -408,7 +408,7 @@ mqg_status mqg_quantize_minmax_tensors(const mqg_quantize_item* items, uint32_t 
     uint64_t tiles = 0;
     for (uint32_t i = 0; i < mqg::kMaxBatchTensors; ++i) {
         a.tile_start[i] = (uint32_t)tiles;
-        a.t[i] = mqg::BatchQuantizeArgs::Tensor{nullptr, 0, 0, nullptr, nullptr, nullptr};
+        a.t[i] = mqg::BatchQuantizeArgs::Tensor{};
         rb.grad[i] = nullptr;
         rb.n[i] = 0;
         rb.range[i] = nullptr;
@@ -421,13 +421,13 @@ mqg_status mqg_quantize_minmax_tensors(const mqg_quantize_item* items, uint32_t 
         if (it.n > (UINT64_MAX >> 4)) return MQG_EINVAL;
         if (misaligned4(it.grad) || misaligned4(it.packed_out) || misaligned8(it.scales_out)) return MQG_EALIGN;
         if (per_tensor) {
-            a.t[i] = mqg::BatchQuantizeArgs::Tensor{it.grad, it.n, 0, it.packed_out, nullptr, it.scales_out};
+            a.t[i] = mqg::BatchQuantizeArgs::Tensor{it.grad, it.n, 0, it.packed_out, nullptr, it.scales_out, 0, 0};
             rb.grad[i] = it.grad;
             rb.n[i] = it.n;
             rb.range[i] = it.scales_out;
             rb.parts[i] = it.packed_out;
         } else {
-            a.t[i] = mqg::BatchQuantizeArgs::Tensor{it.grad, it.n, 0, it.packed_out, it.scales_out, nullptr};
+            a.t[i] = mqg::BatchQuantizeArgs::Tensor{it.grad, it.n, 0, it.packed_out, it.scales_out, nullptr, 0, 0};
         }
         tiles += (it.n + a.tile_elems - 1) / a.tile_elems;
         if (tiles > 0x7FFFFFFFull) return MQG_EINVAL;
@@ -435,7 +435,18 @@ mqg_status mqg_quantize_minmax_tensors(const mqg_quantize_item* items, uint32_t 
     a.tile_start[mqg::kMaxBatchTensors] = (uint32_t)tiles;
     if (tiles == 0) return MQG_OK;
     hipError_t err = hipSuccess;
-    if (per_tensor) err = mqg::launch_tensor_ranges(rb, count, static_cast<hipStream_t>(stream));
+    if (per_tensor) {
+        rb.bits = bits;
+        err = mqg::launch_tensor_ranges(rb, count, static_cast<hipStream_t>(stream));
+        for (uint32_t i = 0; i < count; ++i) {
+            if (rb.in_slots == 0u || rb.slots[i].parts == 0u) continue;
+            a.t[i].scales = items[i].scales_out;   // the range is in the slots: the encoder stores it
+            a.t[i].scales_in = nullptr;
+            a.t[i].parts = rb.slots[i].parts;
+            a.t[i].borrowed = rb.slots[i].borrowed;
+            a.common.parts = 1u;
+        }
+    }
     if (err == hipSuccess) err = mqg::launch_quantize_minmax_tensors(a, (uint32_t)tiles, static_cast<hipStream_t>(stream));
     return err == hipSuccess ? MQG_OK : MQG_ELAUNCH;
 }

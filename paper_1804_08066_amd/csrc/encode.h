@@ -150,6 +150,13 @@ __device__ __forceinline__ float key_value(uint32_t k) {
     const uint32_t u = (k & 0x80000000u) ? (k ^ 0x80000000u) : ~k;
     return __builtin_bit_cast(float, u);
 }
+// keys -> floats; a zero bound is stored as +0
+__device__ __forceinline__ float2 range_of_keys(uint32_t kl, uint32_t kh) {
+    float mn = key_value(kl), mx = key_value(kh);
+    if (mn == 0.0f) mn = 0.0f;
+    if (mx == 0.0f) mx = 0.0f;
+    return make_float2(mn, mx);
+}
 
 // a ^ b ^ c in one instruction: gfx950's three-input bitwise operation with the parity truth table
 // (bit i of 0x96 is the parity of i's three bits).

@@ -23,7 +23,27 @@ struct QuantizeArgs {
     float* scales;           // ceil(n/bucket) floats
     uint32_t drop_nan = 0;       // [min, max] ranges: 1: a NaN takes no part, also where a lane holds nothing else (whole-tensor ranges)
     uint32_t stream_codes = 0;   // 1: the code words are stored with the streaming hint instead of agent scope
+    uint32_t parts = 0;          // whole-tensor [min, max] ranges that travel in slots (RangeSlots below); scales receives the range
+    uint32_t borrowed = 0;
 };
+
+// A whole-tensor range found by `parts` workgroups and used by the workgroups of the next launch, one per tile of kSlotTile
+// elements: every finder leaves its pair of keys at the front of EVERY user's own code words, and a user folds the pairs it
+// finds there before it overwrites them.  No launch in between folds them for all (2 us and 3 us of the caller's time), and
+// no memory is needed but the output's.  parts * tiles pairs are written, so this is for small tensors.
+constexpr uint32_t kSlotTile = 4096;
+struct RangeSlots {
+    uint32_t parts;      // 0: does not fit
+    uint32_t borrowed;   // elements that the last tile takes from the one before it, so that its words hold the pairs too
+};
+inline RangeSlots range_slots(uint64_t n, uint32_t bits, uint64_t parts) {
+    constexpr uint64_t kMostParts = 128;
+    const uint64_t most = 32u * bits < kMostParts ? 32u * bits : kMostParts;   // two tiles' pairs in one tile's words
+    if (parts < 2u || parts > most || n <= kSlotTile) return {0u, 0u};
+    const uint32_t need = ((64u * (uint32_t)parts + bits - 1u) / bits + 31u) / 32u * 32u;   // elements whose words hold them: at most half a tile
+    const uint32_t tail = (uint32_t)((n - 1u) % kSlotTile) + 1u;
+    return {(uint32_t)parts, tail >= need ? 0u : (need - tail + 31u) / 32u * 32u};
+}
 
 struct AggregateArgs {
     const uint32_t* packed[MQG_MAX_WORKERS];
@@ -90,7 +110,8 @@ struct QuantizeTensor {
     uint64_t elem_base;
     uint32_t* packed;
     float* scales;
-    const float* scales_in;   // nullable: the layer's scales are read, not computed
+    const float* scales_in;      // nullable: the layer's scales are read, not computed
+    uint32_t parts, borrowed;    // as in QuantizeArgs
 };
 struct QuantizeBatchHead {
     QuantizeArgs common;      // bits, bucket, stream selection, n = elements of all tensors; the other per-tensor fields are taken from t[]
@@ -166,7 +187,9 @@ hipError_t launch_tensor_range(const float* grad, uint64_t n, float* range_out, 
 template <uint32_t TENSORS>
 struct TensorRanges {
     using Few = TensorRanges<4>;         // one tensor, or the paper's two layers
-    uint32_t count;
+    uint32_t count, bits;
+    uint32_t in_slots;                   // set by the launch: tensors of several workgroups have their keys in slots
+    RangeSlots slots[TENSORS];           // set by the launch
     const float* grad[TENSORS];
     uint64_t n[TENSORS];                 // 0: no such tensor (or an empty one)
     float* range[TENSORS];               // 2 floats each
@@ -175,7 +198,10 @@ struct TensorRanges {
     bool few() const { return count <= 4u; }
     void copy_to(Few& f) const {
         f.count = count;
+        f.bits = bits;
+        f.in_slots = in_slots;
         for (uint32_t i = 0; i < 4u; ++i) {
+            f.slots[i] = slots[i];
             f.grad[i] = grad[i];
             f.n[i] = n[i];
             f.range[i] = range[i];

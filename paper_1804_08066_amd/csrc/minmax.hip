@@ -444,14 +444,6 @@ __device__ __forceinline__ void fold_into(uint32_t* keys, uint32_t kl, uint32_t 
     if (kl < __atomic_load_n(&keys[0], __ATOMIC_RELAXED)) atomicMin(&keys[0], kl);
     if (kh > __atomic_load_n(&keys[1], __ATOMIC_RELAXED)) atomicMax(&keys[1], kh);
 }
-// keys -> floats; a zero bound is stored as +0
-__device__ __forceinline__ float2 range_of_keys(uint32_t kl, uint32_t kh) {
-    float mn = key_value(kl), mx = key_value(kh);
-    if (mn == 0.0f) mn = 0.0f;
-    if (mx == 0.0f) mx = 0.0f;
-    return make_float2(mn, mx);
-}
-
 // Two floats as the place of the keys: one-thread launches prime them, turn them back into floats and, for
 // the mean, divide by W.
 __global__ void range_init_kernel(uint32_t* keys) {
@@ -476,10 +468,11 @@ constexpr uint64_t kMostFoldedTiles = 32768;   // 268 M elements at 8192 per til
 
 template <int NT, bool STRADDLE, bool ONCE>
 __global__ __launch_bounds__(NT) void sum_range_minmax_tensor_kernel(const RequantArgs ra, uint32_t* keys) {
+    static_assert(4u * NT * 4u == kSlotTile, "one workgroup per tile");
     constexpr int R = 4;
     constexpr uint32_t kCap = 4u * NT * R;
     __shared__ float2 s_tab[MQG_MAX_WORKERS];
-    __shared__ uint32_t s_lo[NT / 64], s_hi[NT / 64];
+    __shared__ uint32_t s_lo[NT / 64], s_hi[NT / 64], s_keys[2];
     const uint32_t tid = threadIdx.x;
     const uint64_t tile_base = (uint64_t)blockIdx.x * kCap;
     const uint64_t left = ra.q.n - tile_base;
@@ -498,7 +491,9 @@ __global__ __launch_bounds__(NT) void sum_range_minmax_tensor_kernel(const Requa
     }
     uint32_t kl = order_key(lo), kh = order_key(hi);
     fold_keys<NT>(kl, kh, s_lo, s_hi);
-    if (tid == 0u) {
+    if (ra.q.parts != 0u) {
+        keys_to_slots(ra.q.packed, ra.q.n, ra.q.bits, ra.q.borrowed, blockIdx.x, kl, kh, s_keys);
+    } else if (tid == 0u) {
         if (keys != nullptr) {
             fold_into(keys, kl, kh);
         } else {
@@ -556,8 +551,16 @@ __global__ __launch_bounds__(NT) void requantize_minmax_tensor_kernel(const Requ
     const uint64_t end = blockIdx.x + 1u == gridDim.x ? ra.q.n : second_pass_base(blockIdx.x + 1u, gridDim.x, borrowed, kSumTile);
     const uint32_t tile_count = (uint32_t)(end - tile_base);
     // every lane holds the sum's range before the barrier below; the words are overwritten after it
-    const float* slot = sum_range != nullptr ? sum_range : reinterpret_cast<const float*>(ra.q.packed + (tile_base >> 5) * ra.q.bits);
-    const float2 range = make_float2(slot[0], slot[1]);
+    const uint32_t* own = ra.q.packed + (tile_base >> 5) * ra.q.bits;
+    const float* slot = sum_range != nullptr ? sum_range : reinterpret_cast<const float*>(own);
+    float2 range = make_float2(slot[0], slot[1]);
+    if (ra.q.parts != 0u) {
+        range = range_from_slot(own, ra.q.parts);
+        if (blockIdx.x == 0u && threadIdx.x == 0u) {   // the grid of the mean is the grid of the sum scaled by 1 / W
+            ra.q.scales[0] = range.x / (float)ra.W;
+            ra.q.scales[1] = range.y / (float)ra.W;
+        }
+    }
     clear_shared(sm, tile_count, ra.q.bits);
     float4 x[R];
     decode_sum_tile_tensor<NT, STRADDLE, ONCE>(ra, tile_base, s_tab, x);   // its barrier also covers clear_shared
@@ -734,12 +737,14 @@ __global__ __launch_bounds__(kSumThreads) void tensor_range_kernel(const float* 
 template <class Batch>
 __global__ __launch_bounds__(kSumThreads) void tensor_range_parts_kernel(const Batch b) {
     drop_every_nan();
-    __shared__ uint32_t s_lo[kSumThreads / 64], s_hi[kSumThreads / 64];
+    __shared__ uint32_t s_lo[kSumThreads / 64], s_hi[kSumThreads / 64], s_keys[2];
     const uint32_t k = tensor_of_block(b.block_start, b.count, blockIdx.x);
     const uint32_t block = blockIdx.x - b.block_start[k], nblocks = b.block_start[k + 1u] - b.block_start[k];
     uint32_t kl, kh;
     block_range(b.grad[k], b.n[k], block, nblocks, kl, kh, s_lo, s_hi);
-    if (threadIdx.x == 0u) {
+    if (b.in_slots != 0u && nblocks > 1u) {
+        keys_to_slots(b.parts[k], b.n[k], b.bits, b.slots[k].borrowed, block, kl, kh, s_keys);
+    } else if (threadIdx.x == 0u) {
         if (nblocks == 1u) {
             const float2 r = range_of_keys(kl, kh);
             b.range[k][0] = r.x;
@@ -998,22 +1003,28 @@ hipError_t launch_quantize_minmax_tensors(const BatchQuantizeArgs& a, uint32_t t
 hipError_t launch_tensor_ranges(TensorRangeBatch& b, uint32_t count, hipStream_t stream) {
     constexpr uint64_t kPiece = 16u * kSumThreads;   // elements; 512 words at one bit: two for each workgroup's keys
     uint32_t blocks = 0;
-    bool parts = false;
+    bool parts = false, fit = true;
     for (uint32_t k = 0; k < kMaxBatchTensors; ++k) {
         b.block_start[k] = blocks;
+        b.slots[k] = RangeSlots{0u, 0u};
         if (k >= count || b.n[k] == 0) continue;
         const uint64_t most = b.n[k] / kPiece;
         const uint32_t mine = most < 1u ? 1u : (uint32_t)(most > kSumBlocks ? kSumBlocks : most);
-        parts = parts || mine > 1u;
+        if (mine > 1u) {
+            parts = true;
+            b.slots[k] = range_slots(b.n[k], b.bits, mine);
+            fit = fit && b.slots[k].parts != 0u;
+        }
         blocks += mine;
     }
+    b.in_slots = parts && fit ? 1u : 0u;
     b.block_start[kMaxBatchTensors] = blocks;
     if (blocks == 0) return hipSuccess;
     b.count = count;
     with_few(b, [&](const auto& batch) {
         using Batch = std::decay_t<decltype(batch)>;
         hipLaunchKernelGGL((tensor_range_parts_kernel<Batch>), dim3(blocks), dim3(kSumThreads), 0, stream, batch);
-        if (parts) hipLaunchKernelGGL((fold_parts_kernel<Batch>), dim3(count), dim3(kFoldPartsThreads), 0, stream, batch);
+        if (parts && !fit) hipLaunchKernelGGL((fold_parts_kernel<Batch>), dim3(count), dim3(kFoldPartsThreads), 0, stream, batch);
     });
     return hipGetLastError();
 }
@@ -1038,10 +1049,16 @@ hipError_t launch_quantize_minmax_tensor(const QuantizeArgs& a_in, hipStream_t s
     b.n[0] = a.n;
     b.range[0] = a.scales;
     b.parts[0] = a.packed;
+    b.bits = a.bits;
     const hipError_t e = launch_tensor_ranges(b, 1u, stream);
     if (e != hipSuccess) return e;
-    a.scales_in = a.scales;
-    a.scales = nullptr;          // not written when the range is given
+    if (b.in_slots != 0u) {
+        a.parts = b.slots[0].parts;
+        a.borrowed = b.slots[0].borrowed;
+    } else {
+        a.scales_in = a.scales;
+        a.scales = nullptr;      // not written when the range is given
+    }
     return launch_quantize_minmax(a, stream);
 }
 
@@ -1094,35 +1111,41 @@ hipError_t launch_requantize_minmax_tensor(const RequantArgs& ra_in, hipStream_t
         atomics = atomics || (in < out + 4u * words && out < in + 4u * words);
     }
     const uint64_t tail = ra_in.q.n % tile;
-    const uint32_t borrowed = !atomics && tail != 0 && tail * ra_in.q.bits <= 32u ? 64u : 0u;   // 64 elements are two words at one bit
-    uint32_t* keys = atomics ? reinterpret_cast<uint32_t*>(ra_in.q.scales) : nullptr;
-    const float* sum_range = atomics ? ra_in.q.scales : nullptr;
+    // small tensors: every workgroup of the second pass folds the keys itself
+    RequantArgs ra = ra_in;
+    const RangeSlots slots = cells || atomics ? RangeSlots{0u, 0u} : range_slots(ra.q.n, ra.q.bits, tiles);
+    ra.q.parts = slots.parts;
+    ra.q.borrowed = slots.borrowed;
+    const uint32_t borrowed = slots.parts != 0u ? slots.borrowed
+                              : !atomics && tail != 0 && tail * ra.q.bits <= 32u ? 64u : 0u;   // 64 elements are two words at one bit
+    uint32_t* keys = atomics ? reinterpret_cast<uint32_t*>(ra.q.scales) : nullptr;
+    const float* sum_range = atomics ? ra.q.scales : nullptr;
     const dim3 grid((uint32_t)tiles), block(NT);
     if (atomics) hipLaunchKernelGGL(range_init_kernel, dim3(1), dim3(1), 0, stream, keys);
     if (cells) {
-        launch_sum_range_cells(ra_in, (uint32_t)tiles, tile, keys, stream);
+        launch_sum_range_cells(ra, (uint32_t)tiles, tile, keys, stream);
     } else {
-        with_codes(ra_in.q.bits, [&](auto straddle, auto once) {
-            hipLaunchKernelGGL((sum_range_minmax_tensor_kernel<NT, decltype(straddle)::value, decltype(once)::value>), grid, block, 0, stream, ra_in, keys);
+        with_codes(ra.q.bits, [&](auto straddle, auto once) {
+            hipLaunchKernelGGL((sum_range_minmax_tensor_kernel<NT, decltype(straddle)::value, decltype(once)::value>), grid, block, 0, stream, ra, keys);
         });
     }
     if (atomics) {
         hipLaunchKernelGGL(range_finish_kernel, dim3(1), dim3(1), 0, stream, keys);
-    } else {
-        hipLaunchKernelGGL(fold_sum_range_kernel, dim3(1), dim3(kFoldThreads), 0, stream, ra_in.q.packed, (uint32_t)tiles, tile,
-                           borrowed, ra_in.q.bits, ra_in.q.scales, (float)ra_in.W);
+    } else if (ra.q.parts == 0u) {
+        hipLaunchKernelGGL(fold_sum_range_kernel, dim3(1), dim3(kFoldThreads), 0, stream, ra.q.packed, (uint32_t)tiles, tile,
+                           borrowed, ra.q.bits, ra.q.scales, (float)ra.W);
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (cells) {
-        launch_requantize_tensor_cells(ra_in, (uint32_t)tiles, tile, sum_range, borrowed, stream);
+        launch_requantize_tensor_cells(ra, (uint32_t)tiles, tile, sum_range, borrowed, stream);
     } else {
-        with_codes(ra_in.q.bits, [&](auto straddle, auto once) {
-            hipLaunchKernelGGL((requantize_minmax_tensor_kernel<NT, decltype(straddle)::value, decltype(once)::value>), grid, block, 0, stream, ra_in,
+        with_codes(ra.q.bits, [&](auto straddle, auto once) {
+            hipLaunchKernelGGL((requantize_minmax_tensor_kernel<NT, decltype(straddle)::value, decltype(once)::value>), grid, block, 0, stream, ra,
                                sum_range, borrowed);
         });
     }
-    if (atomics) hipLaunchKernelGGL(range_divide_kernel, dim3(1), dim3(1), 0, stream, ra_in.q.scales, (float)ra_in.W);
+    if (atomics) hipLaunchKernelGGL(range_divide_kernel, dim3(1), dim3(1), 0, stream, ra.q.scales, (float)ra.W);
     return hipGetLastError();
 }
 

@@ -907,11 +907,12 @@ template <int R, int WPB, int NW, bool FULL>
 __device__ __forceinline__ void encode_minmax_and_pack(const QuantizeArgs& a, uint64_t cb, uint32_t count, uint32_t lane,
                                                        uint32_t wave, const uint32_t (&slot)[R], uint32_t nbc,
                                                        uint64_t kb_first, const float4 (&x)[R], WaveShared<R, NW>& sm,
-                                                       WaveLows<R, NW>& lw) {
+                                                       WaveLows<R, NW>& lw, const bool known, const float2 range) {
+    // known: `range` holds for every element; else a.scales_in gives one that does, or each bucket has its own
     const uint32_t b = a.bits;
     const uint32_t shift = (uint32_t)a.bucket_shift;
     const float Lf = (float)((1u << b) - 1u);
-    const bool given = a.scales_in != nullptr;
+    const bool given = known || a.scales_in != nullptr;
 
     wave_lds_fence();   // the keys other lanes of this wave published are read below
     if (WPB > 1 && !given && lane == 0u) {
@@ -930,7 +931,10 @@ __device__ __forceinline__ void encode_minmax_and_pack(const QuantizeArgs& a, ui
         const bool exists = WPB > 1 ? true : ((lane << shift) < count);   // bucket starts inside the vector
         float mn = 0.0f, mx = 0.0f;
         if (exists) {
-            if (given) {
+            if (known) {
+                mn = range.x;
+                mx = range.y;
+            } else if (given) {
                 mn = a.scales_in[0];
                 mx = a.scales_in[1];
             } else {
@@ -982,13 +986,26 @@ __device__ __forceinline__ void encode_minmax_and_pack(const QuantizeArgs& a, ui
     store_chunk_words<R, NW, FULL>(out, count, b, lane, wave, sm, a.stream_codes != 0u);
 }
 
-template <int R, int WPB, int NW>
+// SLOTS: the tensor's range may have to be folded from the keys in the workgroup's own code words (a.parts of them).
+template <int R, int WPB, int NW, bool SLOTS>
 __device__ __forceinline__ void quantize_minmax_wave_block(const QuantizeArgs& a, const uint32_t block, WaveShared<R, NW>& sm,
                                                            WaveLows<R, NW>& lw) {
-    const ChunkShape<R> c = chunk_shape<R, WPB, NW>(a, block);
+    static_assert(!SLOTS || (WPB == 1 && 256 * R * NW == kSlotTile), "a workgroup's tile is the slots'");
+    ChunkShape<R> c = chunk_shape<R, WPB, NW>(a, block);
     const uint32_t lane = c.lane, wave = c.wave;
     uint32_t slot[R];
     chunk_slots<R, WPB>(a, lane, slot);
+    const bool in_slot = SLOTS && a.parts != 0u;
+    uint64_t tile_base = 0;
+    if (in_slot) {   // the last tile borrows from the one before it
+        const uint32_t tiles = (uint32_t)((a.n + kSlotTile - 1u) / kSlotTile);
+        const uint64_t end = slot_tile_end(block, tiles, a.borrowed, a.n);
+        tile_base = slot_tile_base(block, tiles, a.borrowed);
+        c.cb = tile_base + 256u * R * wave;
+        c.active = c.cb < end;
+        c.count = !c.active ? 0u : (end - c.cb < 256u * R ? (uint32_t)(end - c.cb) : 256u * R);
+        c.full = c.count == 256u * R;
+    }
 
     float4 x[R];
     if (c.full) {
@@ -997,32 +1014,39 @@ __device__ __forceinline__ void quantize_minmax_wave_block(const QuantizeArgs& a
         load_chunk<R, false>(a.grad + c.cb, c.count, lane, x);
     }
     clear_words<R, NW>(lane, wave, sm);   // while the loads are in flight
-    if (a.scales_in == nullptr) {
+    float2 range = make_float2(0.0f, 0.0f);
+    if (in_slot) {
+        range = range_from_slot(a.packed + (tile_base >> 5) * a.bits, a.parts);
+        if (block == 0u && threadIdx.x == 0u) {
+            a.scales[0] = range.x;
+            a.scales[1] = range.y;
+        }
+    } else if (a.scales_in == nullptr) {
         if (c.full) {
             reduce_minmax<R, WPB, NW, true>(x, c.count, lane, wave, slot, c.seg_lanes, c.rpb, sm, lw, a.drop_nan != 0u);
         } else {
             reduce_minmax<R, WPB, NW, false>(x, c.count, lane, wave, slot, c.seg_lanes, c.rpb, sm, lw, a.drop_nan != 0u);
         }
     }
-    if (WPB > 1) __syncthreads();   // every wave of the group arrives here exactly once
+    if (WPB > 1 || SLOTS) __syncthreads();   // every wave of the group arrives here exactly once
     if (!c.active) return;
     if (c.full) {
-        encode_minmax_and_pack<R, WPB, NW, true>(a, c.cb, c.count, lane, wave, slot, c.nbc, c.kb_first, x, sm, lw);
+        encode_minmax_and_pack<R, WPB, NW, true>(a, c.cb, c.count, lane, wave, slot, c.nbc, c.kb_first, x, sm, lw, in_slot, range);
     } else {
-        encode_minmax_and_pack<R, WPB, NW, false>(a, c.cb, c.count, lane, wave, slot, c.nbc, c.kb_first, x, sm, lw);
+        encode_minmax_and_pack<R, WPB, NW, false>(a, c.cb, c.count, lane, wave, slot, c.nbc, c.kb_first, x, sm, lw, in_slot, range);
     }
 }
 
-template <int R, int WPB, int NW>
+template <int R, int WPB, int NW, bool SLOTS = false>
 __global__ __launch_bounds__(64 * NW) void quantize_minmax_wave_kernel(const QuantizeArgs a) {
     drop_every_nan();
     __shared__ WaveShared<R, NW> sm;
     __shared__ WaveLows<R, NW> lw;
-    quantize_minmax_wave_block<R, WPB, NW>(a, blockIdx.x, sm, lw);
+    quantize_minmax_wave_block<R, WPB, NW, SLOTS>(a, blockIdx.x, sm, lw);
 }
 
 // Several layer tensors in one launch, as quantize_tensors_wave_kernel maps them.
-template <int R, int WPB, int NW, class Batch>
+template <int R, int WPB, int NW, class Batch, bool SLOTS = false>
 __global__ __launch_bounds__(64 * NW) void quantize_minmax_tensors_wave_kernel(const Batch ba) {
     drop_every_nan();
     __shared__ WaveShared<R, NW> sm;
@@ -1034,7 +1058,9 @@ __global__ __launch_bounds__(64 * NW) void quantize_minmax_tensors_wave_kernel(c
     a.packed = ba.t[lo].packed;
     a.scales = ba.t[lo].scales;
     a.scales_in = ba.t[lo].scales_in;
-    quantize_minmax_wave_block<R, WPB, NW>(a, blockIdx.x - ba.tile_start[lo], sm, lw);
+    a.parts = ba.t[lo].parts;
+    a.borrowed = ba.t[lo].borrowed;
+    quantize_minmax_wave_block<R, WPB, NW, SLOTS>(a, blockIdx.x - ba.tile_start[lo], sm, lw);
 }
 
 // The measured choice of (R, WPB, NW) per bucket size (100 M elements, every width): buckets up to 1024
@@ -1248,6 +1274,10 @@ auto with_minmax_wave_shape(uint32_t bucket, F f) {
 }
 
 hipError_t launch_quantize_minmax_wave(const QuantizeArgs& a, hipStream_t stream) {
+    if (a.parts != 0u) {   // a whole tensor whose range is in slots
+        hipLaunchKernelGGL((quantize_minmax_wave_kernel<4, 1, 4, true>), dim3((uint32_t)((a.n + kSlotTile - 1u) / kSlotTile)), dim3(256), 0, stream, a);
+        return hipGetLastError();
+    }
     return with_minmax_wave_shape(a.bucket, [&](auto r, auto wpb, auto nw) {
         return launch_minmax_wave<decltype(r)::value, decltype(wpb)::value, decltype(nw)::value>(a, stream);
     });
@@ -1259,6 +1289,12 @@ uint32_t quantize_minmax_wave_block_elems(uint32_t bucket) {
 }
 
 hipError_t launch_quantize_minmax_tensors_wave(const BatchQuantizeArgs& a, uint32_t blocks, hipStream_t stream) {
+    if (a.common.parts != 0u) {   // whole tensors, the ranges of some of them in slots
+        with_few(a, [&](const auto& batch) {
+            hipLaunchKernelGGL((quantize_minmax_tensors_wave_kernel<4, 1, 4, std::decay_t<decltype(batch)>, true>), dim3(blocks), dim3(256), 0, stream, batch);
+        });
+        return hipGetLastError();
+    }
     return with_minmax_wave_shape(a.common.bucket, [&](auto r, auto wpb, auto nw) {
         constexpr int R = decltype(r)::value, WPB = decltype(wpb)::value, NW = decltype(nw)::value;
         with_few(a, [&](const auto& batch) {

@@ -159,3 +159,47 @@ def test_infinities_and_zeros_of_both_signs_in_a_bucket(bucket):
                 assert np.array_equal(code[k * bucket:(k + 1) * bucket], codes(torch.from_numpy(ref.quantize_minmax(part, bits, bucket)[0].view(np.int32)), bucket, bits))
         assert not np.signbit(rg[4, 0])
         assert not code[4 * bucket:5 * bucket:3].any() and not code[4 * bucket + 1:5 * bucket:3].any()
+
+
+def most_parts(bits):
+    return min(32 * bits, 128)          # pairs of keys that two tiles' words hold
+
+
+@pytest.mark.parametrize("bits", range(1, 9))
+@pytest.mark.parametrize("tail", [1, 33, 64 * 4 + 1, TILE // 2, TILE - 1, TILE])
+def test_ranges_that_travel_in_the_output(bits, tail):
+    """Small tensors, where every workgroup of the encoder and of the server's second pass folds the range itself: the most
+    workgroups that may find it, one more, and two, with every kind of last tile."""
+    W = 2
+    for find, per in ((8192, "encoder"), (TILE, "server")):
+        for parts in (2, most_parts(bits), most_parts(bits) + 1):
+            n = (parts - 1) * TILE + tail if per == "server" else parts * 8192 - 8192 % TILE + tail % 8192
+            if n <= 16384:
+                continue
+            grads = [workloads.laplace(n + 1, 1e-3, 7 * w + bits, DEV)[1:] + 1e-4 * w for w in range(W)]
+            grads[0][n - 1], grads[1][0], grads[1][n // 2] = 0.5, -0.75, 0.25
+            q = encode(grads, bits)
+            want_pk, want_rg = ref.aggregate_requantize_minmax([to_u32(x[0]) for x in q], [x[1].cpu().numpy() for x in q], n, bits, n)
+            pk, rg = mqgrad.mqg_aggregate_requantize_minmax_tensor([x[0] for x in q], [x[1] for x in q], n, bits)
+            torch.cuda.synchronize()
+            assert rg.cpu().numpy().tobytes() == want_rg.tobytes()
+            assert np.array_equal(to_u32(pk), want_pk)
+
+
+@pytest.mark.parametrize("bits", [1, 3, 4])
+@pytest.mark.parametrize("sizes", [(20000, 17, 100_000, 8191), (0, 16384, 40_961, 5), (33_000, 2_000_000, 70_001), tuple(16385 + 77 * i for i in range(14))])
+def test_ranges_of_several_layers(sizes, bits):
+    """All layers' ranges in the output, some layers of one workgroup, one layer too large (none in the output), more layers
+    than the small form of the arguments takes."""
+    grads = [workloads.laplace(n, 1e-3, i + bits, DEV) + 1e-4 * i for i, n in enumerate(sizes)]
+    for g in grads:
+        if g.numel() > 3:
+            g[-1], g[g.numel() // 2] = 0.5, -0.25
+    out = mqgrad.mqg_quantize_minmax_tensors(grads, bits, 0)
+    torch.cuda.synchronize()
+    for g, (pk, rg) in zip(grads, out):
+        if g.numel() == 0:
+            continue
+        want_pk, want_rg = ref.quantize_minmax(g.cpu().numpy(), bits, g.numel())
+        assert rg.cpu().numpy().tobytes() == want_rg.tobytes(), g.numel()
+        assert np.array_equal(to_u32(pk), want_pk), g.numel()
