@@ -291,3 +291,17 @@ def test_per_tensor_encoding_of_an_unaligned_view():
     torch.cuda.synchronize()
     want_pk, want_rg = ref.quantize_minmax(g.cpu().numpy(), 6, g.numel())
     assert np.array_equal(rg.cpu().numpy(), want_rg) and np.array_equal(to_u32(pk), want_pk)
+
+
+@pytest.mark.parametrize("sizes", [(0, 1, 3, 8191), (8192, 4 * 8192 - 1, 4 * 8192), (5 * 8192, 17, 512 * 8192 + 5), (100_003,)])
+def test_norms_with_fewer_workgroups(sizes):
+    """Tensors that fill few of the workgroups whose partial sums are added, beside ones that fill more: each result is the
+    one of a call of its own, and a workspace full of NaN leaves no trace."""
+    grads = [workloads.normal(max(n, 1), 1e-2, 3 + i, DEV)[:n] for i, n in enumerate(sizes)]
+    ws = torch.full((mqgrad.mqg_sum_squares_workspace_bytes(len(grads)) // 8,), float("nan"), dtype=torch.float64, device=DEV)
+    out = mqgrad.mqg_sum_squares_batch(grads, workspace=ws)
+    alone = [mqgrad.mqg_sum_squares_batch([g]) for g in grads]
+    torch.cuda.synchronize()
+    for g, t, a in zip(grads, out.tolist(), alone):
+        want = float((g.double() ** 2).sum())
+        assert t == a.item() and abs(t - want) <= 1e-14 * want      # some hundred fp64 additions in another order
