@@ -293,15 +293,13 @@ __global__ __launch_bounds__(NT) void quantize_minmax_tensors_kernel(const Batch
 // sum over the W workers' de-quantized gradients, decoded from their streams in worker order; the
 // stored range is divided by W.  (step, min) of every worker's buckets of the tile sit in an LDS table.
 //
-// Bound by latency: that of the code words, hidden by other waves in long launches and by more words in flight in short
-// ones.  CH: workers whose words are in flight together; left alone the compiler takes 112-117 registers for eight
-// and their table entries (four waves per SIMD), with four seven waves fit (MANY and 256 lanes: six, since seven spill).
+// This kernel takes the short launches and the smallest buckets (requantize_minmax_cells_supported).  Bound by latency, that
+// of the code words, hidden by more words in flight in short launches and by other waves in long ones.  CH: workers whose
+// words are in flight together; left alone the compiler takes 112-117 registers for eight and their table entries (four
+// waves per SIMD), with four seven waves fit (MANY and 256 lanes: six, since seven spill).
 // us at 4 bits, eight in flight / four:                 (256 lanes, seven waves with 8-16 bytes of scratch memory)
 //   bucket 1024, 24 workers, 1 M elements     9.0 /  9.4   (11.1)
 //   bucket 4096, 16 workers, 1 M              7.2 /  7.4   ( 8.4)
-//   bucket 1024,  8 workers, 30 M            42.0 / 39.5   (39.9)
-//   bucket 2304,  4 workers, 30 M            63.5 / 35.6
-//   bucket 12320, 8 workers, 30 M            74.1 / 49.2
 // MANY: more than CH workers.  Without the loop over them 58 registers do (eight waves).
 constexpr int requant_waves(int NT, bool one, int CH, bool many) {
     if (NT == 768) return 6;                     // two workgroups per compute unit
@@ -966,10 +964,10 @@ hipError_t launch_requantize_minmax(const RequantArgs& ra, hipStream_t stream) {
     with_tile_waves(ra.q.bucket, waves, [&](auto nt, auto one) {
         constexpr int NT = decltype(nt)::value;
         constexpr bool ONE = decltype(one)::value;
-        // Short: at most one workgroup per compute unit, or two of four waves.  Eight in flight / four at 4 bits, 8 workers
-        // (seven waves): bucket 1024 at 1, 2, 3, 5 M elements 0.90, 0.89, 0.95, 1.02 of the time; 2304 at 1, 2, 3 M 0.93,
-        // 0.98, 1.24; 8192 0.95, 0.94, 1.03; 12320 (1024 lanes) 1.00, 1.02, 1.02.
-        const bool short_launch = NT <= 512 && tiles <= (NT == 256 ? 2u : 1u) * kComputeUnits;
+        // Eight in flight up to two workgroups of four waves per compute unit (the time with eight / with four at 4 bits, 8
+        // workers, bucket 1024: 0.90, 0.89, 0.95, 1.02 at 1, 2, 3, 5 M elements).  More of them come with buckets below 128
+        // only; the larger shapes but those above 512 lanes (12320 at 1 M: 1.00) have at most one workgroup per compute unit.
+        const bool many_tiles = NT == 256 && tiles > 2u * kComputeUnits;
         with_codes(ra.q.bits, [&](auto straddle, auto once) {
             const auto launch = [&](auto ch, auto many) {
                 hipLaunchKernelGGL((requantize_minmax_kernel<NT, ONE, decltype(straddle)::value, decltype(once)::value, decltype(ch)::value, decltype(many)::value>),
@@ -977,11 +975,11 @@ hipError_t launch_requantize_minmax(const RequantArgs& ra, hipStream_t stream) {
             };
             using four = std::integral_constant<int, 4>;
             using eight = std::integral_constant<int, 8>;
+            if (ra.W <= 4u) return launch(four{}, std::bool_constant<ONE>{});
             if constexpr (NT <= 512) {
-                if (ra.W > 4u && short_launch) return launch(eight{}, std::true_type{});
+                if (!many_tiles) return launch(eight{}, std::true_type{});
             }
-            if (ra.W <= 4u) launch(four{}, std::bool_constant<ONE>{});
-            else launch(four{}, std::true_type{});
+            if constexpr (NT == 256 || NT > 512) launch(four{}, std::true_type{});
         });
     });
     return hipGetLastError();

@@ -1,7 +1,8 @@
 // Quantize(g, K) of Algorithm 1 on gfx950, workgroup-cooperative variant: the range-linear K-bit
 // encode of the Section 3.2 footnote in ONE pass over its input.  This kernel takes every bucket
 // size (any multiple of 32) and both scale modes; power-of-two buckets go to the wave-local kernel in
-// quantize_wave.hip instead.
+// quantize_wave.hip instead.  The re-encoding of a sum goes to requantize_cells.hip wherever that is faster: here it
+// keeps the L2 scale, streams of less than one cell, and bucket 32 with many workers in short launches.
 //
 //   a1  per-bucket range  s = max |g|            (DPP max over 8-lane cells, LDS max per bucket)
 //   a2  position on the 2^K-level grid           u = clamp(fma(g, (L/2)/s, L/2), 0, L)

@@ -679,6 +679,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1, OCC)
 // RPB: rows of the chunk per bucket (bucket = 256 * RPB when WPB == 1; R when the chunk is part of one
 // bucket), a compile-time number so that rows of one bucket share one division and one v_readlane per
 // worker.  RPB = 0 stands for bucket 128: a row is two buckets, lanes 0-31 and 32-63 select their step.
+// This kernel keeps the L2 scale, launches of up to 2^20 elements, and 1 and 2 bits with more than four workers; the others
+// are faster with a lane per cell (requantize_centred_cells_supported).
 // LUT = 1 .. 4: the decode takes (float)(2c - L) from a table in LDS (decode::accumulate_quad_lut; the
 // workgroup fills it first, one barrier) -- half the vector operations of the arithmetic decode per
 // code, and this step is bound by their issue.
@@ -816,8 +818,8 @@ hipError_t launch_requant_wave(const RequantArgs& ra, hipStream_t stream) {
     const uint64_t groups = (ra.q.n + per_group - 1) / per_group;
     if (groups > 0x7FFFFFFFull) return hipErrorInvalidValue;
     const dim3 grid((uint32_t)groups), block(64 * NW);
-    // 1 .. 4 bits: multipliers from a table in LDS (bucket 1024, 8 workers, 100 M elements: 120 / 138 / 151 /
-    // 141 us with the arithmetic decode, 100 / 98 / 122 / 122 us with the table)
+    // 1 .. 4 bits: multipliers from a table in LDS (bucket 1024, 8 workers, 100 M elements, 1 and 2 bits: 120 / 138 us with
+    // the arithmetic decode, 100 / 98 us with the table; 3 and 4 bits in short launches and with the L2 scale 151 / 141, 122 / 122)
     if (ra.q.bits == 1u) {
         hipLaunchKernelGGL((requantize_wave_kernel<R, WPB, NW, RPB, false, false, 0, 1>), grid, block, 0, stream, ra);
     } else if (ra.q.bits == 2u) {
@@ -1305,7 +1307,7 @@ hipError_t launch_quantize_minmax_tensors_wave(const BatchQuantizeArgs& a, uint3
 }
 
 // The re-quantizing server step takes the wave-local kernel for power-of-two buckets of 128 elements
-// and more.
+// and more, where requantize_centred_cells_supported() does not take it first.
 bool requantize_wave_supported(const RequantArgs& ra) { return ra.q.bucket_shift >= 7; }
 
 hipError_t launch_requantize_wave(const RequantArgs& ra, hipStream_t stream) {
