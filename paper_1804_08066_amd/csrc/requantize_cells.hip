@@ -634,7 +634,11 @@ struct CentredCode {
                 place<B>(o, 8 * q + 4 * u, pack_quad_hi(t[0], t[1], t[2], t[3], B, 2 * B, 3 * B), 4);
             }
         }
-        store_parts<B, WHOLE, true>(a.packed, at, o);   // 1 % of the exchange of 25.6 M elements, 8 workers, 4 bits: the worker's update reads them next
+        // Written through and kept in L2, where the worker's update reads them next (1 % of the exchange of 25.6 M elements, 8
+        // workers, 4 bits); but streaming where a lane's 20 to 28 bytes leave in two or three pieces, each of which would go
+        // to memory as a part of a line: us at 25.6 M, 8 workers, bucket 1024, written through / streaming, 5 bits 34.3 / 32.1,
+        // 6 bits 38.7 / 34.1, 7 bits 47.6 / 36.6 (3 bits 31.7 / 31.0, and the update 39.0 / 39.5; 8 bits at 100 M 139.9 / 154.4).
+        store_parts<B, WHOLE, (B <= 4 || B == 8)>(a.packed, at, o);
     }
 };
 
