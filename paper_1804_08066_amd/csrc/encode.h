@@ -28,16 +28,16 @@ typedef v4u v4u_a4 __attribute__((aligned(4)));
 // 128-bit store with agent scope (the sc1 cache-policy bit): the data is written through to memory at
 // once and the line stays valid in L2.  HIP has no builtin for a scoped 128-bit store.  `base` must be
 // wave-uniform (it travels in scalar registers), `byte_off` is the lane's offset from it; the forms without an offset
-// take the lane's own address.  A store of more than 64 bits still reads its data in the cycle after it issues: a vector
-// operation that writes one of those registers must not come right behind it.  The compiler keeps that distance for the
-// stores it knows; here the s_nop does.
+// take the lane's own address.  A store of more than 64 bits still reads its data after it has issued: on gfx940 and gfx950
+// two wait states must lie between it and a vector operation that writes one of those registers (one on gfx90a).  The
+// compiler keeps that distance for the stores it knows; here s_nop 1, two wait states, does.
 // (One dword with the same scope: for the odd words beside such stores -- ordinary stores into cache
 // lines that also receive agent-scope stores are very slow.)
 __device__ __forceinline__ void store_u32_agent(const void* base, uint32_t byte_off, uint32_t w) {
     asm volatile("global_store_dword %0, %1, %2 sc1" ::"v"(byte_off), "v"(w), "s"(base) : "memory");
 }
 __device__ __forceinline__ void store_v4u_agent(const void* base, uint32_t byte_off, v4u w) {
-    asm volatile("global_store_dwordx4 %0, %1, %2 sc1\n\ts_nop 0" ::"v"(byte_off), "v"(w), "s"(base) : "memory");
+    asm volatile("global_store_dwordx4 %0, %1, %2 sc1\n\ts_nop 1" ::"v"(byte_off), "v"(w), "s"(base) : "memory");
 }
 __device__ __forceinline__ void store_u32_agent(void* p, uint32_t w) {
     asm volatile("global_store_dword %0, %1, off sc1" ::"v"(p), "v"(w) : "memory");
@@ -46,7 +46,7 @@ __device__ __forceinline__ void store_v2u_agent(void* p, v2u w) {
     asm volatile("global_store_dwordx2 %0, %1, off sc1" ::"v"(p), "v"(w) : "memory");
 }
 __device__ __forceinline__ void store_v4u_agent(void* p, v4u w) {
-    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(p), "v"(w) : "memory");
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(w) : "memory");
 }
 
 // DPP reads of a switched-off lane return 0: call these with every lane of the wave active.
