@@ -25,9 +25,7 @@ constexpr uint32_t kCell = 32;          // elements
 
 // How much there is to do.  kShort: the launch does not fill the chip several times over, and what counts is a wave's own
 // chain and how many compute units have a wave: small tiles, many words in flight.  kStream: the streams together exceed
-// the last-level cache, and streaming loads are faster where a wave's loads leave no gaps (4, 6 and 8 bits).  us, ordinary /
-// streaming loads: 8 bits, 16 workers, 30 M elements, [min, max] 95.6 / 87.8; 6 bits, 16 workers, 60 M 144 / 136; 5 bits 121 / 129;
-// 7 bits 165 / 179; with the streams in the cache (8 workers, 25.6 M, 4 bits) 25.5 / 27.5.
+// the last-level cache by so much that streaming loads are faster (size_of).
 enum class Size { kShort, kLong, kStream };
 
 typedef float v2f __attribute__((ext_vector_type(2)));
@@ -711,11 +709,25 @@ void with_bits(uint32_t bits, F f) {
     }
 }
 
+constexpr uint64_t kLastLevelCache = 256ull << 20;
+uint64_t stream_bytes(const RequantArgs& ra) { return (ra.q.n >> 3) * ra.q.bits * ra.W; }
+bool past_cache(const RequantArgs& ra) { return stream_bytes(ra) > kLastLevelCache / 4u * 5u; }
+// Where streaming loads begin: with the cache's size at 4, 6 and 8 bits, whose loads leave no gaps; later at 7 and 5 bits, where a
+// wave's next load asks for the same cache lines again.  us of the max-abs step, ordinary / streaming loads, inside the exchange (the
+// workers' quantizers just before it) and in a loop of its own; bucket 1024, * 2304:
+//   bits, workers, elements, MB        exchange        alone       |  bits, workers, elements, MB      exchange        alone
+//   6     8         50 M     300     64.7 /  66.3   64.1 /  63.4   |  7     4         80 M   280     67.2 /  75.5   63.7 /  71.0
+//   6     8        100 M     600    158.9 / 121.2  125.2 / 119.5   |  7     4        100 M   350     96.8 /  97.8   86.0 /  87.2
+//   8     8         50 M     400    103.4 /  71.2   84.9 /  77.3   |  7     6         80 M   420    112.5 / 101.9   90.0 /  96.4
+//   5    16         35 M     350     86.0 /  82.3   74.5 /  77.1   |  7     4        150 M   525    152.4 / 135.3  121.2 / 127.3
+//   5    16         40 M     400     99.4 /  92.1   88.0 /  86.9   |  7*    8        100 M   700    206.6 / 169.8  143.7 / 158.1
+//   5     8         80 M     400    103.4 / 100.9   91.9 /  95.3   |  5     8        100 M   500    132.8 / 122.9  113.4 / 114.3
 Size size_of(const RequantArgs& ra) {
-    constexpr uint64_t kShortElems = 1ull << 21, kLastLevelCache = 256ull << 20;
+    constexpr uint64_t kShortElems = 1ull << 21;
     if (ra.q.n <= kShortElems) return Size::kShort;
-    const bool gapless = ra.q.bits == 4u || ra.q.bits == 6u || ra.q.bits == 8u;
-    return gapless && (ra.q.n >> 3) * ra.q.bits * ra.W > kLastLevelCache ? Size::kStream : Size::kLong;
+    if (ra.q.bits < 4u) return Size::kLong;
+    const bool streams = ra.q.bits == 7u ? past_cache(ra) : stream_bytes(ra) > (ra.q.bits == 5u ? kLastLevelCache / 2u * 3u : kLastLevelCache);
+    return streams ? Size::kStream : Size::kLong;
 }
 // Calls f(B, SIZE) with the width and the size as compile-time constants.
 template <class F>
@@ -724,7 +736,7 @@ void with_shape(const RequantArgs& ra, F f) {
     with_bits(ra.q.bits, [&](auto b) {
         constexpr int B = decltype(b)::value;
         if (size == Size::kShort) return f(b, std::integral_constant<Size, Size::kShort>{});
-        if constexpr (B == 4 || B == 6 || B == 8) {
+        if constexpr (B >= 4) {
             if (size == Size::kStream) return f(b, std::integral_constant<Size, Size::kStream>{});
         }
         f(b, std::integral_constant<Size, Size::kLong>{});
@@ -778,7 +790,10 @@ hipError_t launch_requantize_cells(const RequantArgs& ra, hipStream_t stream) {
 // From 1.5 M elements on; below, a wave's chain counts, and that of the rows form is half as long (sixteen elements per
 // lane).  us, rows / cells: 3 bits, 12 workers, 1 M elements 12.8 / 14.6, 4 bits 13.8 / 13.1; 2 M 3 bits 15.5 / 15.1; 10 M, 4
 // workers, 3 bits 22.9 / 16.6, 4 bits 23.1 / 16.8; 12 workers, 4 bits 41 / 33, 6 bits 51 / 38; 100 M 300 / 236.
-bool tensor_cells_supported(const RequantArgs& ra) { return ra.q.n > 3ull << 19; }
+// Not at 7 bits with streams past the cache, unless they are few (inside the exchange; size_of has the reason): 2 workers, 250 M
+// elements 297 / 259, 4 workers, 120 M 204 / 211, 8 workers, 45 M (315 MB) 132 / 121, 50 M (350) 143 / 155, 100 M 294 / 319, 24
+// workers, 20 M 174 / 198.
+bool tensor_cells_supported(const RequantArgs& ra) { return ra.q.n > 3ull << 19 && (ra.q.bits != 7u || ra.W <= 4u || !past_cache(ra)); }
 uint32_t tensor_cells_tile(const RequantArgs& ra) { return size_of(ra) == Size::kShort ? 64u * kCell : 256u * kCell; }
 void launch_sum_range_cells(const RequantArgs& ra, uint32_t tiles, uint32_t tile, uint32_t* keys, hipStream_t stream) {
     with_shape(ra, [&](auto b, auto size) {
@@ -802,6 +817,9 @@ void launch_requantize_tensor_cells(const RequantArgs& ra, uint32_t tiles, uint3
 //   64, 24, 6 bits       11.3 / 12.4   12.9 / 14.5   15.0 / 17.0
 bool requantize_minmax_cells_supported(const RequantArgs& ra) {
     if (ra.q.drop_nan != 0u) return false;   // a whole tensor as one bucket
+    // 7 bits past the cache (size_of): 8 workers, bucket 1024, 50 M elements 83.6 / 84.6 inside the exchange, 81.4 / 75.2 alone, 100 M
+    // 157.6 / 158.8, 157 / 151; 16 workers, 50 M 146.6 / 152.8, 145.9 / 147.1; but 2304, 8 workers, 100 M 343 / 159
+    if (ra.q.bits == 7u && ra.W > 8u && ra.q.bucket_shift >= 0 && past_cache(ra)) return false;
     if (ra.q.n <= 1ull << 20) return ra.q.n >= 1ull << 16 && ra.q.bucket >= 128u && local_buckets(ra.q);
     return ra.q.bucket >= 128u || ra.W <= 8u;
 }
@@ -815,9 +833,25 @@ hipError_t launch_requantize_minmax_cells(const RequantArgs& ra, hipStream_t str
 //   2304, 8, 4 bits       7.6 /  5.6    7.9 /  6.4   17.6 /  8.9   35.9 / 14.5   85.0 / 33.5
 //   64, 8, 4 bits         6.5 /  5.7    6.8 /  6.0                 23.2 / 15.1
 //   32, 24, 6 bits       14.6 / 15.6   16.3 / 17.2   (2 M: 18.5 / 22.6)
+// and further on, in the exchange's loop, both in turn:
+//                          25.6 M          50 M           100 M elements            16 M           40 M           100 M elements
+//   1024, 8, 3 bits     31.3 /  31.7   52.6 /  52.6   103.3 / 104.0   1024, 16   32.8 / 32.2    66.4 /  68.7   169.2 / 174.4
+//   1024, 8, 4 bits     34.0 /  29.9   56.6 /  49.4   108.0 /  95.1   512, 16    24.9 / 23.0    69.6 /  68.7   (10 M, 40 M)
+//   1024, 8, 5 bits     41.4 /  32.6   71.3 /  54.3   149.9 / 122.9   4096, 24   30.9 / 29.7    97.8 / 100.3   (10 M, 40 M)
+//   1024, 8, 6 bits     42.4 /  34.6   77.7 /  64.1   138.9 / 117.5   8192, 8    24.6 / 22.6    48.6 /  45.5   121.5 / 105.8
+//   1024, 8, 7 bits     42.5 /  36.8   80.3 /  85.1   152.8 / 158.3   (43 M, 301 MB: 71.3 / 62.4)
+//   1024, 8, 8 bits     45.2 /  39.6   81.8 /  71.1   155.8 / 143.1
+//   128, 8, 4 bits      36.5 /  31.4   62.0 /  52.0   119.9 / 104.5
+//   8192, 8, 4 bits     37.9 /  29.8   63.5 /  49.4   128.5 /  95.1
+//   1024, 6, 7 bits: 55 M 74.3 / 62.4, 80 M (420 MB) 105.7 / 101.9; 1024, 16, 7 bits: 22 M 69.0 / 62.4, 25 M (350 MB) 73.5 / 79.1
+// (both take a fifth longer in the throttled launches after an idle gap: 4 bits, 100 M, 135-168 / 120-145)
 bool requantize_centred_cells_supported(const RequantArgs& ra) {
     if (ra.q.scale_mode != MQG_SCALE_MAXABS || ra.q.n < kCell) return false;   // a lane reads its words at once: the stream must hold as many
-    if (requantize_wave_supported(ra)) return ra.q.n > 1ull << 20 && (ra.q.bits > 2u || ra.W <= 4u);
+    if (requantize_wave_supported(ra)) {
+        if (ra.q.bits == 7u && ra.W > 6u && past_cache(ra)) return false;
+        if (ra.q.bits == 3u && ra.W > 6u && ra.q.n > 1ull << 24 && ra.q.bucket >= 1024u && ra.q.bucket <= 4096u) return false;
+        return ra.q.n > 1ull << 20 && (ra.q.bits > 2u || ra.W <= 4u);
+    }
     return ra.q.bucket > 32u || ra.W <= 8u || ra.q.n > 1ull << 21;
 }
 hipError_t launch_requantize_centred_cells(const RequantArgs& ra, hipStream_t stream) { return launch_requantize_cells<CentredCode>(ra, stream); }

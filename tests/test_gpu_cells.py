@@ -149,3 +149,51 @@ def test_a_tensors_range_that_is_not_finite(bad):
     torch.cuda.synchronize()
     assert rg.tolist() == [float("inf"), float("-inf")]
     assert not to_u32(pk).any()
+
+
+def against_the_sum(kind, n, bits, bucket, W):
+    """The re-encoding step against the encoder on the fp32 sum.  The sum comes from the server's update of zeros at a rate of
+    -W: p <- fma(1, sum, 0), the sum itself.  W workers that send one of three streams: as many bytes as the rules count."""
+    grads = gradients(n, min(W, 3), bits)
+    params = torch.zeros(n, device=DEV)
+    if kind == "centred":
+        q = [mqgrad.mqg_quantize(g, bits, bucket, 7, 2, w) for w, g in enumerate(grads)]
+        del grads
+        pk, sc = [q[w % len(q)][0] for w in range(W)], [q[w % len(q)][1] for w in range(W)]
+        got = mqgrad.mqg_aggregate_requantize(pk, sc, n, bits, bucket, 11, 5, 3, 8)
+        mqgrad.mqg_aggregate_update(pk, sc, n, bits, bucket, -float(W), params)
+        want = mqgrad.mqg_quantize(params, bits, bucket, 11, 5, 3, 8)
+    elif kind == "minmax":
+        q = [mqgrad.mqg_quantize_minmax(g, bits, bucket) for g in grads]
+        del grads
+        pk, rg = [q[w % len(q)][0] for w in range(W)], [q[w % len(q)][1] for w in range(W)]
+        got = mqgrad.mqg_aggregate_requantize_minmax(pk, rg, n, bits, bucket)
+        mqgrad.mqg_aggregate_update_minmax(pk, rg, n, bits, bucket, -float(W), params)
+        want = mqgrad.mqg_quantize_minmax(params, bits, bucket)
+    else:
+        q = [mqgrad.mqg_quantize_minmax_tensor(g, bits) for g in grads]
+        del grads
+        pk, rg = [q[w % len(q)][0] for w in range(W)], [q[w % len(q)][1] for w in range(W)]
+        got = mqgrad.mqg_aggregate_requantize_minmax_tensor(pk, rg, n, bits)
+        mqgrad.mqg_aggregate_update_minmax_tensor(pk, rg, n, bits, -float(W), params)
+        want = mqgrad.mqg_quantize_minmax_tensor(params, bits)
+    torch.cuda.synchronize()
+    assert torch.equal(got[0], want[0])
+    assert np.array_equal(got[1].cpu().numpy(), want[1].cpu().numpy() / np.float32(W))
+
+
+@pytest.mark.parametrize("kind,bits,bucket,W", [
+    ("centred", 5, 1024, 64), ("centred", 5, 2304, 32), ("minmax", 5, 512, 64), ("minmax", 5, 352, 24), ("tensor", 5, 0, 64),   # streaming loads
+    ("centred", 7, 1024, 6), ("centred", 7, 96, 40), ("minmax", 7, 2048, 8), ("minmax", 7, 2304, 24), ("tensor", 7, 0, 4),
+    ("centred", 7, 128, 24), ("minmax", 7, 1024, 24), ("tensor", 7, 0, 24)])                                                   # rows past the cache
+def test_streams_past_the_last_level_cache_at_five_and_seven_bits(kind, bits, bucket, W):
+    limit = (384 << 20) if bits == 5 else (320 << 20)
+    for n in (limit * 8 // bits // W - 2048, limit * 8 // bits // W + 2048 + 33):
+        assert (n // 8 * bits * W > limit) == (n > limit * 8 // bits // W)
+        against_the_sum(kind, n, bits, bucket, W)
+
+
+@pytest.mark.parametrize("bucket", [512, 1024, 4096, 8192])
+def test_long_tensors_at_three_bits(bucket):
+    for n in (16 * M, 16 * M + bucket + 5):
+        against_the_sum("centred", n, 3, bucket, 7)
