@@ -299,8 +299,8 @@ mqg_status mqg_aggregate_requantize_minmax(const uint32_t* const* packed, const 
  *   so that what a worker de-quantizes (mqg_aggregate_update_minmax_tensor with W = 1) is the mean.  The
  *   range of the sum is known only after every element has been decoded, so the W streams are read twice
  *   ((2 W + 1) * bits / 8 bytes per element; no fp32 copy of the sum is written).  Up to three launches on
- *   the stream (five when packed_out lies over one of the streams it reads, and above 2^28 elements; at 7 bits
- *   from 2^27 on).
+ *   the stream (five when packed_out lies over one of the streams it reads, and above 2^28 elements; above
+ *   2^27 at 7 bits with more than four workers).
  *   ranges      HOST array of W device pointers, each to 2 floats (8-byte aligned).
  *   packed_out  device, mqg_packed_words(n, bits) words;  range_out: device, 2 floats, 8-byte aligned.
  */

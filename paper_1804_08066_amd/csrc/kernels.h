@@ -175,7 +175,7 @@ hipError_t launch_requantize_minmax_tensor(const RequantArgs& a, hipStream_t str
 // requantize_cells.hip: the re-encoding steps with one cell of 32 elements per lane.  The two passes of the whole-tensor
 // one (tile: elements per workgroup), and the bucketed ones: [min, max], and the max-abs range with stochastic rounding
 bool tensor_cells_supported(const RequantArgs& a);
-uint32_t tensor_cells_tile(const RequantArgs& a);
+uint32_t tensor_cells_tile();
 void launch_sum_range_cells(const RequantArgs& a, uint32_t tiles, uint32_t tile, uint32_t* keys, hipStream_t stream);
 void launch_requantize_tensor_cells(const RequantArgs& a, uint32_t tiles, uint32_t tile, const float* sum_range, uint32_t borrowed, hipStream_t stream);
 bool requantize_minmax_cells_supported(const RequantArgs& a);

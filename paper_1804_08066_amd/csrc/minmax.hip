@@ -1125,7 +1125,7 @@ hipError_t launch_requantize_minmax_tensor(const RequantArgs& ra_in, hipStream_t
         return launch_requantize_minmax(one, stream);
     }
     const bool cells = tensor_cells_supported(ra_in);
-    const uint32_t tile = cells ? tensor_cells_tile(ra_in) : kSumTile;
+    const uint32_t tile = cells ? tensor_cells_tile() : kSumTile;
     const uint64_t tiles = (ra_in.q.n + tile - 1) / tile;
     if (tiles > 0x7FFFFFFFull) return hipErrorInvalidValue;
     const uint64_t words = (ra_in.q.n >> 5) * ra_in.q.bits + (((ra_in.q.n & 31u) * ra_in.q.bits + 31u) >> 5);

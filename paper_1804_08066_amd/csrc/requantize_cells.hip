@@ -402,7 +402,7 @@ __device__ __forceinline__ void sum_range_tile(const RequantArgs& ra, uint32_t* 
     }
 }
 template <int B, Size SIZE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SIZE == Size::kShort ? 4 : 5, 8))) void sum_range_cells_kernel(const RequantArgs ra, uint32_t* keys) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) void sum_range_cells_kernel(const RequantArgs ra, uint32_t* keys) {
     __shared__ float2 s_tab[MQG_MAX_WORKERS];
     __shared__ uint32_t s_lo[4], s_hi[4];
     const uint64_t tile_base = (uint64_t)blockIdx.x * (blockDim.x * kCell);
@@ -432,7 +432,7 @@ __device__ __forceinline__ void requantize_tensor_tile(const RequantArgs& ra, co
     encode_minmax<B, WHOLE>(ra.q.packed, at, v, mn, a);
 }
 template <int B, Size SIZE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SIZE == Size::kShort ? 4 : 5, 8))) void requantize_tensor_cells_kernel(const RequantArgs ra, const float* sum_range, const uint32_t borrowed) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) void requantize_tensor_cells_kernel(const RequantArgs ra, const float* sum_range, const uint32_t borrowed) {
     __shared__ float2 s_tab[MQG_MAX_WORKERS];
     const uint32_t tile = blockDim.x * kCell;
     const bool last = blockIdx.x + 1u == gridDim.x;
@@ -557,6 +557,7 @@ __device__ __forceinline__ void bucket_max(const uint32_t (&m)[N][Parts<B>::kCou
 struct MinmaxCode {
     using Sum = MinmaxSum;
     static constexpr int kKeys = 2;
+    static constexpr bool kShortShared = false;   // short launches with buckets across waves: not taken (requantize_minmax_cells_supported)
     template <int B, bool WHOLE>
     static __device__ __forceinline__ void keys(const float (&v)[32], const Window<B>& at, uint32_t (&m)[2][Parts<B>::kCount]) {
         float lo[Parts<B>::kCount], hi[Parts<B>::kCount];
@@ -585,6 +586,7 @@ struct MinmaxCode {
 struct CentredCode {
     using Sum = CentredSum;
     static constexpr int kKeys = 1;
+    static constexpr bool kShortShared = true;
     template <int B, bool WHOLE>
     static __device__ __forceinline__ void keys(const float (&v)[32], const Window<B>& at, uint32_t (&m)[1][Parts<B>::kCount]) {
         constexpr int E = Parts<B>::kElems;
@@ -713,29 +715,37 @@ constexpr uint64_t kLastLevelCache = 256ull << 20;
 uint64_t stream_bytes(const RequantArgs& ra) { return (ra.q.n >> 3) * ra.q.bits * ra.W; }
 bool past_cache(const RequantArgs& ra) { return stream_bytes(ra) > kLastLevelCache / 4u * 5u; }
 // Where streaming loads begin: with the cache's size at 4, 6 and 8 bits, whose loads leave no gaps; later at 7 and 5 bits, where a
-// wave's next load asks for the same cache lines again.  us of the max-abs step, ordinary / streaming loads, inside the exchange (the
-// workers' quantizers just before it) and in a loop of its own; bucket 1024, * 2304:
+// wave's next load asks for the same cache lines again, and there only where tiles begin with a cache line (power-of-two buckets and
+// whole tensors: else neighbours ask again too, and [min, max] takes 8-12 % longer at buckets 352 to 5152).  us of the max-abs step,
+// ordinary / streaming loads, inside the exchange (the workers' quantizers just before it) and in a loop of its own, bucket 1024:
 //   bits, workers, elements, MB        exchange        alone       |  bits, workers, elements, MB      exchange        alone
 //   6     8         50 M     300     64.7 /  66.3   64.1 /  63.4   |  7     4         80 M   280     67.2 /  75.5   63.7 /  71.0
 //   6     8        100 M     600    158.9 / 121.2  125.2 / 119.5   |  7     4        100 M   350     96.8 /  97.8   86.0 /  87.2
 //   8     8         50 M     400    103.4 /  71.2   84.9 /  77.3   |  7     6         80 M   420    112.5 / 101.9   90.0 /  96.4
 //   5    16         35 M     350     86.0 /  82.3   74.5 /  77.1   |  7     4        150 M   525    152.4 / 135.3  121.2 / 127.3
-//   5    16         40 M     400     99.4 /  92.1   88.0 /  86.9   |  7*    8        100 M   700    206.6 / 169.8  143.7 / 158.1
+//   5    16         40 M     400     99.4 /  92.1   88.0 /  86.9   |  5    16         50 M   500    131.6 / 112.3  108.1 / 107.1
 //   5     8         80 M     400    103.4 / 100.9   91.9 /  95.3   |  5     8        100 M   500    132.8 / 122.9  113.4 / 114.3
+//   5     8         70 M     350     88.6 /  90.2   82.5 /  84.7   |  5    24         25 M   375     92.2 /  83.7   79.3 /  79.2
+// kShort up to 2^20 elements: above, the large tiles are level or better almost everywhere.  us, small / large tiles: [min, max],
+// bucket 2304, 8 workers, 1 bit, 1.05, 1.4 and 2.05 M elements 6.4 / 4.9, 6.7 / 5.1, 6.9 / 6.4; 4096, 16 workers, 1 bit, 1.2 M 8.6 / 6.5;
+// max-abs, 1024, 2 workers, 4 bits, 1.6 M 4.3 / 4.0; 2304, 8 workers, 4 bits 7.4 / 5.8; 3 bits, 16 workers, bucket 8192 7.9 / 8.4
 Size size_of(const RequantArgs& ra) {
-    constexpr uint64_t kShortElems = 1ull << 21;
+    constexpr uint64_t kShortElems = 1ull << 20;
     if (ra.q.n <= kShortElems) return Size::kShort;
     if (ra.q.bits < 4u) return Size::kLong;
-    const bool streams = ra.q.bits == 7u ? past_cache(ra) : stream_bytes(ra) > (ra.q.bits == 5u ? kLastLevelCache / 2u * 3u : kLastLevelCache);
-    return streams ? Size::kStream : Size::kLong;
+    if ((ra.q.bits & 1u) == 0u) return stream_bytes(ra) > kLastLevelCache ? Size::kStream : Size::kLong;
+    const bool streams = ra.q.bits == 7u || ra.W >= 16u ? past_cache(ra) : stream_bytes(ra) > kLastLevelCache / 2u * 3u;
+    return streams && ra.q.bucket_shift >= 0 ? Size::kStream : Size::kLong;
 }
-// Calls f(B, SIZE) with the width and the size as compile-time constants.
-template <class F>
+// Calls f(B, SIZE) with the width and the size as compile-time constants.  SHORT: the form takes launches that are.
+template <bool SHORT, class F>
 void with_shape(const RequantArgs& ra, F f) {
     const Size size = size_of(ra);
     with_bits(ra.q.bits, [&](auto b) {
         constexpr int B = decltype(b)::value;
-        if (size == Size::kShort) return f(b, std::integral_constant<Size, Size::kShort>{});
+        if constexpr (SHORT) {
+            if (size == Size::kShort) return f(b, std::integral_constant<Size, Size::kShort>{});
+        }
         if constexpr (B >= 4) {
             if (size == Size::kStream) return f(b, std::integral_constant<Size, Size::kStream>{});
         }
@@ -745,16 +755,16 @@ void with_shape(const RequantArgs& ra, F f) {
 
 bool local_buckets(const QuantizeArgs& a) { return a.bucket_shift >= 5 && a.bucket <= 64u * kCell; }
 
-// The tile of a bucket size.  Short launches: as few waves as hold a bucket (the tensor passes likewise).  Others: up to 256
-// cells, or 320 where whole buckets fill them a tenth better; one bucket where it has more cells.  At 4 M elements, 8 workers,
-// 2 bits the small tiles take 9.9 us at bucket 2304 (72 cells in two waves) and the large ones 7.8; 16 workers, 8 bits, bucket
-// 1024 15.1 and 12.8; at 2 M they are level or better.  At most 4096 steps in LDS.
+// The tile of a bucket size.  Short launches: as few waves as hold a bucket.  Others: up to 256 cells; one bucket where it has more.
+// Five waves only where two buckets fill them and four hold one (129 to 160 cells), in long launches: bucket 4128 at 2.5, 8, 16 M
+// elements 1.02, 0.92, 0.98 of the time with four.  Where they hold three instead of two (2752) they take 1.28, 1.04, 1.16 of it, and where
+// six instead of four (1664) 1.00, 1.05, 1.03: five waves share four SIMDs badly.  At most 4096 steps in LDS.
 CellTile cell_tile(const RequantArgs& ra, uint32_t* lanes) {
     const uint32_t bc = ra.q.bucket / kCell;
     const bool local = local_buckets(ra.q);
     uint32_t waves = (bc + 63u) / 64u;
     if (size_of(ra) != Size::kShort && bc <= 256u) {
-        waves = !local && (320u / bc) * 4u * 10u > (256u / bc) * 5u * 11u ? 5u : 4u;   // used fractions, compared by cross-multiplication
+        waves = bc > 128u && bc <= 160u && ra.q.n > 5ull << 20 ? 5u : 4u;
     }
     uint32_t buckets = (waves * 64u) / bc;
     const uint32_t most = 4096u / ra.W;   // >= 64
@@ -772,15 +782,12 @@ hipError_t launch_requantize_cells(const RequantArgs& ra, hipStream_t stream) {
     const uint64_t tiles = (ra.q.n + elems - 1) / elems;
     if (tiles > 0x7FFFFFFFull) return hipErrorInvalidValue;
     const size_t lds = sizeof(typename Code::Sum::Step) * ra.W * g.buckets;
-    with_shape(ra, [&](auto b, auto size) {
-        constexpr int B = decltype(b)::value;
-        constexpr Size SIZE = decltype(size)::value;
-        if (local_buckets(ra.q)) {
-            hipLaunchKernelGGL((requantize_cells_kernel<B, Code, true, SIZE>), dim3((uint32_t)tiles), dim3(lanes), lds, stream, ra, g);
-        } else {
-            hipLaunchKernelGGL((requantize_cells_kernel<B, Code, false, SIZE>), dim3((uint32_t)tiles), dim3(lanes), lds, stream, ra, g);
-        }
-    });
+    const auto launch = [&](auto local, auto b, auto size) {
+        hipLaunchKernelGGL((requantize_cells_kernel<decltype(b)::value, Code, decltype(local)::value, decltype(size)::value>), dim3((uint32_t)tiles),
+                           dim3(lanes), lds, stream, ra, g);
+    };
+    if (local_buckets(ra.q)) with_shape<true>(ra, [&](auto b, auto size) { launch(std::true_type{}, b, size); });
+    else with_shape<Code::kShortShared>(ra, [&](auto b, auto size) { launch(std::false_type{}, b, size); });
     return hipGetLastError();
 }
 
@@ -794,14 +801,14 @@ hipError_t launch_requantize_cells(const RequantArgs& ra, hipStream_t stream) {
 // elements 297 / 259, 4 workers, 120 M 204 / 211, 8 workers, 45 M (315 MB) 132 / 121, 50 M (350) 143 / 155, 100 M 294 / 319, 24
 // workers, 20 M 174 / 198.
 bool tensor_cells_supported(const RequantArgs& ra) { return ra.q.n > 3ull << 19 && (ra.q.bits != 7u || ra.W <= 4u || !past_cache(ra)); }
-uint32_t tensor_cells_tile(const RequantArgs& ra) { return size_of(ra) == Size::kShort ? 64u * kCell : 256u * kCell; }
+uint32_t tensor_cells_tile() { return 256u * kCell; }
 void launch_sum_range_cells(const RequantArgs& ra, uint32_t tiles, uint32_t tile, uint32_t* keys, hipStream_t stream) {
-    with_shape(ra, [&](auto b, auto size) {
+    with_shape<false>(ra, [&](auto b, auto size) {
         hipLaunchKernelGGL((sum_range_cells_kernel<decltype(b)::value, decltype(size)::value>), dim3(tiles), dim3(tile / kCell), 0, stream, ra, keys);
     });
 }
 void launch_requantize_tensor_cells(const RequantArgs& ra, uint32_t tiles, uint32_t tile, const float* sum_range, uint32_t borrowed, hipStream_t stream) {
-    with_shape(ra, [&](auto b, auto size) {
+    with_shape<false>(ra, [&](auto b, auto size) {
         hipLaunchKernelGGL((requantize_tensor_cells_kernel<decltype(b)::value, decltype(size)::value>), dim3(tiles), dim3(tile / kCell), 0, stream, ra, sum_range,
                            borrowed);
     });
@@ -815,12 +822,21 @@ void launch_requantize_tensor_cells(const RequantArgs& ra, uint32_t tiles, uint3
 //   2304, 16, 2 bits      7.1 /  7.1    7.9 /  8.8   10.0 /  9.4   32.1 / 20.3
 //   32, 24, 4 bits       11.7 / 13.4   13.8 / 14.4   15.6 / 20.0   55.0 / 57.4   (a division per lane and worker in either)
 //   64, 24, 6 bits       11.3 / 12.4   12.9 / 14.5   15.0 / 17.0
+//   1024, 24, 3 bits      9.1 /  9.3    9.4 /  9.9  (1.1 M: 10.8 / 9.8)    128, 24, 3 bits   10.0 / 10.9   11.5 / 13.0
+//   128, 24, 6 bits      10.2 / 11.0   12.0 / 12.0                         128, 16, 6 bits    7.9 /  8.2    8.9 /  8.7
+//   128, 64, 6 bits      24.2 / 25.4   27.1 / 31.2   31.3 / 32.6           128, 64, 8 bits   23.0 / 21.6   27.1 / 27.9
+//   8192, 8, 8 bits              (1.05 M: 5.3 /  5.8)  5.5 /  5.7          8192, 8, 4 bits  (1.05 M: 5.8 / 5.3)
 bool requantize_minmax_cells_supported(const RequantArgs& ra) {
     if (ra.q.drop_nan != 0u) return false;   // a whole tensor as one bucket
     // 7 bits past the cache (size_of): 8 workers, bucket 1024, 50 M elements 83.6 / 84.6 inside the exchange, 81.4 / 75.2 alone, 100 M
     // 157.6 / 158.8, 157 / 151; 16 workers, 50 M 146.6 / 152.8, 145.9 / 147.1; but 2304, 8 workers, 100 M 343 / 159
     if (ra.q.bits == 7u && ra.W > 8u && ra.q.bucket_shift >= 0 && past_cache(ra)) return false;
-    if (ra.q.n <= 1ull << 20) return ra.q.n >= 1ull << 16 && ra.q.bucket >= 128u && local_buckets(ra.q);
+    const bool narrow = ra.q.bucket == 128u && ra.W > 32u && ra.q.bits >= 5u;
+    if (ra.q.n <= 1ull << 20) {
+        const bool many = ra.q.bits == 3u || (ra.q.bits == 6u && ra.q.bucket == 128u) ? ra.W > 12u : narrow && ra.q.n > 1ull << 19;
+        return ra.q.n >= 1ull << 16 && ra.q.bucket >= 128u && local_buckets(ra.q) && !many;
+    }
+    if (ra.q.n <= 1ull << 21 && (narrow || (ra.q.bucket == 8192u && ra.q.bits == 8u))) return false;
     return ra.q.bucket >= 128u || ra.W <= 8u;
 }
 hipError_t launch_requantize_minmax_cells(const RequantArgs& ra, hipStream_t stream) { return launch_requantize_cells<MinmaxCode>(ra, stream); }
@@ -833,6 +849,12 @@ hipError_t launch_requantize_minmax_cells(const RequantArgs& ra, hipStream_t str
 //   2304, 8, 4 bits       7.6 /  5.6    7.9 /  6.4   17.6 /  8.9   35.9 / 14.5   85.0 / 33.5
 //   64, 8, 4 bits         6.5 /  5.7    6.8 /  6.0                 23.2 / 15.1
 //   32, 24, 6 bits       14.6 / 15.6   16.3 / 17.2   (2 M: 18.5 / 22.6)
+// Buckets of the rows kernel that begin a new round of it (2^20 elements each) or not, 1.05, 1.3, 2.05, 2.2, 5 and 6 M, cells / rows:
+//   1024, 8, 4 bits      1.07  0.92  0.88  0.92  0.88  0.81              1024, 16, 5 bits     1.05  0.89  0.91  0.82  0.80  0.72
+//   1024, 16, 3 bits     1.17  1.09  1.03  1.09  1.06  0.95  (3.5 M 0.94, 4.2 M 1.12)         128, 16, 3 bits  1.13  1.05  1.03  0.99  1.00  0.89
+//   1024, 2, 3 bits      (1.6 M 0.95, 3 M 0.99, 4.2 M 1.04)              1024, 2, 8 bits      1.00  1.06  0.95  1.04  0.98  0.90
+//   1024, 4, 1 bit       1.02  1.00  0.97  1.12  1.06  0.98              1024, 2, 1 bit       (1.6 M 0.94, 2.2 M 1.05, 3 M 1.03)
+//   8192, 8, 8 bits      1.08  1.09  1.06  0.89  0.92  0.97              8192, 8, 4 bits      (1.6 M 0.92, 2.2 M 0.83)
 // and further on, in the exchange's loop, both in turn:
 //                          25.6 M          50 M           100 M elements            16 M           40 M           100 M elements
 //   1024, 8, 3 bits     31.3 /  31.7   52.6 /  52.6   103.3 / 104.0   1024, 16   32.8 / 32.2    66.4 /  68.7   169.2 / 174.4
@@ -850,7 +872,13 @@ bool requantize_centred_cells_supported(const RequantArgs& ra) {
     if (requantize_wave_supported(ra)) {
         if (ra.q.bits == 7u && ra.W > 6u && past_cache(ra)) return false;
         if (ra.q.bits == 3u && ra.W > 6u && ra.q.n > 1ull << 24 && ra.q.bucket >= 1024u && ra.q.bucket <= 4096u) return false;
-        return ra.q.n > 1ull << 20 && (ra.q.bits > 2u || ra.W <= 4u);
+        if (ra.q.bits <= 2u && ra.W > 4u) return false;
+        if (ra.q.bucket == 16384u) return ra.q.n > 1ull << 20;
+        if (ra.W > 2u && ra.q.bits <= 3u && ra.q.bucket >= 512u && ra.q.bucket <= 4096u) {   // the fourth million is a round of its own to the rows kernel
+            return ra.q.n > 11ull << 19 || (ra.q.n > 3ull << 20 && ra.q.n <= 1ull << 22);
+        }
+        if ((ra.W > 2u && ra.q.bits <= 3u) || (ra.W <= 4u && ra.q.bits == 8u) || (ra.q.bucket == 8192u && ra.q.bits >= 6u)) return ra.q.n > 1ull << 21;
+        return ra.q.n > (ra.W <= 8u ? 9ull << 17 : 1ull << 20);
     }
     return ra.q.bucket > 32u || ra.W <= 8u || ra.q.n > 1ull << 21;
 }

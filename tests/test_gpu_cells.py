@@ -183,11 +183,12 @@ def against_the_sum(kind, n, bits, bucket, W):
 
 
 @pytest.mark.parametrize("kind,bits,bucket,W", [
-    ("centred", 5, 1024, 64), ("centred", 5, 2304, 32), ("minmax", 5, 512, 64), ("minmax", 5, 352, 24), ("tensor", 5, 0, 64),   # streaming loads
-    ("centred", 7, 1024, 6), ("centred", 7, 96, 40), ("minmax", 7, 2048, 8), ("minmax", 7, 2304, 24), ("tensor", 7, 0, 4),
-    ("centred", 7, 128, 24), ("minmax", 7, 1024, 24), ("tensor", 7, 0, 24)])                                                   # rows past the cache
+    ("centred", 5, 1024, 64), ("centred", 5, 4096, 15), ("minmax", 5, 512, 64), ("minmax", 5, 8192, 12), ("tensor", 5, 0, 64),   # streaming loads
+    ("centred", 7, 1024, 6), ("centred", 7, 64, 40), ("centred", 7, 4096, 5), ("minmax", 7, 2048, 8), ("minmax", 7, 4096, 7), ("tensor", 7, 0, 4),
+    ("centred", 7, 128, 24), ("minmax", 7, 1024, 24), ("tensor", 7, 0, 24),                                                     # rows past the cache
+    ("centred", 5, 2304, 32), ("centred", 7, 96, 40), ("minmax", 5, 352, 24), ("minmax", 7, 2304, 24)])                         # ordinary loads
 def test_streams_past_the_last_level_cache_at_five_and_seven_bits(kind, bits, bucket, W):
-    limit = (384 << 20) if bits == 5 else (320 << 20)
+    limit = (384 << 20) if bits == 5 and W < 16 else (320 << 20)
     for n in (limit * 8 // bits // W - 2048, limit * 8 // bits // W + 2048 + 33):
         assert (n // 8 * bits * W > limit) == (n > limit * 8 // bits // W)
         against_the_sum(kind, n, bits, bucket, W)
@@ -197,3 +198,20 @@ def test_streams_past_the_last_level_cache_at_five_and_seven_bits(kind, bits, bu
 def test_long_tensors_at_three_bits(bucket):
     for n in (16 * M, 16 * M + bucket + 5):
         against_the_sum("centred", n, 3, bucket, 7)
+
+
+@pytest.mark.parametrize("kind,bits,bucket,W,line", [
+    ("centred", 4, 1024, 8, 9 << 17), ("centred", 7, 512, 9, M), ("centred", 1, 128, 1, 9 << 17), ("centred", 2, 2048, 4, 11 << 19),
+    ("centred", 3, 512, 3, 3 << 20), ("centred", 3, 4096, 8, 4 * M), ("centred", 3, 1024, 3, 11 << 19), ("centred", 3, 128, 5, 2 * M),
+    ("centred", 8, 256, 4, 2 * M), ("centred", 6, 8192, 5, 2 * M), ("centred", 5, 4128, 3, 5 * M), ("centred", 8, 5120, 2, 5 * M),
+    ("minmax", 4, 4128, 6, 5 * M), ("minmax", 8, 8192, 3, 2 * M), ("minmax", 5, 128, 33, M // 2), ("minmax", 7, 128, 64, 2 * M),
+    ("minmax", 2, 2752, 5, M), ("minmax", 6, 5120, 9, M), ("minmax", 3, 12320, 4, M), ("tensor", 3, 0, 5, 3 << 19)])
+def test_on_both_sides_of_the_rules_lines(kind, bits, bucket, W, line):
+    for n in (line, line + 1, line + bucket + 41):
+        against_the_sum(kind, n, bits, bucket, W)
+
+
+@pytest.mark.parametrize("bits,bucket", [(3, 128), (3, 2048), (6, 128), (6, 256)])
+def test_short_launches_with_few_and_many_workers(bits, bucket):
+    for W in (12, 13):
+        against_the_sum("minmax", M // 4 + 77, bits, bucket, W)
