@@ -849,6 +849,16 @@ hipError_t launch_requantize_minmax_cells(const RequantArgs& ra, hipStream_t str
 //   2304, 8, 4 bits       7.6 /  5.6    7.9 /  6.4   17.6 /  8.9   35.9 / 14.5   85.0 / 33.5
 //   64, 8, 4 bits         6.5 /  5.7    6.8 /  6.0                 23.2 / 15.1
 //   32, 24, 6 bits       14.6 / 15.6   16.3 / 17.2   (2 M: 18.5 / 22.6)
+// and with many workers, cells / rows at 64 K, 700 K, 1.05, 2.2, 3, 4, 5, 6, 8 and 12 M elements:
+//   64, 24, 6 bits       1.01  0.97  0.95  1.02  1.04  0.96  0.86  0.84  0.81  0.81
+//   64, 48, 4 bits       0.86  0.79  0.85  1.12  1.13  1.01  0.82  0.81  0.77
+//   64, 64, 6 bits       1.06  1.16  1.13  1.10  1.09  1.03  0.85  0.88                    64, 64, 2 bits  0.88  0.88  0.85  1.07  1.07  0.95
+//   96, 64, 6 bits       0.95  1.03  0.98  0.97  0.95  0.93  0.79  0.78
+//   32, 12, 6 bits       1.04  0.98  0.99  0.93  1.09  1.00  0.92  0.89  0.84  0.80
+//   32, 24, 4 bits       0.97  0.90  0.91  1.19  1.27  1.16  0.92  0.88  0.84  0.77         32, 24, 8 bits  (8 M) 0.86  1.02
+//   32, 32, 8 bits       1.00  1.05  1.27  1.19  1.24  1.14  0.89  0.85  0.91  1.11         32, 32, 3 bits  (12 M) 0.92 (21 M) 0.88
+//   32, 48, 4 bits       0.99  0.94  1.12  1.31  1.29  1.11  0.82  0.79  1.07
+//   32, 64, 4 bits       0.98  1.14  1.25  1.31  1.23  1.04  1.12  1.20
 // Buckets of the rows kernel that begin a new round of it (2^20 elements each) or not, 1.05, 1.3, 2.05, 2.2, 5 and 6 M, cells / rows:
 //   1024, 8, 4 bits      1.07  0.92  0.88  0.92  0.88  0.81              1024, 16, 5 bits     1.05  0.89  0.91  0.82  0.80  0.72
 //   1024, 16, 3 bits     1.17  1.09  1.03  1.09  1.06  0.95  (3.5 M 0.94, 4.2 M 1.12)         128, 16, 3 bits  1.13  1.05  1.03  0.99  1.00  0.89
@@ -880,7 +890,11 @@ bool requantize_centred_cells_supported(const RequantArgs& ra) {
         if ((ra.W > 2u && ra.q.bits <= 3u) || (ra.W <= 4u && ra.q.bits == 8u) || (ra.q.bucket == 8192u && ra.q.bits >= 6u)) return ra.q.n > 1ull << 21;
         return ra.q.n > (ra.W <= 8u ? 9ull << 17 : 1ull << 20);
     }
-    return ra.q.bucket > 32u || ra.W <= 8u || ra.q.n > 1ull << 21;
+    // a division per bucket, lane and worker where rows share one: the smallest buckets of many workers
+    if (ra.q.bucket == 64u) return ra.W <= 24u || ra.q.bits <= 3u || ra.q.n <= 1ull << 19 || ra.q.n > 1ull << 22;
+    if (ra.q.bucket > 32u || ra.W <= 8u) return true;
+    if (ra.W <= 24u) return ra.q.n > (ra.W <= 12u ? 1ull << 21 : 1ull << 22);
+    return ra.q.n > 1ull << 22 && ((ra.W <= 32u && ra.q.bits <= 5u) || (ra.W <= 48u && ra.q.n * ra.W <= 340000000ull));
 }
 hipError_t launch_requantize_centred_cells(const RequantArgs& ra, hipStream_t stream) { return launch_requantize_cells<CentredCode>(ra, stream); }
 

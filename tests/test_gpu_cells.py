@@ -205,7 +205,9 @@ def test_long_tensors_at_three_bits(bucket):
     ("centred", 3, 512, 3, 3 << 20), ("centred", 3, 4096, 8, 4 * M), ("centred", 3, 1024, 3, 11 << 19), ("centred", 3, 128, 5, 2 * M),
     ("centred", 8, 256, 4, 2 * M), ("centred", 6, 8192, 5, 2 * M), ("centred", 5, 4128, 3, 5 * M), ("centred", 8, 5120, 2, 5 * M),
     ("minmax", 4, 4128, 6, 5 * M), ("minmax", 8, 8192, 3, 2 * M), ("minmax", 5, 128, 33, M // 2), ("minmax", 7, 128, 64, 2 * M),
-    ("minmax", 2, 2752, 5, M), ("minmax", 6, 5120, 9, M), ("minmax", 3, 12320, 4, M), ("tensor", 3, 0, 5, 3 << 19)])
+    ("minmax", 2, 2752, 5, M), ("minmax", 6, 5120, 9, M), ("minmax", 3, 12320, 4, M), ("tensor", 3, 0, 5, 3 << 19),
+    ("centred", 4, 64, 25, M // 2), ("centred", 6, 64, 64, 4 * M), ("centred", 3, 64, 33, 4 * M), ("centred", 5, 32, 12, 2 * M),
+    ("centred", 8, 32, 13, 4 * M), ("centred", 2, 32, 24, 4 * M), ("centred", 4, 32, 25, 4 * M), ("centred", 6, 32, 30, 340000000 // 30), ("centred", 1, 32, 48, 340000000 // 48)])
 def test_on_both_sides_of_the_rules_lines(kind, bits, bucket, W, line):
     for n in (line, line + 1, line + bucket + 41):
         against_the_sum(kind, n, bits, bucket, W)
