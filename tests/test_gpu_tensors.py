@@ -194,3 +194,35 @@ def test_batched_minmax_calls_report_bad_arguments():
         mqgrad.mqg_aggregate_update_minmax_tensors(layers, 8, 4, 0, 0.1)   # 272 pointers
     mqgrad.mqg_aggregate_update_minmax_tensors(layers[:16], 8, 4, 0, 0.1)
     torch.cuda.synchronize()
+
+
+# (layers, encoded ones among them, workers): the largest batch that travels in the small form of the kernels' arguments (12
+# layers, 96 pointers), one more layer, more pointers, and the most of both
+@pytest.mark.parametrize("count,encoded,W", [(12, 4, 6), (13, 4, 1), (12, 4, 7), (12, 12, 5), (32, 32, 4), (20, 5, 10)])
+@pytest.mark.parametrize("kind,bits,bucket", [("centred", 2, 512), ("centred", 4, 96), ("centred", 5, 1024), ("centred", 8, 32),
+                                              ("minmax", 2, 160), ("minmax", 3, 1024), ("minmax", 8, 512), ("minmax", 4, 0)])
+def test_batched_server_steps_of_many_layers_and_workers(kind, bits, bucket, count, encoded, W):
+    lr = 0.1
+    sizes = [(i * 7919 + 613) % 9000 + 1 for i in range(count)]
+    sizes[1] = 0
+    grads = [[workloads.laplace(n, 2e-3, 100 * w + i, DEV) + 5e-4 * w if n else torch.empty(0, device=DEV) for i, n in enumerate(sizes)] for w in range(W)]
+    params = [workloads.uniform(max(n, 1), -0.05, 0.05, 40 + i, DEV)[:n] for i, n in enumerate(sizes)]
+    p0 = [p.cpu().numpy().copy() for p in params]
+    if kind == "centred":
+        outs = [mqgrad.mqg_quantize_tensors(grads[w][:encoded], bits, bucket, seed=w, iteration=1, worker=w) for w in range(W)]
+    else:
+        outs = [mqgrad.mqg_quantize_minmax_tensors(grads[w][:encoded], bits, bucket) for w in range(W)]
+    layers = [{"params": params[i], "packed": [outs[w][i][0] for w in range(W)], "scales": [outs[w][i][1] for w in range(W)]} if i < encoded
+              else {"params": params[i], "raw": [grads[w][i] for w in range(W)]} for i in range(count)]
+    (mqgrad.mqg_aggregate_update_tensors if kind == "centred" else mqgrad.mqg_aggregate_update_minmax_tensors)(layers, W, bits, bucket, lr)
+    torch.cuda.synchronize()
+    for i, n in enumerate(sizes):
+        if n == 0:
+            continue
+        if i >= encoded:
+            p1 = ref.average_update_raw([grads[w][i].cpu().numpy() for w in range(W)], lr, p0[i])
+        else:
+            pk, sc = [to_u32(outs[w][i][0]) for w in range(W)], [outs[w][i][1].cpu().numpy() for w in range(W)]
+            step = ref.aggregate_update if kind == "centred" else ref.aggregate_update_minmax
+            p1 = step(pk, sc, n, bits, bucket if bucket else n, lr, p0[i])
+        assert ulp_distance(params[i].cpu().numpy(), p1).max() == 0, "layer %d" % i
