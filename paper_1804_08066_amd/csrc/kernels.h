@@ -71,7 +71,7 @@ struct RequantArgs {
 // Several layer tensors of one model in one launch.  A launch's arguments are copied for every launch, at about 0.45 us of
 // the caller's time per KB, so a batch that fits takes the form with room for few (with_few below): the small CNN's two
 // launches carry 1.9 KB instead of 4.8.
-constexpr uint32_t kMaxBatchTensors = 32, kFewTensors = 12;
+constexpr uint32_t kMaxBatchTensors = 32, kFewTensors = 12, kFewRanges = 4;   // kFewRanges: one tensor, or the paper's two layers
 constexpr uint32_t kMaxBatchPointers = 256, kFewPointers = 96;   // per quantized tensor 2*W pointers, per raw tensor W
 
 struct AggregateTensor {
@@ -186,7 +186,7 @@ hipError_t launch_tensor_range(const float* grad, uint64_t n, float* range_out, 
 // the same for several tensors that are encoded next, with their code words as the workgroups' scratch memory
 template <uint32_t TENSORS>
 struct TensorRanges {
-    using Few = TensorRanges<4>;         // one tensor, or the paper's two layers
+    using Few = TensorRanges<kFewRanges>;
     uint32_t count, bits;
     uint32_t in_slots;                   // set by the launch: tensors of several workgroups have their keys in slots
     RangeSlots slots[TENSORS];           // set by the launch
@@ -195,19 +195,19 @@ struct TensorRanges {
     float* range[TENSORS];               // 2 floats each
     uint32_t* parts[TENSORS];            // the tensor's code words
     uint32_t block_start[TENSORS + 1];   // filled by the launch: prefix sums of the tensors' workgroups
-    bool few() const { return count <= 4u; }
+    bool few() const { return count <= kFewRanges; }
     void copy_to(Few& f) const {
         f.count = count;
         f.bits = bits;
         f.in_slots = in_slots;
-        for (uint32_t i = 0; i < 4u; ++i) {
+        for (uint32_t i = 0; i < kFewRanges; ++i) {
             f.slots[i] = slots[i];
             f.grad[i] = grad[i];
             f.n[i] = n[i];
             f.range[i] = range[i];
             f.parts[i] = parts[i];
         }
-        for (uint32_t i = 0; i <= 4u; ++i) f.block_start[i] = block_start[i];
+        for (uint32_t i = 0; i <= kFewRanges; ++i) f.block_start[i] = block_start[i];
     }
 };
 using TensorRangeBatch = TensorRanges<kMaxBatchTensors>;

@@ -448,8 +448,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
 struct CellTile {
     uint32_t cells, buckets;   // of a tile
     uint32_t bucket_cells;     // bucket / 32
-    uint32_t magic;            // ceil(2^20 / bucket_cells): (cell * magic) >> 16 = cell / bucket_cells below 512 cells
+    uint32_t magic;            // ceil(2^20 / bucket_cells)
 };
+__device__ __forceinline__ uint32_t bucket_of_cell(const CellTile& g, const uint32_t cell) {   // cell / bucket_cells, below 512 cells
+    return (cell * g.magic) >> 20;
+}
 constexpr uint32_t kMostLanes = 512;                      // the largest bucket is 512 cells
 constexpr uint32_t kMostSharedBuckets = kMostLanes / 3;   // buckets of a tile that is not LOCAL: at least three cells each
 
@@ -652,7 +655,7 @@ __device__ __forceinline__ void requantize_cells_tile(const RequantArgs& ra, con
     const uint64_t first_bucket = (uint64_t)blockIdx.x * g.buckets;
     const Window<B> at(ra.q.n, tile_base, tile_end, g.cells);
     const auto bucket_of = [&](const uint32_t cell) {
-        const uint32_t k = (cell * g.magic) >> 20;
+        const uint32_t k = bucket_of_cell(g, cell);
         return WHOLE || k < buckets ? k : buckets - 1u;   // cells past the end: any
     };
     uint32_t bucket[P];
@@ -674,7 +677,7 @@ __device__ __forceinline__ void requantize_cells_tile(const RequantArgs& ra, con
     uint32_t m[Code::kKeys][P], key[Code::kKeys];
     Code::template keys<B, WHOLE>(v, at, m);
     const uint32_t cell = tid < g.cells ? tid : g.cells - 1u;   // the cell that this lane stands for
-    const uint32_t mine = (cell * g.magic) >> 20;
+    const uint32_t mine = bucket_of_cell(g, cell);
     bucket_max<B, LOCAL, Code::kKeys>(m, g, cell, mine, s_max, key);
     const bool stores = tid < g.cells && cell == mine * g.bucket_cells && mine < buckets;
     Code::template encode<B, WHOLE>(ra, at, tile_base, v, key, stores, first_bucket + mine);
