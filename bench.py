@@ -181,6 +181,17 @@ def condition(wl, bits, bucket, lr, ms):
     return done, (time.perf_counter() - t0) * 1e3
 
 
+def settle(one, ms):
+    """Untimed iterations of a loop, one(k), until `ms` milliseconds have passed (condition() has the reason; the first call of a
+    kernel is such a gap too: its code object is loaded then)."""
+    import torch
+    t0, k = time.perf_counter(), 0
+    while (time.perf_counter() - t0) * 1e3 < ms:
+        for k in range(k, k + 16):
+            one(k)
+        torch.cuda.synchronize()
+
+
 def time_cold_codes(wl, bits, bucket, lr, steps=20, warmup=5, origin=0):
     """The server step when the code words are NOT in this GPU's caches -- the state on a real parameter
     server, where the W streams arrive over the network: each step quantizes as usual, then copies two
@@ -432,7 +443,23 @@ def alu_row(kernel, ms, ops, extra=None):
     return row
 
 
-def time_exchange(wl, bits, bucket, lr, steps, warmup):
+def past_cache(n, bits, W):
+    """Do the W code streams exceed the last-level cache by a quarter?  At 7 bits the re-encoding steps change kernels there."""
+    return n // 8 * bits * W > 320 << 20
+
+
+def maxabs_cells(n, bits, bucket, W):
+    """Does the max-abs re-encoding of a long tensor run with a cell per lane?  (Below 2^24 elements there are further lines.)"""
+    if bucket & (bucket - 1) or bucket < 128:
+        return bucket > 32 or W <= 24
+    if (bits <= 2 and W > 4) or (bits == 7 and W > 6 and past_cache(n, bits, W)):
+        return False
+    if bits == 3 and W > 6 and 1024 <= bucket <= 4096 and n > 1 << 24:
+        return False
+    return n > 11 << 19 or (n > 1 << 21 and bits > 3)
+
+
+def time_exchange(wl, bits, bucket, lr, steps, warmup, condition_ms=0.0):
     """The second leg of Algorithm 1: mqg_aggregate_requantize (server) + mqg_dequantize_update (worker).
 
     The re-quantize kernel's vector operations take about as long as its (W + 1) * bits / 8 bytes per element:
@@ -446,8 +473,8 @@ def time_exchange(wl, bits, bucket, lr, steps, warmup):
         mqgrad.mqg_quantize(wl.grads[w], bits, bucket, seed=1234, iteration=0, worker=w, packed_out=pk[w], scales_out=sc[w])
     mean_pk, mean_sc = mqgrad.alloc_outputs(n, bits, bucket, wl.device)
     mean_out = torch.empty(n, dtype=torch.float32, device=wl.device)
-    ev = []
-    for k in range(warmup + steps):
+
+    def one(k):
         e = [torch.cuda.Event(enable_timing=True) for _ in range(4)]
         e[0].record()
         mqgrad.mqg_aggregate_requantize(pk, sc, n, bits, bucket, seed=1234, iteration=k, worker=W,
@@ -457,8 +484,10 @@ def time_exchange(wl, bits, bucket, lr, steps, warmup):
         e[2].record()
         mqgrad.mqg_aggregate_mean(pk, sc, n, bits, bucket, mean_out)
         e[3].record()
-        if k >= warmup:
-            ev.append(e)
+        return e
+
+    settle(one, condition_ms)
+    ev = [one(k) for k in range(warmup + steps)][warmup:]
     torch.cuda.synchronize()
     r_ms = sum(e[0].elapsed_time(e[1]) for e in ev) / len(ev)
     d_ms = sum(e[1].elapsed_time(e[2]) for e in ev) / len(ev)
@@ -467,8 +496,7 @@ def time_exchange(wl, bits, bucket, lr, steps, warmup):
     m_bytes = W * (n * bits / 8.0 + 4.0 * nb) + 4.0 * n
     r_bytes = (W + 1) * (n * bits / 8.0 + 4.0 * nb)
     d_bytes = n * bits / 8.0 + 4.0 * nb + 8.0 * n
-    # a cell per lane, or rows: the smallest tensors, and 1 and 2 bits with more than four workers (a table in LDS there)
-    cells = not (bucket & (bucket - 1) == 0 and bucket >= 128) or (n > 1 << 20 and (bits > 2 or W <= 4))
+    cells = maxabs_cells(n, bits, bucket, W)
     # vector operations the kernel's algorithm issues per element: per worker's code 1.5 (1 bit: quad table) or 1.75
     # (pair table) for table offsets + the chain's fma in the rows form, 3 at 8 bits, 3.5 at 5-7 bits; with cells 2.9 at 1, 2
     # and 4 bits, 3 at 8, 4 at the others; about 14 (12) to encode (range, Philox / 8, fixed-point rounding, packing)
@@ -570,7 +598,7 @@ def time_tensors(W, bits, bucket, lr, steps, warmup, device):
     return res
 
 
-def time_minmax(wl, bits, bucket, lr, steps, warmup):
+def time_minmax(wl, bits, bucket, lr, steps, warmup, condition_ms=0.0):
     """The footnote's deterministic [min, max] encoding and the sum of squares of the Adaptive rule."""
     import torch
     from paper_1804_08066_amd import mqgrad
@@ -582,8 +610,8 @@ def time_minmax(wl, bits, bucket, lr, steps, warmup):
     mrg = torch.empty_like(rg[0])
     trg = torch.zeros(2, dtype=torch.float32, device=wl.device)
     trs = [torch.tensor([-0.06, 0.06], dtype=torch.float32, device=wl.device) for _ in range(W)]   # one range per worker
-    ev = []
-    for k in range(warmup + steps):
+
+    def one(k):
         e = [torch.cuda.Event(enable_timing=True) for _ in range(7)]
         e[0].record()
         for w in range(W):
@@ -600,8 +628,10 @@ def time_minmax(wl, bits, bucket, lr, steps, warmup):
         e[5].record()
         mqgrad.mqg_aggregate_requantize_minmax_tensor(pk, trs, n, bits, mpk, trg)
         e[6].record()
-        if k >= warmup:
-            ev.append(e)
+        return e
+
+    settle(one, condition_ms)
+    ev = [one(k) for k in range(warmup + steps)][warmup:]
     torch.cuda.synchronize()
     q_ms = sum(e[0].elapsed_time(e[1]) for e in ev) / len(ev) / W
     a_ms = sum(e[1].elapsed_time(e[2]) for e in ev) / len(ev)
@@ -616,7 +646,8 @@ def time_minmax(wl, bits, bucket, lr, steps, warmup):
     s_bytes = 4.0 * n
     t_bytes = n * (8.0 + bits / 8.0)   # two passes over the gradient (range, then encode)
     frac = lambda by, ms: by / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS
-    cells = n > 1 << 20 and (bucket >= 128 or W <= 8)
+    past = bits == 7 and past_cache(n, bits, W)
+    cells = n > 1 << 20 and (bucket >= 128 or W <= 8) and not (past and W > 8 and bucket & (bucket - 1) == 0)
     decode = 2.9 if bits in (1, 2, 4) else (3.0 if bits == 8 else 4.0)   # extract, convert, fma, add per worker
     r_ops = n * ((decode if cells else 4.0) * W + 12.0)                  # encode about 12
     log("minmax b=%d B=%d: quantize %.1f us (%.1f%%), aggregate %.1f us (%.1f%%), sum_squares %.1f us (%.1f%%), "
@@ -634,7 +665,7 @@ def time_minmax(wl, bits, bucket, lr, steps, warmup):
             "requantize_minmax": alu_row("requantize_cells_kernel" if cells else "requantize_minmax_kernel", r_ms, r_ops),
             "requantize_minmax_tensor": alu_row(
                 ("range_init + sum_range_cells + range_finish + requantize_tensor_cells + range_divide kernels" if n > 1 << 28
-                 else "sum_range_cells + fold_sum_range + requantize_tensor_cells kernels" if n > 3 << 19
+                 else "sum_range_cells + fold_sum_range + requantize_tensor_cells kernels" if n > 3 << 19 and not (past and W > 4)
                  else "sum_range_minmax_tensor + fold_sum_range + requantize_minmax_tensor kernels"), rt_ms,
                                                 n * (2.0 * decode * W + 14.0),   # two decodes of W workers, min/max, encode
                                                 {"algorithmic_bytes_per_launch": rt_bytes, "hbm_gbs": rt_bytes / (rt_ms * 1e-3) / 1e9})}
@@ -843,10 +874,10 @@ def main():
         choose_code_stores(wl, bits, bucket, args.lr, stores["chosen"])   # back to the headline's policy
 
     if args.exchange:
-        out["exchange"] = time_exchange(wl, bits, bucket, args.lr, max(10, args.steps // 4), max(5, args.warmup // 4))
+        out["exchange"] = time_exchange(wl, bits, bucket, args.lr, max(10, args.steps // 4), max(5, args.warmup // 4), args.condition_ms)
 
     if args.minmax:
-        out["minmax"] = [time_minmax(wl, b, bucket, args.lr, max(10, args.steps // 4), max(5, args.warmup // 4))
+        out["minmax"] = [time_minmax(wl, b, bucket, args.lr, max(10, args.steps // 4), max(5, args.warmup // 4), args.condition_ms)
                          for b in ((1, 2, 4, 8) if args.sweep else (bits,))]
 
     if args.tensors:
