@@ -443,16 +443,16 @@ def alu_row(kernel, ms, ops, extra=None):
     return row
 
 
-def past_cache(n, bits, W):
-    """Do the W code streams exceed the last-level cache by a quarter?  At 7 bits the re-encoding steps change kernels there."""
-    return n // 8 * bits * W > 320 << 20
+def past_cache(n, bits, bucket, W):
+    """Do the W streams exceed the last-level cache by a quarter?  At 7 bits the re-encoding steps change kernels there."""
+    return (n // 8 * bits + n // bucket * 8) * W > 320 << 20
 
 
 def maxabs_cells(n, bits, bucket, W):
     """Does the max-abs re-encoding of a long tensor run with a cell per lane?  (Below 2^24 elements there are further lines.)"""
     if bucket & (bucket - 1) or bucket < 128:
         return bucket > 32 or W <= 24
-    if (bits <= 2 and W > 4) or (bits == 7 and W > 6 and past_cache(n, bits, W)):
+    if (bits <= 2 and W > 4) or (bits == 7 and W > 6 and past_cache(n, bits, bucket, W)):
         return False
     if bits == 3 and W > 6 and 1024 <= bucket <= 4096 and n > 1 << 24:
         return False
@@ -646,7 +646,7 @@ def time_minmax(wl, bits, bucket, lr, steps, warmup, condition_ms=0.0):
     s_bytes = 4.0 * n
     t_bytes = n * (8.0 + bits / 8.0)   # two passes over the gradient (range, then encode)
     frac = lambda by, ms: by / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS
-    past = bits == 7 and past_cache(n, bits, W)
+    past = bits == 7 and past_cache(n, bits, bucket, W)
     cells = n > 1 << 20 and (bucket >= 128 or W <= 8) and not (past and W > 8 and bucket & (bucket - 1) == 0)
     decode = 2.9 if bits in (1, 2, 4) else (3.0 if bits == 8 else 4.0)   # extract, convert, fma, add per worker
     r_ops = n * ((decode if cells else 4.0) * W + 12.0)                  # encode about 12

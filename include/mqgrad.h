@@ -182,6 +182,8 @@ mqg_status mqg_aggregate_mean(const uint32_t* const* packed, const float* const*
  * copy of the sum or the mean is ever written to memory.
  *   packed, scales  HOST arrays of W device pointers, as for mqg_aggregate_update.
  *   packed_out      device, mqg_packed_words(n, bits) words;  scales_out: mqg_num_buckets(n, bucket) floats.
+ * A bucket whose sums are not all finite (scales that are infinite or not numbers, sums that overflow) gets an
+ * unspecified range and unspecified codes; which ones may depend on n, bits and bucket.
  * Errors as for mqg_quantize and mqg_aggregate_update. */
 mqg_status mqg_aggregate_requantize(const uint32_t* const* packed, const float* const* scales, uint32_t W,
                                     uint64_t n, uint32_t bits, uint32_t bucket,
@@ -278,6 +280,7 @@ mqg_status mqg_aggregate_update_minmax(const uint32_t* const* packed, const floa
  * de-quantizes is the mean.  No fp32 copy of the sum or the mean is written to memory.
  *   packed, ranges          HOST arrays of W device pointers, as for mqg_aggregate_update_minmax.
  *   packed_out, ranges_out  device, as for mqg_quantize_minmax.
+ * As for mqg_aggregate_requantize, a bucket whose sums are not all finite gets an unspecified range and codes.
  * The worker's half, w <- w - eta De-quantize(gbar), is mqg_aggregate_update_minmax with W = 1. */
 mqg_status mqg_aggregate_requantize_minmax(const uint32_t* const* packed, const float* const* ranges, uint32_t W,
                                            uint64_t n, uint32_t bits, uint32_t bucket,

@@ -4,7 +4,7 @@
 //
 // The calls of a training iteration go on from there: the library's entry is called from here, with the interpreter's lock
 // released, and its status is returned.  Through the foreign-function layer a call of a dozen arguments cost 1.3 us of 4.5
-// (65,536 elements quantized and the server's update: 10.6 -> 7.6 us for both).
+// (65,536 elements quantized and the server's update: 10.8 -> 8.5 us for both; 7.6 to 8.6 from machine to machine).
 //
 // Every function returns None for anything but plain tensors of the right kind and size (subclasses, wrapped or
 // storage-less tensors, other containers, values out of range); the binding then runs its own checks, which

@@ -328,8 +328,8 @@ __device__ __forceinline__ float inverse_step(float mn, float mx, float Lf) {
     return (r >= 0x1p-96f) ? Lf / r : 0.0f;   // IEEE-correct fp32 division
 }
 
-// Extremes of each part's values; elements past the end take no part (none at all: +inf, -inf), nor does a NaN unless
-// there is nothing else.
+// Extremes of each part's values; elements past the end take no part (none at all: +inf, -inf), nor does a NaN unless the part
+// holds nothing else.  (The rows kernels: unless a quad does.  Sums that are partly not numbers have no specified range.)
 template <int B, bool WHOLE>
 __device__ __forceinline__ void part_ranges(const float (&v)[32], const Window<B>& at, float (&lo)[Parts<B>::kCount], float (&hi)[Parts<B>::kCount]) {
     constexpr int E = Parts<B>::kElems;
@@ -715,7 +715,8 @@ void with_bits(uint32_t bits, F f) {
 }
 
 constexpr uint64_t kLastLevelCache = 256ull << 20;
-uint64_t stream_bytes(const RequantArgs& ra) { return (ra.q.n >> 3) * ra.q.bits * ra.W; }
+// of all workers: the codes, and two floats per bucket (the max-abs range has one, a whole tensor none to speak of)
+uint64_t stream_bytes(const RequantArgs& ra) { return ((ra.q.n >> 3) * ra.q.bits + ra.q.n / ra.q.bucket * 8u) * ra.W; }
 bool past_cache(const RequantArgs& ra) { return stream_bytes(ra) > kLastLevelCache / 4u * 5u; }
 // Where streaming loads begin: with the cache's size at 4, 6 and 8 bits, whose loads leave no gaps; later at 7 and 5 bits, where a
 // wave's next load asks for the same cache lines again, and there only where tiles begin with a cache line (power-of-two buckets and
@@ -839,7 +840,7 @@ bool requantize_minmax_cells_supported(const RequantArgs& ra) {
         const bool many = ra.q.bits == 3u || (ra.q.bits == 6u && ra.q.bucket == 128u) ? ra.W > 12u : narrow && ra.q.n > 1ull << 19;
         return ra.q.n >= 1ull << 16 && ra.q.bucket >= 128u && local_buckets(ra.q) && !many;
     }
-    if (ra.q.n <= 1ull << 21 && (narrow || (ra.q.bucket == 8192u && ra.q.bits == 8u))) return false;
+    if (ra.q.n <= 1ull << 21 && (narrow || (ra.q.bucket == 8192u && ra.q.bits == 8u && ra.W <= 16u))) return false;
     return ra.q.bucket >= 128u || ra.W <= 8u;
 }
 hipError_t launch_requantize_minmax_cells(const RequantArgs& ra, hipStream_t stream) { return launch_requantize_cells<MinmaxCode>(ra, stream); }
@@ -891,7 +892,7 @@ bool requantize_centred_cells_supported(const RequantArgs& ra) {
             return ra.q.n > 11ull << 19 || (ra.q.n > 3ull << 20 && ra.q.n <= 1ull << 22);
         }
         if ((ra.W > 2u && ra.q.bits <= 3u) || (ra.W <= 4u && ra.q.bits == 8u) || (ra.q.bucket == 8192u && ra.q.bits >= 6u)) return ra.q.n > 1ull << 21;
-        return ra.q.n > (ra.W <= 8u ? 9ull << 17 : 1ull << 20);
+        return ra.q.n > 65ull << 14;
     }
     // a division per bucket, lane and worker where rows share one: the smallest buckets of many workers
     if (ra.q.bucket == 64u) return ra.W <= 24u || ra.q.bits <= 3u || ra.q.n <= 1ull << 19 || ra.q.n > 1ull << 22;

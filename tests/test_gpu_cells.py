@@ -189,8 +189,10 @@ def against_the_sum(kind, n, bits, bucket, W):
     ("centred", 5, 2304, 32), ("centred", 7, 96, 40), ("minmax", 5, 352, 24), ("minmax", 7, 2304, 24)])                         # ordinary loads
 def test_streams_past_the_last_level_cache_at_five_and_seven_bits(kind, bits, bucket, W):
     limit = (384 << 20) if bits == 5 and W < 16 else (320 << 20)
-    for n in (limit * 8 // bits // W - 2048, limit * 8 // bits // W + 2048 + 33):
-        assert (n // 8 * bits * W > limit) == (n > limit * 8 // bits // W)
+    of = bucket if bucket else 1024
+    line = limit * 8 * of // (W * (bits * of + 64))        # codes, and two floats per bucket
+    for n in (line - 8192, line + 8192 + 33):
+        assert ((n // 8 * bits + n // of * 8) * W > limit) == (n > line)
         against_the_sum(kind, n, bits, bucket, W)
 
 
@@ -201,10 +203,10 @@ def test_long_tensors_at_three_bits(bucket):
 
 
 @pytest.mark.parametrize("kind,bits,bucket,W,line", [
-    ("centred", 4, 1024, 8, 9 << 17), ("centred", 7, 512, 9, M), ("centred", 1, 128, 1, 9 << 17), ("centred", 2, 2048, 4, 11 << 19),
+    ("centred", 4, 1024, 8, 65 << 14), ("centred", 7, 512, 9, 65 << 14), ("centred", 1, 128, 1, 65 << 14), ("centred", 2, 2048, 4, 11 << 19),
     ("centred", 3, 512, 3, 3 << 20), ("centred", 3, 4096, 8, 4 * M), ("centred", 3, 1024, 3, 11 << 19), ("centred", 3, 128, 5, 2 * M),
     ("centred", 8, 256, 4, 2 * M), ("centred", 6, 8192, 5, 2 * M), ("centred", 5, 4128, 3, 5 * M), ("centred", 8, 5120, 2, 5 * M),
-    ("minmax", 4, 4128, 6, 5 * M), ("minmax", 8, 8192, 3, 2 * M), ("minmax", 5, 128, 33, M // 2), ("minmax", 7, 128, 64, 2 * M),
+    ("minmax", 4, 4128, 6, 5 * M), ("minmax", 8, 8192, 16, 2 * M), ("minmax", 5, 128, 33, M // 2), ("minmax", 7, 128, 64, 2 * M),
     ("minmax", 2, 2752, 5, M), ("minmax", 6, 5120, 9, M), ("minmax", 3, 12320, 4, M), ("tensor", 3, 0, 5, 3 << 19),
     ("centred", 4, 64, 25, M // 2), ("centred", 6, 64, 64, 4 * M), ("centred", 3, 64, 33, 4 * M), ("centred", 5, 32, 12, 2 * M),
     ("centred", 8, 32, 13, 4 * M), ("centred", 2, 32, 24, 4 * M), ("centred", 4, 32, 25, 4 * M), ("centred", 6, 32, 30, 340000000 // 30), ("centred", 1, 32, 48, 340000000 // 48)])
