@@ -219,3 +219,19 @@ def test_on_both_sides_of_the_rules_lines(kind, bits, bucket, W, line):
 def test_short_launches_with_few_and_many_workers(bits, bucket):
     for W in (12, 13):
         against_the_sum("minmax", M // 4 + 77, bits, bucket, W)
+
+
+# streaming loads of whole tensors, and of buckets across waves; few workers' short launches at every width
+@pytest.mark.parametrize("kind,bits,bucket,W,n", [
+    ("tensor", 6, 0, 64, (256 << 20) // 48 + 77), ("minmax", 4, 2304, 24, (256 << 20) // 12 + 77), ("minmax", 6, 4096, 48, (256 << 20) // 36 + 77),
+    ("minmax", 8, 352, 16, (256 << 20) // 16 + 77), ("centred", 4, 12320, 32, (256 << 20) // 16 + 77), ("centred", 6, 3072, 64, (256 << 20) // 48 + 77),
+    *[("minmax", b, bucket, 7, M // 8 + 45) for b in range(1, 9) for bucket in (128, 2048)]])
+def test_every_form_of_the_cell_kernels(kind, bits, bucket, W, n):
+    against_the_sum(kind, n, bits, bucket, W)
+
+
+# what is left to the kernel that loads rows: small buckets of many workers in long launches, and one bucket per workgroup in short ones
+@pytest.mark.parametrize("bits,bucket,W,n", [(1, 32, 12, 5 * M + 9), (3, 64, 10, 3 * M + 31), (2, 96, 64, 3 * M), (1, 4128, 9, M // 4 + 7), (3, 5152, 24, M // 4 + 1),
+                                             (2, 6144, 33, M // 2 + 31)])
+def test_what_is_left_to_the_rows(bits, bucket, W, n):
+    against_the_sum("minmax", n, bits, bucket, W)

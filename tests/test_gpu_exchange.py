@@ -101,7 +101,7 @@ def test_mean_gradient_output_matches_oracle(bits, W, bucket):
     assert store[0].item() == 7.0 and store[n + 1].item() == 7.0          # neighbours untouched
 
 
-@pytest.mark.parametrize("bucket", [96, 128, 512, 1024, 4096, 16384])
+@pytest.mark.parametrize("bucket", [96, 128, 512, 1024, 4096, 12320, 16384])
 def test_requantize_with_the_l2_range(bucket):
     # the server's re-encoding step with the bucket's L2 norm of the sum as the range: the stored scales are
     # S / W with S within 1e-6 of the oracle's norm (summed in fp64) and never below max |sum|; the codes are

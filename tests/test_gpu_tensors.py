@@ -199,8 +199,8 @@ def test_batched_minmax_calls_report_bad_arguments():
 # (layers, encoded ones among them, workers): the largest batch that travels in the small form of the kernels' arguments (12
 # layers, 96 pointers), one more layer, more pointers, and the most of both
 @pytest.mark.parametrize("count,encoded,W", [(12, 4, 6), (13, 4, 1), (12, 4, 7), (12, 12, 5), (32, 32, 4), (20, 5, 10)])
-@pytest.mark.parametrize("kind,bits,bucket", [("centred", 2, 512), ("centred", 4, 96), ("centred", 5, 1024), ("centred", 8, 32),
-                                              ("minmax", 2, 160), ("minmax", 3, 1024), ("minmax", 8, 512), ("minmax", 4, 0)])
+@pytest.mark.parametrize("kind,bits,bucket", [("centred", 2, 512), ("centred", 3, 64), ("centred", 4, 96), ("centred", 5, 1024), ("centred", 8, 32),
+                                              ("minmax", 2, 160), ("minmax", 7, 2048), ("minmax", 3, 1024), ("minmax", 8, 512), ("minmax", 4, 0)])
 def test_batched_server_steps_of_many_layers_and_workers(kind, bits, bucket, count, encoded, W):
     lr = 0.1
     sizes = [(i * 7919 + 613) % 9000 + 1 for i in range(count)]
@@ -226,3 +226,26 @@ def test_batched_server_steps_of_many_layers_and_workers(kind, bits, bucket, cou
             step = ref.aggregate_update if kind == "centred" else ref.aggregate_update_minmax
             p1 = step(pk, sc, n, bits, bucket if bucket else n, lr, p0[i])
         assert ulp_distance(params[i].cpu().numpy(), p1).max() == 0, "layer %d" % i
+
+
+# (kind, bits, bucket, elements of the first tensor): each encoder's shapes, in batches of 12 tensors and of 13
+@pytest.mark.parametrize("count", [12, 13])
+@pytest.mark.parametrize("kind,bits,bucket,first", [
+    ("maxabs", 2, 512, (1 << 24) + 5), ("maxabs", 5, 512, (1 << 24) + 5), ("maxabs", 4, 4096, 9001), ("maxabs", 2, 1184, 9001), ("maxabs", 8, 1184, 9001),
+    ("maxabs", 2, 1376, 9001), ("maxabs", 8, 1376, 9001), ("maxabs", 2, 1760, 9001), ("maxabs", 8, 1760, 9001), ("maxabs", 5, 6176, 20001),
+    ("maxabs", 6, 12320, 30001), ("l2", 3, 96, 9001), ("minmax", 4, 832, 9001), ("minmax", 3, 1088, 9001), ("minmax", 5, 1760, 9001),
+    ("minmax", 2, 7200, 20001), ("minmax", 7, 14400, 40001)])
+def test_batched_encoders_equal_the_single_ones_at_either_size_of_batch(kind, bits, bucket, first, count):
+    sizes = [first] + [(i * 7919 + 613) % 9000 + 1 for i in range(1, count)]
+    grads = [workloads.normal(n, 0.01, 60 + i, DEV) for i, n in enumerate(sizes)]
+    if kind == "minmax":
+        batch = mqgrad.mqg_quantize_minmax_tensors(grads, bits, bucket)
+        alone = [mqgrad.mqg_quantize_minmax(g, bits, bucket) for g in grads]
+    else:
+        mode = mqgrad.MQG_SCALE_L2 if kind == "l2" else mqgrad.MQG_SCALE_MAXABS
+        bases = [(1 << 25) * i for i in range(count)]
+        batch = mqgrad.mqg_quantize_tensors(grads, bits, bucket, seed=4, iteration=7, worker=2, elem_bases=bases, scale_mode=mode)
+        alone = [mqgrad.mqg_quantize(g, bits, bucket, 4, 7, 2, bases[i], mode=mode) for i, g in enumerate(grads)]
+    torch.cuda.synchronize()
+    for i, (b, a) in enumerate(zip(batch, alone)):
+        assert torch.equal(b[0], a[0]) and torch.equal(b[1], a[1]), "tensor %d" % i
